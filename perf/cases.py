@@ -64,7 +64,7 @@ def _log(rng, lo, hi):
 
 MOST_OPS = 8.0e12            # below documents_8192
 MOST_BYTES = 2.0e9
-MOST_STATIC_HEADS = 32       # with at most 16384 keys the built-in workspace always holds this
+MOST_STATIC = (32, 8192)     # heads and keys that the built-in workspace holds at up to 32 queries per head
 
 
 def draw(rng):
@@ -86,7 +86,7 @@ def draw(rng):
             Nk = _log(rng, 256, 32768)
             Nq = rng.choice([1, 1, 1, rng.randint(2, 8), rng.randint(9, 32), _log(rng, 33, 2048)])
             call = rng.choice(["fwd", "splitk", "splitk", "static"]) if variant == "full" and Nq <= 32 else "fwd"
-            if Nq > Nk or (call == "static" and (B * H > MOST_STATIC_HEADS or Nk > 16384)):
+            if Nq > Nk or (call == "static" and (B * H > MOST_STATIC[0] or Nk > MOST_STATIC[1])):
                 continue
             c = _case(None, "cached", B, H, Nq, Nk, d, True, dtype if dtype != "fp32" else "fp16", variant, call, dist)
             if variant == "half":
