@@ -81,8 +81,8 @@ int quantize_tokenwise_hadamard(const void *X, int x_dtype, long rows, int d,
  *   scale   [heads] fp32 out.  global_scale = 0: one scalar per head (the paper's single-head
  *           statement applied to each head).  global_scale = 1: one scalar for the whole
  *           array, written to every slot.
- * Uses `scale` itself as its only scratch (it holds the absmax between the two passes), so the
- * array is read twice.  N*d must be a multiple of 8.
+ * One launch with many heads or short ones; otherwise two, the first of which leaves partial maxima in Xq (with
+ * global_scale = 1: four, with `scale` as scratch).  No other memory is used.  N*d must be a multiple of 8.
  */
 int quantize_headwise(const void *X, int x_dtype, long heads, long N, int d,
                       signed char *Xq, float *scale, int global_scale);
@@ -104,11 +104,10 @@ int quantize_qk(const void *Q, const void *K, int x_dtype, long rows, int d, sig
                 float *s_Q, float *s_K, float s_Q_mul, int hadamard, void *hip_stream);
 
 /*
- * The whole input preparation of Section 3.2 for one attention call, in three launches instead of the six the
- * three separate calls take: token-level quantization of Q and K in ONE launch, which also carries the absmax pass of V
- * (a few workgroups per head leave the maximum of their part in the tail of V_i8: no atomics, nothing to clear); then
- * the quantization pass of V; then one thread per head writes s_V and the tail of V_i8.  With fewer than 32 heads, or
- * heads of fewer than 512 elements, V goes through the general two-pass path of quantize_headwise instead (four launches).
+ * The whole input preparation of Section 3.2 for one attention call: token-level quantization of Q and K and
+ * tensor-level quantization of V in ONE launch with many heads or short ones (a workgroup takes a whole head of V
+ * beside those of Q and K); otherwise that launch carries the absmax pass of V, which leaves partial maxima in V_i8, and a
+ * second one quantizes V.
  *   Q, K, V          [heads, N, d] real activations of dtype x_dtype, heads = B*H
  *   Q_i8, K_i8, V_i8 [heads, N, d] int8 out;  s_Q, s_K [heads, N] and s_V [heads] fp32 out
  *   s_Q_mul          multiplier folded into the stored s_Q (1/sqrt(d) for the usual softmax scale; 1 for none)

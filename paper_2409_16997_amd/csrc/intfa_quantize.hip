@@ -8,41 +8,65 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_bf16.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "intfa.h"
 #include "intfa_internal.h"
 
 namespace {
 
-// ---- 8 consecutive elements of any supported dtype, widened exactly to fp32 ------------------
-template <typename T> struct Load8;
-
-template <> struct Load8<float> {
-    static __device__ __forceinline__ void get(const void *p, long idx, float (&x)[8]) {
-        const float4 *q = reinterpret_cast<const float4 *>(static_cast<const float *>(p) + idx);
-        float4 a = q[0], b = q[1];
-        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+// ---- 8 consecutive elements of any supported dtype, as loaded and widened exactly to fp32 -------
+template <typename T> struct Raw8 {                   // fp16, bf16: one 128-bit load
+    uint4 raw;
+    // held as loaded: the compiler may not keep the widened values (twice the registers) in its place
+    __device__ __forceinline__ void hold() { asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w)); }
+    template <typename I> __device__ __forceinline__ void load(const void *p, I idx) { raw = *reinterpret_cast<const uint4 *>(static_cast<const T *>(p) + idx); }
+    template <typename I> __device__ __forceinline__ void load_once(const void *p, I idx) {      // with the non-temporal hint
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(static_cast<const T *>(p) + idx));
+        raw = make_uint4(v[0], v[1], v[2], v[3]);
     }
-};
-template <> struct Load8<__half> {
-    static __device__ __forceinline__ void get(const void *p, long idx, float (&x)[8]) {
-        uint4 raw = *reinterpret_cast<const uint4 *>(static_cast<const __half *>(p) + idx);
-        const __half2 *h = reinterpret_cast<const __half2 *>(&raw);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { float2 f = __half22float2(h[i]); x[2 * i] = f.x; x[2 * i + 1] = f.y; }
-    }
-};
-template <> struct Load8<__hip_bfloat16> {
-    static __device__ __forceinline__ void get(const void *p, long idx, float (&x)[8]) {
-        uint4 raw = *reinterpret_cast<const uint4 *>(static_cast<const __hip_bfloat16 *>(p) + idx);
+    __device__ __forceinline__ void widen(float (&x)[8]) const {
         const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {                 // bf16 -> fp32 is a 16-bit shift
-            x[2 * i] = __uint_as_float(w[i] << 16);
-            x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (std::is_same_v<T, __half>) {
+                const float2 f = __half22float2(__builtin_bit_cast(__half2, w[i]));
+                x[2 * i] = f.x;
+                x[2 * i + 1] = f.y;
+            } else {                                  // bf16 -> fp32 is a 16-bit shift
+                x[2 * i] = __uint_as_float(w[i] << 16);
+                x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+            }
         }
     }
 };
+template <> struct Raw8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void hold() {
+        asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w), "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w));
+    }
+    template <typename I> __device__ __forceinline__ void load_once(const void *p, I idx) {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const f4 *q = reinterpret_cast<const f4 *>(static_cast<const float *>(p) + idx);
+        const f4 v = __builtin_nontemporal_load(q), w = __builtin_nontemporal_load(q + 1);
+        a = make_float4(v[0], v[1], v[2], v[3]);
+        b = make_float4(w[0], w[1], w[2], w[3]);
+    }
+    template <typename I> __device__ __forceinline__ void load(const void *p, I idx) {
+        const float4 *q = reinterpret_cast<const float4 *>(static_cast<const float *>(p) + idx);
+        a = q[0];
+        b = q[1];
+    }
+    __device__ __forceinline__ void widen(float (&x)[8]) const {
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    }
+};
+template <typename T, typename I> __device__ __forceinline__ void load8(const void *p, I idx, float (&x)[8]) {
+    Raw8<T> r;
+    r.load(p, idx);
+    r.widen(x);
+}
 
 __device__ __forceinline__ float absmax8(const float (&x)[8]) {
     float a = fmaxf(fabsf(x[0]), fabsf(x[1]));
@@ -120,71 +144,23 @@ template <int LPR> __device__ __forceinline__ void hadamard_row(float (&x)[8], i
 }
 
 // ---- token-level: one row = LPR lanes ---------------------------------------------------------
-// One launch serves up to two tensors of the same shape (Q and K of a step), can clear an array of words on the side
-// (the absmax slots the tensor-level quantizer of V accumulates into afterwards) and can carry the first pass of that
-// tensor-level quantizer along (HeadJob): blockIdx.y picks the job.
 struct TokenJob {
     const void *X;
     int8_t *Xq;
     float *scale;
     float scale_mul;
 };
-// First pass of the tensor-level quantizer without atomics and without slots to clear: HEAD_PARTS workgroups per head
-// each take a contiguous part of the head and leave the absmax of their part (fp32 bits) in the LAST 4 * HEAD_PARTS
-// bytes of that head's OUTPUT codes, which nobody writes before head_tail_finalize_kernel does (it reads them first).
-constexpr int HEAD_PARTS = 8;
-struct HeadJob {
-    const void *X;       // [heads, per_head]; null: no such job in this launch
-    int8_t *Xq;
-    long per_head;
-    int heads;
-};
-template <typename T>
-__device__ __forceinline__ void head_partial_absmax(const HeadJob &hj) {
-    if (blockIdx.x >= static_cast<unsigned>(hj.heads) * HEAD_PARTS) return;
-    const long head = blockIdx.x / HEAD_PARTS;
-    const int part = blockIdx.x % HEAD_PARTS;
-    const long chunks = hj.per_head / 8, per_part = (chunks + HEAD_PARTS - 1) / HEAD_PARTS;
-    const long c0 = part * per_part, c1 = (c0 + per_part < chunks) ? c0 + per_part : chunks;
-    float a = 0.0f;
-#pragma unroll 8
-    for (long c = c0 + threadIdx.x; c < c1; c += 256) {
+// Rows row0, row0 + row_stride, ... of one tensor; the caller's LPR adjacent lanes `sub` = 0 .. LPR - 1 share a row.
+// ONCE: the loads carry the non-temporal hint.
+template <typename T, int LPR, bool HADAMARD, bool ONCE = false>
+__device__ __forceinline__ void quantize_token_rows(const TokenJob &job, long rows, long row0, long row_stride, int sub) {
+    for (long row = row0; row < rows; row += row_stride) {
         float x[8];
-        Load8<T>::get(hj.X, head * hj.per_head + 8 * c, x);
-        a = fmaxf(a, absmax8(x));
-    }
-    a = group_max<64>(a);
-    __shared__ float wmax[4];
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = a;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        reinterpret_cast<unsigned *>(hj.Xq + (head + 1) * hj.per_head - 4 * HEAD_PARTS)[part] =
-            __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
-}
-
-template <typename T, int LPR, bool HADAMARD>
-__global__ __launch_bounds__(256) void quantize_tokenwise_kernel(TokenJob j0, TokenJob j1, long rows,
-                                                                 unsigned *__restrict__ clear, long clear_words, HeadJob hj) {
-    constexpr int D = LPR * 8;
-    constexpr int ROWS_PER_BLOCK = 256 / LPR;
-    // the head job, if any, comes last in dispatch order: V is then the most recently read tensor when the second pass
-    // of its quantizer starts, and that pass finds most of it in the Infinity Cache
-    const int y = static_cast<int>(blockIdx.y);
-    if (hj.X && y == static_cast<int>(gridDim.y) - 1) {
-        head_partial_absmax<T>(hj);
-        return;
-    }
-    const TokenJob job = y == 0 ? j0 : j1;
-    const int sub = threadIdx.x % LPR;
-    if (y == 0)
-        for (long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x; i < clear_words; i += static_cast<long>(gridDim.x) * 256)
-            clear[i] = 0u;
-    const long row_stride = static_cast<long>(gridDim.x) * ROWS_PER_BLOCK;
-    for (long row = static_cast<long>(blockIdx.x) * ROWS_PER_BLOCK + threadIdx.x / LPR; row < rows;
-         row += row_stride) {
-        float x[8];
-        const long idx = row * D + sub * 8;
-        Load8<T>::get(job.X, idx, x);
+        const long idx = row * (LPR * 8) + sub * 8;
+        Raw8<T> raw;
+        if (ONCE) raw.load_once(job.X, idx);
+        else raw.load(job.X, idx);
+        raw.widen(x);
         if (HADAMARD) hadamard_row<LPR>(x, sub);
         const float a = group_max<LPR>(absmax8(x));
         const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
@@ -193,93 +169,205 @@ __global__ __launch_bounds__(256) void quantize_tokenwise_kernel(TokenJob j0, To
     }
 }
 
-// ---- tensor-level: absmax of a head, then quantize ---------------------------------------------
-// |x| >= 0, so the fp32 bit pattern orders like the value and an integer atomic max works.
-template <typename T>
-__global__ __launch_bounds__(256) void head_absmax_kernel(const void *__restrict__ X, long per_head,
-                                                          unsigned *__restrict__ amax_bits, int global_scale) {
-    const long head = blockIdx.y;
-    const long base = head * per_head;
-    float a = 0.0f;
-    for (long i = (static_cast<long>(blockIdx.x) * 256 + threadIdx.x) * 8; i < per_head;
-         i += static_cast<long>(gridDim.x) * 256 * 8) {
-        float x[8];
-        Load8<T>::get(X, base + i, x);
-        a = fmaxf(a, absmax8(x));
-    }
+// One launch serves up to two tensors of the same shape (Q and K of a step): blockIdx.y picks the job.
+template <typename T, int LPR, bool HADAMARD>
+__global__ __launch_bounds__(256) void quantize_tokenwise_kernel(TokenJob j0, TokenJob j1, long rows) {
+    constexpr int ROWS_PER_BLOCK = 256 / LPR;
+    const TokenJob job = blockIdx.y == 0 ? j0 : j1;
+    quantize_token_rows<T, LPR, HADAMARD>(job, rows, static_cast<long>(blockIdx.x) * ROWS_PER_BLOCK + threadIdx.x / LPR,
+                                          static_cast<long>(gridDim.x) * ROWS_PER_BLOCK, threadIdx.x % LPR);
+}
+
+// ---- tensor-level, one scale per head ----------------------------------------------------------
+// A head's absmax has to be known before its first code.  Two ways, neither with atomics or slots to clear:
+//   whole  one workgroup of HEAD_THREADS takes the whole head, keeps its first KEEP_BYTES in registers and reads the rest a
+//          second time right after the first, out of the caches; one launch;
+//   parts  `parts` workgroups per head leave the absmax of their part (fp32 bits) at the START of each of the `regions`
+//          the second launch cuts the head's codes into: a workgroup of that launch reads the words in front of its own
+//          region before it writes its codes over them, so nobody else's words are touched and no third launch is needed.
+constexpr int HEAD_THREADS = 1024;
+template <typename T> constexpr int LOADS_IN_FLIGHT = sizeof(T) == 2 ? 4 : 2;   // chunks of 8 per thread
+constexpr int KEEP_BYTES = 96 << 10;   // 24 registers per thread: two workgroups per CU
+struct HeadJob {
+    const void *X;                 // [heads, per_head]
+    int8_t *Xq;
+    float *scale;                  // [heads]
+    long per_head;
+    int heads, parts, regions;     // parts = 0: whole heads
+    long chunks_per_part, chunks_per_region;   // in chunks of 8 elements; the last part and region take the remainder
+};
+
+template <int THREADS> __device__ __forceinline__ float workgroup_max(float a) {
+    __shared__ float wmax[THREADS / 64];
     a = group_max<64>(a);
-    __shared__ float wmax[4];
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = a;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        a = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-        // Atomics on one address serialise (hundreds of workgroups per head): look first.  The slot only grows, so a
-        // value read here, however stale, is a lower bound of the final one and skipping below it loses nothing.
-        unsigned *slot = amax_bits + (global_scale ? 0 : head);
-        if (__float_as_uint(a) > __builtin_nontemporal_load(slot)) atomicMax(slot, __float_as_uint(a));
+    a = wmax[0];
+#pragma unroll
+    for (int i = 1; i < THREADS / 64; ++i) a = fmaxf(a, wmax[i]);
+    return a;
+}
+
+template <typename T> __device__ __forceinline__ void head_whole(const HeadJob &hj, long head) {
+    constexpr int KEEP = sizeof(T) == 2 ? KEEP_BYTES / 16384 : KEEP_BYTES / 32768;   // chunks per thread
+    constexpr int U = LOADS_IN_FLIGHT<T>;
+    const T *X = static_cast<const T *>(hj.X) + head * hj.per_head;
+    int8_t *Xq = hj.Xq + head * hj.per_head;
+    const int chunks = static_cast<int>(hj.per_head / 8), tid = threadIdx.x;   // 32-bit offsets from a uniform base
+    Raw8<T> keep[KEEP];
+    float a = 0.0f, x[8];
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (tid + i * HEAD_THREADS < chunks) keep[i].load(X, 8 * (tid + i * HEAD_THREADS));
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (tid + i * HEAD_THREADS < chunks) {
+            keep[i].widen(x);
+            a = fmaxf(a, absmax8(x));
+        }
+    const int first = KEEP * HEAD_THREADS + tid;
+    int c = first;
+    for (; c + (U - 1) * HEAD_THREADS < chunks; c += U * HEAD_THREADS) {
+        Raw8<T> r[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) r[i].load(X, 8 * (c + i * HEAD_THREADS));
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            r[i].widen(x);
+            a = fmaxf(a, absmax8(x));
+        }
     }
+    for (; c < chunks; c += HEAD_THREADS) {
+        load8<T>(X, 8 * c, x);
+        a = fmaxf(a, absmax8(x));
+    }
+    a = workgroup_max<HEAD_THREADS>(a);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) keep[i].hold();
+    const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
+    if (tid == 0) hj.scale[head] = (a == 0.0f) ? 1.0f : a / 127.0f;
+    // backwards: what was read last is nearest
+    for (c -= HEAD_THREADS; c - (U - 1) * HEAD_THREADS >= first; c -= U * HEAD_THREADS) {
+        Raw8<T> r[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) r[i].load(X, 8 * (c - i * HEAD_THREADS));
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            r[i].widen(x);
+            *reinterpret_cast<uint2 *>(Xq + 8 * (c - i * HEAD_THREADS)) = quant8(x, inv);
+        }
+    }
+    for (; c >= first; c -= HEAD_THREADS) {
+        load8<T>(X, 8 * c, x);
+        *reinterpret_cast<uint2 *>(Xq + 8 * c) = quant8(x, inv);
+    }
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (tid + i * HEAD_THREADS < chunks) {
+            keep[i].widen(x);
+            *reinterpret_cast<uint2 *>(Xq + 8 * (tid + i * HEAD_THREADS)) = quant8(x, inv);
+        }
+}
+
+template <typename T> __device__ __forceinline__ void head_part_absmax(const HeadJob &hj, long head, int part) {
+    constexpr int U = LOADS_IN_FLIGHT<T>;
+    const long base = head * hj.per_head, chunks = hj.per_head / 8;
+    const long c1 = part + 1 < hj.parts ? (part + 1) * hj.chunks_per_part : chunks;
+    float a = 0.0f, x[8];
+    long c = part * hj.chunks_per_part + threadIdx.x;
+    for (; c + (U - 1) * HEAD_THREADS < c1; c += U * HEAD_THREADS) {
+        Raw8<T> r[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) r[i].load(hj.X, base + 8 * (c + i * HEAD_THREADS));
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            r[i].widen(x);
+            a = fmaxf(a, absmax8(x));
+        }
+    }
+    for (; c < c1; c += HEAD_THREADS) {
+        load8<T>(hj.X, base + 8 * c, x);
+        a = fmaxf(a, absmax8(x));
+    }
+    a = workgroup_max<HEAD_THREADS>(a);
+    for (int r = threadIdx.x; r < hj.regions; r += HEAD_THREADS)
+        reinterpret_cast<float *>(hj.Xq + base + 8 * r * hj.chunks_per_region)[part] = a;
+}
+
+// What workgroup `wg` of a launch does for V before any row of Q and K is touched; the number of such workgroups is
+// heads (whole) or heads * parts.
+template <typename T> __device__ __forceinline__ void head_first_pass(const HeadJob &hj, int wg) {
+    if (hj.parts == 0) head_whole<T>(hj, wg);
+    else head_part_absmax<T>(hj, wg / hj.parts, wg % hj.parts);
+}
+template <typename T> __global__ __launch_bounds__(HEAD_THREADS, 8) void head_first_pass_kernel(HeadJob hj) {
+    head_first_pass<T>(hj, static_cast<int>(blockIdx.x));
+}
+
+// Second launch of `parts`: one workgroup per (region, head).
+template <typename T> __global__ __launch_bounds__(256) void head_quantize_regions_kernel(HeadJob hj) {
+    const long head = blockIdx.y, base = head * hj.per_head, chunks = hj.per_head / 8;
+    const long c0 = blockIdx.x * hj.chunks_per_region, c1 = static_cast<int>(blockIdx.x) + 1 < hj.regions ? c0 + hj.chunks_per_region : chunks;
+    const float *words = reinterpret_cast<const float *>(hj.Xq + base + 8 * c0);
+    float a = 0.0f;
+    for (int p = 0; p < hj.parts; ++p) a = fmaxf(a, words[p]);
+    const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
+    __syncthreads();                                             // every thread has read the words its workgroup now overwrites
+    for (long c = c0 + threadIdx.x; c < c1; c += 256) {
+        float x[8];
+        load8<T>(hj.X, base + 8 * c, x);
+        *reinterpret_cast<uint2 *>(hj.Xq + base + 8 * c) = quant8(x, inv);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) hj.scale[head] = (a == 0.0f) ? 1.0f : a / 127.0f;
+}
+
+// Q and K token-level and the first pass of V in one launch.  Bound by HBM: 3 elements in and 3 bytes out each, and V a
+// second time as far as the caches do not hold it.  The workgroups of V come first: a whole head is the longest piece of
+// work in the launch, and the rows of Q and K fill in around it.  `once`: Q and K are read past the caches, which leaves
+// more of V there for its second read.  128 heads x 4096 x 128 fp16: 124 us (4.9 TB/s of 604 MB; a plain copy of 1 GiB
+// reaches 5.0 on this card), 135 as three launches with V's passes apart; without the hint 130; 64 heads x 1024 x 64: 10.4 us,
+// before 13.9; one head of 128 x 64 fp32: 5 us, before 14.4.
+template <typename T, int LPR>
+__global__ __launch_bounds__(HEAD_THREADS, 8) void quantize_qkv_kernel(TokenJob jq, TokenJob jk, long rows, HeadJob hj, int head_wgs, int once) {
+    constexpr int ROWS_PER_BLOCK = HEAD_THREADS / LPR;
+    if (static_cast<int>(blockIdx.x) < head_wgs) {
+        head_first_pass<T>(hj, static_cast<int>(blockIdx.x));
+        return;
+    }
+    const int wg = static_cast<int>(blockIdx.x) - head_wgs, per_tensor = (static_cast<int>(gridDim.x) - head_wgs) / 2;
+    const TokenJob job = wg < per_tensor ? jq : jk;
+    const long row0 = static_cast<long>(wg < per_tensor ? wg : wg - per_tensor) * ROWS_PER_BLOCK + threadIdx.x / LPR;
+    const long stride = static_cast<long>(per_tensor) * ROWS_PER_BLOCK;
+    if (once) quantize_token_rows<T, LPR, false, true>(job, rows, row0, stride, threadIdx.x % LPR);
+    else quantize_token_rows<T, LPR, false>(job, rows, row0, stride, threadIdx.x % LPR);
+}
+
+// ---- tensor-level, one scale for the whole array -------------------------------------------------
+// |x| >= 0, so the fp32 bit pattern orders like the value and an integer atomic max works.
+template <typename T>
+__global__ __launch_bounds__(256) void array_absmax_kernel(const void *__restrict__ X, long n, unsigned *__restrict__ slot) {
+    float a = 0.0f;
+    for (long i = (static_cast<long>(blockIdx.x) * 256 + threadIdx.x) * 8; i < n; i += static_cast<long>(gridDim.x) * 256 * 8) {
+        float x[8];
+        load8<T>(X, i, x);
+        a = fmaxf(a, absmax8(x));
+    }
+    a = workgroup_max<256>(a);
+    // Atomics on one address serialise: look first.  The slot only grows, so a value read here, however stale, is a
+    // lower bound of the final one and skipping below it loses nothing.
+    if (threadIdx.x == 0 && __float_as_uint(a) > __builtin_nontemporal_load(slot)) atomicMax(slot, __float_as_uint(a));
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void head_quantize_kernel(const void *__restrict__ X, long per_head,
-                                                            const unsigned *__restrict__ amax_bits,
-                                                            int8_t *__restrict__ Xq, int global_scale) {
-    const long head = blockIdx.y;
-    const long base = head * per_head;
-    const float a = __uint_as_float(amax_bits[global_scale ? 0 : head]);
+__global__ __launch_bounds__(256) void array_quantize_kernel(const void *__restrict__ X, long n, const unsigned *__restrict__ slot,
+                                                             int8_t *__restrict__ Xq) {
+    const float a = __uint_as_float(*slot);
     const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
-    for (long i = (static_cast<long>(blockIdx.x) * 256 + threadIdx.x) * 8; i < per_head;
-         i += static_cast<long>(gridDim.x) * 256 * 8) {
+    for (long i = (static_cast<long>(blockIdx.x) * 256 + threadIdx.x) * 8; i < n; i += static_cast<long>(gridDim.x) * 256 * 8) {
         float x[8];
-        Load8<T>::get(X, base + i, x);
-        *reinterpret_cast<uint2 *>(Xq + base + i) = quant8(x, inv);
+        load8<T>(X, i, x);
+        *reinterpret_cast<uint2 *>(Xq + i) = quant8(x, inv);
     }
-}
-
-// Second pass after head_partial_absmax: everything but the last 4 * HEAD_PARTS elements of the head (where the partial
-// maxima still sit).
-template <typename T>
-__global__ __launch_bounds__(256) void head_quantize_from_parts_kernel(const void *__restrict__ X, long per_head, int8_t *__restrict__ Xq) {
-    const long head = blockIdx.y;
-    const long base = head * per_head;
-    const unsigned *parts = reinterpret_cast<const unsigned *>(Xq + base + per_head - 4 * HEAD_PARTS);
-    unsigned bits = 0u;
-#pragma unroll
-    for (int p = 0; p < HEAD_PARTS; ++p) bits = max(bits, parts[p]);   // |x| >= 0: the bit patterns order like the values
-    const float a = __uint_as_float(bits);
-    const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
-    for (long i = (static_cast<long>(blockIdx.x) * 256 + threadIdx.x) * 8; i < per_head - 4 * HEAD_PARTS;
-         i += static_cast<long>(gridDim.x) * 256 * 8) {
-        float x[8];
-        Load8<T>::get(X, base + i, x);
-        *reinterpret_cast<uint2 *>(Xq + base + i) = quant8(x, inv);
-    }
-}
-
-// Last pass: one thread per head reads the partial maxima, then writes the scale and the head's last 4 * HEAD_PARTS codes
-// over them.
-template <typename T>
-__global__ __launch_bounds__(64) void head_tail_finalize_kernel(const void *__restrict__ X, long per_head, int8_t *__restrict__ Xq,
-                                                                float *__restrict__ scale, long heads) {
-    const long head = static_cast<long>(blockIdx.x) * 64 + threadIdx.x;
-    if (head >= heads) return;
-    const long tail = head * per_head + per_head - 4 * HEAD_PARTS;
-    const unsigned *parts = reinterpret_cast<const unsigned *>(Xq + tail);
-    unsigned bits = 0u;
-#pragma unroll
-    for (int p = 0; p < HEAD_PARTS; ++p) bits = max(bits, parts[p]);
-    const float a = __uint_as_float(bits);
-    const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
-    uint2 q[4 * HEAD_PARTS / 8];
-#pragma unroll
-    for (int k = 0; k < 4 * HEAD_PARTS / 8; ++k) {
-        float x[8];
-        Load8<T>::get(X, tail + 8 * k, x);
-        q[k] = quant8(x, inv);
-    }
-#pragma unroll
-    for (int k = 0; k < 4 * HEAD_PARTS / 8; ++k) *reinterpret_cast<uint2 *>(Xq + tail + 8 * k) = q[k];
-    scale[head] = (a == 0.0f) ? 1.0f : a / 127.0f;
 }
 
 // ---- block-level: one scale per (head, block of `block` keys), single pass -----------------------
@@ -298,7 +386,7 @@ __global__ __launch_bounds__(256) void block_quantize_kernel(const void *__restr
     for (int i = 0; i < 8; ++i) {
         const int c = threadIdx.x + 256 * i;
         if (c < chunks) {
-            Load8<T>::get(X, first + 8L * c, x[i]);
+            load8<T>(X, first + 8L * c, x[i]);
             a = fmaxf(a, absmax8(x[i]));
         }
     }
@@ -316,59 +404,103 @@ __global__ __launch_bounds__(256) void block_quantize_kernel(const void *__restr
     if (threadIdx.x == 0) scale[head * gridDim.x + jb] = (a == 0.0f) ? 1.0f : a / 127.0f;
 }
 
-__global__ void zero_words_kernel(unsigned *p, long n) {
-    const long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
+__global__ void zero_word_kernel(unsigned *p) { *p = 0u; }
 
-// absmax bits -> scale, in place.  One block; slot 0 is read by every thread before any write.
-__global__ void head_scale_finalize_kernel(float *scale, long heads, int global_scale) {
-    const float a0 = __uint_as_float(reinterpret_cast<const unsigned *>(scale)[0]);
+// absmax bits in slot 0 -> the scale in every slot.  One block; slot 0 is read by every thread before any write.
+__global__ void array_scale_finalize_kernel(float *scale, long heads) {
+    const float a = __uint_as_float(reinterpret_cast<const unsigned *>(scale)[0]);
     __syncthreads();
-    for (long h = threadIdx.x; h < heads; h += blockDim.x) {
-        const float a = global_scale ? a0 : __uint_as_float(reinterpret_cast<const unsigned *>(scale)[h]);
-        scale[h] = (a == 0.0f) ? 1.0f : a / 127.0f;
-    }
+    for (long h = threadIdx.x; h < heads; h += blockDim.x) scale[h] = (a == 0.0f) ? 1.0f : a / 127.0f;
 }
 
-template <typename T, bool HADAMARD>
-int launch_tokenwise(const TokenJob &j0, const TokenJob &j1, int jobs, long rows, int d, unsigned *clear, long clear_words,
-                     const HeadJob &hj, hipStream_t st) {
-    const int lpr = d / 8;
-    const long rows_per_block = 256 / lpr;
-    long blocks = (rows + rows_per_block - 1) / rows_per_block;
-    const long cap = 256L * 64 / jobs;                   // grid-stride beyond 64 blocks per CU (4 to 64 measured alike)
-    if (blocks > cap) blocks = cap;
-    if (hj.X && blocks < static_cast<long>(hj.heads) * HEAD_PARTS) blocks = static_cast<long>(hj.heads) * HEAD_PARTS;
-    const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(jobs + (hj.X ? 1 : 0))), block(256);
-    switch (lpr) {
-    case 4: hipLaunchKernelGGL((quantize_tokenwise_kernel<T, 4, HADAMARD>), grid, block, 0, st, j0, j1, rows, clear, clear_words, hj); break;
-    case 8: hipLaunchKernelGGL((quantize_tokenwise_kernel<T, 8, HADAMARD>), grid, block, 0, st, j0, j1, rows, clear, clear_words, hj); break;
-    case 16: hipLaunchKernelGGL((quantize_tokenwise_kernel<T, 16, HADAMARD>), grid, block, 0, st, j0, j1, rows, clear, clear_words, hj); break;
-    case 32: hipLaunchKernelGGL((quantize_tokenwise_kernel<T, 32, HADAMARD>), grid, block, 0, st, j0, j1, rows, clear, clear_words, hj); break;
-    case 64: hipLaunchKernelGGL((quantize_tokenwise_kernel<T, 64, HADAMARD>), grid, block, 0, st, j0, j1, rows, clear, clear_words, hj); break;
+// fn.template operator()<LPR>() for the row length d = 8 LPR
+template <typename F> int by_row_lanes(int d, F fn) {
+    switch (d / 8) {
+    case 4: fn(std::integral_constant<int, 4>{}); break;
+    case 8: fn(std::integral_constant<int, 8>{}); break;
+    case 16: fn(std::integral_constant<int, 16>{}); break;
+    case 32: fn(std::integral_constant<int, 32>{}); break;
+    case 64: fn(std::integral_constant<int, 64>{}); break;
     default: return IFA_ERR_UNSUPPORTED;
     }
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 
-template <typename T>
-int launch_headwise(const void *X, long heads, long per_head, int8_t *Xq, float *scale, int global_scale,
-                    hipStream_t st, bool slots_cleared = false) {
-    unsigned *bits = reinterpret_cast<unsigned *>(scale);
-    if (!slots_cleared)
-        hipLaunchKernelGGL(zero_words_kernel, dim3(static_cast<unsigned>((heads + 255) / 256)), dim3(256), 0, st, bits, heads);
-    long bx = (per_head / 8 + 255) / 256;
-    // About 4 workgroups per CU in total: measured on MI355X (c3's V, 134 MB) the two passes take 92 us with 1 per
-    // CU, 64 with 2, 57 with 4 or 8, 64 with 16, 72 with 32 -- more workgroups only add atomics on the head's slot.
-    const long cap = (256L * 4 + heads - 1) / heads;
-    if (bx > cap) bx = cap;
-    if (bx < 1) bx = 1;
-    const dim3 grid(static_cast<unsigned>(bx), static_cast<unsigned>(heads)), block(256);
-    hipLaunchKernelGGL((head_absmax_kernel<T>), grid, block, 0, st, X, per_head, bits, global_scale);
-    hipLaunchKernelGGL((head_quantize_kernel<T>), grid, block, 0, st, X, per_head, bits, Xq, global_scale);
-    hipLaunchKernelGGL(head_scale_finalize_kernel, dim3(1), dim3(256), 0, st, scale, heads, global_scale);
+template <typename T, bool HADAMARD>
+int launch_tokenwise(const TokenJob &j0, const TokenJob &j1, int jobs, long rows, int d, hipStream_t st) {
+    const long rows_per_block = 256 / (d / 8);
+    long blocks = (rows + rows_per_block - 1) / rows_per_block;
+    const long cap = 256L * 64 / jobs;                   // grid-stride beyond 64 blocks per CU (4 to 64 measured alike)
+    if (blocks > cap) blocks = cap;
+    const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(jobs)), block(256);
+    return by_row_lanes(d, [&](auto lpr) {
+        hipLaunchKernelGGL((quantize_tokenwise_kernel<T, decltype(lpr)::value, HADAMARD>), grid, block, 0, st, j0, j1, rows);
+    });
+}
+
+// Whole heads or parts.  From 96 heads on, whole heads keep enough workgroups busy and the second read of V is partly a
+// cache hit (Q, K, V of 96 x 2048 x 128 fp16: 47 us whole, 55 in parts; 128 x 4096 x 128: 124 and 145; 64 x 4096 x 128, below
+// the line: 81 and 73).  With fewer heads one workgroup walks its head at about 40 GB/s next to the fixed 4 us, and what
+// the second launch costs (2.5 us) only buys the chip's bandwidth for heads that are long: 4 heads of 256 KB 10.7 us whole
+// and 7.6 in parts, 64 heads of 128 KB 10.2 and 12.0.
+HeadJob plan_heads(const void *X, long heads, long per_head, int elem_bytes, int8_t *Xq, float *scale) {
+    HeadJob hj = {X, Xq, scale, per_head, static_cast<int>(heads), 0, 0, 0, 0};
+    if ((heads >= 96 && per_head < (1L << 29)) || per_head * elem_bytes <= (64L << 10) + heads * (4L << 10)) return hj;
+    const long chunks = per_head / 8;
+    auto split = [&](long want, long &per) {             // at most `want` pieces of at least HEAD_THREADS chunks
+        long n = chunks / HEAD_THREADS < want ? chunks / HEAD_THREADS : want;
+        if (n < 1) n = 1;
+        per = chunks / n;
+        return static_cast<int>(n);
+    };
+    hj.parts = split((512 + heads - 1) / heads < 64 ? (512 + heads - 1) / heads : 64, hj.chunks_per_part);
+    hj.regions = split((1024 + heads - 1) / heads, hj.chunks_per_region);   // 8 KB of codes or more: the words of 64 parts fit
+    return hj;
+}
+int head_workgroups(const HeadJob &hj) { return hj.parts == 0 ? hj.heads : hj.heads * hj.parts; }
+
+template <typename T> int launch_head_second(const HeadJob &hj, hipStream_t st) {
+    if (hj.parts > 0)
+        hipLaunchKernelGGL((head_quantize_regions_kernel<T>), dim3(static_cast<unsigned>(hj.regions), static_cast<unsigned>(hj.heads)), dim3(256),
+                           0, st, hj);
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+}
+
+template <typename T>
+int launch_headwise(const void *X, long heads, long per_head, int8_t *Xq, float *scale, int global_scale, hipStream_t st) {
+    if (!global_scale) {
+        const HeadJob hj = plan_heads(X, heads, per_head, sizeof(T), Xq, scale);
+        hipLaunchKernelGGL((head_first_pass_kernel<T>), dim3(static_cast<unsigned>(head_workgroups(hj))), dim3(HEAD_THREADS), 0, st, hj);
+        return launch_head_second<T>(hj, st);
+    }
+    unsigned *slot = reinterpret_cast<unsigned *>(scale);
+    const long n = heads * per_head;
+    long bx = (n / 8 + 255) / 256;
+    if (bx > 1024) bx = 1024;                            // about 4 workgroups per CU: more only add atomics on the slot
+    hipLaunchKernelGGL(zero_word_kernel, dim3(1), dim3(1), 0, st, slot);
+    hipLaunchKernelGGL((array_absmax_kernel<T>), dim3(static_cast<unsigned>(bx)), dim3(256), 0, st, X, n, slot);
+    hipLaunchKernelGGL((array_quantize_kernel<T>), dim3(static_cast<unsigned>(bx)), dim3(256), 0, st, X, n, slot, Xq);
+    hipLaunchKernelGGL(array_scale_finalize_kernel, dim3(1), dim3(256), 0, st, scale, heads);
+    return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+}
+
+template <typename T>
+int launch_qkv(const TokenJob &jq, const TokenJob &jk, const void *V, long heads, long N, int d, int8_t *Vq, float *sV, hipStream_t st) {
+    const HeadJob hj = plan_heads(V, heads, N * d, sizeof(T), Vq, sV);
+    const int head_wgs = head_workgroups(hj);
+    const long rows = heads * N, rows_per_block = HEAD_THREADS / (d / 8);
+    long per_tensor = (rows + rows_per_block - 1) / rows_per_block;
+    // grid-stride beyond 32 (whole heads) or 16 workgroups per CU for Q and K together (128 x 4096 x 128: 124 us at 32, 128 at
+    // 16, 132 at 64; in parts, 32 x 16384 x 128: 144 at 16, 154 at 64)
+    const long cap = 256L * (hj.parts == 0 ? 16 : 8);
+    if (per_tensor > cap) per_tensor = cap;
+    // below 64 MB the caches hold V whatever Q and K do (64 x 1024 x 64, 25 MB: 10.7 us with the hint, 10.4 without)
+    const int once = hj.parts == 0 && 3 * heads * N * d * static_cast<long>(sizeof(T)) > (64L << 20);
+    const int rc = by_row_lanes(d, [&](auto lpr) {
+        hipLaunchKernelGGL((quantize_qkv_kernel<T, decltype(lpr)::value>), dim3(static_cast<unsigned>(head_wgs + 2 * per_tensor)), dim3(HEAD_THREADS),
+                           0, st, jq, jk, rows, hj, head_wgs, once);
+    });
+    return rc == IFA_OK ? launch_head_second<T>(hj, st) : rc;
 }
 
 }  // namespace
@@ -385,12 +517,11 @@ int tokenwise_args(const void *X, int x_dtype, long rows, int d, const signed ch
 }
 
 template <bool HADAMARD>
-int tokenwise_launch(const TokenJob &j0, const TokenJob &j1, int jobs, int x_dtype, long rows, int d, unsigned *clear,
-                     long clear_words, const HeadJob &hj, hipStream_t st) {
+int tokenwise_launch(const TokenJob &j0, const TokenJob &j1, int jobs, int x_dtype, long rows, int d, hipStream_t st) {
     switch (x_dtype) {
-    case IFA_F32: return launch_tokenwise<float, HADAMARD>(j0, j1, jobs, rows, d, clear, clear_words, hj, st);
-    case IFA_F16: return launch_tokenwise<__half, HADAMARD>(j0, j1, jobs, rows, d, clear, clear_words, hj, st);
-    default: return launch_tokenwise<__hip_bfloat16, HADAMARD>(j0, j1, jobs, rows, d, clear, clear_words, hj, st);
+    case IFA_F32: return launch_tokenwise<float, HADAMARD>(j0, j1, jobs, rows, d, st);
+    case IFA_F16: return launch_tokenwise<__half, HADAMARD>(j0, j1, jobs, rows, d, st);
+    default: return launch_tokenwise<__hip_bfloat16, HADAMARD>(j0, j1, jobs, rows, d, st);
     }
 }
 
@@ -400,7 +531,7 @@ int tokenwise_entry(const void *X, int x_dtype, long rows, int d, signed char *X
     const int rc = tokenwise_args(X, x_dtype, rows, d, Xq, scale, scale_mul);
     if (rc != IFA_OK) return rc;
     const TokenJob job = {X, reinterpret_cast<int8_t *>(Xq), scale, scale_mul};
-    return tokenwise_launch<HADAMARD>(job, job, 1, x_dtype, rows, d, nullptr, 0, HeadJob{nullptr, nullptr, 0, 0}, static_cast<hipStream_t>(hip_stream));
+    return tokenwise_launch<HADAMARD>(job, job, 1, x_dtype, rows, d, static_cast<hipStream_t>(hip_stream));
 }
 
 int headwise_args(const void *X, int x_dtype, long heads, long N, int d, const signed char *Xq, const float *scale) {
@@ -412,16 +543,6 @@ int headwise_args(const void *X, int x_dtype, long heads, long N, int d, const s
     return IFA_OK;
 }
 
-int headwise_launch(const void *X, int x_dtype, long heads, long N, int d, signed char *Xq, float *scale, int global_scale,
-                    hipStream_t st, bool slots_cleared) {
-    int8_t *q = reinterpret_cast<int8_t *>(Xq);
-    const int g = global_scale ? 1 : 0;
-    switch (x_dtype) {
-    case IFA_F32: return launch_headwise<float>(X, heads, N * d, q, scale, g, st, slots_cleared);
-    case IFA_F16: return launch_headwise<__half>(X, heads, N * d, q, scale, g, st, slots_cleared);
-    default: return launch_headwise<__hip_bfloat16>(X, heads, N * d, q, scale, g, st, slots_cleared);
-    }
-}
 }  // namespace
 
 extern "C" int quantize_tokenwise_ex(const void *X, int x_dtype, long rows, int d, signed char *Xq, float *scale,
@@ -462,7 +583,13 @@ extern "C" int quantize_headwise_ex(const void *X, int x_dtype, long heads, long
                                     float *scale, int global_scale, void *hip_stream) {
     const int rc = headwise_args(X, x_dtype, heads, N, d, Xq, scale);
     if (rc != IFA_OK) return rc;
-    return headwise_launch(X, x_dtype, heads, N, d, Xq, scale, global_scale, static_cast<hipStream_t>(hip_stream), false);
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    int8_t *q = reinterpret_cast<int8_t *>(Xq);
+    switch (x_dtype) {
+    case IFA_F32: return launch_headwise<float>(X, heads, N * d, q, scale, global_scale, st);
+    case IFA_F16: return launch_headwise<__half>(X, heads, N * d, q, scale, global_scale, st);
+    default: return launch_headwise<__hip_bfloat16>(X, heads, N * d, q, scale, global_scale, st);
+    }
 }
 
 extern "C" int quantize_headwise(const void *X, int x_dtype, long heads, long N, int d, signed char *Xq,
@@ -476,10 +603,8 @@ extern "C" int quantize_qk(const void *Q, const void *K, int x_dtype, long rows,
     if (rc == IFA_OK) rc = tokenwise_args(K, x_dtype, rows, d, K_i8, s_K, 1.0f);
     if (rc != IFA_OK) return rc;
     const TokenJob jq = {Q, reinterpret_cast<int8_t *>(Q_i8), s_Q, s_Q_mul}, jk = {K, reinterpret_cast<int8_t *>(K_i8), s_K, 1.0f};
-    const HeadJob none = {nullptr, nullptr, 0, 0};
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    return hadamard ? tokenwise_launch<true>(jq, jk, 2, x_dtype, rows, d, nullptr, 0, none, st)
-                    : tokenwise_launch<false>(jq, jk, 2, x_dtype, rows, d, nullptr, 0, none, st);
+    return hadamard ? tokenwise_launch<true>(jq, jk, 2, x_dtype, rows, d, st) : tokenwise_launch<false>(jq, jk, 2, x_dtype, rows, d, st);
 }
 
 extern "C" int quantize_qkv(const void *Q, const void *K, const void *V, int x_dtype, long heads, long N, int d,
@@ -491,37 +616,10 @@ extern "C" int quantize_qkv(const void *Q, const void *K, const void *V, int x_d
     if (rc != IFA_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const TokenJob jq = {Q, reinterpret_cast<int8_t *>(Q_i8), s_Q, s_Q_mul}, jk = {K, reinterpret_cast<int8_t *>(K_i8), s_K, 1.0f};
-    const long per_head = N * d;
-    // With enough heads to fill the chip at HEAD_PARTS workgroups each, the absmax pass of V rides in the launch of Q and K
-    // (no atomics, no slots to clear) and three launches do the whole preparation; otherwise the general tensor-level
-    // path follows the launch of Q and K, which then also clears its slots.
-    if (heads >= 32 && per_head >= 64 * HEAD_PARTS) {
-        const HeadJob hj = {V, reinterpret_cast<int8_t *>(V_i8), per_head, static_cast<int>(heads)};
-        rc = tokenwise_launch<false>(jq, jk, 2, x_dtype, heads * N, d, nullptr, 0, hj, st);
-        if (rc != IFA_OK) return rc;
-        long bx = (per_head / 8 + 255) / 256;
-        const long cap = (256L * 4 + heads - 1) / heads;     // about 4 workgroups per CU in total, as in launch_headwise
-        if (bx > cap) bx = cap;
-        const dim3 grid(static_cast<unsigned>(bx), static_cast<unsigned>(heads)), tail_grid(static_cast<unsigned>((heads + 63) / 64));
-        int8_t *vq = reinterpret_cast<int8_t *>(V_i8);
-        switch (x_dtype) {
-        case IFA_F32:
-            hipLaunchKernelGGL((head_quantize_from_parts_kernel<float>), grid, dim3(256), 0, st, V, per_head, vq);
-            hipLaunchKernelGGL((head_tail_finalize_kernel<float>), tail_grid, dim3(64), 0, st, V, per_head, vq, s_V, heads);
-            break;
-        case IFA_F16:
-            hipLaunchKernelGGL((head_quantize_from_parts_kernel<__half>), grid, dim3(256), 0, st, V, per_head, vq);
-            hipLaunchKernelGGL((head_tail_finalize_kernel<__half>), tail_grid, dim3(64), 0, st, V, per_head, vq, s_V, heads);
-            break;
-        default:
-            hipLaunchKernelGGL((head_quantize_from_parts_kernel<__hip_bfloat16>), grid, dim3(256), 0, st, V, per_head, vq);
-            hipLaunchKernelGGL((head_tail_finalize_kernel<__hip_bfloat16>), tail_grid, dim3(64), 0, st, V, per_head, vq, s_V, heads);
-            break;
-        }
-        return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+    int8_t *vq = reinterpret_cast<int8_t *>(V_i8);
+    switch (x_dtype) {
+    case IFA_F32: return launch_qkv<float>(jq, jk, V, heads, N, d, vq, s_V, st);
+    case IFA_F16: return launch_qkv<__half>(jq, jk, V, heads, N, d, vq, s_V, st);
+    default: return launch_qkv<__hip_bfloat16>(jq, jk, V, heads, N, d, vq, s_V, st);
     }
-    // one launch for Q and K, which also clears the slots the absmax pass of V accumulates into
-    rc = tokenwise_launch<false>(jq, jk, 2, x_dtype, heads * N, d, reinterpret_cast<unsigned *>(s_V), heads, HeadJob{nullptr, nullptr, 0, 0}, st);
-    if (rc != IFA_OK) return rc;
-    return headwise_launch(V, x_dtype, heads, N, d, V_i8, s_V, 0, st, true);
 }

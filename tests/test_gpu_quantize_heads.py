@@ -1,0 +1,45 @@
+"""Tensor-level quantization of V where its ways of walking a head meet: a head held in registers by one workgroup, read a
+second time by it, or cut into parts and regions over two launches.  Bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# 2-byte elements: 6144 chunks of 8 stay in registers, 4096 more per step of the loop behind; whole heads up to 64 KB + 4 KB
+# per head or from 96 heads on
+SHAPES = [
+    (1, 1, 64), (1, 511, 64), (1, 512, 64),              # one workgroup; 32768 elements is the last size it takes alone
+    (1, 513, 64), (3, 577, 128), (2, 1151, 64),          # parts: one past the line, remainders in the last part and region
+    (1, 16384, 128), (5, 4099, 128),                     # 64 and more parts wanted
+    (96, 767, 64), (96, 768, 64), (97, 769, 64),         # whole heads at the end of the registers (6144 chunks)
+    (96, 1279, 64), (96, 1280, 64), (96, 1281, 64),      # ... and at one full step of the loop (10240 chunks)
+    (96, 1025, 128), (100, 1793, 64),
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("heads,N,d", SHAPES)
+def test_headwise_codes_and_scales(heads, N, d, dtype):
+    import paper_2409_16997_amd as ifa
+    g = torch.Generator(device="cuda").manual_seed(heads * 7919 + N)
+    V = torch.randn((1, heads, N, d), generator=g, device="cuda").to(dtype)
+    at = torch.randint(0, N * d, (heads,), generator=g, device="cuda")
+    V.view(heads, -1)[torch.arange(heads, device="cuda"), at] = 9.0     # the maximum of each head, once, anywhere in it
+    V[0, 0, N - 1, d - 1] = -11.0                                       # ... and at the very end of the first
+    V[0, heads // 2] *= 0.0 if heads > 1 else 1.0
+    pick = sorted({0, heads // 2, heads - 1})
+    rq, rs = oracle.quantize_headwise(V[0, pick].float().cpu().numpy())
+    q, s = ifa.quantize_headwise(V)
+    assert np.array_equal(q[0, pick].cpu().numpy(), rq) and np.array_equal(s[0, pick].cpu().numpy(), rs)
+    Q, K = (torch.randn((1, heads, N, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    out = tuple(torch.full((1, heads, N, d), 77, dtype=torch.int8, device="cuda") for _ in range(3)) + tuple(
+        torch.full(sh, 3.0e38, device="cuda") for sh in ((1, heads, N), (1, heads, N), (1, heads)))
+    ifa.quantize_qkv(Q, K, V, out=out)
+    assert torch.equal(out[2], q) and torch.equal(out[5], s)
+    for x, c, sc in ((Q, out[0], out[3]), (K, out[1], out[4])):
+        rq, rs = ifa.quantize_tokenwise(x)
+        assert torch.equal(c, rq) and torch.equal(sc, rs)
