@@ -24,42 +24,44 @@ using namespace ifa_tiles;
 
 // ---- few queries, many keys (a decode step, a short chunk of a prefill) ---------------------------------------
 // With at most a few dozen queries per head the fused kernel would keep three of its four wavefronts idle and one
-// workgroup per head cannot fill the chip; what limits such a call is how fast K and V stream in.  Here the four
-// wavefronts of a workgroup share ONE group of 32 queries and split each 128-key block instead:
-//     wavefront w computes S^T for key tile w (32 keys; 4 MFMAs), scales it, takes its minimum / maximum;
-//     the four per-query extrema meet in LDS (first barrier of the block): everyone knows m of line 10 for the whole block;
-//     wavefront w computes the 16 P bytes per lane of its key tile and leaves them in LDS (second barrier);
-//     wavefront w then computes the d tile w (32 of the d columns) of O^T = V^T P^T over ALL 128 keys (4 MFMAs,
-//     P operands of the four key tiles from LDS) and folds it into its 16 registers of the running output.
+// workgroup per head cannot fill the chip; what limits such a call is the latency of one key block after the other.
+// Here the twelve wavefronts of a workgroup share ONE group of 32 queries and take NARROW_NB = 2 key blocks at a time,
+// in two roles that run one group of blocks apart:
+//   eight S wavefronts (block b of the group, key tile t): lines 9-11 for that tile.  A wavefront copies the K rows it reads
+//       itself, two groups ahead, and holds the operands of the next group in registers, so its own counted waits order the
+//       copies.  The extrema of the tiles meet in LDS (first barrier), every wavefront then knows m of line 10 after each
+//       block of the group in order, and the P bytes go to LDS (second barrier);
+//   four PV wavefronts (d tile): lines 12-13 for the group before, block by block in order.  They take its P bytes and V^T
+//       operands to registers by the first barrier, which frees both places in LDS, and also copy V, a group ahead.
+// What bounds it: one CU takes in about 60 GB/s however many copies are in flight (a plain streaming kernel measures 59-61
+// with 32 workgroups), which is 1.07 us per group of 64 KB at d = 128; the chain MFMA - scale - exchange - exp - exchange of a
+// group takes 1.0 us.  One block at a time by four wavefronts took 1.29 us per 32 KB.  32 heads of 4099 keys, one query:
+// 22 us, before 42.5; 128 heads of 16384: 93 us (5.8 TB/s), before 144; 512 of 8192: 153 us (7.0 TB/s), before 183.
 // Every number is computed by the same instruction sequence on the same operands as in the fused kernel (the
 // integer sums are exact, the extremum is order-independent, the row sum l is taken over the same P dwords), so
 // the output is bit-identical to the corresponding rows of a square call: still Algorithm 1 at B_c = 128.
-// K and V come in through a ring of NSTAGE blocks (one workgroup per CU: there are few workgroups anyway), filled
-// three blocks ahead so that enough bytes are in flight to cover the HBM latency; the wait for a block is a
-// counted s_waitcnt (every wavefront issues the same number of copy instructions per block) in front of the second
-// barrier of the block before, which thereby also publishes the staged block; the first barrier releases the
-// stage of the block before for refilling.
 constexpr int NARROW_BR = 32;      // queries per workgroup
-constexpr int NSTAGE = 4;
+constexpr int NARROW_NB = 2;       // key blocks per group
+constexpr int NARROW_S_WAVES = 4 * NARROW_NB;
+constexpr int NARROW_THREADS = (NARROW_S_WAVES + 4) * 64;
 
 template <int D> struct SmemNarrow {
-    alignas(4096) int8_t k[NSTAGE][BC * D];
-    alignas(4096) int8_t v[NSTAGE][BC * D];
-    alignas(512) float sk[NSTAGE][BC];
-    alignas(16) float ext[4][32];          // per key tile and query: the tile's extremum of a (line 10)
-    alignas(16) v4i p[4][64];              // per key tile and lane: the 16 P bytes of that lane (line 11)
+    alignas(4096) int8_t k[2][NARROW_NB][BC * D];
+    alignas(4096) int8_t v[2][NARROW_NB][BC * D];
+    alignas(256) float sk[2][NARROW_NB * 4][64];          // per S wavefront: the 32 s_K of its key tile (+ 32 unused)
+    alignas(16) v4i p[NARROW_NB][4][64];                  // per block, key tile and lane: the 16 P bytes of that lane (line 11)
+    alignas(16) float ext[2][NARROW_NB][32][4];           // per block, query and key tile: the extremum of a (line 10)
 };
-static_assert(sizeof(SmemNarrow<128>) <= 160 * 1024 && offsetof(SmemNarrow<64>, v) % 4096 == 0, "LDS budget and tile bases");
+static_assert(sizeof(SmemNarrow<128>) <= 160 * 1024, "LDS budget");
 
 template <int D, bool CAUSAL, bool VB, typename OutT>
-__global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_narrow_kernel(
+__global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_kernel(
     const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
     const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
-    int heads, int Nq, int Nk, OutT *__restrict__ O) {
+    int heads, int Nq, int Nk, int once, OutT *__restrict__ O) {
 #if defined(__HIP_DEVICE_COMPILE__)
     __shared__ SmemNarrow<D> sm;
-    constexpr int KS = D / 32;
-    constexpr int PER_BLOCK = 2 * KS + 1;                        // copy instructions per wavefront and block
+    constexpr int KS = D / 32, NB = NARROW_NB;
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -73,142 +75,221 @@ __global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_narrow_kernel(
     const int first_q = qg * NARROW_BR;
     const int q_head = first_q + r;
     const long qrow = static_cast<long>(head) * Nq + min(q_head, Nq - 1);   // rows past Nq: a clamped copy, never stored
-
-    const int8_t *Kh = K + static_cast<long>(head) * Nk * D;
-    const int8_t *Vh = V + static_cast<long>(head) * Nk * D;
-    const float *sKh = sK + static_cast<long>(head) * Nk;
-    const lds_ptr kbuf = (lds_ptr)(&sm.k[0][0]);
-    const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0]);
-    const lds_ptr skbuf = (lds_ptr)(&sm.sk[0][0]);
+    const float nq2 = sQ[qrow] * (-LOG2E * ACC_UNIT);
     const int nblocks = CAUSAL ? min(Nk - 1, min(first_q + NARROW_BR, Nq) - 1 + shift) / BC + 1 : T_c;
-
-    const BufRsrc rK = make_rsrc(Kh, static_cast<unsigned>(Nk) * D);
-    const BufRsrc rV = make_rsrc(Vh, static_cast<unsigned>(Nk) * D);
-    const BufRsrc rSK = make_rsrc(sKh, static_cast<unsigned>(Nk) * 4);
-    const LaneOffsets<D> lo(lane, wave);
-
-    // line 8 for block jb into stage jb % NSTAGE; a block past the last one is requested nowhere (no data moves), so
-    // that every block costs every wavefront PER_BLOCK copy instructions and the counted wait below stays valid
-    auto stage_block = [&](int jb) {
-        const int st = jb % NSTAGE;
-        const bool real = jb < nblocks;
-        const Prefetch pf = {rK, rV, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE,
-                             kbuf + st * BC * D, vbuf + st * BC * D, skbuf + st * BC * 4};
-#pragma unroll
-        for (int i = 0; i < KS; ++i) { prefetch_k_piece<D>(pf, lo, wave, i); prefetch_v_piece<D>(pf, lo, wave, i); }
-        lds_copy4(pf.sk, pf.lsk + 256 * (wave & 1), 4 * lane + 256 * (wave & 1), pf.skoff);   // wavefronts 2, 3 repeat 0, 1
-    };
-    stage_block(0);
-    stage_block(1);
-    stage_block(2);
-
-    // line 5
-    const int8_t *qptr = Q + qrow * D + 16 * g;
-    v4i qf[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 32 * kk);
-    float nq2 = sQ[qrow] * (-LOG2E * ACC_UNIT);
-    // The loads above must have landed BEFORE the loop as far as the compiler is concerned: a wait for them inside the
-    // loop would be a wait for every outstanding vector-memory operation, the staged copies included.
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[kk]));
-    asm volatile("" : "+v"(nq2));
-
-    // line 6: this wavefront's d tile of the running output (units of 2^26), m and l of the whole row
-    float m2 = -INFINITY, l = 0.0f, o[16];
+    const int ngroups = (nblocks + NB - 1) / NB;
+    float m2 = -INFINITY;                                        // line 6; kept in step by both roles
     v16i acc0;                                                   // what both accumulations start from
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { o[v] = 0.0f; acc0[v] = ACC_START_I; }
+    for (int v = 0; v < 16; ++v) acc0[v] = ACC_START_I;
+    // line 10 for the four blocks of a group: the running maximum after each; leaves m2 at the last
+    auto maxima = [&](int parity) {
+        struct { float v[NB]; } m;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const v4f e = *reinterpret_cast<const v4f *>(&sm.ext[parity][b][r][0]);
+            m2 = fmaxf(m2, fminf(fminf(e[0], e[1]), fminf(e[2], e[3])) * nq2);
+            m.v[b] = m2;
+        }
+        return m;
+    };
 
+    if (wave < NARROW_S_WAVES) {
+        // ---- S wavefront: key tile t of block `blk` of every group
+        constexpr int PER_GROUP = KS + 1;                        // copy instructions per group
+        const int t = wave & 3, blk = wave >> 2;
+        const BufRsrc rK = make_rsrc(K + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+        const BufRsrc rSK = make_rsrc(sK + static_cast<long>(head) * Nk, static_cast<unsigned>(Nk) * 4);
+        const lds_ptr kbuf = (lds_ptr)(&sm.k[0][blk][0]);
+        const lds_ptr skbuf = (lds_ptr)(&sm.sk[0][wave][0]);
+        const LaneOffsets<D> lo(lane, t);
+        // line 8: this wavefront's 32 rows of K and their s_K (lanes 32-63 repeat lanes 0-31): it alone reads what it
+        // copies, so its own counted wait orders the two.  Rows past the end come as zeros and are masked below; a group past
+        // the last one is requested nowhere, so that every group costs PER_GROUP copies.
+        auto stage_group = [&](int gi) {
+            const int jb = gi * NB + blk;
+            const bool real = jb < nblocks;
+            const Prefetch pf = {rK, rK, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE, kbuf + (gi & 1) * (NB * BC * D), kbuf,
+                                 skbuf + (gi & 1) * (NB * 4 * 256)};
+            if (once) {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) prefetch_k_piece<D, true>(pf, lo, t, i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) prefetch_k_piece<D>(pf, lo, t, i);
+            }
+            lds_copy4(pf.sk, pf.lsk, 4 * r + 128 * t, pf.skoff);
+        };
+        stage_group(0);
+        stage_group(1);
+        const int8_t *qptr = Q + qrow * D + 16 * g;              // line 5
+        v4i qf[KS];
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 32 * kk);
+        // landed BEFORE the loop as far as the compiler is concerned: a wait of its own inside the loop would be a wait for
+        // the staged copies as well
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[kk]));
+        v4i kop[KS];
+        v4f skv[4];
+        auto read_group = [&](int gi) {
+            const lds_ptr ks = kbuf + (gi & 1) * (NB * BC * D), sk = skbuf + (gi & 1) * (NB * 4 * 256);
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) kop[kk] = *reinterpret_cast<LDS_AS const v4i *>(k_operand<D>(ks, lo, kk) + 32 * t * D);
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) skv[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + lo.sk + 32 * vq);
+        };
+        wait_vmcnt<PER_GROUP>();
+        __builtin_amdgcn_sched_barrier(0);
+        read_group(0);
+        wait_lds();
+        __builtin_amdgcn_sched_barrier(0);
+        stage_group(2);                                          // into the place group 0 has left
+        for (int gi = 0; gi < ngroups; ++gi) {                   // line 7
+            // line 9, integer part
+            v16i sacc = acc0;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[kk], sacc, 0, 0, 0);
+            // line 9, fp32 part, and the extrema; kept keys: index inside the block <= klimit (the causal diagonal, the
+            // ragged end of the sequence, a block past the last one)
+            const int j0 = (gi * NB + blk) * BC;
+            const int tail = Nk - 1 - j0;
+            const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;
+            const bool masked = CAUSAL ? (j0 + BC - 1 > min(first_q + shift, Nk - 1)) : (tail < BC - 1);   // wave-uniform
+            float a[16], bmin = INFINITY;
+            auto scale = [&](auto with_mask) {
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float x = (ACC_START_F - __int_as_float(sacc[4 * vq + e])) * skv[vq][e];
+                        if (decltype(with_mask)::value && (32 * t + 8 * vq + 4 * g + e > klimit)) x = INFINITY;
+                        a[4 * vq + e] = x;
+                        bmin = fminf(bmin, x);
+                    }
+            };
+            if (masked) scale(std::true_type{});
+            else scale(std::false_type{});
+            bmin = pair_min(bmin);
+            if (g == 0) sm.ext[gi & 1][blk][r][t] = bmin;
+            __syncthreads();
+            // lines 10, 11, while the operands of the next group come in from LDS
+            const auto m = maxima(gi & 1);
+            wait_vmcnt<PER_GROUP>();                             // group gi + 1 has landed (group gi + 2 may be in flight)
+            __builtin_amdgcn_sched_barrier(0);
+            read_group(gi + 1);
+            const float mm = (blk ? m.v[1] : m.v[0]) - LOG2_R_NORM;
+            v4i pw;
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[4 * vq + e], nq2, -mm));
+                pw[vq] = static_cast<int>(pack_p4(x));
+            }
+            sm.p[blk][t][lane] = pw;
+            wait_lds();
+            __builtin_amdgcn_sched_barrier(0);
+            stage_group(gi + 3);                                 // into the place group gi + 1 has left
+            __syncthreads();
+        }
+        wait_all_memory();                                       // requests past the last group: nothing of mine stays in flight
+        __syncthreads();                                         // the PV wavefronts' last group
+        return;
+    }
+
+    // ---- PV wavefront: d tile dt of O^T = V^T P^T, one group of blocks behind
+    const int dt = wave - NARROW_S_WAVES;
+    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+    const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0][0]);
+    const LaneOffsets<D> lo(lane, dt);
+    // V of group gi (this wavefront's quarter of every block); a block past the last one is requested nowhere and comes as
+    // zeros, so that every group costs NB * KS copies
+    auto stage_blocks = [&](int gi, auto nt) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int jb = gi * NB + b;
+            const Prefetch pf = {rV, rV, rV, jb < nblocks ? jb * BC * D : NOWHERE, NOWHERE, vbuf, vbuf + ((gi & 1) * NB + b) * (BC * D), vbuf};
+#pragma unroll
+            for (int i = 0; i < KS; ++i) prefetch_v_piece<D, decltype(nt)::value>(pf, lo, dt, i);
+        }
+    };
+    auto stage_group = [&](int gi) {
+        if (once) stage_blocks(gi, std::true_type{});
+        else stage_blocks(gi, std::false_type{});
+    };
+    float l = 0.0f, o[16];                                       // this d tile of the running output (units of 2^26), l of the whole row
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] = 0.0f;
     // s_V: one scalar per head, or (VB) one per key block of this head, read through the scalar cache
     const float *sVh = VB ? sV + static_cast<long>(head) * T_c : sV + head;
     float sv_prev = 1.0f;
-    wait_vmcnt<2 * PER_BLOCK>();                                 // my pieces of block 0 have landed (blocks 1 and 2 may be in flight)
-    __syncthreads();                                             // everyone's have
-    for (int jb = 0; jb < nblocks; ++jb) {                       // line 7
-        const int st = jb % NSTAGE, j0 = jb * BC;
-        // with one V scale per key block the running output is kept in units of the current block's scale (as in the fused kernel)
-        const float sv_j = VB ? uniform(sVh[jb]) : 1.0f;
-        const float oscale = VB ? uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j)) : 1.0f;
-        sv_prev = sv_j;
-        const lds_ptr ks = kbuf + st * BC * D, vs = vbuf + st * BC * D, sk = skbuf + st * BC * 4;
-
-        // line 9 for key tile `wave`
-        v4i kop[KS];
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) kop[kk] = *reinterpret_cast<LDS_AS const v4i *>(k_operand<D>(ks, lo, kk) + 32 * wave * D);
-        v4f skv[4];
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) skv[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + lo.sk + 128 * wave + 32 * vq);
-        // (registers are plentiful here: the accumulators start from a register block holding the constant, and every
-        // MFMA is the compiler's own, with its dependency handling)
-        v16i sacc = acc0;
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[kk], sacc, 0, 0, 0);
-        // kept keys: index inside the block <= klimit (the causal diagonal, the ragged end of the sequence)
-        const int tail = Nk - 1 - j0;
-        const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;
-        const bool masked = CAUSAL ? (j0 + BC - 1 > min(first_q + shift, Nk - 1)) : (tail < BC - 1);   // wave-uniform
-        float a[16], bmin = INFINITY;
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float x = (ACC_START_F - __int_as_float(sacc[4 * vq + e])) * skv[vq][e];
-                if (masked && (32 * wave + 8 * vq + 4 * g + e > klimit)) x = INFINITY;
-                a[4 * vq + e] = x;
-                bmin = fminf(bmin, x);
-            }
-        bmin = pair_min(bmin);
-        if (g == 0) sm.ext[wave][r] = bmin;
-        __syncthreads();
-        // every wavefront is past the second GEMM of block jb - 1: the stage that block used takes block jb + 3
-        stage_block(jb + 3);
-        // line 10 over the whole block
-        bmin = fminf(fminf(sm.ext[0][r], sm.ext[1][r]), fminf(sm.ext[2][r], sm.ext[3][r]));
-        const float m_new = fmaxf(m2, bmin * nq2);
-        const float alpha = __builtin_amdgcn_exp2f(m2 - m_new);
-        const float mm = m_new - LOG2_R_NORM;
-        m2 = m_new;
-        // line 11 for key tile `wave`
-        v4i pw;
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-            float x[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[4 * vq + e], nq2, -mm));
-            const uint32_t w = pack_p4(x);
-            pw[vq] = static_cast<int>(w);
+    // lines 12, 13 for block b of group gi - 1 on operands in registers.  (A block past the last one: the maximum stays, P is
+    // 0, nothing changes.)
+    v4i pf[NB][4], vop[NB][4];
+    auto block = [&](int gi, int b, float m_prev, float m_new) {
+        const int jb = (gi - 1) * NB + b;
+        const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
+        float alpha_o = alpha;
+        if (VB && jb < nblocks) {                                // one V scale per key block: the running output is kept in units of the current block's
+            const float sv_j = uniform(sVh[jb]);
+            alpha_o = alpha * uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j));
+            sv_prev = sv_j;
         }
-        sm.p[wave][lane] = pw;
-        wait_vmcnt<2 * PER_BLOCK>();                             // my pieces of block jb + 1 have landed (two later blocks may be in flight)
-        __syncthreads();                                         // everyone's have, and every P tile of this block is in LDS
-        // lines 12, 13: d tile `wave` of O^T = V^T P^T over the four key tiles, the row sum over the same P dwords
-        if (wave >= KS) continue;                                // D = 64: two d tiles; the other wavefronts only take part above
-        v16i pacc;
+        v16i pacc = acc0;
         uint32_t psum = 0;
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
-            const v4i pf = sm.p[mt][lane];
-            const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, wave) + 32 * mt * D));
-            const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, wave) + 16 * D + 32 * mt * D));
-            const v4i vop = {t0[0], t0[1], t1[0], t1[1]};
+            pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop[b][mt], pf[b][mt], pacc, 0, 0, 0);
 #pragma unroll
-            for (int vq = 0; vq < 4; ++vq) psum = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[vq]), 0u, psum);
-            pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop, pf, mt == 0 ? acc0 : pacc, 0, 0, 0);
+            for (int vq = 0; vq < 4; ++vq) psum = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[b][mt][vq]), 0u, psum);
         }
-        l = __builtin_fmaf(l, alpha, static_cast<float>(psum));
-        const float alpha_o = VB ? alpha * oscale : alpha;
+        l = __builtin_fmaf(l, alpha, static_cast<float>(psum));                       // line 12
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[v])));
+        for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[v])));   // line 13
+    };
+    const bool works = dt < KS;                                  // D = 64: two d tiles; the other wavefronts only copy
+    stage_group(0);
+    for (int gi = 0; gi <= ngroups; ++gi) {
+        // everything group gi - 1 needs goes to registers first, so that its place in LDS is free after the first barrier
+        float m_before = m2;
+        struct { float v[NB]; } m = {};
+        if (gi > 0 && works) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BC * D);
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, dt) + 32 * mt * D));
+                    const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, dt) + 16 * D + 32 * mt * D));
+                    vop[b][mt] = v4i{t0[0], t0[1], t1[0], t1[1]};
+                    pf[b][mt] = sm.p[b][mt][lane];
+                }
+            }
+            const auto mx = maxima((gi - 1) & 1);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) m.v[b] = mx.v[b];
+            __builtin_amdgcn_sched_barrier(0);
+            block(gi, 0, m_before, m.v[0]);
+        }
+        __syncthreads();
+        if (gi < ngroups) stage_group(gi + 1);
+        if (gi > 0 && works) {
+#pragma unroll
+            for (int b = 1; b < NB; ++b) block(gi, b, m.v[b - 1], m.v[b]);
+        }
+        if (gi < ngroups) {
+            wait_vmcnt<NB * KS>();                               // my part of V of group gi has landed (group gi + 1 may be in flight)
+            __syncthreads();                                     // everyone's has, and P of group gi is in LDS
+        }
     }
-    wait_all_memory();                                           // requests past the last block: nothing of mine stays in flight
+    wait_all_memory();
 
-    // lines 15-17 for d tile `wave` (d = 32 * wave + 8 * (v / 4) + 4 * g + v % 4 of query r)
+    // lines 15-17 for d tile dt (d = 32 * dt + 8 * (v / 4) + 4 * g + v % 4 of query r)
     const float lt = l + swap32(l);
     const float f = (VB ? sv_prev : sVh[0]) * ACC_UNIT / lt;
-    if (q_head < Nq && wave < KS) {
-        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * wave + 4 * g;
+    if (q_head < Nq && dt < KS) {
+        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * dt + 4 * g;
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
             if constexpr (sizeof(OutT) == 2) {
@@ -737,9 +818,12 @@ __global__ __launch_bounds__(THREADS) void splitk_combine_kernel(const float *__
 template <int D, bool CAUSAL, bool VB, typename OutT>
 int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
-    const long wgs = static_cast<long>(heads) * ((Nq + NARROW_BR - 1) / NARROW_BR);
-    hipLaunchKernelGGL((int_flash_attn_fwd_narrow_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0, st,
-                       Q, K, V, sQ, sK, sV, heads, Nq, Nk, static_cast<OutT *>(O));
+    const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, wgs = heads * qgroups;
+    // K and V with the non-temporal hint where each byte is read once and there are more of them than the caches could keep
+    // for the next call (128 heads of 4096 x 128, 134 MB: 26.9 us with the hint, 29.2 without; 32 heads, 34 MB: 25.5 and 22.0)
+    const int once = qgroups == 1 && 2L * heads * Nk * D > (64L << 20);
+    hipLaunchKernelGGL((int_flash_attn_fwd_narrow_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(NARROW_THREADS), 0, st,
+                       Q, K, V, sQ, sK, sV, heads, Nq, Nk, once, static_cast<OutT *>(O));
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 

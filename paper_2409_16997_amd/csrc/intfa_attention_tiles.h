@@ -116,6 +116,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "6-bit counter");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
+// ... and one that waits for every LDS operation of this wavefront, leaving the copies in flight
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
 #endif  // __HIP_DEVICE_COMPILE__
 
 }  // namespace ifa_tiles

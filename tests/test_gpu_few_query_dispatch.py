@@ -1,0 +1,54 @@
+"""The few-query kernel and the fused kernel on the two sides of the dispatcher's rule: the same rows, bit for bit.
+
+A call with many heads runs the fused kernel; the same problem on a few of the heads (or on the last few queries) runs the
+few-query kernel.  Both perform Algorithm 1 with the same operations on the same operands, so torch.equal is the bar; one
+head of each shape is also held to the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# (heads, N): more than 512 groups of 32 queries each, so that the whole call is the fused kernel's.  Lengths at the edges
+# of the 128-key block, of the few-query kernel's group of two blocks and of its 32 queries.
+SHAPES = [(180, 65), (140, 127), (132, 128), (110, 129), (90, 191), (80, 255), (80, 256), (64, 257), (60, 384), (48, 385), (40, 513), (17, 1100)]
+
+
+def problem(heads, N, d, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q8, k8, v8 = (torch.randint(-127, 128, (1, heads, N, d), generator=g, device="cuda", dtype=torch.int8) for _ in range(3))
+    base = (2.0 / (73.3 * 73.3 * d ** 0.5)) ** 0.5
+    sq, sk = (base * (0.5 + torch.rand((1, heads, N), generator=g, device="cuda")) for _ in range(2))
+    return q8, k8, v8, sq, sk
+
+
+@pytest.mark.parametrize("vblock", [False, True])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,N", SHAPES)
+def test_both_kernels_give_the_same_rows(heads, N, d, causal, vblock):
+    import paper_2409_16997_amd as ifa
+    q8, k8, v8, sq, sk = problem(heads, N, d, heads + N)
+    Bc = ifa.block_cols(d, causal)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    sv = 0.005 + 0.02 * torch.rand((1, heads) + ((-(-N // Bc),) if vblock else ()), generator=g, device="cuda")
+    call = lambda q, k, v, a, b, c: ifa.int_flash_attn_fwd(q, k, v, a, b, c, causal=causal, out_dtype=torch.float32)
+    full = call(q8, k8, v8, sq, sk, sv)
+    cut = [t[:, 1:6].contiguous() for t in (q8, k8, v8, sq, sk, sv)]
+    assert torch.equal(call(*cut), full[:, 1:6])
+    for nq in (1, 33, 64):                                       # the last rows only, all heads
+        if causal or nq == 33:
+            few = call(q8[:, :, N - nq:].contiguous(), k8, v8, sq[:, :, N - nq:].contiguous(), sk, sv)
+            if vblock and causal:
+                # a row may share its group with one that sees a block it does not see itself: with one V scale per block
+                # its output then goes through one more change of unit, s_a * rcp(s_b) on the way and s_b for s_a at the end
+                # (four roundings and a 1-ulp reciprocal: below 2^-21 of the value)
+                assert bool(((few - full[:, :, N - nq:]).abs() <= 2.0 ** -21 * full[:, :, N - nq:].abs()).all())
+            else:
+                assert torch.equal(few, full[:, :, N - nq:])
+    n = lambda t: t[0, :1].cpu().numpy()
+    res = oracle.compare_up_to_ties(full[0, 0].cpu().numpy(), n(q8), n(k8), n(v8), n(sq), n(sk), n(sv), causal, Bc)
+    assert float(res["err"].max()) <= 1e-3 * float(res["scale"])
