@@ -74,49 +74,71 @@ def _check(code: int, what: str):
         raise IntfaError(f"{what}: {status_str(code)} ({code})")
 
 
+# What a call costs the host is most of what a short one takes, so the helpers below are kept to the attribute reads they
+# need: pointers go to ctypes as plain integers (an int8 [1, 32, 1, 128] query quantized and attended to: 25 us of Python
+# and launches with c_void_p objects, torch.cuda.current_stream() and torch.empty; 13 us like this).
+
 def _dtype_enum(t):
     import torch
-    try:
-        return {torch.float32: IFA_F32, torch.float16: IFA_F16, torch.bfloat16: IFA_BF16}[t.dtype]
-    except KeyError:
-        raise IntfaError(f"unsupported dtype {t.dtype}") from None
+    dt = t.dtype
+    if dt is torch.float16:
+        return IFA_F16
+    if dt is torch.bfloat16:
+        return IFA_BF16
+    if dt is torch.float32:
+        return IFA_F32
+    raise IntfaError(f"unsupported dtype {dt}")
 
 
 def _dev(t, dtype=None):
+    """Address of a contiguous tensor in GPU memory, of the given dtype if one is named."""
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
         raise IntfaError("expected a contiguous tensor in GPU memory")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise IntfaError(f"expected dtype {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
+    """The raw handle of torch's current stream on the current device (torch.cuda.current_stream() builds an object around
+    it: 3 us)."""
+    from torch import _C
+    return _C._cuda_getCurrentRawStream(_C._cuda_getDevice())
+
+
+def _codes(X):
+    """An int8 tensor of X's shape (X is contiguous)."""
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.empty_like(X, dtype=torch.int8)
+
+
+def _scales(X, shape):
+    import torch
+    return torch.empty(tuple(shape), dtype=torch.float32, device=X.device)
 
 
 def quantize_tokenwise(X, scale_mul=1.0, hadamard=False):
     """X [..., d] fp32/fp16/bf16 on the GPU -> (int8 [..., d], fp32 scale [...] times scale_mul).
     hadamard=True quantizes the Walsh-Hadamard transform H_d x of every row instead of x."""
-    import torch
-    d = X.shape[-1]
+    x = _dev(X)
+    shape = X.shape
+    d = shape[-1]
     rows = X.numel() // d
-    Xq = torch.empty(X.shape, dtype=torch.int8, device=X.device)
-    scale = torch.empty(X.shape[:-1], dtype=torch.float32, device=X.device)
+    Xq, scale = _codes(X), _scales(X, shape[:-1])
     fn = lib().quantize_tokenwise_hadamard if hadamard else lib().quantize_tokenwise_ex
-    _check(fn(_dev(X), _dtype_enum(X), rows, d, _dev(Xq), _dev(scale), float(scale_mul), _stream()), "quantize_tokenwise")
+    _check(fn(x, _dtype_enum(X), rows, d, Xq.data_ptr(), scale.data_ptr(), float(scale_mul), _stream()), "quantize_tokenwise")
     return Xq, scale
 
 
 def quantize_headwise(X, global_scale=False):
     """X [B, H, N, d] (or [heads, N, d]) -> (int8 same shape, fp32 scale [B, H] (or [heads]))."""
-    import torch
-    N, d = X.shape[-2], X.shape[-1]
+    x = _dev(X)
+    shape = X.shape
+    N, d = shape[-2], shape[-1]
     heads = X.numel() // (N * d)
-    Xq = torch.empty(X.shape, dtype=torch.int8, device=X.device)
-    scale = torch.empty(X.shape[:-2], dtype=torch.float32, device=X.device)
-    _check(lib().quantize_headwise_ex(_dev(X), _dtype_enum(X), heads, N, d, _dev(Xq), _dev(scale), int(bool(global_scale)),
+    Xq, scale = _codes(X), _scales(X, shape[:-2])
+    _check(lib().quantize_headwise_ex(x, _dtype_enum(X), heads, N, d, Xq.data_ptr(), scale.data_ptr(), int(bool(global_scale)),
                                       _stream()), "quantize_headwise_ex")
     return Xq, scale
 
@@ -126,16 +148,18 @@ def quantize_qkv(Q, K, V, s_Q_mul=1.0, out=None):
     Q, K, V [B, H, N, d] -> (Q_i8, K_i8, V_i8, s_Q [B, H, N] (times s_Q_mul), s_K [B, H, N], s_V [B, H]);
     out: optional tuple of those six tensors to write into."""
     import torch
-    assert Q.shape == K.shape == V.shape and Q.dtype == K.dtype == V.dtype
-    N, d = Q.shape[-2], Q.shape[-1]
+    shape = Q.shape
+    assert shape == K.shape == V.shape and Q.dtype == K.dtype == V.dtype
+    q, k, v = _dev(Q), _dev(K), _dev(V)
+    N, d = shape[-2], shape[-1]
     heads = Q.numel() // (N * d)
     if out is None:
-        q8, k8, v8 = (torch.empty(Q.shape, dtype=torch.int8, device=Q.device) for _ in range(3))
-        sq, sk = (torch.empty(Q.shape[:-1], dtype=torch.float32, device=Q.device) for _ in range(2))
-        sv = torch.empty(Q.shape[:-2], dtype=torch.float32, device=Q.device)
+        q8, k8, v8 = _codes(Q), _codes(Q), _codes(Q)
+        sq, sv = _scales(Q, shape[:-1]), _scales(Q, shape[:-2])
+        sk = torch.empty_like(sq)
     else:
         q8, k8, v8, sq, sk, sv = out
-    _check(lib().quantize_qkv(_dev(Q), _dev(K), _dev(V), _dtype_enum(Q), heads, N, d, _dev(q8, torch.int8), _dev(k8, torch.int8),
+    _check(lib().quantize_qkv(q, k, v, _dtype_enum(Q), heads, N, d, _dev(q8, torch.int8), _dev(k8, torch.int8),
                               _dev(v8, torch.int8), _dev(sq, torch.float32), _dev(sk, torch.float32), _dev(sv, torch.float32),
                               float(s_Q_mul), _stream()), "quantize_qkv")
     return q8, k8, v8, sq, sk, sv
@@ -145,15 +169,18 @@ def quantize_qk(Q, K, s_Q_mul=1.0, hadamard=False, out=None):
     """Q and K token-level in one launch.  Q, K [..., d] of one shape -> (Q_i8, K_i8, s_Q [...] (times s_Q_mul), s_K [...]);
     out: optional tuple of those four tensors to write into."""
     import torch
-    assert Q.shape == K.shape and Q.dtype == K.dtype
-    d = Q.shape[-1]
+    shape = Q.shape
+    assert shape == K.shape and Q.dtype == K.dtype
+    q, k = _dev(Q), _dev(K)
+    d = shape[-1]
     rows = Q.numel() // d
     if out is None:
-        q8, k8 = (torch.empty(Q.shape, dtype=torch.int8, device=Q.device) for _ in range(2))
-        sq, sk = (torch.empty(Q.shape[:-1], dtype=torch.float32, device=Q.device) for _ in range(2))
+        q8, k8 = _codes(Q), _codes(Q)
+        sq = _scales(Q, shape[:-1])
+        sk = torch.empty_like(sq)
     else:
         q8, k8, sq, sk = out
-    _check(lib().quantize_qk(_dev(Q), _dev(K), _dtype_enum(Q), rows, d, _dev(q8, torch.int8), _dev(k8, torch.int8),
+    _check(lib().quantize_qk(q, k, _dtype_enum(Q), rows, d, _dev(q8, torch.int8), _dev(k8, torch.int8),
                              _dev(sq, torch.float32), _dev(sk, torch.float32), float(s_Q_mul), int(bool(hadamard)), _stream()),
            "quantize_qk")
     return q8, k8, sq, sk
@@ -161,12 +188,12 @@ def quantize_qk(Q, K, s_Q_mul=1.0, hadamard=False, out=None):
 
 def quantize_blockwise(X, block_keys):
     """X [B, H, N, d] (or [heads, N, d]) -> (int8 same shape, fp32 scale [B, H, ceil(N/block_keys)])."""
-    import torch
-    N, d = X.shape[-2], X.shape[-1]
+    x = _dev(X)
+    shape = X.shape
+    N, d = shape[-2], shape[-1]
     heads = X.numel() // (N * d)
-    Xq = torch.empty(X.shape, dtype=torch.int8, device=X.device)
-    scale = torch.empty(tuple(X.shape[:-2]) + (-(-N // block_keys),), dtype=torch.float32, device=X.device)
-    _check(lib().quantize_blockwise(_dev(X), _dtype_enum(X), heads, N, d, int(block_keys), _dev(Xq), _dev(scale), _stream()),
+    Xq, scale = _codes(X), _scales(X, tuple(shape[:-2]) + (-(-N // block_keys),))
+    _check(lib().quantize_blockwise(x, _dtype_enum(X), heads, N, d, int(block_keys), Xq.data_ptr(), scale.data_ptr(), _stream()),
            "quantize_blockwise")
     return Xq, scale
 
@@ -178,10 +205,10 @@ def int_flash_attn_fwd(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out_dtype=
     import torch
     B, H, N, d = Q_i8.shape
     Nk = K_i8.shape[2]
-    if out is None:
-        out = torch.empty((B, H, N, d), dtype=out_dtype or torch.float16, device=Q_i8.device)
     args = (_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_i8, torch.int8),
             _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32))
+    if out is None:
+        out = torch.empty_like(Q_i8, dtype=out_dtype or torch.float16)
     tail = (d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
     if K_i8.shape != (B, H, Nk, d) or V_i8.shape != K_i8.shape or s_K.shape != (B, H, Nk) or s_Q.shape != (B, H, N):
         raise IntfaError("Q/K/V/scale shapes do not agree")
@@ -214,24 +241,22 @@ def int_flash_attn_fwd_splitk(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out
     if K_i8.shape != (B, H, Nk, d) or V_i8.shape != K_i8.shape or s_K.shape != (B, H, Nk) or s_Q.shape != (B, H, N) \
             or s_V.shape != (B, H):
         raise IntfaError("Q/K/V/scale shapes do not agree")
+    ptrs = (_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_i8, torch.int8),
+            _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32))
     if out is None:
-        out = torch.empty((B, H, N, d), dtype=out_dtype or torch.float16, device=Q_i8.device)
+        out = torch.empty_like(Q_i8, dtype=out_dtype or torch.float16)
     need = splitk_workspace_bytes(B, H, N, Nk, d)
     if need == 0:
         raise IntfaError("int_flash_attn_fwd_splitk: shape not supported (at most 32 queries per head, d in {64, 128})")
     if isinstance(workspace, str):
         if workspace != "static":
             raise IntfaError("workspace: a uint8 device tensor, None or 'static'")
-        code = lib().int_flash_attn_fwd_splitk_static(_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_i8, torch.int8),
-                                                      _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32),
-                                                      B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
+        code = lib().int_flash_attn_fwd_splitk_static(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
         _check(code, "int_flash_attn_fwd_splitk_static")
         return out
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=Q_i8.device)
-    code = lib().int_flash_attn_fwd_splitk(_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_i8, torch.int8),
-                                           _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32),
-                                           B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out),
+    code = lib().int_flash_attn_fwd_splitk(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out),
                                            _dev(workspace, torch.uint8), workspace.numel(), _stream())
     _check(code, "int_flash_attn_fwd_splitk")
     return out
@@ -246,14 +271,14 @@ def int_flash_attn_fwd_half(Q_i8, K_i8, V_f16, s_Q, s_K, causal=False, out_dtype
     (Nq = Nk in the paper; under the mask the queries are the last Nq positions).  Returns O [B, H, Nq, d]."""
     import torch
     B, H, N, d = Q_i8.shape
+    ptrs = (_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_f16, torch.float16),
+            _dev(s_Q, torch.float32), _dev(s_K, torch.float32))
     if out is None:
-        out = torch.empty((B, H, N, d), dtype=out_dtype or torch.float16, device=Q_i8.device)
+        out = torch.empty_like(Q_i8, dtype=out_dtype or torch.float16)
     Nk = K_i8.shape[2]
     if K_i8.shape != (B, H, Nk, d) or V_f16.shape != K_i8.shape or s_K.shape != (B, H, Nk) or s_Q.shape != (B, H, N):
         raise IntfaError("Q/K/V/scale shapes do not agree")
-    code = lib().int_flash_attn_fwd_half_rect(_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_f16, torch.float16),
-                                              _dev(s_Q, torch.float32), _dev(s_K, torch.float32),
-                                              B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
+    code = lib().int_flash_attn_fwd_half_rect(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
     _check(code, "int_flash_attn_fwd_half")
     return out
 
