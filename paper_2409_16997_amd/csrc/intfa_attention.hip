@@ -472,22 +472,10 @@ int launch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *s
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 
-// Which calls the few-query kernel of intfa_attention_fewq.hip takes (same results, bit for bit): up to 64 queries per head, and
-// longer ones that would leave the fused kernel's two workgroups per CU mostly empty.  It has four workgroups of 32 queries
-// where the fused kernel has one of 128, one per CU at a time, and walks 256 keys in 1.0 - 1.5 us where a fused workgroup
-// alone on its CU takes 3.3: one wave of 256 workgroups always wins (32 heads x 256 queries x 8192 keys 49 us against 106,
-// 4 x 1024 x 1024 9.9 against 16.6, 32 x 256 x 256 6.6 against 7.4), two waves win on long key sequences (32 x 512 x 8192: 87
-// against 106, 128 x 128 x 4096: 55 against 56) and lose on short ones (64 x 200 x 200: 7.5 against 5.9), three lose
-// (32 x 700 x 8192: 120 against 107).
-inline bool few_queries(int heads, int Nq, int Nk) {
-    const long wgs = static_cast<long>(heads) * ((Nq + 31) / 32);
-    return Nq <= 64 || wgs <= 256 || (wgs <= 512 && Nk >= 2048);
-}
-
 template <int D, bool CAUSAL, bool VB>
 int launch_fwd_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK,
                      const float *sV, int heads, int Nq, int Nk, void *O, int o_dtype, hipStream_t st) {
-    if (few_queries(heads, Nq, Nk))
+    if (ifa_few_queries(heads, Nq, Nk))
         return ifa_launch_narrow(Q, K, V, sQ, sK, sV, heads, Nq, Nk, D, CAUSAL ? 1 : 0, VB ? 1 : 0, O, o_dtype, st);
     switch (o_dtype) {
     case IFA_F32: return launch_fwd<D, CAUSAL, VB, float>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);

@@ -387,9 +387,285 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
 #endif
 }
 
+// ---- few queries, many keys -------------------------------------------------------------------------------------
+// The half-INT8 counterpart of the few-query kernel of intfa_attention_fewq.hip: the wavefronts of a workgroup share one
+// group of 32 queries and take FEW_NB key blocks of 64 keys at a time, in two roles that run one group of blocks apart.
+//   2 FEW_NB S wavefronts (block b of the group, key tile t): lines 9-11 for that tile and its part of l.  A wavefront copies the
+//       K rows it reads itself, two groups ahead, and holds the operands of the next group in registers; the extrema of the tiles
+//       meet in LDS (first barrier), then the weights go to LDS (second barrier);
+//   four PV wavefronts (d tile): O = alpha O + P~ V for the group before, block by block in order, on weights and V^T operands
+//       they have taken to registers by the first barrier; they also copy V, a group ahead.
+// The running maximum in front of each block of 64 keys is that of the sequential walk, so the fp16 weights are those of the
+// kernel above; only l is added up in another order.
+// What bounds it is what one CU takes in (about 60 GB/s: 48 KB per group in 0.8 us at d = 128) and the chain of a group next to
+// it. Three blocks per group fill LDS and measure 4-8 % slower from 128 heads on. 128 heads of 4096 keys, one query: 38.4 us
+// (5.3 TB/s), before 73.9 on the kernel above, which gives such a call one busy wavefront in four; 32 heads of 4099: 30.7, before 73.9;
+// 512 heads: 116, before 144.
+constexpr int FEW_BR = 32;         // queries per workgroup
+constexpr int FEW_NB = 2;          // key blocks per group
+constexpr int FEW_S_WAVES = 2 * FEW_NB;
+constexpr int FEW_THREADS = (FEW_S_WAVES + 4) * 64;
+
+template <int D> struct SmemFewH {
+    alignas(4096) int8_t k[2][FEW_NB][BCH * D];
+    alignas(4096) int8_t v[2][FEW_NB][BCH * D * 2];
+    alignas(128) float sk[2][FEW_S_WAVES][32];            // per S wavefront: the s_K of its key tile
+    alignas(16) v4i p[FEW_NB][NT][2][64];                 // per block, key tile, 16-key step and lane: 8 weights
+    alignas(16) float ext[2][FEW_NB][32][NT];             // per block, query and key tile: the maximum of a (line 10)
+};
+static_assert(sizeof(SmemFewH<128>) <= 160 * 1024, "LDS budget");
+
+template <int D, bool CAUSAL, typename OutT>
+__global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kernel(
+    const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const _Float16 *__restrict__ V,
+    const float *__restrict__ sQ, const float *__restrict__ sK, int heads, int Nq, int Nk, int once, OutT *__restrict__ O) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __shared__ SmemFewH<D> sm;
+    constexpr int KS = D / 32, NB = FEW_NB;
+
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T_c = (Nk + BCH - 1) / BCH;
+    const int qgroups = (Nq + FEW_BR - 1) / FEW_BR;
+    const int shift = CAUSAL ? Nk - Nq : 0;
+    // all query groups of a head on one XCD (workgroups go round-robin over the 8 XCDs by linear id)
+    int head, qg;
+    if ((heads & 7) == 0) { const int s_ = blockIdx.x >> 3; head = (s_ / qgroups) * 8 + (blockIdx.x & 7); qg = s_ % qgroups; }
+    else { head = blockIdx.x / qgroups; qg = blockIdx.x % qgroups; }
+    const int first_q = qg * FEW_BR;
+    const int q_head = first_q + r;
+    const long qrow = static_cast<long>(head) * Nq + min(q_head, Nq - 1);   // rows past Nq: a clamped copy, never stored
+    const float sq2 = sQ[qrow] * LOG2E;
+    const int nblocks = CAUSAL ? min(Nk - 1, min(first_q + FEW_BR, Nq) - 1 + shift) / BCH + 1 : T_c;
+    const int ngroups = (nblocks + NB - 1) / NB;
+    float m2 = -INFINITY;                                        // running maximum in log2 units, kept in step by both roles
+    struct Maxima { float v[NB]; };
+    auto maxima = [&](int parity) {                              // line 10: the running maximum after each block of a group
+        Maxima m;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const float2 e = *reinterpret_cast<const float2 *>(&sm.ext[parity][b][r][0]);
+            m2 = fmaxf(m2, fmaxf(e.x, e.y) * sq2);
+            m.v[b] = m2;
+        }
+        return m;
+    };
+
+    if (wave < FEW_S_WAVES) {
+        // ---- S wavefront: key tile t of block `blk` of every group
+        constexpr int PER_GROUP = KS + 1;                        // copy instructions per group
+        const int t = wave & 1, blk = wave >> 1;
+        const BufRsrc rK = make_rsrc(K + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+        const BufRsrc rSK = make_rsrc(sK + static_cast<long>(head) * Nk, static_cast<unsigned>(Nk) * 4);
+        const lds_ptr kbuf = (lds_ptr)(&sm.k[0][blk][0]);
+        const lds_ptr skbuf = (lds_ptr)(&sm.sk[0][wave][0]);
+        const LaneOffsetsH<D> lo(lane, 2 * t);                   // the pieces of tile t are those of wavefronts 2t, 2t + 1 of the kernel above
+        // this wavefront's 32 rows of K and their s_K: it alone reads what it copies, so its own counted wait orders the
+        // two.  Rows past the end come as zeros and are masked below; a group past the last one is requested nowhere, so
+        // that every group costs PER_GROUP copies.
+        auto stage_group = [&](int gi) {
+            const int jb = gi * NB + blk;
+            const bool real = jb < nblocks;
+            const int koff = real ? jb * BCH * D : NOWHERE_H;
+            const lds_ptr dst = kbuf + (gi & 1) * (NB * BCH * D) + t * (32 * D);
+            if (once) {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) lds_copy16_nt(rK, dst + i * 1024, lo.gk, koff + 1024 * i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) lds_copy16(rK, dst + i * 1024, lo.gk, koff + 1024 * i);
+            }
+            if (g == 0) lds_copy4(rSK, skbuf + (gi & 1) * (FEW_S_WAVES * 128), 4 * r + 128 * t, real ? jb * BCH * 4 : NOWHERE_H);
+        };
+        stage_group(0);
+        stage_group(1);
+        const int8_t *qptr = Q + qrow * D + 16 * g;
+        v4i qf[KS];
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 32 * kk);
+        // landed BEFORE the loop as far as the compiler is concerned: a wait of its own inside the loop would be a wait for
+        // the staged copies as well
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[kk]));
+        v4i kop[KS];
+        v4f skv[4];
+        auto read_group = [&](int gi) {
+            const lds_ptr ks = kbuf + (gi & 1) * (NB * BCH * D), sk = skbuf + (gi & 1) * (FEW_S_WAVES * 128);
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) kop[kk] = *reinterpret_cast<LDS_AS const v4i *>(lds_xor(ks, 32 * kk, lo.k0) + 32 * t * D);
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) skv[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + 16 * g + 32 * vq);
+        };
+        v16i bias;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bias[v] = ACC_BIAS_I;
+        wait_vmcnt<PER_GROUP>();
+        __builtin_amdgcn_sched_barrier(0);
+        read_group(0);
+        wait_lds();
+        __builtin_amdgcn_sched_barrier(0);
+        stage_group(2);                                          // into the place group 0 has left
+        float l = 0.0f, m_own = -INFINITY;                       // this wavefront's part of l and the maximum it refers to
+        for (int gi = 0; gi < ngroups; ++gi) {
+            v16i sacc = bias;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[kk], sacc, 0, 0, 0);
+            const int j0 = (gi * NB + blk) * BCH;
+            const int tail = Nk - 1 - j0;
+            const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;         // kept keys: index inside the block <= klimit
+            const bool masked = CAUSAL ? (j0 + BCH - 1 > min(first_q + shift, Nk - 1)) : (tail < BCH - 1);   // wave-uniform
+            float a[16], bmax = -INFINITY;
+            auto scale = [&](auto with_mask) {
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float x = (__int_as_float(sacc[4 * vq + e]) - ACC_BIAS_F) * skv[vq][e];
+                        if (decltype(with_mask)::value && (32 * t + 8 * vq + 4 * g + e > klimit)) x = -INFINITY;
+                        a[4 * vq + e] = x;
+                        bmax = fmaxf(bmax, x);
+                    }
+            };
+            if (masked) scale(std::true_type{});
+            else scale(std::false_type{});
+            bmax = pair_max(bmax);
+            if (g == 0) sm.ext[gi & 1][blk][r][t] = bmax;
+            __syncthreads();
+            const Maxima m = maxima(gi & 1);
+            wait_vmcnt<PER_GROUP>();                        // group gi + 1 has landed (group gi + 2 may be in flight)
+            __builtin_amdgcn_sched_barrier(0);
+            read_group(gi + 1);
+            float mb = m.v[0];
+#pragma unroll
+            for (int b = 1; b < NB; ++b) mb = blk == b ? m.v[b] : mb;
+            h2 ph[8];
+            float psum = 0.0f;
+            const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const h2 w = {(_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(a[2 * c], sq2, -mb)),
+                              (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(a[2 * c + 1], sq2, -mb))};
+                ph[c] = w;
+                psum = __builtin_amdgcn_fdot2(w, ones, psum, false);
+            }
+            l = __builtin_fmaf(l, __builtin_amdgcn_exp2f(m_own - mb), psum);
+            m_own = mb;
+#pragma unroll
+            for (int s_ = 0; s_ < 2; ++s_) {
+                const h8 pb = {ph[4 * s_][0], ph[4 * s_][1], ph[4 * s_ + 1][0], ph[4 * s_ + 1][1], ph[4 * s_ + 2][0], ph[4 * s_ + 2][1], ph[4 * s_ + 3][0], ph[4 * s_ + 3][1]};
+                sm.p[blk][t][s_][lane] = __builtin_bit_cast(v4i, pb);
+            }
+            wait_lds();
+            __builtin_amdgcn_sched_barrier(0);
+            stage_group(gi + 3);                                 // into the place group gi + 1 has left
+            __syncthreads();
+        }
+        wait_all_memory();                                       // requests past the last group: nothing of mine stays in flight
+        // this wavefront's l on the final maximum; the K rows are free (its own part of them) for the sums
+        l *= __builtin_amdgcn_exp2f(m_own - m2);
+        l += swap32(l);
+        if (g == 0) *reinterpret_cast<LDS_AS float *>(kbuf + t * (32 * D) + 4 * r) = l;
+        __syncthreads();                                         // the PV wavefronts' last group
+        return;
+    }
+
+    // ---- PV wavefront: d tile dt of O^T = V^T P~^T, one group of blocks behind
+    const int dt = wave - FEW_S_WAVES;
+    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D * 2);
+    const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0][0]);
+    const LaneOffsetsH<D> lo(lane, dt);
+    // V of group gi (this wavefront's quarter of every block); a block past the last one is requested nowhere and comes as
+    // zeros, so that every group costs NB * KS copies
+    auto stage_group = [&](int gi) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int jb = gi * NB + b;
+            const int voff = jb < nblocks ? jb * BCH * D * 2 : NOWHERE_H;
+            const lds_ptr dst = vbuf + ((gi & 1) * NB + b) * (BCH * D * 2) + dt * KS * 1024;
+            if (once) {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) lds_copy16_nt(rV, dst + i * 1024, lo.gv, voff + 1024 * i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < KS; ++i) lds_copy16(rV, dst + i * 1024, lo.gv, voff + 1024 * i);
+            }
+        }
+    };
+    v16f o;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] = 0.0f;
+    const bool works = dt < KS;                                  // D = 64: two d tiles; the other wavefronts only copy
+    h8 vop[NB][4], pf[NB][4];
+    auto block = [&](int b, float m_prev, float m_new) {         // (a block past the last one: the maximum stays, the weights are 0)
+        const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[v] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
+    };
+    stage_group(0);
+    for (int gi = 0; gi <= ngroups; ++gi) {
+        const float m_before = m2;
+        Maxima m = {};
+        if (gi > 0 && works) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BCH * D * 2);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const h4 t0 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + 16 * i * (2 * D))));
+                    const h4 t1 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + (16 * i + 8) * (2 * D))));
+                    vop[b][i] = h8{t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
+                    pf[b][i] = __builtin_bit_cast(h8, sm.p[b][i >> 1][i & 1][lane]);
+                }
+            }
+            m = maxima((gi - 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            block(0, m_before, m.v[0]);
+        }
+        __syncthreads();
+        if (gi < ngroups) stage_group(gi + 1);
+        if (gi > 0 && works) {
+#pragma unroll
+            for (int b = 1; b < NB; ++b) block(b, m.v[b - 1], m.v[b]);
+        }
+        if (gi < ngroups) {
+            wait_vmcnt<NB * KS>();                          // my part of V of group gi has landed (group gi + 1 may be in flight)
+            __syncthreads();                                     // everyone's has, and the weights of group gi are in LDS
+        }
+    }
+    wait_all_memory();
+
+    if (q_head < Nq && works) {
+        float l = 0.0f;
+#pragma unroll
+        for (int w = 0; w < FEW_S_WAVES; ++w) l += *reinterpret_cast<const float *>(&sm.k[0][w >> 1][(w & 1) * (32 * D) + 4 * r]);
+        const float f = 1.0f / l;
+        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * dt + 4 * g;
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+            if constexpr (sizeof(OutT) == 2) {
+                *reinterpret_cast<uint2 *>(orow + 8 * vq) = Pack4<OutT>::pack(o[4 * vq] * f, o[4 * vq + 1] * f, o[4 * vq + 2] * f, o[4 * vq + 3] * f);
+            } else {
+                *reinterpret_cast<v4f *>(orow + 8 * vq) = v4f{o[4 * vq] * f, o[4 * vq + 1] * f, o[4 * vq + 2] * f, o[4 * vq + 3] * f};
+            }
+        }
+    }
+#endif
+}
+
 template <int D, bool CAUSAL, typename OutT>
 int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float *sQ, const float *sK, int heads, int Nq, int Nk,
                 void *O, hipStream_t st) {
+    // as for INT8: 32 heads x 256 queries x 8192 keys 67 us against 145 on the kernel below, x 512: 128 and 145, x 700: 184 and
+    // 146; 512 heads x 32 x 2048: 66 and 79, x 64: 94 and 81
+    if (ifa_few_queries(heads, Nq, Nk)) {
+        const long qgroups = (Nq + FEW_BR - 1) / FEW_BR;
+        const int once = qgroups == 1 && 3L * heads * Nk * D > (64L << 20);   // the rule of launch_narrow in intfa_attention_fewq.hip
+        hipLaunchKernelGGL((int_flash_attn_fwd_half_few_kernel<D, CAUSAL, OutT>), dim3(static_cast<unsigned>(heads * qgroups)), dim3(FEW_THREADS), 0,
+                           st, Q, K, V, sQ, sK, heads, Nq, Nk, once, static_cast<OutT *>(O));
+        return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+    }
     const long wgs = static_cast<long>(heads) * ((Nq + BR - 1) / BR);
     // T_r = 0: under the mask this kernel keeps 4 heads per group (8 measured 4-17 % slower here at N = 1280 .. 2048)
     hipLaunchKernelGGL((int_flash_attn_fwd_half_kernel<D, CAUSAL, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,

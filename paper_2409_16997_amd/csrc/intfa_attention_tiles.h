@@ -109,15 +109,6 @@ __device__ __forceinline__ void prefetch_sk(const Prefetch &nx, int wave, int la
     // scales start at an arbitrary 4-byte boundary when N is not a multiple of 4.
     if (wave >= 2) lds_copy4(nx.sk, nx.lsk + 256 * (wave - 2), 4 * lane + 256 * (wave - 2), nx.skoff);
 }
-
-
-// s_waitcnt that waits only for the vector-memory counter to drop to n (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "6-bit counter");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-// ... and one that waits for every LDS operation of this wavefront, leaving the copies in flight
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
 #endif  // __HIP_DEVICE_COMPILE__
 
 }  // namespace ifa_tiles

@@ -111,6 +111,14 @@ __device__ __forceinline__ lds_ptr lds_xor(lds_ptr base, unsigned step, unsigned
 // every outstanding memory operation of this wavefront has completed (vmcnt = expcnt = lgkmcnt = 0)
 __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0); }
 
+// s_waitcnt that waits only for the vector-memory counter to drop to n (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "6-bit counter");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+// ... and one that waits for every LDS operation of this wavefront, leaving the copies in flight
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
+
 // a value that is the same in every lane, moved to a scalar register
 __device__ __forceinline__ float uniform(float x) {
     return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));

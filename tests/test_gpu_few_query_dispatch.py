@@ -39,8 +39,8 @@ def test_both_kernels_give_the_same_rows(heads, N, d, causal, vblock):
     full = call(q8, k8, v8, sq, sk, sv)
     cut = [t[:, 1:6].contiguous() for t in (q8, k8, v8, sq, sk, sv)]
     assert torch.equal(call(*cut), full[:, 1:6])
-    for nq in (1, 33, 64):                                       # the last rows only, all heads
-        if causal or nq == 33:
+    for nq in (1, 31, 32):                                       # the last rows only, all heads
+        if causal or nq == 31:
             few = call(q8[:, :, N - nq:].contiguous(), k8, v8, sq[:, :, N - nq:].contiguous(), sk, sv)
             if vblock and causal:
                 # a row may share its group with one that sees a block it does not see itself: with one V scale per block
@@ -52,3 +52,26 @@ def test_both_kernels_give_the_same_rows(heads, N, d, causal, vblock):
     n = lambda t: t[0, :1].cpu().numpy()
     res = oracle.compare_up_to_ties(full[0, 0].cpu().numpy(), n(q8), n(k8), n(v8), n(sq), n(sk), n(sv), causal, Bc)
     assert float(res["err"].max()) <= 1e-3 * float(res["scale"])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,N", SHAPES + [(300, 33), (100, 192), (80, 193)])
+def test_half_int8_kernels_agree(heads, N, d, causal):
+    # Same weights, same order of the MFMA sums; only l is added up in another order: at most one fp32 rounding per block of
+    # 64 keys and wavefront on either side (plus the last products), relative to l.
+    import paper_2409_16997_amd as ifa
+    q8, k8, v8, sq, sk = problem(heads, N, d, heads + N)
+    v = v8.to(torch.float16) / 64
+    call = lambda q, k, x, a, b: ifa.int_flash_attn_fwd_half(q, k, x, a, b, causal=causal, out_dtype=torch.float32)
+    full = call(q8, k8, v, sq, sk)
+    bound = (2 * N / 64 + 24) * 2.0 ** -24
+    cut = [t[:, 1:5].contiguous() for t in (q8, k8, v, sq, sk)]
+    assert bool(((call(*cut) - full[:, 1:5]).abs() <= bound * full[:, 1:5].abs()).all())
+    for nq in (1, 31, 32):
+        few, ref = call(q8[:, :, N - nq:].contiguous(), k8, v, sq[:, :, N - nq:].contiguous(), sk), full[:, :, N - nq:]
+        assert bool(((few - ref).abs() <= bound * ref.abs()).all())
+    n = lambda t: t[0, :1].cpu().numpy()
+    ref = oracle.int_flash_attn_fwd_half(n(q8), n(k8), n(v), n(sq), n(sk), causal, ifa.block_cols_half(d, causal))["O"]
+    few = call(*[t[:, :1].contiguous() for t in (q8, k8, v, sq, sk)])[0, 0].cpu().numpy()
+    assert np.abs(few - ref).max() <= 1e-3 * np.abs(ref).max()
