@@ -35,8 +35,11 @@ using namespace ifa_tiles;
 //       operands to registers by the first barrier, which frees both places in LDS, and also copy V, a group ahead.
 // What bounds it: one CU takes in about 60 GB/s however many copies are in flight (a plain streaming kernel measures 59-61
 // with 32 workgroups), which is 1.07 us per group of 64 KB at d = 128; the chain MFMA - scale - exchange - exp - exchange of a
-// group takes 1.0 us.  One block at a time by four wavefronts took 1.29 us per 32 KB.  32 heads of 4099 keys, one query:
-// 22 us, before 42.5; 128 heads of 16384: 93 us (5.8 TB/s), before 144; 512 of 8192: 153 us (7.0 TB/s), before 183.
+// group takes 1.0 us.  One block at a time by four wavefronts took 1.29 us per 32 KB.  DS = 2 (d = 128): two workgroups per
+// (head, query group), each with half of the d columns of V and O.  Both compute the scores; K and the lines of V are then
+// read twice, but by CUs of one XCD at about the same time, so memory sees them once, and each CU takes in 48 KB per group.
+// 32 heads of 4099 keys, one query: 21 us (without DS = 2 23.7, the former kernel 42.5); 128 heads of 16384: 89.5 us = 6.0 TB/s (95,
+// 144); 512 of 4096 (DS = 1): 79 us = 6.8 TB/s.
 // Every number is computed by the same instruction sequence on the same operands as in the fused kernel (the
 // integer sums are exact, the extremum is order-independent, the row sum l is taken over the same P dwords), so
 // the output is bit-identical to the corresponding rows of a square call: still Algorithm 1 at B_c = 128.
@@ -45,33 +48,46 @@ constexpr int NARROW_NB = 2;       // key blocks per group
 constexpr int NARROW_S_WAVES = 4 * NARROW_NB;
 constexpr int NARROW_THREADS = (NARROW_S_WAVES + 4) * 64;
 
-template <int D> struct SmemNarrow {
+template <int D, int DS> struct SmemNarrow {
     alignas(4096) int8_t k[2][NARROW_NB][BC * D];
-    alignas(4096) int8_t v[2][NARROW_NB][BC * D];
+    alignas(4096) int8_t v[2][NARROW_NB][BC * (D / DS)];
     alignas(256) float sk[2][NARROW_NB * 4][64];          // per S wavefront: the 32 s_K of its key tile (+ 32 unused)
     alignas(16) v4i p[NARROW_NB][4][64];                  // per block, key tile and lane: the 16 P bytes of that lane (line 11)
     alignas(16) float ext[2][NARROW_NB][32][4];           // per block, query and key tile: the extremum of a (line 10)
 };
-static_assert(sizeof(SmemNarrow<128>) <= 160 * 1024, "LDS budget");
+static_assert(sizeof(SmemNarrow<128, 1>) <= 160 * 1024, "LDS budget");
 
-template <int D, bool CAUSAL, bool VB, typename OutT>
+template <int D, bool CAUSAL, bool VB, typename OutT, int DS>
 __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_kernel(
     const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
     const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
     int heads, int Nq, int Nk, int once, OutT *__restrict__ O) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __shared__ SmemNarrow<D> sm;
-    constexpr int KS = D / 32, NB = NARROW_NB;
+    __shared__ SmemNarrow<D, DS> sm;
+    constexpr int KS = D / 32, NB = NARROW_NB, DV = D / DS;
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T_c = (Nk + BC - 1) / BC;
     const int qgroups = (Nq + NARROW_BR - 1) / NARROW_BR;
     const int shift = CAUSAL ? Nk - Nq : 0;
-    // all query groups of a head on one XCD (workgroups go round-robin over the 8 XCDs by linear id)
-    int head, qg;
-    if ((heads & 7) == 0) { const int s_ = blockIdx.x >> 3; head = (s_ / qgroups) * 8 + (blockIdx.x & 7); qg = s_ % qgroups; }
-    else { head = blockIdx.x / qgroups; qg = blockIdx.x % qgroups; }
+    // Workgroups go round-robin over the 8 XCDs by linear id.  With whole eights of heads all workgroups of a head run on one
+    // XCD; otherwise the query groups are spread over all of them, the DS halves of one (8 apart) still on the same.  The
+    // grid is padded to whole eights.
+    int head, qg, half;
+    if ((heads & 7) == 0) {
+        const int unit = blockIdx.x >> 3, in_head = unit % (qgroups * DS);
+        head = unit / (qgroups * DS) * 8 + (blockIdx.x & 7);
+        qg = in_head / DS;
+        half = in_head % DS;
+    } else {
+        const int group = blockIdx.x / (8 * DS) * 8 + (blockIdx.x & 7);
+        if (group >= heads * qgroups) return;
+        head = group / qgroups;
+        qg = group % qgroups;
+        half = (blockIdx.x >> 3) % DS;
+    }
+    const int col0 = half * DV;                                  // first column of V and O
     const int first_q = qg * NARROW_BR;
     const int q_head = first_q + r;
     const long qrow = static_cast<long>(head) * Nq + min(q_head, Nq - 1);   // rows past Nq: a clamped copy, never stored
@@ -83,8 +99,9 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc0[v] = ACC_START_I;
     // line 10 for the four blocks of a group: the running maximum after each; leaves m2 at the last
+    struct Maxima { float v[NB]; };
     auto maxima = [&](int parity) {
-        struct { float v[NB]; } m;
+        Maxima m;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const v4f e = *reinterpret_cast<const v4f *>(&sm.ext[parity][b][r][0]);
@@ -143,13 +160,14 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
         __builtin_amdgcn_sched_barrier(0);
         read_group(0);
         wait_lds();
-        __builtin_amdgcn_sched_barrier(0);
-        stage_group(2);                                          // into the place group 0 has left
         for (int gi = 0; gi < ngroups; ++gi) {                   // line 7
             // line 9, integer part
             v16i sacc = acc0;
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[kk], sacc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            stage_group(gi + 2);                                 // under the MFMAs, into the place group gi has left
+            __builtin_amdgcn_sched_barrier(0);
             // line 9, fp32 part, and the extrema; kept keys: index inside the block <= klimit (the causal diagonal, the
             // ragged end of the sequence, a block past the last one)
             const int j0 = (gi * NB + blk) * BC;
@@ -188,9 +206,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
                 pw[vq] = static_cast<int>(pack_p4(x));
             }
             sm.p[blk][t][lane] = pw;
-            wait_lds();
-            __builtin_amdgcn_sched_barrier(0);
-            stage_group(gi + 3);                                 // into the place group gi + 1 has left
+            wait_lds();                                          // (the operands of group gi + 1 are in registers too)
             __syncthreads();
         }
         wait_all_memory();                                       // requests past the last group: nothing of mine stays in flight
@@ -202,16 +218,27 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     const int dt = wave - NARROW_S_WAVES;
     const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
     const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0][0]);
-    const LaneOffsets<D> lo(lane, dt);
+    const LaneOffsets<DV> lo(lane, dt);
+    // With DS = 2 a row of the tile is a half row of V: the copies of LaneOffsets<DV> with the row stride of V (a piece is
+    // 1024 / DV = 16 rows, which its swizzle does not see).
+    constexpr int PIECES = DV / 32;
+    const int srow = dt * 32 + lane / (DV / 16);
+    const unsigned gvs = srow * D + col0 + 16 * ((lane % (DV / 16)) ^ v_swz<DV>(srow));
     // V of group gi (this wavefront's quarter of every block); a block past the last one is requested nowhere and comes as
-    // zeros, so that every group costs NB * KS copies
+    // zeros, so that every group costs NB * PIECES copies
     auto stage_blocks = [&](int gi, auto nt) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int jb = gi * NB + b;
-            const Prefetch pf = {rV, rV, rV, jb < nblocks ? jb * BC * D : NOWHERE, NOWHERE, vbuf, vbuf + ((gi & 1) * NB + b) * (BC * D), vbuf};
+            const int voff = jb < nblocks ? jb * BC * D : NOWHERE;
+            const lds_ptr dst = vbuf + ((gi & 1) * NB + b) * (BC * DV);
+            const Prefetch pf = {rV, rV, rV, voff, NOWHERE, vbuf, dst, vbuf};
 #pragma unroll
-            for (int i = 0; i < KS; ++i) prefetch_v_piece<D, decltype(nt)::value>(pf, lo, dt, i);
+            for (int i = 0; i < PIECES; ++i) {
+                if constexpr (DS == 1) prefetch_v_piece<D, decltype(nt)::value>(pf, lo, dt, i);
+                else if constexpr (decltype(nt)::value) lds_copy16_nt(rV, dst + (dt * PIECES + i) * 1024, gvs, voff + i * (1024 / DV) * D);
+                else lds_copy16(rV, dst + (dt * PIECES + i) * 1024, gvs, voff + i * (1024 / DV) * D);
+            }
         }
     };
     auto stage_group = [&](int gi) {
@@ -224,62 +251,61 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     // s_V: one scalar per head, or (VB) one per key block of this head, read through the scalar cache
     const float *sVh = VB ? sV + static_cast<long>(head) * T_c : sV + head;
     float sv_prev = 1.0f;
-    // lines 12, 13 for block b of group gi - 1 on operands in registers.  (A block past the last one: the maximum stays, P is
-    // 0, nothing changes.)
-    v4i pf[NB][4], vop[NB][4];
-    auto block = [&](int gi, int b, float m_prev, float m_new) {
-        const int jb = (gi - 1) * NB + b;
-        const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
-        float alpha_o = alpha;
-        if (VB && jb < nblocks) {                                // one V scale per key block: the running output is kept in units of the current block's
-            const float sv_j = uniform(sVh[jb]);
-            alpha_o = alpha * uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j));
-            sv_prev = sv_j;
-        }
-        v16i pacc = acc0;
-        uint32_t psum = 0;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop[b][mt], pf[b][mt], pacc, 0, 0, 0);
-#pragma unroll
-            for (int vq = 0; vq < 4; ++vq) psum = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[b][mt][vq]), 0u, psum);
-        }
-        l = __builtin_fmaf(l, alpha, static_cast<float>(psum));                       // line 12
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[v])));   // line 13
-    };
-    const bool works = dt < KS;                                  // D = 64: two d tiles; the other wavefronts only copy
+    const bool works = dt < PIECES;                              // two d tiles in a half (or D = 64): the other wavefronts only copy
     stage_group(0);
     for (int gi = 0; gi <= ngroups; ++gi) {
-        // everything group gi - 1 needs goes to registers first, so that its place in LDS is free after the first barrier
-        float m_before = m2;
-        struct { float v[NB]; } m = {};
+        // Everything group gi - 1 needs goes to registers first, so that its place in LDS is free after the first barrier.
+        // (A block past the last one: the maximum stays, P is 0, nothing changes.)
+        const float m_before = m2;
+        Maxima m = {};
+        v16i pacc[NB];
+        uint32_t psum[NB] = {};
         if (gi > 0 && works) {
+            v4i pf[NB][4], vop[NB][4];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BC * D);
+                const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BC * DV);
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt) {
-                    const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, dt) + 32 * mt * D));
-                    const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, dt) + 16 * D + 32 * mt * D));
+                    const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<DV>(vs, lo, dt) + 32 * mt * DV));
+                    const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<DV>(vs, lo, dt) + 16 * DV + 32 * mt * DV));
                     vop[b][mt] = v4i{t0[0], t0[1], t1[0], t1[1]};
                     pf[b][mt] = sm.p[b][mt][lane];
                 }
             }
-            const auto mx = maxima((gi - 1) & 1);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) m.v[b] = mx.v[b];
+            m = maxima((gi - 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
-            block(gi, 0, m_before, m.v[0]);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) pacc[b] = acc0;
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) pacc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop[b][mt], pf[b][mt], pacc[b], 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) psum[b] = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[b][i >> 2][i & 3]), 0u, psum[b]);
         }
         __syncthreads();
         if (gi < ngroups) stage_group(gi + 1);
         if (gi > 0 && works) {
 #pragma unroll
-            for (int b = 1; b < NB; ++b) block(gi, b, m.v[b - 1], m.v[b]);
+            for (int b = 0; b < NB; ++b) {
+                const int jb = (gi - 1) * NB + b;
+                const float alpha = __builtin_amdgcn_exp2f((b == 0 ? m_before : m.v[b == 0 ? 0 : b - 1]) - m.v[b]);
+                float alpha_o = alpha;
+                if (VB && jb < nblocks) {                        // one V scale per key block: the running output is kept in units of the current block's
+                    const float sv_j = uniform(sVh[jb]);
+                    alpha_o = alpha * uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j));
+                    sv_prev = sv_j;
+                }
+                l = __builtin_fmaf(l, alpha, static_cast<float>(psum[b]));            // line 12
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[b][v])));   // line 13
+            }
         }
         if (gi < ngroups) {
-            wait_vmcnt<NB * KS>();                               // my part of V of group gi has landed (group gi + 1 may be in flight)
+            wait_vmcnt<NB * PIECES>();                           // my part of V of group gi has landed (group gi + 1 may be in flight)
             __syncthreads();                                     // everyone's has, and P of group gi is in LDS
         }
     }
@@ -288,8 +314,8 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     // lines 15-17 for d tile dt (d = 32 * dt + 8 * (v / 4) + 4 * g + v % 4 of query r)
     const float lt = l + swap32(l);
     const float f = (VB ? sv_prev : sVh[0]) * ACC_UNIT / lt;
-    if (q_head < Nq && dt < KS) {
-        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * dt + 4 * g;
+    if (q_head < Nq && works) {
+        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + col0 + 32 * dt + 4 * g;
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
             if constexpr (sizeof(OutT) == 2) {
@@ -818,12 +844,20 @@ __global__ __launch_bounds__(THREADS) void splitk_combine_kernel(const float *__
 template <int D, bool CAUSAL, bool VB, typename OutT>
 int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
-    const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, wgs = heads * qgroups;
+    const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
     // K and V with the non-temporal hint where each byte is read once and there are more of them than the caches could keep
-    // for the next call (128 heads of 4096 x 128, 134 MB: 26.9 us with the hint, 29.2 without; 32 heads, 34 MB: 25.5 and 22.0)
+    // for the next call (128 heads of 4096 x 128, 134 MB: 26.9 us with the hint, 29.2 without; 32 heads, 34 MB: 25.5 and 22.0; DS = 1)
     const int once = qgroups == 1 && 2L * heads * Nk * D > (64L << 20);
-    hipLaunchKernelGGL((int_flash_attn_fwd_narrow_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(NARROW_THREADS), 0, st,
-                       Q, K, V, sQ, sK, sV, heads, Nq, Nk, once, static_cast<OutT *>(O));
+    auto launch = [&](auto ds) {
+        constexpr int DS = decltype(ds)::value;
+        hipLaunchKernelGGL((int_flash_attn_fwd_narrow_kernel<D, CAUSAL, VB, OutT, DS>), dim3(static_cast<unsigned>(padded * DS)), dim3(NARROW_THREADS), 0,
+                           st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, once, static_cast<OutT *>(O));
+    };
+    if constexpr (D == 128) {
+        // two workgroups per query group as long as each then has a CU of its own
+        if (heads * qgroups <= 128) launch(std::integral_constant<int, 2>{});
+        else launch(std::integral_constant<int, 1>{});
+    } else launch(std::integral_constant<int, 1>{});
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 

@@ -12,7 +12,7 @@ hipStream_t ifa_current_stream();
 // would leave the fused kernel's two workgroups per CU mostly empty.  They have four workgroups of 32 queries where the
 // fused kernel has one of 128, one per CU at a time, and walk 256 keys in 1.0 - 1.5 us where a fused workgroup alone on its
 // CU takes 3.3: one wave of 256 workgroups always wins (32 heads x 256 queries x 8192 keys 49 us against 106,
-// 4 x 1024 x 1024 9.9 against 16.6, 32 x 256 x 256 6.6 against 7.4), two waves win on long key sequences (32 x 512 x 8192: 87
+// 4 x 1024 x 1024 9.0 against 16.6, 32 x 256 x 256 6.6 against 7.4), two waves win on long key sequences (32 x 512 x 8192: 79
 // against 106, 256 x 64 x 2048: 37 and 37) and lose on short ones (64 x 200 x 200: 7.5 against 5.9), more lose
 // (32 x 700 x 8192: 120 against 107, 512 x 64 x 2048: 71 against 59).
 static inline bool ifa_few_queries(int heads, int Nq, int Nk) {
