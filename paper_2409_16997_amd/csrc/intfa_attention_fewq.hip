@@ -71,22 +71,8 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     const int T_c = (Nk + BC - 1) / BC;
     const int qgroups = (Nq + NARROW_BR - 1) / NARROW_BR;
     const int shift = CAUSAL ? Nk - Nq : 0;
-    // Workgroups go round-robin over the 8 XCDs by linear id.  With whole eights of heads all workgroups of a head run on one
-    // XCD; otherwise the query groups are spread over all of them, the DS halves of one (8 apart) still on the same.  The
-    // grid is padded to whole eights.
     int head, qg, half;
-    if ((heads & 7) == 0) {
-        const int unit = blockIdx.x >> 3, in_head = unit % (qgroups * DS);
-        head = unit / (qgroups * DS) * 8 + (blockIdx.x & 7);
-        qg = in_head / DS;
-        half = in_head % DS;
-    } else {
-        const int group = blockIdx.x / (8 * DS) * 8 + (blockIdx.x & 7);
-        if (group >= heads * qgroups) return;
-        head = group / qgroups;
-        qg = group % qgroups;
-        half = (blockIdx.x >> 3) % DS;
-    }
+    if (!map_query_group<DS>(blockIdx.x, heads, qgroups, head, qg, half)) return;
     const int col0 = half * DV;                                  // first column of V and O
     const int first_q = qg * NARROW_BR;
     const int q_head = first_q + r;

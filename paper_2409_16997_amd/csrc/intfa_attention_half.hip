@@ -398,40 +398,40 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
 // The running maximum in front of each block of 64 keys is that of the sequential walk, so the fp16 weights are those of the
 // kernel above; only l is added up in another order.
 // What bounds it is what one CU takes in (about 60 GB/s: 48 KB per group in 0.8 us at d = 128) and the chain of a group next to
-// it. Three blocks per group fill LDS and measure 4-8 % slower from 128 heads on. 128 heads of 4096 keys, one query: 38.4 us
-// (5.3 TB/s), before 73.9 on the kernel above, which gives such a call one busy wavefront in four; 32 heads of 4099: 30.7, before 73.9;
-// 512 heads: 116, before 144.
+// it.  Three blocks per group fill LDS and measure 4-8 % slower from 128 heads on.  DS = 2 (d = 128): two workgroups per query
+// group, each with half of the d columns, as in the INT8 kernel (32 KB per group and CU).  One query against 4096 keys: 128
+// heads 33.2 us = 6.1 TB/s (DS = 1: 38.6; 73.9 on the kernel above, which gives such a call one busy wavefront in four), 32 heads
+// of 4099 28.9 (30.7, 73.9), 512 heads (DS = 1) 117 (144).
 constexpr int FEW_BR = 32;         // queries per workgroup
 constexpr int FEW_NB = 2;          // key blocks per group
 constexpr int FEW_S_WAVES = 2 * FEW_NB;
 constexpr int FEW_THREADS = (FEW_S_WAVES + 4) * 64;
 
-template <int D> struct SmemFewH {
+template <int D, int DS> struct SmemFewH {
     alignas(4096) int8_t k[2][FEW_NB][BCH * D];
-    alignas(4096) int8_t v[2][FEW_NB][BCH * D * 2];
+    alignas(4096) int8_t v[2][FEW_NB][BCH * (D / DS) * 2];
     alignas(128) float sk[2][FEW_S_WAVES][32];            // per S wavefront: the s_K of its key tile
     alignas(16) v4i p[FEW_NB][NT][2][64];                 // per block, key tile, 16-key step and lane: 8 weights
     alignas(16) float ext[2][FEW_NB][32][NT];             // per block, query and key tile: the maximum of a (line 10)
 };
-static_assert(sizeof(SmemFewH<128>) <= 160 * 1024, "LDS budget");
+static_assert(sizeof(SmemFewH<128, 1>) <= 160 * 1024, "LDS budget");
 
-template <int D, bool CAUSAL, typename OutT>
+template <int D, bool CAUSAL, typename OutT, int DS>
 __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kernel(
     const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const _Float16 *__restrict__ V,
     const float *__restrict__ sQ, const float *__restrict__ sK, int heads, int Nq, int Nk, int once, OutT *__restrict__ O) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __shared__ SmemFewH<D> sm;
-    constexpr int KS = D / 32, NB = FEW_NB;
+    __shared__ SmemFewH<D, DS> sm;
+    constexpr int KS = D / 32, NB = FEW_NB, DV = D / DS;
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T_c = (Nk + BCH - 1) / BCH;
     const int qgroups = (Nq + FEW_BR - 1) / FEW_BR;
     const int shift = CAUSAL ? Nk - Nq : 0;
-    // all query groups of a head on one XCD (workgroups go round-robin over the 8 XCDs by linear id)
-    int head, qg;
-    if ((heads & 7) == 0) { const int s_ = blockIdx.x >> 3; head = (s_ / qgroups) * 8 + (blockIdx.x & 7); qg = s_ % qgroups; }
-    else { head = blockIdx.x / qgroups; qg = blockIdx.x % qgroups; }
+    int head, qg, half;
+    if (!map_query_group<DS>(blockIdx.x, heads, qgroups, head, qg, half)) return;
+    const int col0 = half * DV;                                  // first column of V and O
     const int first_q = qg * FEW_BR;
     const int q_head = first_q + r;
     const long qrow = static_cast<long>(head) * Nq + min(q_head, Nq - 1);   // rows past Nq: a clamped copy, never stored
@@ -503,13 +503,14 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
         __builtin_amdgcn_sched_barrier(0);
         read_group(0);
         wait_lds();
-        __builtin_amdgcn_sched_barrier(0);
-        stage_group(2);                                          // into the place group 0 has left
         float l = 0.0f, m_own = -INFINITY;                       // this wavefront's part of l and the maximum it refers to
         for (int gi = 0; gi < ngroups; ++gi) {
             v16i sacc = bias;
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[kk], sacc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            stage_group(gi + 2);                                 // under the MFMAs, into the place group gi has left
+            __builtin_amdgcn_sched_barrier(0);
             const int j0 = (gi * NB + blk) * BCH;
             const int tail = Nk - 1 - j0;
             const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;         // kept keys: index inside the block <= klimit
@@ -555,9 +556,7 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
                 const h8 pb = {ph[4 * s_][0], ph[4 * s_][1], ph[4 * s_ + 1][0], ph[4 * s_ + 1][1], ph[4 * s_ + 2][0], ph[4 * s_ + 2][1], ph[4 * s_ + 3][0], ph[4 * s_ + 3][1]};
                 sm.p[blk][t][s_][lane] = __builtin_bit_cast(v4i, pb);
             }
-            wait_lds();
-            __builtin_amdgcn_sched_barrier(0);
-            stage_group(gi + 3);                                 // into the place group gi + 1 has left
+            wait_lds();                                          // (the operands of group gi + 1 are in registers too)
             __syncthreads();
         }
         wait_all_memory();                                       // requests past the last group: nothing of mine stays in flight
@@ -573,28 +572,33 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
     const int dt = wave - FEW_S_WAVES;
     const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D * 2);
     const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0][0]);
-    const LaneOffsetsH<D> lo(lane, dt);
+    const LaneOffsetsH<DV> lo(lane, dt);
+    // With DS = 2 a row of the tile is a half row of V: the copies of LaneOffsetsH<DV> with the row stride of V (a piece is
+    // 512 / DV = 8 rows, which its swizzle does not see).
+    constexpr int PIECES = DV / 32;
+    const int srow = dt * 16 + lane / (DV / 8);
+    const unsigned gvs = DS == 1 ? lo.gv : srow * (2 * D) + 2 * col0 + 16 * ((lane % (DV / 8)) ^ (vh_swz<DV>(srow) << 2));
     // V of group gi (this wavefront's quarter of every block); a block past the last one is requested nowhere and comes as
-    // zeros, so that every group costs NB * KS copies
+    // zeros, so that every group costs NB * PIECES copies
     auto stage_group = [&](int gi) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int jb = gi * NB + b;
             const int voff = jb < nblocks ? jb * BCH * D * 2 : NOWHERE_H;
-            const lds_ptr dst = vbuf + ((gi & 1) * NB + b) * (BCH * D * 2) + dt * KS * 1024;
+            const lds_ptr dst = vbuf + ((gi & 1) * NB + b) * (BCH * DV * 2) + dt * PIECES * 1024;
             if (once) {
 #pragma unroll
-                for (int i = 0; i < KS; ++i) lds_copy16_nt(rV, dst + i * 1024, lo.gv, voff + 1024 * i);
+                for (int i = 0; i < PIECES; ++i) lds_copy16_nt(rV, dst + i * 1024, gvs, voff + 1024 * DS * i);
             } else {
 #pragma unroll
-                for (int i = 0; i < KS; ++i) lds_copy16(rV, dst + i * 1024, lo.gv, voff + 1024 * i);
+                for (int i = 0; i < PIECES; ++i) lds_copy16(rV, dst + i * 1024, gvs, voff + 1024 * DS * i);
             }
         }
     };
     v16f o;
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[v] = 0.0f;
-    const bool works = dt < KS;                                  // D = 64: two d tiles; the other wavefronts only copy
+    const bool works = dt < PIECES;                              // two d tiles in a half (or D = 64): the other wavefronts only copy
     h8 vop[NB][4], pf[NB][4];
     auto block = [&](int b, float m_prev, float m_new) {         // (a block past the last one: the maximum stays, the weights are 0)
         const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
@@ -610,11 +614,11 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
         if (gi > 0 && works) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BCH * D * 2);
+                const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BCH * DV * 2);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const h4 t0 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + 16 * i * (2 * D))));
-                    const h4 t1 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + (16 * i + 8) * (2 * D))));
+                    const h4 t0 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + 16 * i * (2 * DV))));
+                    const h4 t1 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + (16 * i + 8) * (2 * DV))));
                     vop[b][i] = h8{t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
                     pf[b][i] = __builtin_bit_cast(h8, sm.p[b][i >> 1][i & 1][lane]);
                 }
@@ -630,7 +634,7 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
             for (int b = 1; b < NB; ++b) block(b, m.v[b - 1], m.v[b]);
         }
         if (gi < ngroups) {
-            wait_vmcnt<NB * KS>();                          // my part of V of group gi has landed (group gi + 1 may be in flight)
+            wait_vmcnt<NB * PIECES>();                        // my part of V of group gi has landed (group gi + 1 may be in flight)
             __syncthreads();                                     // everyone's has, and the weights of group gi are in LDS
         }
     }
@@ -641,7 +645,7 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
 #pragma unroll
         for (int w = 0; w < FEW_S_WAVES; ++w) l += *reinterpret_cast<const float *>(&sm.k[0][w >> 1][(w & 1) * (32 * D) + 4 * r]);
         const float f = 1.0f / l;
-        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * dt + 4 * g;
+        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + col0 + 32 * dt + 4 * g;
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
             if constexpr (sizeof(OutT) == 2) {
@@ -657,13 +661,21 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
 template <int D, bool CAUSAL, typename OutT>
 int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float *sQ, const float *sK, int heads, int Nq, int Nk,
                 void *O, hipStream_t st) {
-    // as for INT8: 32 heads x 256 queries x 8192 keys 67 us against 145 on the kernel below, x 512: 128 and 145, x 700: 184 and
+    // as for INT8: 32 heads x 256 queries x 8192 keys 64 us against 145 on the kernel below, x 512: 119 and 145, x 700: 184 and
     // 146; 512 heads x 32 x 2048: 66 and 79, x 64: 94 and 81
     if (ifa_few_queries(heads, Nq, Nk)) {
-        const long qgroups = (Nq + FEW_BR - 1) / FEW_BR;
+        const long qgroups = (Nq + FEW_BR - 1) / FEW_BR, padded = (heads * qgroups + 7) / 8 * 8;
         const int once = qgroups == 1 && 3L * heads * Nk * D > (64L << 20);   // the rule of launch_narrow in intfa_attention_fewq.hip
-        hipLaunchKernelGGL((int_flash_attn_fwd_half_few_kernel<D, CAUSAL, OutT>), dim3(static_cast<unsigned>(heads * qgroups)), dim3(FEW_THREADS), 0,
-                           st, Q, K, V, sQ, sK, heads, Nq, Nk, once, static_cast<OutT *>(O));
+        auto launch = [&](auto ds) {
+            constexpr int DS = decltype(ds)::value;
+            hipLaunchKernelGGL((int_flash_attn_fwd_half_few_kernel<D, CAUSAL, OutT, DS>), dim3(static_cast<unsigned>(padded * DS)), dim3(FEW_THREADS), 0,
+                               st, Q, K, V, sQ, sK, heads, Nq, Nk, once, static_cast<OutT *>(O));
+        };
+        if constexpr (D == 128) {
+            // two workgroups per query group as long as each then has a CU of its own (160 heads x 1 x 4096: 40 us with one, 57 with two)
+            if (heads * qgroups <= 128) launch(std::integral_constant<int, 2>{});
+            else launch(std::integral_constant<int, 1>{});
+        } else launch(std::integral_constant<int, 1>{});
         return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
     }
     const long wgs = static_cast<long>(heads) * ((Nq + BR - 1) / BR);

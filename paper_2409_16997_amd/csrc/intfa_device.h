@@ -66,6 +66,24 @@ __device__ __forceinline__ void map_workgroup(int L, int heads, int T_r, int hea
     } else { head = L / T_r; qord = L % T_r; }
 }
 
+// The few-query kernels: DS workgroups for each (head, group of 32 queries), the grid padded to whole eights of groups.
+// With whole eights of heads all workgroups of a head run on one XCD; otherwise the groups are spread over all XCDs, the DS
+// workgroups of one (8 apart) still on the same.  False: a workgroup of the padding.
+template <int DS> __device__ __forceinline__ bool map_query_group(int L, int heads, int qgroups, int &head, int &qg, int &part) {
+    if ((heads & 7) == 0) {
+        const int unit = L >> 3, in_head = unit % (qgroups * DS);
+        head = unit / (qgroups * DS) * 8 + (L & 7);
+        qg = in_head / DS;
+        part = in_head % DS;
+        return true;
+    }
+    const int group = L / (8 * DS) * 8 + (L & 7);
+    head = group / qgroups;
+    qg = group % qgroups;
+    part = (L >> 3) % DS;
+    return group < heads * qgroups;
+}
+
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources and LDS builtins do not exist in the host pass
 struct BufRsrc { int w[4]; };        // raw buffer resource: base, base hi (stride 0), bytes, flags
 __device__ __forceinline__ BufRsrc make_rsrc(const void *base, unsigned bytes) {
