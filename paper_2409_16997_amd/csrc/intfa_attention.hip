@@ -331,7 +331,7 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
     const int shift = CAUSAL ? Nk - Nq : 0;
 
     int head, qord;
-    map_workgroup(blockIdx.x, heads, T_r, head_group, head, qord);
+    map_workgroup(blockIdx.x, heads, T_r, head_group, CAUSAL, head, qord);
     const int qb = CAUSAL ? (T_r - 1 - qord) : qord;
     const int q_local = 32 * wave + r;                           // this lane's query inside the block
     const int q_head = qb * BR + q_local;                        // this lane's query inside the head

@@ -295,7 +295,7 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
     const int shift = CAUSAL ? Nk - Nq : 0;
 
     int head, qord;
-    map_workgroup(blockIdx.x, heads, T_r, head_group, head, qord);
+    map_workgroup(blockIdx.x, heads, T_r, head_group, CAUSAL, head, qord);
     const int qb = CAUSAL ? (T_r - 1 - qord) : qord;
     const int q_local = 32 * wave + r;
     const int q_head = qb * BR + q_local;

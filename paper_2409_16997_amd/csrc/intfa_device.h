@@ -51,19 +51,42 @@ inline int head_group_for(bool causal, long kv_bytes_per_head, int T_r) {
     return static_cast<int>(fit < 1 ? 1 : (fit > HEAD_GROUP ? HEAD_GROUP : fit));
 }
 
-// Workgroups go round-robin over the 8 XCDs by linear id.  All query blocks of a head run on one XCD,
-// so its K/V stay in that XCD's L2; an XCD takes its heads `head_group` at a time and, inside a group,
-// the query blocks of all its heads in the order `qord` = 0, 1, ... (a causal kernel maps qord 0 to the
-// heaviest, i.e. last, query block so that the last workgroups to start are the light ones).
-__device__ __forceinline__ void map_workgroup(int L, int heads, int T_r, int head_group, int &head, int &qord) {
-    if ((heads & 7) == 0) {
-        const int s = L >> 3, per_group = head_group * T_r;
+// Workgroup L of heads * T_r -> its head and the rank `qord` of its query block (a causal kernel maps qord 0 to the heaviest,
+// i.e. last, query block).  Workgroups go round-robin over the 8 XCDs by linear id; s is the position on the XCD.
+//   Locality: all query blocks of a head run on one XCD, so its K and V stay in that XCD's L2; an XCD takes its heads
+// `head_group` at a time and, inside a group, the query blocks of all its heads in the order of their rank.  The last
+// `heads & 7` heads are shared out over all XCDs, rank by rank, as a fractional head of every XCD's last group.  Without the
+// mask and from 16 query blocks per head on, such a call is dealt out head by head instead, at least two query blocks of a
+// head to an XCD, which is as fast or faster (12 heads x 8192 544 us against 564, half-INT8 36 x 4096 306 against 319;
+// 100 x 1024: 49 against 45, shared out).
+//   Order under the mask: the last workgroups to start are the light ones.  When all start at once, the second 32 of an XCD
+// join the first 32 on its 32 CUs in the same order (seen in the workgroups' CU ids), so they go backwards and every CU gets
+// a heavy and a light one.  (With more workgroups than that the order hardly matters: 128 x 1024 5 % faster backwards, 80 x
+// 1024 and 128 x 600 3 % slower.)
+//   Before, causal calls with heads & 7 were dealt out head by head, uneven work on the CUs, and nothing went backwards, d = 128:
+// 36 x 4096 200.7 -> 118.7 us, 12 x 16384 683 -> 582, 4 x 16384 289 -> 236, 36 x 1777 37.4 -> 33.9; 8 x 8192 134 -> 122,
+// 64 x 1024 25.6 -> 22.0.
+__host__ __device__ __forceinline__ void map_workgroup(int L, int heads, int T_r, int head_group, bool causal, int &head, int &qord) {
+    const int x = L & 7, hpx = heads >> 3, rem = heads & 7;          // whole heads per XCD, heads shared out
+    if (!causal && rem && T_r >= 16) { head = L / T_r; qord = L % T_r; return; }
+    int s = L >> 3;
+    if (causal && s >= 32 && heads * T_r <= 512) s = ((heads * T_r - x + 7) >> 3) + 31 - s;
+    const int nfull = hpx > 0 ? (hpx - 1) / head_group : 0;          // groups before the last
+    const int per_group = head_group * T_r, base = nfull * head_group;
+    if (s < nfull * per_group) {
         const int grp = s / per_group, t = s % per_group;
-        const int hpx = heads >> 3;                                  // heads per XCD
-        const int gsz = min(head_group, hpx - grp * head_group);     // the last group may be short
-        head = (grp * head_group + t % gsz) * 8 + (L & 7);
-        qord = t / gsz;
-    } else { head = L / T_r; qord = L % T_r; }
+        head = (grp * head_group + t % head_group) * 8 + x;
+        qord = t / head_group;
+        return;
+    }
+    const int t = s - nfull * per_group, m = hpx - base;             // the last group: m heads and its share of the `rem`
+    // the shared workgroup of rank q and head 8 hpx + i runs on XCD (q rem + i) % 8; before rank q the XCD has this many:
+    auto before = [&](int q) { return q * m + ((q * rem - x + 7) >> 3); };
+    qord = static_cast<int>(8u * static_cast<unsigned>(t) / static_cast<unsigned>(8 * m + rem));
+    while (before(qord) > t) --qord;
+    while (before(qord + 1) <= t) ++qord;
+    const int i = t - before(qord);
+    head = i < m ? (base + i) * 8 + x : hpx * 8 + ((x - qord * rem) & 7);
 }
 
 // The few-query kernels: DS workgroups for each (head, group of 32 queries), the grid padded to whole eights of groups.
