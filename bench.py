@@ -85,7 +85,8 @@ def decode_bench(args, torch, ifa):
               "config": {"workload": f"decode: B={B} H={H} Nq={Nq} Nk={Nk} d={d} causal, N(0,1) fp16 activations quantized beforehand; "
                                      "step = one attention call on the quantized cache", "workspace_bytes": need, "int8_ops_per_step": ops},
               "ms_one_workgroup_per_head": round(ms["one_workgroup_per_head"], 4),
-              "roofline": {"bound": "hbm", "kernel": "splitk_scores_kernel + splitk_pv_kernel + splitk_combine_kernel (one call)",
+              "roofline": {"bound": "hbm", "kernel": "splitk_scores_kernel + splitk_pv_kernel + splitk_combine_kernel, or int_flash_attn_fwd_narrow_kernel "
+                                                  "with many heads (one call)",
                            "achieved": round(algo_bytes / (ms["key_split"] * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
                            "frac": round(algo_bytes / (ms["key_split"] * 1e-3) / 8e12, 4), "traffic": None,
                            "note": "algorithmic bytes: K, V int8 and s_K read once, Q, s_Q, s_V read, O written; the scores that pass "

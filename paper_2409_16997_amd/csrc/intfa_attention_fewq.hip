@@ -1,9 +1,9 @@
 // INT-FlashAttention forward (Algorithm 1) for gfx950: calls with few queries per head (a decode step, a few draft
 // tokens, a short chunk of a prefill).  Two families, both built from the tile code of the fused kernel
 // (intfa_attention_tiles.h: same LDS layout, same MFMA operand order, same staging copies) and the same arithmetic:
-//   int_flash_attn_fwd_narrow_kernel   one workgroup per head and group of 32 queries, each key block split over its
-//                                      four wavefronts; bit-identical to the fused kernel's rows, needs no memory
-//                                      beyond inputs and outputs; what int_flash_attn_fwd_rect runs for N_q <= 64;
+//   int_flash_attn_fwd_narrow_kernel   one or two workgroups per head and group of 32 queries, the key blocks split over
+//                                      their wavefronts; bit-identical to the fused kernel's rows, needs no memory
+//                                      beyond inputs and outputs; what int_flash_attn_fwd_rect runs by ifa_few_queries();
 //   splitk_*                           the key axis of a head split over many workgroups, exactly: lines 9-10 for every
 //                                      block first, then lines 11-13 on the known running maximum, then a merge;
 //                                      int_flash_attn_fwd_splitk (caller's workspace) and _splitk_static (built in).
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     v16i acc0;                                                   // what both accumulations start from
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc0[v] = ACC_START_I;
-    // line 10 for the four blocks of a group: the running maximum after each; leaves m2 at the last
+    // line 10 for the blocks of a group: the running maximum after each; leaves m2 at the last
     struct Maxima { float v[NB]; };
     auto maxima = [&](int parity) {
         Maxima m;
@@ -315,8 +315,8 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
 }
 
 // ---- few queries, many keys, any number of heads: the key axis split across workgroups, exactly ----------------
-// One workgroup per head (the narrow kernel) cannot fill the chip when there are few heads, and even with 128 of them
-// it is bound by its own block-to-block latency.  Splitting the keys of a head over workgroups is not Algorithm 1 as
+// The narrow kernel cannot fill the chip when there are few heads, and walks a long key sequence at what one or two CUs take
+// in.  Splitting the keys of a head over workgroups is not Algorithm 1 as
 // long as each part rounds P on the grid of ITS OWN running maximum; it is Algorithm 1 once the maximum after every
 // key block is known before any P is formed.  With at most SPLIT_MAX_Q queries per head the scores are small next to
 // K and V (4 N_q bytes per key against 2 d), so they go through memory:
@@ -338,7 +338,6 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
 // are combined through LDS.
 constexpr int SPLIT_MAX_Q = 8;       // queries per head up to which the scores go through memory (a decode step, a few speculative tokens)
 constexpr int SPLIT_MAX_Q_RECOMPUTE = 32;   // ... and up to which the second pass recomputes them from K instead (one column tile)
-constexpr int SPLIT_RECOMPUTE_MAX_HEADS = 96;   // ... as long as there are fewer heads than this
 constexpr int SPLIT_NSTAGE_K = 4;    // pass 1: ring of K blocks, filled three ahead
 constexpr int SPLIT_NSTAGE_V = 3;    // pass 2: ring of V blocks, filled two ahead
 [[maybe_unused]] constexpr bool SPLIT_NT = true;      // staging copies carry the non-temporal hint: every byte is read once (measured +7 % at 537 MB of K and V)
@@ -879,6 +878,20 @@ int launch_splitk_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const
     }
 }
 
+// Which calls of the key-split entry points the narrow kernel takes.  It walks 1000 keys of every head in 4.4 us (d = 64: 3.5)
+// however many heads there are, until the chip is full; the split passes stream K, V and the scores (or K twice) of all heads
+// at 5 - 6 TB/s, in three launches that take 15 us together on short sequences.  Narrow / split, us, d = 128 unless stated:
+//   up to 2048 keys  8 heads x 1 x 2048 13.5 / 23.1, 64 x 8 x 2048 12.2 / 17.3, 128 x 1 x 2048 13.2 / 26.0; d = 64, 8 x 1 x 2048 9.9 / 16.0
+//   many heads       128 x 1 x 16384 88.3 / 95.1, 128 x 8 x 8192 45.9 / 68.1, 96 x 8 x 16384 82.1 / 98.3, 64 x 16 x 8192 40.0 / 60.3; d = 64,
+//                    192 x 1 x 16384 61.2 / 87.3, 96 x 8 x 16384 59.4 / 64.4
+//   below the line   96 x 1 x 16384 82.0 / 76.4, 64 x 8 x 16384 77.0 / 68.1, 32 x 16 x 16384 71.7 / 60.7; d = 64, 128 x 1 x 16384 58.9 / 56.1,
+//                    64 x 8 x 8192 32.0 / 27.7, 64 x 16 x 8192 32.1 / 30.2
+//   up to 4096 keys half as many heads do: 64 x 1 x 4096 19.6 / 26.2, 48 x 16 20.2 / 29.1; 32 x 1 19.0 / 16.3, 32 x 16 19.4 / 18.9
+inline bool narrow_beats_split(int heads, int Nq, int Nk, int d) {
+    const int enough = Nq > SPLIT_MAX_Q ? (d == 128 ? 64 : 96) : Nq > 4 ? (d == 128 ? 96 : 112) : (d == 128 ? 112 : 160);
+    return heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2);
+}
+
 // argument checks of the key-split path that do not concern the workspace
 int splitk_args(const signed char *Q_i8, const signed char *K_i8, const signed char *V_i8, const float *s_Q, const float *s_K,
                 const float *s_V, int B, int H, int Nq, int Nk, int d, int causal, const void *O, int o_dtype) {
@@ -906,10 +919,7 @@ int splitk_dispatch(const signed char *Q_i8, const signed char *K_i8, const sign
     const int8_t *K = reinterpret_cast<const int8_t *>(K_i8);
     const int8_t *V = reinterpret_cast<const int8_t *>(V_i8);
     const int hd = B * H;
-    // From 9 queries on the second pass reads K again: with many heads the one-workgroup-per-head kernel already fills the
-    // chip and is the faster one (measured: 128 heads x 32 queries x 16384 keys 148 us against 167 us; 32 heads 160 against 73).
-    if (Nq > SPLIT_MAX_Q && hd >= SPLIT_RECOMPUTE_MAX_HEADS)
-        return int_flash_attn_fwd_rect(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, B, H, Nq, Nk, d, causal, O, o_dtype, st);
+    if (narrow_beats_split(hd, Nq, Nk, d)) return ifa_launch_narrow(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, d, causal, 0, O, o_dtype, st);
     if (d == 128)
         return causal ? launch_splitk_dtype<128, true>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, ws, st)
                       : launch_splitk_dtype<128, false>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, ws, st);
@@ -961,7 +971,7 @@ extern "C" int int_flash_attn_fwd_splitk(const signed char *Q_i8, const signed c
 }
 
 // ---- the key-split path for callers that cannot allocate -------------------------------------------------------
-// The same three launches with the workspace in a file-scope device array instead of a buffer of the caller's.  In
+// The same launches with the workspace in a file-scope device array instead of a buffer of the caller's.  In
 // host code the array's name is only a stand-in for the symbol: the device address is asked for once per device
 // (hipGetSymbolAddress, with that device current) and kept; every GPU holds its own copy of the array.
 constexpr long STATIC_WORKSPACE_BYTES = 16L << 20;

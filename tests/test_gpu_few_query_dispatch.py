@@ -75,3 +75,26 @@ def test_half_int8_kernels_agree(heads, N, d, causal):
     ref = oracle.int_flash_attn_fwd_half(n(q8), n(k8), n(v), n(sq), n(sk), causal, ifa.block_cols_half(d, causal))["O"]
     few = call(*[t[:, :1].contiguous() for t in (q8, k8, v, sq, sk)])[0, 0].cpu().numpy()
     assert np.abs(few - ref).max() <= 1e-3 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,Nq,heads", [(128, 1, 112), (128, 8, 96), (128, 32, 64), (64, 4, 160), (64, 5, 112), (64, 9, 96)])
+def test_key_split_entry_point_on_both_sides_of_its_rule(d, Nq, heads, causal):
+    # `heads` is the number from which the entry point runs the few-query kernel at any length: the same result, bit for bit.
+    # Below it, and with more than 2048 keys, the split passes run, which add up O in another order (a few ulp of the
+    # largest value; in the last case the last run of key blocks is masked for the early queries).
+    import paper_2409_16997_amd as ifa
+    for H, Nk, same in ((heads, 4099, True), (heads - 1, 4097, False), (heads - 1, 4096, True), (heads // 2, 4096, False),
+                        (heads // 2 + 1, 2049, True), (3, 2048, True), (3, 2049, False), (2, 4098, False)):
+        q8, k8, v8, sq, sk = problem(H, Nk, d, H + Nk)
+        q8, sq = q8[:, :, Nk - Nq:].contiguous(), sq[:, :, Nk - Nq:].contiguous()
+        sv = 0.005 + 0.02 * torch.rand((1, H), device="cuda", generator=torch.Generator(device="cuda").manual_seed(Nk))
+        ref = ifa.int_flash_attn_fwd(q8, k8, v8, sq, sk, sv, causal=causal, out_dtype=torch.float32)
+        need = ifa.splitk_workspace_bytes(1, H, Nq, Nk, d)
+        ws = torch.full((need // 4,), float("nan"), device="cuda").view(torch.uint8)
+        out = ifa.int_flash_attn_fwd_splitk(q8, k8, v8, sq, sk, sv, causal=causal, out_dtype=torch.float32, workspace=ws)
+        if same:
+            assert torch.equal(out, ref), (H, Nk)
+        else:
+            assert not bool(torch.isnan(ws.view(torch.float32)).all()), (H, Nk)      # the passes ran
+            assert float((out - ref).abs().max()) <= 4e-6 * float(ref.abs().max()), (H, Nk)
