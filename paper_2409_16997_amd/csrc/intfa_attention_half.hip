@@ -426,7 +426,6 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int T_c = (Nk + BCH - 1) / BCH;
     const int qgroups = (Nq + FEW_BR - 1) / FEW_BR;
     const int shift = CAUSAL ? Nk - Nq : 0;
     int head, qg, half;
@@ -436,7 +435,8 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
     const int q_head = first_q + r;
     const long qrow = static_cast<long>(head) * Nq + min(q_head, Nq - 1);   // rows past Nq: a clamped copy, never stored
     const float sq2 = sQ[qrow] * LOG2E;
-    const int nblocks = CAUSAL ? min(Nk - 1, min(first_q + FEW_BR, Nq) - 1 + shift) / BCH + 1 : T_c;
+    const int last_key = CAUSAL ? min(Nk - 1, min(first_q + FEW_BR, Nq) - 1 + shift) : Nk - 1;   // ... of any query of the group
+    const int nblocks = last_key / BCH + 1;
     const int ngroups = (nblocks + NB - 1) / NB;
     float m2 = -INFINITY;                                        // running maximum in log2 units, kept in step by both roles
     struct Maxima { float v[NB]; };
@@ -600,12 +600,17 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
     for (int v = 0; v < 16; ++v) o[v] = 0.0f;
     const bool works = dt < PIECES;                              // two d tiles in a half (or D = 64): the other wavefronts only copy
     h8 vop[NB][4], pf[NB][4];
-    auto block = [&](int b, float m_prev, float m_new) {         // (a block past the last one: the maximum stays, the weights are 0)
+    // The second key tile of the last block may lie behind every query of the group.  It is left out, as in the kernel above: its
+    // weights are 0, but V is the caller's and 0 times an infinity or a NaN there is not.
+    auto block = [&](int gi, int b, float m_prev, float m_new) { // (a block past the last one: the maximum stays, the weights are 0)
         const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[v] *= alpha;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
+        for (int i = 0; i < 2; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
+        if ((gi * NB + b) * BCH + 32 > last_key) return;         // wave-uniform
+#pragma unroll
+        for (int i = 2; i < 4; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
     };
     stage_group(0);
     for (int gi = 0; gi <= ngroups; ++gi) {
@@ -625,13 +630,13 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
             }
             m = maxima((gi - 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
-            block(0, m_before, m.v[0]);
+            block(gi - 1, 0, m_before, m.v[0]);
         }
         __syncthreads();
         if (gi < ngroups) stage_group(gi + 1);
         if (gi > 0 && works) {
 #pragma unroll
-            for (int b = 1; b < NB; ++b) block(b, m.v[b - 1], m.v[b]);
+            for (int b = 1; b < NB; ++b) block(gi - 1, b, m.v[b - 1], m.v[b]);
         }
         if (gi < ngroups) {
             wait_vmcnt<NB * PIECES>();                        // my part of V of group gi has landed (group gi + 1 may be in flight)

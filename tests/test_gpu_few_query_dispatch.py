@@ -98,3 +98,22 @@ def test_key_split_entry_point_on_both_sides_of_its_rule(d, Nq, heads, causal):
         else:
             assert not bool(torch.isnan(ws.view(torch.float32)).all()), (H, Nk)      # the passes ran
             assert float((out - ref).abs().max()) <= 4e-6 * float(ref.abs().max()), (H, Nk)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N", [128, 161, 200])
+def test_half_int8_rows_stay_clear_of_values_they_do_not_see(N, d):
+    # V is the caller's fp16 and may hold infinities.  Rows of a 32-query group that see no key of a 32-key tile do not depend on
+    # what V holds there, on either kernel (inside the tile that the diagonal crosses 0 * inf is a NaN on both).
+    import paper_2409_16997_amd as ifa
+    heads = 600                                                  # the whole call: the fused kernel
+    q8, k8, v8, sq, sk = problem(heads, N, d, N)
+    v = v8.to(torch.float16) / 64
+    for key, value in ((40, float("inf")), (97, float("nan")), (N - 1, float("-inf"))):
+        bad = v.clone()
+        bad[:, :, key] = value
+        call = lambda n, x: ifa.int_flash_attn_fwd_half(q8[:, :n].contiguous(), k8[:, :n].contiguous(), x[:, :n].contiguous(), sq[:, :n].contiguous(),
+                                                        sk[:, :n].contiguous(), causal=True, out_dtype=torch.float32)
+        first = key // 32 * 32                                   # the first row of the first group that sees the tile
+        for n in (heads, 2):
+            assert torch.equal(call(n, bad)[:, :, :first], call(n, v)[:, :, :first]), (n, key)
