@@ -570,7 +570,9 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
 
     // ---- PV wavefront: d tile dt of O^T = V^T P~^T, one group of blocks behind
     const int dt = wave - FEW_S_WAVES;
-    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D * 2);
+    // V ends for this workgroup with the last key tile that a query of the group sees: what lies behind comes as zeros.  Its
+    // weights are 0, but 0 times an infinity or a NaN of the caller's V is not (the kernel above leaves such a tile out).
+    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(min(Nk, (last_key | 31) + 1)) * D * 2);
     const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0][0]);
     const LaneOffsetsH<DV> lo(lane, dt);
     // With DS = 2 a row of the tile is a half row of V: the copies of LaneOffsetsH<DV> with the row stride of V (a piece is
@@ -600,17 +602,12 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
     for (int v = 0; v < 16; ++v) o[v] = 0.0f;
     const bool works = dt < PIECES;                              // two d tiles in a half (or D = 64): the other wavefronts only copy
     h8 vop[NB][4], pf[NB][4];
-    // The second key tile of the last block may lie behind every query of the group.  It is left out, as in the kernel above: its
-    // weights are 0, but V is the caller's and 0 times an infinity or a NaN there is not.
-    auto block = [&](int gi, int b, float m_prev, float m_new) { // (a block past the last one: the maximum stays, the weights are 0)
+    auto block = [&](int b, float m_prev, float m_new) {         // (a block past the last one: the maximum stays, the weights are 0)
         const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[v] *= alpha;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
-        if ((gi * NB + b) * BCH + 32 > last_key) return;         // wave-uniform
-#pragma unroll
-        for (int i = 2; i < 4; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
+        for (int i = 0; i < 4; ++i) o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vop[b][i], pf[b][i], o, 0, 0, 0);
     };
     stage_group(0);
     for (int gi = 0; gi <= ngroups; ++gi) {
@@ -630,13 +627,13 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
             }
             m = maxima((gi - 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
-            block(gi - 1, 0, m_before, m.v[0]);
+            block(0, m_before, m.v[0]);
         }
         __syncthreads();
         if (gi < ngroups) stage_group(gi + 1);
         if (gi > 0 && works) {
 #pragma unroll
-            for (int b = 1; b < NB; ++b) block(gi - 1, b, m.v[b - 1], m.v[b]);
+            for (int b = 1; b < NB; ++b) block(b, m.v[b - 1], m.v[b]);
         }
         if (gi < ngroups) {
             wait_vmcnt<NB * PIECES>();                        // my part of V of group gi has landed (group gi + 1 may be in flight)
