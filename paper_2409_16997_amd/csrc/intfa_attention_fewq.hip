@@ -889,7 +889,7 @@ int launch_splitk_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const
 //   up to 4096 keys half as many heads do: 64 x 1 x 4096 19.6 / 26.2, 48 x 16 20.2 / 29.1; 32 x 1 19.0 / 16.3, 32 x 16 19.4 / 18.9
 inline bool narrow_beats_split(int heads, int Nq, int Nk, int d) {
     const int enough = Nq > SPLIT_MAX_Q ? (d == 128 ? 64 : 96) : Nq > 4 ? (d == 128 ? 96 : 112) : (d == 128 ? 112 : 160);
-    return heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2);
+    return heads <= IFA_FEW_MAX_GROUPS && (heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2));
 }
 
 // argument checks of the key-split path that do not concern the workspace

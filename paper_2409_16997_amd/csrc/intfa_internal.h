@@ -8,6 +8,10 @@
 // Stream set by ifa_set_stream(); the null stream until then.
 hipStream_t ifa_current_stream();
 
+// Groups of 32 queries that one launch of a few-query kernel holds: a launch has less than 2^32 threads and their workgroups up to
+// 768 (the other kernels have 256, which is three times as many heads).
+constexpr long IFA_FEW_MAX_GROUPS = 5L << 20;
+
 // Which calls the few-query kernels take (INT8: same results, bit for bit): up to 32 queries per head, and longer ones that
 // would leave the fused kernel's two workgroups per CU mostly empty.  They have four workgroups of 32 queries where the
 // fused kernel has one of 128, one per CU at a time, and walk 256 keys in 1.0 - 1.5 us where a fused workgroup alone on its
@@ -17,6 +21,7 @@ hipStream_t ifa_current_stream();
 // (32 x 700 x 8192: 120 against 107, 512 x 64 x 2048: 71 against 59).
 static inline bool ifa_few_queries(int heads, int Nq, int Nk) {
     const long wgs = static_cast<long>(heads) * ((Nq + 31) / 32);
+    if (wgs > IFA_FEW_MAX_GROUPS) return false;
     return Nq <= 32 || wgs <= 256 || (wgs <= 512 && Nk >= 2048);
 }
 

@@ -117,3 +117,20 @@ def test_half_int8_rows_stay_clear_of_values_they_do_not_see(N, d):
         first = key // 32 * 32                                   # the first row of the first group that sees the tile
         for n in (heads, 2):
             assert torch.equal(call(n, bad)[:, :, :first], call(n, v)[:, :, :first]), (n, key)
+
+
+@pytest.mark.parametrize("variant,heads", [("full", 6_000_000), ("splitk", 6_000_000), ("half", 9_000_000)])
+def test_more_heads_than_one_few_query_launch_holds(variant, heads):
+    # 768 (half-INT8: 512) threads per head are more than 2^32 in one launch: such a call takes a kernel with 256
+    import paper_2409_16997_amd as ifa
+    few, Nk, d = 1000, 2, 64
+    q8, k8, v8, sq, sk = problem(few, Nk, d, 5)
+    q8, sq = q8[:, :, 1:].contiguous(), sq[:, :, 1:].contiguous()
+    v = v8.to(torch.float16) / 64 if variant == "half" else v8
+    sv = () if variant == "half" else (0.005 + 0.02 * torch.rand((1, few), device="cuda"),)
+    fn = {"full": ifa.int_flash_attn_fwd, "splitk": ifa.int_flash_attn_fwd_splitk, "half": ifa.int_flash_attn_fwd_half}[variant]
+    call = lambda *a: fn(*a, causal=True, out_dtype=torch.float32)
+    ref = call(q8, k8, v, sq, sk, *sv)
+    out = call(*[t.repeat((1, heads // few) + (1,) * (t.dim() - 2)) for t in (q8, k8, v, sq, sk) + sv]).view(heads // few, few, d)
+    # (half-INT8 adds l up in another order, the key-split passes O)
+    assert float((out - ref.view(1, few, d)).abs().max()) <= 2.0 ** -21 * float(ref.abs().max())
