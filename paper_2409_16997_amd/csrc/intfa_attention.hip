@@ -475,13 +475,23 @@ int launch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *s
 template <int D, bool CAUSAL, bool VB>
 int launch_fwd_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK,
                      const float *sV, int heads, int Nq, int Nk, void *O, int o_dtype, hipStream_t st) {
-    if (ifa_few_queries(heads, Nq, Nk))
+    if (ifa_packed_queries(heads, Nq, Nk, D) || ifa_few_queries(heads, Nq, Nk, D == 128 ? 384 : 0))
         return ifa_launch_narrow(Q, K, V, sQ, sK, sV, heads, Nq, Nk, D, CAUSAL ? 1 : 0, VB ? 1 : 0, O, o_dtype, st);
     switch (o_dtype) {
     case IFA_F32: return launch_fwd<D, CAUSAL, VB, float>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     case IFA_F16: return launch_fwd<D, CAUSAL, VB, __half>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     default: return launch_fwd<D, CAUSAL, VB, __hip_bfloat16>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     }
+}
+
+template <bool VB>
+int dispatch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *s_Q, const float *s_K, const float *s_V,
+                 int hd, int Nq, int Nk, int d, int causal, void *O, int o_dtype, hipStream_t st) {
+    if (d == 128)
+        return causal ? launch_fwd_dtype<128, true, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st)
+                      : launch_fwd_dtype<128, false, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st);
+    return causal ? launch_fwd_dtype<64, true, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st)
+                  : launch_fwd_dtype<64, false, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st);
 }
 
 // validation and dispatch shared by the tensor-level and the block-level V scale entry points
@@ -507,17 +517,17 @@ int fwd_entry(const signed char *Q_i8, const signed char *K_i8, const signed cha
     const int8_t *K = reinterpret_cast<const int8_t *>(K_i8);
     const int8_t *V = reinterpret_cast<const int8_t *>(V_i8);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const int hd = static_cast<int>(heads);
-    if (d == 128)
-        return causal ? launch_fwd_dtype<128, true, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st)
-                      : launch_fwd_dtype<128, false, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st);
-    return causal ? launch_fwd_dtype<64, true, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st)
-                  : launch_fwd_dtype<64, false, VB>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, st);
+    return dispatch_fwd<VB>(Q, K, V, s_Q, s_K, s_V, static_cast<int>(heads), Nq, Nk, d, causal, O, o_dtype, st);
 }
 
 }  // namespace
 
 hipStream_t ifa_current_stream() { return g_stream; }
+
+int ifa_launch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads,
+                   int Nq, int Nk, int d, int causal, void *O, int o_dtype, hipStream_t st) {
+    return dispatch_fwd<false>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, d, causal, O, o_dtype, st);
+}
 
 extern "C" const char *ifa_status_str(int status) {
     switch (status) {

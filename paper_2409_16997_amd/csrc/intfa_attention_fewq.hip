@@ -1,6 +1,8 @@
 // INT-FlashAttention forward (Algorithm 1) for gfx950: calls with few queries per head (a decode step, a few draft
-// tokens, a short chunk of a prefill).  Two families, both built from the tile code of the fused kernel
+// tokens, a short chunk of a prefill).  Three families, all built from the tile code of the fused kernel
 // (intfa_attention_tiles.h: same LDS layout, same MFMA operand order, same staging copies) and the same arithmetic:
+//   int_flash_attn_fwd_packed_kernel   one workgroup of four wavefronts per head and group of 32 queries, one key block at a time;
+//                                      the calls of ifa_packed_queries();
 //   int_flash_attn_fwd_narrow_kernel   one or two workgroups per head and group of 32 queries, the key blocks split over
 //                                      their wavefronts; bit-identical to the fused kernel's rows, needs no memory
 //                                      beyond inputs and outputs; what int_flash_attn_fwd_rect runs by ifa_few_queries();
@@ -302,6 +304,201 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     const float f = (VB ? sv_prev : sVh[0]) * ACC_UNIT / lt;
     if (q_head < Nq && works) {
         OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + col0 + 32 * dt + 4 * g;
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+            if constexpr (sizeof(OutT) == 2) {
+                *reinterpret_cast<uint2 *>(orow + 8 * vq) = Pack4<OutT>::pack(o[4 * vq] * f, o[4 * vq + 1] * f, o[4 * vq + 2] * f, o[4 * vq + 3] * f);
+            } else {
+                *reinterpret_cast<v4f *>(orow + 8 * vq) = v4f{o[4 * vq] * f, o[4 * vq + 1] * f, o[4 * vq + 2] * f, o[4 * vq + 3] * f};
+            }
+        }
+    }
+#endif
+}
+
+// ---- few queries, few keys (or d = 64 and more workgroups than CUs) ----------------------------------------------
+// The kernel above needs twelve wavefronts and a CU for one group of queries, takes two key blocks at a time and ends one step after
+// its scores do.  On few keys that is mostly start and end.  Here four wavefronts take one key block at a time in one role:
+//     wavefront w computes S^T for key tile w (32 keys), scales it, takes its extremum;
+//     the four per-query extrema meet in LDS (first barrier of the block): everyone knows m of line 10 for the whole block;
+//     wavefront w computes the 16 P bytes per lane of its key tile and leaves them in LDS (second barrier);
+//     wavefront w then computes the d tile w (32 of the d columns) of O^T = V^T P^T over all 128 keys, with the P operands of
+//     the four key tiles from LDS, and folds it into its 16 registers of the running output.
+// What bounds it is that chain, 1.3 us per block, which is why it loses on longer key sequences; at d = 64 two workgroups share a CU
+// and fill in for each other.  K and V come in through a ring of PACKED_NSTAGE blocks, filled three ahead; the wait for a block is
+// a counted s_waitcnt (every wavefront issues the same number of copies per block) in front of the second barrier of the block
+// before, which thereby also publishes the staged block; the first barrier releases the stage of the block before.
+// The arithmetic is that of the other two kernels, operation by operation.  Where the lines lie: ifa_packed_queries().
+constexpr int PACKED_BR = 32;      // queries per workgroup
+constexpr int PACKED_NSTAGE = 4;
+
+template <int D> struct SmemPacked {
+    alignas(4096) int8_t k[PACKED_NSTAGE][BC * D];
+    alignas(4096) int8_t v[PACKED_NSTAGE][BC * D];
+    alignas(512) float sk[PACKED_NSTAGE][BC];
+    alignas(16) float ext[4][32];          // per key tile and query: the tile's extremum of a (line 10)
+    alignas(16) v4i p[4][64];              // per key tile and lane: the 16 P bytes of that lane (line 11)
+};
+static_assert(sizeof(SmemPacked<128>) <= 160 * 1024 && 2 * sizeof(SmemPacked<64>) <= 160 * 1024 && offsetof(SmemPacked<64>, v) % 4096 == 0, "LDS budget (d = 64: two workgroups per CU) and tile bases");
+
+template <int D, bool CAUSAL, bool VB, typename OutT>
+__global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_packed_kernel(
+    const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
+    const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
+    int heads, int Nq, int Nk, OutT *__restrict__ O) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __shared__ SmemPacked<D> sm;
+    constexpr int KS = D / 32;
+    constexpr int PER_BLOCK = 2 * KS + 1;                        // copy instructions per wavefront and block
+
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T_c = (Nk + BC - 1) / BC;
+    const int qgroups = (Nq + PACKED_BR - 1) / PACKED_BR;
+    const int shift = CAUSAL ? Nk - Nq : 0;
+    // all query groups of a head on one XCD (workgroups go round-robin over the 8 XCDs by linear id)
+    int head, qg;
+    if ((heads & 7) == 0) { const int s_ = blockIdx.x >> 3; head = (s_ / qgroups) * 8 + (blockIdx.x & 7); qg = s_ % qgroups; }
+    else { head = blockIdx.x / qgroups; qg = blockIdx.x % qgroups; }
+    const int first_q = qg * PACKED_BR;
+    const int q_head = first_q + r;
+    const long qrow = static_cast<long>(head) * Nq + min(q_head, Nq - 1);   // rows past Nq: a clamped copy, never stored
+
+    const int8_t *Kh = K + static_cast<long>(head) * Nk * D;
+    const int8_t *Vh = V + static_cast<long>(head) * Nk * D;
+    const float *sKh = sK + static_cast<long>(head) * Nk;
+    const lds_ptr kbuf = (lds_ptr)(&sm.k[0][0]);
+    const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0]);
+    const lds_ptr skbuf = (lds_ptr)(&sm.sk[0][0]);
+    const int nblocks = CAUSAL ? min(Nk - 1, min(first_q + PACKED_BR, Nq) - 1 + shift) / BC + 1 : T_c;
+
+    const BufRsrc rK = make_rsrc(Kh, static_cast<unsigned>(Nk) * D);
+    const BufRsrc rV = make_rsrc(Vh, static_cast<unsigned>(Nk) * D);
+    const BufRsrc rSK = make_rsrc(sKh, static_cast<unsigned>(Nk) * 4);
+    const LaneOffsets<D> lo(lane, wave);
+
+    // line 8 for block jb into stage jb % PACKED_NSTAGE; a block past the last one is requested nowhere (no data moves), so
+    // that every block costs every wavefront PER_BLOCK copy instructions and the counted wait below stays valid
+    auto stage_block = [&](int jb) {
+        const int st = jb % PACKED_NSTAGE;
+        const bool real = jb < nblocks;
+        const Prefetch pf = {rK, rV, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE,
+                             kbuf + st * BC * D, vbuf + st * BC * D, skbuf + st * BC * 4};
+#pragma unroll
+        for (int i = 0; i < KS; ++i) { prefetch_k_piece<D>(pf, lo, wave, i); prefetch_v_piece<D>(pf, lo, wave, i); }
+        lds_copy4(pf.sk, pf.lsk + 256 * (wave & 1), 4 * lane + 256 * (wave & 1), pf.skoff);   // wavefronts 2, 3 repeat 0, 1
+    };
+    stage_block(0);
+    stage_block(1);
+    stage_block(2);
+
+    // line 5
+    const int8_t *qptr = Q + qrow * D + 16 * g;
+    v4i qf[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 32 * kk);
+    float nq2 = sQ[qrow] * (-LOG2E * ACC_UNIT);
+    // The loads above must have landed BEFORE the loop as far as the compiler is concerned: a wait for them inside the
+    // loop would be a wait for every outstanding vector-memory operation, the staged copies included.
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[kk]));
+    asm volatile("" : "+v"(nq2));
+
+    // line 6: this wavefront's d tile of the running output (units of 2^26), m and l of the whole row
+    float m2 = -INFINITY, l = 0.0f, o[16];
+    v16i acc0;                                                   // what both accumulations start from
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { o[v] = 0.0f; acc0[v] = ACC_START_I; }
+
+    // s_V: one scalar per head, or (VB) one per key block of this head, read through the scalar cache
+    const float *sVh = VB ? sV + static_cast<long>(head) * T_c : sV + head;
+    float sv_prev = 1.0f;
+    wait_vmcnt<2 * PER_BLOCK>();                                 // my pieces of block 0 have landed (blocks 1 and 2 may be in flight)
+    __syncthreads();                                             // everyone's have
+    for (int jb = 0; jb < nblocks; ++jb) {                       // line 7
+        const int st = jb % PACKED_NSTAGE, j0 = jb * BC;
+        // with one V scale per key block the running output is kept in units of the current block's scale (as in the fused kernel)
+        const float sv_j = VB ? uniform(sVh[jb]) : 1.0f;
+        const float oscale = VB ? uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j)) : 1.0f;
+        sv_prev = sv_j;
+        const lds_ptr ks = kbuf + st * BC * D, vs = vbuf + st * BC * D, sk = skbuf + st * BC * 4;
+
+        // line 9 for key tile `wave`
+        v4i kop[KS];
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) kop[kk] = *reinterpret_cast<LDS_AS const v4i *>(k_operand<D>(ks, lo, kk) + 32 * wave * D);
+        v4f skv[4];
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) skv[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + lo.sk + 128 * wave + 32 * vq);
+        // (registers are plentiful here: the accumulators start from a register block holding the constant, and every
+        // MFMA is the compiler's own, with its dependency handling)
+        v16i sacc = acc0;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[kk], sacc, 0, 0, 0);
+        // kept keys: index inside the block <= klimit (the causal diagonal, the ragged end of the sequence)
+        const int tail = Nk - 1 - j0;
+        const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;
+        const bool masked = CAUSAL ? (j0 + BC - 1 > min(first_q + shift, Nk - 1)) : (tail < BC - 1);   // wave-uniform
+        float a[16], bmin = INFINITY;
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float x = (ACC_START_F - __int_as_float(sacc[4 * vq + e])) * skv[vq][e];
+                if (masked && (32 * wave + 8 * vq + 4 * g + e > klimit)) x = INFINITY;
+                a[4 * vq + e] = x;
+                bmin = fminf(bmin, x);
+            }
+        bmin = pair_min(bmin);
+        if (g == 0) sm.ext[wave][r] = bmin;
+        __syncthreads();
+        // every wavefront is past the second GEMM of block jb - 1: the stage that block used takes block jb + 3
+        stage_block(jb + 3);
+        // line 10 over the whole block
+        bmin = fminf(fminf(sm.ext[0][r], sm.ext[1][r]), fminf(sm.ext[2][r], sm.ext[3][r]));
+        const float m_new = fmaxf(m2, bmin * nq2);
+        const float alpha = __builtin_amdgcn_exp2f(m2 - m_new);
+        const float mm = m_new - LOG2_R_NORM;
+        m2 = m_new;
+        // line 11 for key tile `wave`
+        v4i pw;
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+            float x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[4 * vq + e], nq2, -mm));
+            const uint32_t w = pack_p4(x);
+            pw[vq] = static_cast<int>(w);
+        }
+        sm.p[wave][lane] = pw;
+        wait_vmcnt<2 * PER_BLOCK>();                             // my pieces of block jb + 1 have landed (two later blocks may be in flight)
+        __syncthreads();                                         // everyone's have, and every P tile of this block is in LDS
+        // lines 12, 13: d tile `wave` of O^T = V^T P^T over the four key tiles, the row sum over the same P dwords
+        if (wave >= KS) continue;                                // D = 64: two d tiles; the other wavefronts only take part above
+        v16i pacc;
+        uint32_t psum = 0;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            const v4i pf = sm.p[mt][lane];
+            const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, wave) + 32 * mt * D));
+            const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, wave) + 16 * D + 32 * mt * D));
+            const v4i vop = {t0[0], t0[1], t1[0], t1[1]};
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) psum = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[vq]), 0u, psum);
+            pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop, pf, mt == 0 ? acc0 : pacc, 0, 0, 0);
+        }
+        l = __builtin_fmaf(l, alpha, static_cast<float>(psum));
+        const float alpha_o = VB ? alpha * oscale : alpha;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[v])));
+    }
+    wait_all_memory();                                           // requests past the last block: nothing of mine stays in flight
+
+    // lines 15-17 for d tile `wave` (d = 32 * wave + 8 * (v / 4) + 4 * g + v % 4 of query r)
+    const float lt = l + swap32(l);
+    const float f = (VB ? sv_prev : sVh[0]) * ACC_UNIT / lt;
+    if (q_head < Nq && wave < KS) {
+        OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * wave + 4 * g;
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
             if constexpr (sizeof(OutT) == 2) {
@@ -827,8 +1024,18 @@ __global__ __launch_bounds__(THREADS) void splitk_combine_kernel(const float *__
 
 // ---- host side ----------------------------------------------------------------------------------
 template <int D, bool CAUSAL, bool VB, typename OutT>
+int launch_packed(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
+                  int heads, int Nq, int Nk, void *O, hipStream_t st) {
+    const long wgs = static_cast<long>(heads) * ((Nq + PACKED_BR - 1) / PACKED_BR);
+    hipLaunchKernelGGL((int_flash_attn_fwd_packed_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0, st,
+                       Q, K, V, sQ, sK, sV, heads, Nq, Nk, static_cast<OutT *>(O));
+    return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+}
+
+template <int D, bool CAUSAL, bool VB, typename OutT>
 int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
+    if (ifa_packed_queries(heads, Nq, Nk, D)) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
     // K and V with the non-temporal hint where each byte is read once and there are more of them than the caches could keep
     // for the next call (128 heads of 4096 x 128, 134 MB: 26.9 us with the hint, 29.2 without; 32 heads, 34 MB: 25.5 and 22.0; DS = 1)
@@ -878,7 +1085,7 @@ int launch_splitk_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const
     }
 }
 
-// Which calls of the key-split entry points the narrow kernel takes.  It walks 1000 keys of every head in 4.4 us (d = 64: 3.5)
+// Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  It walks 1000 keys of every head in 4.4 us (d = 64: 3.5)
 // however many heads there are, until the chip is full; the split passes stream K, V and the scores (or K twice) of all heads
 // at 5 - 6 TB/s, in three launches that take 15 us together on short sequences.  Narrow / split, us, d = 128 unless stated:
 //   up to 2048 keys  8 heads x 1 x 2048 13.5 / 23.1, 64 x 8 x 2048 12.2 / 17.3, 128 x 1 x 2048 13.2 / 26.0; d = 64, 8 x 1 x 2048 9.9 / 16.0
@@ -889,7 +1096,7 @@ int launch_splitk_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const
 //   up to 4096 keys half as many heads do: 64 x 1 x 4096 19.6 / 26.2, 48 x 16 20.2 / 29.1; 32 x 1 19.0 / 16.3, 32 x 16 19.4 / 18.9
 inline bool narrow_beats_split(int heads, int Nq, int Nk, int d) {
     const int enough = Nq > SPLIT_MAX_Q ? (d == 128 ? 64 : 96) : Nq > 4 ? (d == 128 ? 96 : 112) : (d == 128 ? 112 : 160);
-    return heads <= IFA_FEW_MAX_GROUPS && (heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2));
+    return heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2);
 }
 
 // argument checks of the key-split path that do not concern the workspace
@@ -919,7 +1126,7 @@ int splitk_dispatch(const signed char *Q_i8, const signed char *K_i8, const sign
     const int8_t *K = reinterpret_cast<const int8_t *>(K_i8);
     const int8_t *V = reinterpret_cast<const int8_t *>(V_i8);
     const int hd = B * H;
-    if (narrow_beats_split(hd, Nq, Nk, d)) return ifa_launch_narrow(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, d, causal, 0, O, o_dtype, st);
+    if (narrow_beats_split(hd, Nq, Nk, d)) return ifa_launch_fwd(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, d, causal, O, o_dtype, st);
     if (d == 128)
         return causal ? launch_splitk_dtype<128, true>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, ws, st)
                       : launch_splitk_dtype<128, false>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, ws, st);

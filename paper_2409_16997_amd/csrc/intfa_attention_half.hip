@@ -663,9 +663,10 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
 template <int D, bool CAUSAL, typename OutT>
 int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float *sQ, const float *sK, int heads, int Nq, int Nk,
                 void *O, hipStream_t st) {
-    // as for INT8: 32 heads x 256 queries x 8192 keys 64 us against 145 on the kernel below, x 512: 119 and 145, x 700: 184 and
-    // 146; 512 heads x 32 x 2048: 66 and 79, x 64: 94 and 81
-    if (ifa_few_queries(heads, Nq, Nk)) {
+    // as for INT8, this kernel / the one below, us.  d = 128: 32 heads x 256 queries x 8192 keys 64 / 145, x 512 119 / 145, x 700 184 / 146;
+    // 512 x 32 x 2048 66 / 79, x 64 94 / 81; short keys 512 x 1 x 128 9.6 / 8.8, 2000 x 32 x 256 53 / 51, 2000 x 1 x 384 54 / 62.
+    // d = 64: 2000 x 1 x 64 15.0 / 13.1, x 128 17.4 / 19.2, 32 x 512 x 2048 20 / 33.
+    if (ifa_few_queries(heads, Nq, Nk, D == 128 ? 256 : 64)) {
         const long qgroups = (Nq + FEW_BR - 1) / FEW_BR, padded = (heads * qgroups + 7) / 8 * 8;
         const int once = qgroups == 1 && 3L * heads * Nk * D > (64L << 20);   // the rule of launch_narrow in intfa_attention_fewq.hip
         auto launch = [&](auto ds) {

@@ -134,3 +134,51 @@ def test_more_heads_than_one_few_query_launch_holds(variant, heads):
     out = call(*[t.repeat((1, heads // few) + (1,) * (t.dim() - 2)) for t in (q8, k8, v, sq, sk) + sv]).view(heads // few, few, d)
     # (half-INT8 adds l up in another order, the key-split passes O)
     assert float((out - ref.view(1, few, d)).abs().max()) <= 2.0 ** -21 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("vblock", [False, True])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,Nk", [(64, 1), (64, 66), (64, 128), (64, 129), (64, 1023), (64, 1024), (64, 1025), (64, 1280), (64, 1281), (64, 2047), (64, 2048),
+                                  (128, 1), (128, 66), (128, 128), (128, 129), (128, 384), (128, 385), (128, 700)])
+def test_few_queries_of_more_heads_than_cus(d, Nk, causal, vblock):
+    # More than 256 groups of 32 queries: up to 32 queries per head the packed kernel (d = 64) or the fused one (d = 128) takes short
+    # key sequences, the twelve-wavefront kernel the rest; d = 64 and 33 to 64 queries the packed kernel between 128 and 2048 keys.
+    # One to 256 groups and at most 128 keys: the packed kernel.  All against the rows of a call with more than 64 queries and more
+    # than 512 groups, which is the fused kernel's.
+    import paper_2409_16997_amd as ifa
+    Bc = ifa.block_cols(d, causal)
+    N = max(Nk, 129) if not causal else Nk                       # queries of that call (more than keys only without the mask)
+    heads = 530 if Nk <= 128 or Nk in (1024, 1025) else 300
+    q8, k8, v8, sq, sk = problem(heads, max(N, Nk), d, Nk)
+    k8, v8, sk = (t[:, :, :Nk].contiguous() for t in (k8, v8, sk))
+    g = torch.Generator(device="cuda").manual_seed(Nk)
+    sv = 0.005 + 0.02 * torch.rand((1, heads) + ((-(-Nk // Bc),) if vblock else ()), generator=g, device="cuda")
+    call = lambda q, a, n: ifa.int_flash_attn_fwd(q[:, :n].contiguous(), k8[:, :n], v8[:, :n], a[:, :n].contiguous(), sk[:, :n], sv[:, :n],
+                                                  causal=causal, out_dtype=torch.float32)
+    full = call(q8, sq, heads)
+    for n, nq in ((heads, 1), (heads, 8), (heads, 32), (257, 32), (257, 31), (256, 32), (256, 33), (140, 64), (140, 40), (7, 1), (3, 33), (2, 128)):
+        if nq > N:
+            continue
+        out, ref = call(q8[:, :, N - nq:], sq[:, :, N - nq:], n), full[:, :n, N - nq:]
+        if vblock and causal:                                    # as above
+            assert bool(((out - ref).abs() <= 2.0 ** -21 * ref.abs()).all()), (n, nq)
+        else:
+            assert torch.equal(out, ref), (n, nq)
+    h = lambda t, n=1: t[0, :n].cpu().numpy()
+    res = oracle.compare_up_to_ties(h(full)[0], h(q8), h(k8), h(v8), h(sq), h(sk), h(sv), causal, Bc)
+    assert float(res["err"].max()) <= 1e-3 * float(res["scale"])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,Nk", [(64, 64), (64, 65), (128, 256), (128, 257)])
+def test_few_queries_of_more_heads_than_cus_half_int8(d, Nk, causal):
+    import paper_2409_16997_amd as ifa
+    heads = 300
+    q8, k8, v8, sq, sk = problem(heads, Nk, d, Nk)
+    v = v8.to(torch.float16) / 64
+    call = lambda q, a, n: ifa.int_flash_attn_fwd_half(q[:, :n].contiguous(), k8[:, :n], v[:, :n], a[:, :n].contiguous(), sk[:, :n], causal=causal,
+                                                       out_dtype=torch.float32)
+    full, bound = call(q8, sq, heads), (2 * Nk / 64 + 24) * 2.0 ** -24   # as above
+    for n, nq in ((heads, 1), (heads, 32), (257, 31), (256, 32)):
+        out, ref = call(q8[:, :, Nk - nq:], sq[:, :, Nk - nq:], n), full[:, :n, Nk - nq:]
+        assert bool(((out - ref).abs() <= bound * ref.abs()).all()), (n, nq)
