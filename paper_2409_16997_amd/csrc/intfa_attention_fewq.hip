@@ -39,9 +39,9 @@ using namespace ifa_tiles;
 // with 32 workgroups), which is 1.07 us per group of 64 KB at d = 128; the chain MFMA - scale - exchange - exp - exchange of a
 // group takes 1.0 us.  One block at a time by four wavefronts took 1.29 us per 32 KB.  DS = 2 (d = 128): two workgroups per
 // (head, query group), each with half of the d columns of V and O.  Both compute the scores; K and the lines of V are then
-// read twice, but by CUs of one XCD at about the same time, so memory sees them once, and each CU takes in 48 KB per group.
-// 32 heads of 4099 keys, one query: 21 us (without DS = 2 23.7, the former kernel 42.5); 128 heads of 16384: 89.5 us = 6.0 TB/s (95,
-// 144); 512 of 4096 (DS = 1): 79 us = 6.8 TB/s.
+// read twice, by CUs of one XCD at about the same time, and each CU takes in 48 KB per group.
+// 32 heads of 4099 keys, one query: 21 us (without DS = 2 23.7, the packed kernel 42.5); K and V not in the caches: 128 heads of
+// 16384 (DS = 1) 95 us = 5.7 TB/s (the packed kernel 148), 512 of 4096 91 us = 5.9 TB/s (131).
 // Every number is computed by the same instruction sequence on the same operands as in the fused kernel (the
 // integer sums are exact, the extremum is order-independent, the row sum l is taken over the same P dwords), so
 // the output is bit-identical to the corresponding rows of a square call: still Algorithm 1 at B_c = 128.
@@ -1037,8 +1037,12 @@ int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
     if (ifa_packed_queries(heads, Nq, Nk, D)) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
-    // K and V with the non-temporal hint where each byte is read once and there are more of them than the caches could keep
-    // for the next call (128 heads of 4096 x 128, 134 MB: 26.9 us with the hint, 29.2 without; 32 heads, 34 MB: 25.5 and 22.0; DS = 1)
+    // K and V with the non-temporal hint where one workgroup reads each byte, and reads it once, and there are more of them than the
+    // caches could keep for the next call; such a call runs with DS = 1.  (With the hint and DS = 2 the second workgroup of a pair may
+    // find a line gone: right after K and V were written that costs the memory traffic twice.)  128 heads x 1 x 16384, 537 MB, us, after
+    // the same call / after a read of 512 MB elsewhere / after a copy of 512 MB / right after K and V were quantized:
+    //   hint, DS = 1 94 / 95 / 112 / 108;  hint, DS = 2 89 / 91 / 109 / 139;  no hint, DS = 2 100 / 100 / 120 / 122;  key split 100 / 103 / 112 / 112.
+    // Below the line, 64 x 1 x 4096, 67 MB: hint, DS = 1 22.9 / 27.3 / 27.8 / 23.5; no hint, DS = 2 20.0 / 27.4 / 32.4 / 22.5.
     const int once = qgroups == 1 && 2L * heads * Nk * D > (64L << 20);
     auto launch = [&](auto ds) {
         constexpr int DS = decltype(ds)::value;
@@ -1047,7 +1051,7 @@ int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float
     };
     if constexpr (D == 128) {
         // two workgroups per query group as long as each then has a CU of its own
-        if (heads * qgroups <= 128) launch(std::integral_constant<int, 2>{});
+        if (heads * qgroups <= 128 && !once) launch(std::integral_constant<int, 2>{});
         else launch(std::integral_constant<int, 1>{});
     } else launch(std::integral_constant<int, 1>{});
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
@@ -1085,17 +1089,20 @@ int launch_splitk_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const
     }
 }
 
-// Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  It walks 1000 keys of every head in 4.4 us (d = 64: 3.5)
-// however many heads there are, until the chip is full; the split passes stream K, V and the scores (or K twice) of all heads
-// at 5 - 6 TB/s, in three launches that take 15 us together on short sequences.  Narrow / split, us, d = 128 unless stated:
-//   up to 2048 keys  8 heads x 1 x 2048 13.5 / 23.1, 64 x 8 x 2048 12.2 / 17.3, 128 x 1 x 2048 13.2 / 26.0; d = 64, 8 x 1 x 2048 9.9 / 16.0
-//   many heads       128 x 1 x 16384 88.3 / 95.1, 128 x 8 x 8192 45.9 / 68.1, 96 x 8 x 16384 82.1 / 98.3, 64 x 16 x 8192 40.0 / 60.3; d = 64,
-//                    192 x 1 x 16384 61.2 / 87.3, 96 x 8 x 16384 59.4 / 64.4
-//   below the line   96 x 1 x 16384 82.0 / 76.4, 64 x 8 x 16384 77.0 / 68.1, 32 x 16 x 16384 71.7 / 60.7; d = 64, 128 x 1 x 16384 58.9 / 56.1,
-//                    64 x 8 x 8192 32.0 / 27.7, 64 x 16 x 8192 32.1 / 30.2
-//   up to 4096 keys half as many heads do: 64 x 1 x 4096 19.6 / 26.2, 48 x 16 20.2 / 29.1; 32 x 1 19.0 / 16.3, 32 x 16 19.4 / 18.9
+// Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  The
+// few-query kernel walks 1000 keys of every head in 4.4 us (d = 64: 3.5) however many heads there are, until the chip is full; the split
+// passes stream K, V and the scores (or K twice) of all heads at 5 - 6 TB/s, in three launches that take 15 us together on short
+// sequences.  Without / with the split, us, after the same call and (beyond 4096 keys) after a read of 512 MB elsewhere, d = 128 unless
+// stated:
+//   up to 2048 keys  8 heads x 1 x 2048 11.4 / 17.0, 64 x 8 x 2048 12.7 / 18.2, 128 x 1 x 2048 13.9 / 27.0; d = 64, 8 x 1 x 2048 10.3 / 17.5
+//   up to 4096 keys  half as many heads do as further on: 57 x 1 x 4096 22 / 28, 49 x 8 21 / 28, 33 x 16 20 / 28; 32 x 1 20 / 18; d = 64, 81 x 1 18 / 19.
+//                    (After a copy of 512 MB, which leaves the caches to write back, 64 x 4 x 4096 36 / 32.)
+//   many heads       1 query: 112 x 16384 90, 92 / 90, 99, 128 x 16384 93, 95 / 97, 103; 5: 96 x 16384 87, 90 / 91, 95, 96 x 32768 171, 174 / 174, 179; 9: 64 x 16384
+//                    82, 85 / 83, 87, 72 x 32768 164, 166 / 165, 168; d = 64, 160 x 1 x 16384 64, 66 / 75, 82, 112 x 5 x 16384 60, 63 / 67, 71, 96 x 16 60, 64 / 124, 125
+//   below the line   96 x 1 x 16384 82 / 76, 80 x 5 x 16384 85, 87 / 80, 83, 64 x 9 x 32768 162, 164 / 146, 150; d = 64, 128 x 1 x 16384 65, 65 / 58, 65,
+//                    96 x 5 x 32768 117, 121 / 106, 110, 80 x 9 x 16384 60, 62 / 54, 59
 inline bool narrow_beats_split(int heads, int Nq, int Nk, int d) {
-    const int enough = Nq > SPLIT_MAX_Q ? (d == 128 ? 64 : 96) : Nq > 4 ? (d == 128 ? 96 : 112) : (d == 128 ? 112 : 160);
+    const int enough = Nq > SPLIT_MAX_Q ? (d == 128 ? (Nk <= 16384 ? 64 : 72) : 96) : Nq > 4 ? (d == 128 ? 96 : 112) : (d == 128 ? 112 : 160);
     return heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2);
 }
 

@@ -668,7 +668,10 @@ int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float
     // d = 64: 2000 x 1 x 64 15.0 / 13.1, x 128 17.4 / 19.2, 32 x 512 x 2048 20 / 33.
     if (ifa_few_queries(heads, Nq, Nk, D == 128 ? 256 : 64)) {
         const long qgroups = (Nq + FEW_BR - 1) / FEW_BR, padded = (heads * qgroups + 7) / 8 * 8;
-        const int once = qgroups == 1 && 3L * heads * Nk * D > (64L << 20);   // the rule of launch_narrow in intfa_attention_fewq.hip
+        // the non-temporal hint where K and V are read once and do not stay in the caches, here with DS = 2 as well, us after the same call /
+        // after a copy of 512 MB / right after K was quantized and V written: 128 x 1 x 4096, 101 MB, 32 / 41 / 36, without it 32 / 61 / 41;
+        // 128 x 1 x 16384 138 / 157 / 174 and 141 / 167 / 172
+        const int once = qgroups == 1 && 3L * heads * Nk * D > (64L << 20);
         auto launch = [&](auto ds) {
             constexpr int DS = decltype(ds)::value;
             hipLaunchKernelGGL((int_flash_attn_fwd_half_few_kernel<D, CAUSAL, OutT, DS>), dim3(static_cast<unsigned>(padded * DS)), dim3(FEW_THREADS), 0,

@@ -80,12 +80,14 @@ def test_half_int8_kernels_agree(heads, N, d, causal):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d,Nq,heads", [(128, 1, 112), (128, 8, 96), (128, 32, 64), (64, 4, 160), (64, 5, 112), (64, 9, 96)])
 def test_key_split_entry_point_on_both_sides_of_its_rule(d, Nq, heads, causal):
-    # `heads` is the number from which the entry point runs the few-query kernel at any length: the same result, bit for bit.
+    # `heads` is the number from which the entry point runs the few-query kernel at any length (d = 128 and more than 8 queries: up
+    # to 16384 keys, 72 heads beyond): the same result, bit for bit.
     # Below it, and with more than 2048 keys, the split passes run, which add up O in another order (a few ulp of the
     # largest value; in the last case the last run of key blocks is masked for the early queries).
     import paper_2409_16997_amd as ifa
     for H, Nk, same in ((heads, 4099, True), (heads - 1, 4097, False), (heads - 1, 4096, True), (heads // 2, 4096, False),
-                        (heads // 2 + 1, 2049, True), (3, 2048, True), (3, 2049, False), (2, 4098, False)):
+                        (heads // 2 + 1, 2049, True), (3, 2048, True), (3, 2049, False), (2, 4098, False)) + (
+            ((64, 16384, True), (64, 16385, False), (71, 16500, False), (72, 16385, True)) if (d, Nq) == (128, 32) else ()):
         q8, k8, v8, sq, sk = problem(H, Nk, d, H + Nk)
         q8, sq = q8[:, :, Nk - Nq:].contiguous(), sq[:, :, Nk - Nq:].contiguous()
         sv = 0.005 + 0.02 * torch.rand((1, H), device="cuda", generator=torch.Generator(device="cuda").manual_seed(Nk))
