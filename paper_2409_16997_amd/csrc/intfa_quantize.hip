@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void quantize_tokenwise_kernel(TokenJob j0, To
 //   parts  `parts` workgroups per head leave the absmax of their part (fp32 bits) at the START of each of the `regions`
 //          the second launch cuts the head's codes into: a workgroup of that launch reads the words in front of its own
 //          region before it writes its codes over them, so nobody else's words are touched and no third launch is needed.
-constexpr int HEAD_THREADS = 1024;
+constexpr int HEAD_THREADS = 1024, SHORT_HEAD_THREADS = 256;
 template <typename T> constexpr int LOADS_IN_FLIGHT = sizeof(T) == 2 ? 4 : 2;   // chunks of 8 per thread
 constexpr int KEEP_BYTES = 96 << 10;   // 24 registers per thread: two workgroups per CU
 struct HeadJob {
@@ -208,7 +208,7 @@ template <int THREADS> __device__ __forceinline__ float workgroup_max(float a) {
     return a;
 }
 
-template <typename T> __device__ __forceinline__ void head_whole(const HeadJob &hj, long head) {
+template <typename T, int THREADS> __device__ __forceinline__ void head_whole(const HeadJob &hj, long head) {
     constexpr int KEEP = sizeof(T) == 2 ? KEEP_BYTES / 16384 : KEEP_BYTES / 32768;   // chunks per thread
     constexpr int U = LOADS_IN_FLIGHT<T>;
     const T *X = static_cast<const T *>(hj.X) + head * hj.per_head;
@@ -218,54 +218,54 @@ template <typename T> __device__ __forceinline__ void head_whole(const HeadJob &
     float a = 0.0f, x[8];
 #pragma unroll
     for (int i = 0; i < KEEP; ++i)
-        if (tid + i * HEAD_THREADS < chunks) keep[i].load(X, 8 * (tid + i * HEAD_THREADS));
+        if (tid + i * THREADS < chunks) keep[i].load(X, 8 * (tid + i * THREADS));
 #pragma unroll
     for (int i = 0; i < KEEP; ++i)
-        if (tid + i * HEAD_THREADS < chunks) {
+        if (tid + i * THREADS < chunks) {
             keep[i].widen(x);
             a = fmaxf(a, absmax8(x));
         }
-    const int first = KEEP * HEAD_THREADS + tid;
+    const int first = KEEP * THREADS + tid;
     int c = first;
-    for (; c + (U - 1) * HEAD_THREADS < chunks; c += U * HEAD_THREADS) {
+    for (; c + (U - 1) * THREADS < chunks; c += U * THREADS) {
         Raw8<T> r[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) r[i].load(X, 8 * (c + i * HEAD_THREADS));
+        for (int i = 0; i < U; ++i) r[i].load(X, 8 * (c + i * THREADS));
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             r[i].widen(x);
             a = fmaxf(a, absmax8(x));
         }
     }
-    for (; c < chunks; c += HEAD_THREADS) {
+    for (; c < chunks; c += THREADS) {
         load8<T>(X, 8 * c, x);
         a = fmaxf(a, absmax8(x));
     }
-    a = workgroup_max<HEAD_THREADS>(a);
+    a = workgroup_max<THREADS>(a);
 #pragma unroll
     for (int i = 0; i < KEEP; ++i) keep[i].hold();
     const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
     if (tid == 0) hj.scale[head] = (a == 0.0f) ? 1.0f : a / 127.0f;
     // backwards: what was read last is nearest
-    for (c -= HEAD_THREADS; c - (U - 1) * HEAD_THREADS >= first; c -= U * HEAD_THREADS) {
+    for (c -= THREADS; c - (U - 1) * THREADS >= first; c -= U * THREADS) {
         Raw8<T> r[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) r[i].load(X, 8 * (c - i * HEAD_THREADS));
+        for (int i = 0; i < U; ++i) r[i].load(X, 8 * (c - i * THREADS));
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             r[i].widen(x);
-            *reinterpret_cast<uint2 *>(Xq + 8 * (c - i * HEAD_THREADS)) = quant8(x, inv);
+            *reinterpret_cast<uint2 *>(Xq + 8 * (c - i * THREADS)) = quant8(x, inv);
         }
     }
-    for (; c >= first; c -= HEAD_THREADS) {
+    for (; c >= first; c -= THREADS) {
         load8<T>(X, 8 * c, x);
         *reinterpret_cast<uint2 *>(Xq + 8 * c) = quant8(x, inv);
     }
 #pragma unroll
     for (int i = 0; i < KEEP; ++i)
-        if (tid + i * HEAD_THREADS < chunks) {
+        if (tid + i * THREADS < chunks) {
             keep[i].widen(x);
-            *reinterpret_cast<uint2 *>(Xq + 8 * (tid + i * HEAD_THREADS)) = quant8(x, inv);
+            *reinterpret_cast<uint2 *>(Xq + 8 * (tid + i * THREADS)) = quant8(x, inv);
         }
 }
 
@@ -297,11 +297,15 @@ template <typename T> __device__ __forceinline__ void head_part_absmax(const Hea
 // What workgroup `wg` of a launch does for V before any row of Q and K is touched; the number of such workgroups is
 // heads (whole) or heads * parts.
 template <typename T> __device__ __forceinline__ void head_first_pass(const HeadJob &hj, int wg) {
-    if (hj.parts == 0) head_whole<T>(hj, wg);
+    if (hj.parts == 0) head_whole<T, HEAD_THREADS>(hj, wg);
     else head_part_absmax<T>(hj, wg / hj.parts, wg % hj.parts);
 }
 template <typename T> __global__ __launch_bounds__(HEAD_THREADS, 8) void head_first_pass_kernel(HeadJob hj) {
     head_first_pass<T>(hj, static_cast<int>(blockIdx.x));
+}
+
+template <typename T> __global__ __launch_bounds__(SHORT_HEAD_THREADS, 8) void short_head_kernel(HeadJob hj) {
+    head_whole<T, SHORT_HEAD_THREADS>(hj, blockIdx.x);
 }
 
 // Second launch of `parts`: one workgroup per (region, head).
@@ -443,9 +447,15 @@ int launch_tokenwise(const TokenJob &j0, const TokenJob &j1, int jobs, long rows
 // the line: 81 and 73).  With fewer heads one workgroup walks its head at about 40 GB/s next to the fixed 4 us, and what
 // the second launch costs (2.5 us) only buys the chip's bandwidth for heads that are long: 4 heads of 256 KB 10.7 us whole
 // and 7.6 in parts, 64 heads of 128 KB 10.2 and 12.0.
-HeadJob plan_heads(const void *X, long heads, long per_head, int elem_bytes, int8_t *Xq, float *scale) {
+// `alone`: no rows of Q and K to fill in around the heads, so long heads that leave CUs without one (256 take a head each, then the
+// next 256) go in parts as well.  V alone, whole / in parts, us, repeated and with inputs in rotation: 96 x 8192 x 128 fp16 101, 121 / 84, 103, fp32 220, 232 /
+// 174, 186; 128 x 4096 x 128 fp32 108, 127 / 95, 108; 260 x 2048 x 128 fp16 60, 71 / 56, 66, fp32 121, 135 / 105, 121; 300 x 8192 x 64 fp16 155, 166 / 149, 157;
+// on the other side 128 x 4096 x 128 fp16 49, 67 / 54, 62, 128 x 1024 x 128 fp32 19, 27 / 25, 28, 160 x 4096 x 128 fp16 59, 78 / 66, 78, 256 x 4096 x 128 fp16 101, 117 / 118, 133.
+HeadJob plan_heads(const void *X, long heads, long per_head, int elem_bytes, int8_t *Xq, float *scale, bool alone) {
     HeadJob hj = {X, Xq, scale, per_head, static_cast<int>(heads), 0, 0, 0, 0};
-    if ((heads >= 96 && per_head < (1L << 29)) || per_head * elem_bytes <= (64L << 10) + heads * (4L << 10)) return hj;
+    const long head_bytes = per_head * elem_bytes, rounds = (heads + 255) / 256;
+    const bool uneven = alone && 8 * heads < 5 * 256 * rounds && head_bytes > (heads > 256 ? 256L << 10 : 1L << 20);
+    if ((heads >= 96 && per_head < (1L << 29) && !uneven) || head_bytes <= (64L << 10) + (heads < 96 ? heads * (4L << 10) : 0)) return hj;
     const long chunks = per_head / 8;
     auto split = [&](long want, long &per) {             // at most `want` pieces of at least HEAD_THREADS chunks
         long n = chunks / HEAD_THREADS < want ? chunks / HEAD_THREADS : want;
@@ -469,7 +479,13 @@ template <typename T> int launch_head_second(const HeadJob &hj, hipStream_t st) 
 template <typename T>
 int launch_headwise(const void *X, long heads, long per_head, int8_t *Xq, float *scale, int global_scale, hipStream_t st) {
     if (!global_scale) {
-        const HeadJob hj = plan_heads(X, heads, per_head, sizeof(T), Xq, scale);
+        const HeadJob hj = plan_heads(X, heads, per_head, sizeof(T), Xq, scale, true);
+        // Many short heads: four workgroups of 256 in the place of one of 1024, most of whose threads have nothing to do (8192 heads of 2 KB
+        // 8.6 us, 25 with 1024; 8192 of 8 KB 17 and 29; 4096 of 32 KB, beyond the line, 34 and 32).
+        if (hj.parts == 0 && heads > 512 && per_head * static_cast<long>(sizeof(T)) <= (16L << 10)) {
+            hipLaunchKernelGGL((short_head_kernel<T>), dim3(static_cast<unsigned>(heads)), dim3(SHORT_HEAD_THREADS), 0, st, hj);
+            return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+        }
         hipLaunchKernelGGL((head_first_pass_kernel<T>), dim3(static_cast<unsigned>(head_workgroups(hj))), dim3(HEAD_THREADS), 0, st, hj);
         return launch_head_second<T>(hj, st);
     }
@@ -486,7 +502,7 @@ int launch_headwise(const void *X, long heads, long per_head, int8_t *Xq, float 
 
 template <typename T>
 int launch_qkv(const TokenJob &jq, const TokenJob &jk, const void *V, long heads, long N, int d, int8_t *Vq, float *sV, hipStream_t st) {
-    const HeadJob hj = plan_heads(V, heads, N * d, sizeof(T), Vq, sV);
+    const HeadJob hj = plan_heads(V, heads, N * d, sizeof(T), Vq, sV, false);
     const int head_wgs = head_workgroups(hj);
     const long rows = heads * N, rows_per_block = HEAD_THREADS / (d / 8);
     long per_tensor = (rows + rows_per_block - 1) / rows_per_block;

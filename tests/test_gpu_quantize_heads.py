@@ -9,15 +9,19 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-# 2-byte elements: 6144 chunks of 8 stay in registers, 4096 more per step of the loop behind; whole heads up to 64 KB + 4 KB
-# per head or from 96 heads on
+# 6144 chunks of 8 elements stay in registers (4-byte ones: 3072), 4096 more per step of the loop behind (2048).  Whole heads up to 64 KB
+# + 4 KB per head or from 96 heads on, except long ones that leave CUs without one (V alone, not in quantize_qkv); heads of up to
+# 16 KB of more than 512 heads go to smaller workgroups (V alone).
 SHAPES = [
-    (1, 1, 64), (1, 511, 64), (1, 512, 64),              # one workgroup; 32768 elements is the last size it takes alone
-    (1, 513, 64), (3, 577, 128), (2, 1151, 64),          # parts: one past the line, remainders in the last part and region
+    (1, 1, 64), (1, 272, 64), (1, 273, 64), (1, 544, 64), (1, 545, 64),   # one workgroup or parts: 68 KB at 4 and at 2 bytes
+    (3, 577, 128), (2, 1151, 64),                        # parts: remainders in the last part and region
     (1, 16384, 128), (5, 4099, 128),                     # 64 and more parts wanted
     (96, 767, 64), (96, 768, 64), (97, 769, 64),         # whole heads at the end of the registers (6144 chunks)
     (96, 1279, 64), (96, 1280, 64), (96, 1281, 64),      # ... and at one full step of the loop (10240 chunks)
     (96, 1025, 128), (100, 1793, 64),
+    (96, 4096, 128), (96, 4097, 128), (260, 1024, 128), (260, 1025, 128),   # 1 MB and 256 KB per head at 2 bytes: whole up to here, then in parts
+    (513, 1, 64), (513, 63, 64), (513, 64, 64), (513, 65, 64), (520, 128, 64), (520, 129, 64), (512, 7, 64),   # 16 KB per head at 4 and at 2 bytes
+    (96, 2741, 128), (33, 4099, 128),                    # more rows of Q and K than one sweep of the launch (whole 262144, parts 131072)
 ]
 
 
