@@ -666,7 +666,7 @@ int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float
     // as for INT8, this kernel / the one below, us.  d = 128: 32 heads x 256 queries x 8192 keys 64 / 145, x 512 119 / 145, x 700 184 / 146;
     // 512 x 32 x 2048 66 / 79, x 64 94 / 81; short keys 512 x 1 x 128 9.6 / 8.8, 2000 x 32 x 256 53 / 51, 2000 x 1 x 384 54 / 62.
     // d = 64: 2000 x 1 x 64 15.0 / 13.1, x 128 17.4 / 19.2, 32 x 512 x 2048 20 / 33.
-    if (ifa_few_queries(heads, Nq, Nk, D == 128 ? 256 : 64)) {
+    if (ifa_few_queries(heads, Nq, Nk, D, true)) {
         const long qgroups = (Nq + FEW_BR - 1) / FEW_BR, padded = (heads * qgroups + 7) / 8 * 8;
         // the non-temporal hint where K and V are read once and do not stay in the caches, here with DS = 2 as well, us after the same call /
         // after a copy of 512 MB / right after K was quantized and V written: 128 x 1 x 4096, 101 MB, 32 / 41 / 36, without it 32 / 61 / 41;

@@ -24,7 +24,8 @@ constexpr long IFA_FEW_MAX_GROUPS = 5L << 20;
 //   more, longer ones                two waves win on long key sequences (32 x 512 x 8192 79 / 106, 256 x 64 x 2048 37 / 37) and lose on short ones
 //                                    (64 x 200 x 200 7.5 / 5.9), more lose (32 x 700 x 8192 120 / 107, 512 x 64 x 2048 71 / 59)
 static inline long ifa_query_groups(int heads, int Nq) { return static_cast<long>(heads) * ((Nq + 31) / 32); }
-static inline bool ifa_few_queries(int heads, int Nq, int Nk, int short_keys) {
+static inline bool ifa_few_queries(int heads, int Nq, int Nk, int d, bool half) {
+    const int short_keys = half ? (d == 128 ? 256 : 64) : (d == 128 ? 384 : 0);   // (INT8, d = 64: the packed kernel's)
     const long groups = ifa_query_groups(heads, Nq);
     if (groups > IFA_FEW_MAX_GROUPS) return false;
     if (groups <= 256) return true;

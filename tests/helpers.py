@@ -34,3 +34,35 @@ def random_int8_problem(rng, heads, N, d, score_sigma=1.0):
     sK = (rng.uniform(0.5, 1.5, (heads, N)) * np.sqrt(base)).astype(np.float32)
     sV = rng.uniform(0.005, 0.02, heads).astype(np.float32)
     return Qq, Kq, Vq, sQ, sK, sV
+
+
+def route(heads, Nq, Nk, d, half=False):
+    """Which kernel a plain attention call runs: "fused", "few" (twelve wavefronts per 32 queries, half-INT8 eight) or "packed".
+    tests/test_routes.py holds this to the library's own rule."""
+    groups = heads * -(-Nq // 32)
+    if not half:
+        if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (1280 if groups <= 512 else 1024) if Nq <= 32 else
+                                                        Nq <= 64 and groups <= 512 and 128 <= Nk < 2048):
+            return "packed"
+    short_keys = {(True, 128): 256, (True, 64): 64, (False, 128): 384, (False, 64): 0}[half, d]
+    if groups <= 5 << 20 and (groups <= 256 or (Nk > short_keys if Nq <= 32 else groups <= 512 and Nk >= 2048)):
+        return "few"
+    return "fused"
+
+
+def copies_for_the_fused_kernel(heads, Nq, Nk, d, half=False):
+    """How many copies of these heads make a call that runs the fused kernel; None if no number does."""
+    copies = -(-513 // (heads * -(-Nq // 32)))
+    return copies if route(heads * copies, Nq, Nk, d, half) == "fused" else None
+
+
+def many(copies, *arrays):
+    """`copies` copies of the heads of each array, one after the other."""
+    return [np.concatenate([a] * copies) for a in arrays]
+
+
+def first_copy(O, copies):
+    """What the first copy of the heads got, as a host array; every copy must have got the same."""
+    o = O.reshape(copies, -1)
+    assert bool((o == o[:1]).all()), "copies of a head differ"
+    return o[0].cpu().numpy()

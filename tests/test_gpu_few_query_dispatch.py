@@ -1,7 +1,7 @@
-"""The few-query kernel and the fused kernel on the two sides of the dispatcher's rule: the same rows, bit for bit.
+"""The few-query kernels and the fused kernel on the two sides of the dispatcher's rule: the same rows, bit for bit.
 
-A call with many heads runs the fused kernel; the same problem on a few of the heads (or on the last few queries) runs the
-few-query kernel.  Both perform Algorithm 1 with the same operations on the same operands, so torch.equal is the bar; one
+A call with many heads runs the fused kernel; the same problem on a few of the heads (or on the last few queries) runs a
+few-query kernel.  All perform Algorithm 1 with the same operations on the same operands, so torch.equal is the bar; one
 head of each shape is also held to the oracle."""
 import numpy as np
 import pytest
@@ -9,6 +9,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle
+from helpers import route
 
 pytestmark = pytest.mark.gpu
 
@@ -31,6 +32,7 @@ def problem(heads, N, d, seed):
 @pytest.mark.parametrize("heads,N", SHAPES)
 def test_both_kernels_give_the_same_rows(heads, N, d, causal, vblock):
     import paper_2409_16997_amd as ifa
+    assert route(heads, N, N, d) == "fused" and route(5, N, N, d) == ("packed" if N <= 128 else "few")
     q8, k8, v8, sq, sk = problem(heads, N, d, heads + N)
     Bc = ifa.block_cols(d, causal)
     g = torch.Generator(device="cuda").manual_seed(N)
@@ -157,6 +159,7 @@ def test_few_queries_of_more_heads_than_cus(d, Nk, causal, vblock):
     sv = 0.005 + 0.02 * torch.rand((1, heads) + ((-(-Nk // Bc),) if vblock else ()), generator=g, device="cuda")
     call = lambda q, a, n: ifa.int_flash_attn_fwd(q[:, :n].contiguous(), k8[:, :n], v8[:, :n], a[:, :n].contiguous(), sk[:, :n], sv[:, :n],
                                                   causal=causal, out_dtype=torch.float32)
+    assert route(heads, N, Nk, d) == "fused"
     full = call(q8, sq, heads)
     for n, nq in ((heads, 1), (heads, 8), (heads, 32), (257, 32), (257, 31), (256, 32), (256, 33), (140, 64), (140, 40), (7, 1), (3, 33), (2, 128)):
         if nq > N:
@@ -184,3 +187,30 @@ def test_few_queries_of_more_heads_than_cus_half_int8(d, Nk, causal):
     for n, nq in ((heads, 1), (heads, 32), (257, 31), (256, 32)):
         out, ref = call(q8[:, :, Nk - nq:], sq[:, :, Nk - nq:], n), full[:, :n, Nk - nq:]
         assert bool(((out - ref).abs() <= bound * ref.abs()).all()), (n, nq)
+
+
+# One query per head and more than 64 MB of K and V: the copies carry the non-temporal hint (INT8: one workgroup per head; half-INT8: two up
+# to 128 heads at d = 128).
+@pytest.mark.parametrize("variant,heads,Nk,d", [("full", 65, 4200, 128), ("full", 136, 2050, 128), ("full", 140, 4100, 64),
+                                                ("half", 100, 2100, 128), ("half", 130, 1500, 128), ("half", 120, 3100, 64), ("half", 300, 1300, 64)])
+def test_long_caches_are_read_past_the_caches(variant, heads, Nk, d):
+    import paper_2409_16997_amd as ifa
+    half = variant == "half"
+    assert heads * Nk * d * (3 if half else 2) > 64 << 20 and route(heads, 1, Nk, d, half) == "few"
+    q8, k8, v8, sq, sk = problem(heads, Nk, d, heads)
+    q8, sq = q8[:, :, 1:2].contiguous(), sq[:, :, 1:2].contiguous()
+    sv = 0.005 + 0.02 * torch.rand((1, heads), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    pick = [0, heads // 2, heads - 1]
+    n = lambda t: t[0, pick].cpu().numpy()
+    if half:
+        v = v8.to(torch.float16) / 64
+        O = ifa.int_flash_attn_fwd_half(q8, k8, v, sq, sk, causal=True, out_dtype=torch.float32)
+        ref = oracle.int_flash_attn_fwd_half(n(q8), n(k8), n(v), n(sq), n(sk), True, ifa.block_cols_half(d, True))["O"].reshape(-1, d)
+        assert np.abs(n(O).reshape(-1, d) - ref).max() <= 1e-3 * np.abs(ref).max()
+        few = ifa.int_flash_attn_fwd_half(*[t[:, :8].contiguous() for t in (q8, k8, v, sq, sk)], causal=True, out_dtype=torch.float32)
+    else:
+        O = ifa.int_flash_attn_fwd(q8, k8, v8, sq, sk, sv, causal=True, out_dtype=torch.float32)
+        res = oracle.compare_up_to_ties(n(O).reshape(-1, d), n(q8), n(k8), n(v8), n(sq), n(sk), n(sv), True, ifa.block_cols(d, True))
+        assert float(res["err"].max()) <= 1e-3 * float(res["scale"])
+        few = ifa.int_flash_attn_fwd(*[t[:, :8].contiguous() for t in (q8, k8, v8, sq, sk, sv)], causal=True, out_dtype=torch.float32)
+    assert torch.equal(few, O[:, :8])                            # without the hint: the same bits

@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import workloads
-from helpers import quantized_inputs
+from helpers import copies_for_the_fused_kernel, first_copy, many, quantized_inputs, route
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -56,6 +56,12 @@ def run(ifa, x, B, H, N, d, causal, out_dtype=torch.float32, out=None):
     return O
 
 
+def wide(x, copies):
+    """The problem with `copies` copies of its heads."""
+    keys = [k for k in ("Qq", "Kq", "Vh", "sQ", "sK") if k in x]
+    return dict(zip(keys, many(copies, *[x[k] for k in keys])))
+
+
 def test_block_cols_half(ifa):
     assert ifa.block_cols_half(128, True) == 64 and ifa.block_cols_half(64, False) == 64
     assert ifa.block_cols_half(96, False) == 0
@@ -64,30 +70,35 @@ def test_block_cols_half(ifa):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,H,N,d", [(1, 1, 128, 128), (1, 3, 256, 64), (2, 4, 384, 128), (1, 5, 640, 128), (1, 8, 512, 64)])
 @pytest.mark.parametrize("dist", ["normal", "uniform_outlier", "student_t3"])
-def test_shapes_masks_distributions(ifa, B, H, N, d, causal, dist):
+@pytest.mark.parametrize("fused", [False, True])
+def test_shapes_masks_distributions(ifa, B, H, N, d, causal, dist, fused):
+    # `fused`: with as many copies of the heads as the kernel for long calls wants
     w = workloads.custom("t", B, H, N, d, causal, dist=dist, seed=7 * B + N + d)
     x = inputs(w)
-    O = run(ifa, x, B, H, N, d, causal).cpu().numpy()
-    check(ifa, O.reshape(-1, d), x, causal, d, label=f"{B}x{H}x{N}x{d} causal={causal} {dist}")
+    copies = copies_for_the_fused_kernel(B * H, N, N, d, half=True) if fused else 1
+    O = first_copy(run(ifa, wide(x, copies), copies * B, H, N, d, causal), copies)
+    check(ifa, O.reshape(-1, d), x, causal, d, label=f"{B}x{H}x{N}x{d} causal={causal} {dist} fused={fused}")
 
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("N,d", [(1, 128), (37, 64), (63, 128), (64, 128), (65, 64), (127, 128), (129, 128), (200, 64),
                                  (333, 128), (1000, 128), (515, 64)])
-def test_ragged_sequence_lengths(ifa, N, d, causal):
+@pytest.mark.parametrize("fused", [False, True])
+def test_ragged_sequence_lengths(ifa, N, d, causal, fused):
     # N not a multiple of the 64-key block or of the 128-row workgroup: keys >= N masked, rows >= N not stored
-    heads = 3
-    w = workloads.custom("t", 1, heads, N, d, causal, dist="normal", seed=3 * N + d)
+    copies = copies_for_the_fused_kernel(3, N, N, d, half=True) if fused else 1
+    heads = 3 * copies
+    w = workloads.custom("t", 1, 3, N, d, causal, dist="normal", seed=3 * N + d)
     x = inputs(w)
     guard = 64
     Obuf = torch.full((heads * N + guard, d), 12345.0, dtype=torch.float32, device="cuda")
     O = Obuf[:heads * N].view(1, heads, N, d)
-    run(ifa, x, 1, heads, N, d, causal, out=O)
+    run(ifa, wide(x, copies), 1, heads, N, d, causal, out=O)
     assert bool((Obuf[heads * N:] == 12345.0).all())
-    check(ifa, O.cpu().numpy().reshape(-1, d), x, causal, d, label=f"ragged N={N} d={d} causal={causal}")
+    check(ifa, first_copy(O, copies).reshape(-1, d), x, causal, d, label=f"ragged N={N} d={d} causal={causal} fused={fused}")
 
 
-@pytest.mark.parametrize("B,H", [(5, 8), (3, 8), (1, 7)])
+@pytest.mark.parametrize("B,H", [(5, 8), (3, 8), (1, 7), (13, 5), (9, 8)])   # from 65 heads on the kernel for long calls
 def test_head_counts_and_grid_shapes(ifa, B, H):
     N, d = 256, 128
     w = workloads.custom("t", B, H, N, d, True, dist="normal", seed=13 * B + H)
@@ -99,19 +110,23 @@ def test_head_counts_and_grid_shapes(ifa, B, H):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Nq,Nk,d", [(1, 1000, 128), (128, 512, 128), (100, 333, 128), (256, 1024, 64), (130, 131, 128),
                                      (64, 2048, 128), (300, 200, 64)])
-def test_rectangular_problems(ifa, Nq, Nk, d, causal):
+@pytest.mark.parametrize("fused", [False, True])
+def test_rectangular_problems(ifa, Nq, Nk, d, causal, fused):
     if causal and Nk < Nq:
         return                                  # refused on the host (tests/test_abi.py)
     H = 3
+    copies = copies_for_the_fused_kernel(H, Nq, Nk, d, half=True) if fused else 1
+    if copies is None:
+        return                                  # up to 32 queries: only short keys are that kernel's
     wq = workloads.custom("t", 1, H, max(Nq, Nk), d, causal, dist="normal", seed=5 * Nq + Nk + d)
     x = inputs(wq)
     y = {"Qq": np.ascontiguousarray(x["Qq"][:, :Nq]), "sQ": np.ascontiguousarray(x["sQ"][:, :Nq]),
          "Kq": np.ascontiguousarray(x["Kq"][:, :Nk]), "sK": np.ascontiguousarray(x["sK"][:, :Nk]),
          "Vh": np.ascontiguousarray(x["Vh"][:, :Nk])}
-    O = ifa.int_flash_attn_fwd_half(dev(y["Qq"][None]), dev(y["Kq"][None]), dev(y["Vh"][None]), dev(y["sQ"][None]),
-                                    dev(y["sK"][None]), causal=causal, out_dtype=torch.float32)
+    z = wide(y, copies)
+    O = ifa.int_flash_attn_fwd_half(*[dev(z[k][None]) for k in ("Qq", "Kq", "Vh", "sQ", "sK")], causal=causal, out_dtype=torch.float32)
     torch.cuda.synchronize()
-    check(ifa, O.cpu().numpy().reshape(-1, d), y, causal, d, label=f"rect Nq={Nq} Nk={Nk} d={d} causal={causal}")
+    check(ifa, first_copy(O, copies).reshape(-1, d), y, causal, d, label=f"rect Nq={Nq} Nk={Nk} d={d} causal={causal} fused={fused}")
 
 
 def test_unscaled_scores_and_wide_range(ifa):
@@ -137,20 +152,24 @@ def test_score_accumulator_extremes(ifa, d):
     x = {"Qq": Qq, "Kq": Kq, "Vh": rng.standard_normal((heads, N, d)).astype(np.float16),
          "sQ": np.full((heads, N), np.sqrt(span), np.float32), "sK": np.full((heads, N), np.sqrt(span), np.float32)}
     for causal in (False, True):
-        O = run(ifa, x, 1, heads, N, d, causal).cpu().numpy()
-        check(ifa, O.reshape(-1, d), x, causal, d, label=f"extremes d={d} causal={causal}")
+        for copies in (1, copies_for_the_fused_kernel(heads, N, N, d, half=True)):
+            O = first_copy(run(ifa, wide(x, copies), copies, heads, N, d, causal), copies)
+            check(ifa, O.reshape(-1, d), x, causal, d, label=f"extremes d={d} causal={causal} copies={copies}")
 
 
-def test_degenerate_inputs(ifa):
+@pytest.mark.parametrize("fused", [False, True])
+def test_degenerate_inputs(ifa, fused):
     B, H, N, d = 1, 2, 256, 128
+    copies = copies_for_the_fused_kernel(H, N, N, d, half=True) if fused else 1
+    heads = lambda x, causal: first_copy(run(ifa, wide(x, copies), copies, H, N, d, causal), copies).reshape(H, N, d)
     rng = np.random.default_rng(5)
     V = rng.standard_normal((H, N, d)).astype(np.float16)
     s = np.full((H, N), 0.01, np.float32)
     # Q = 0: uniform weights, O = mean of V over the visible keys
     x = {"Qq": np.zeros((H, N, d), np.int8), "Kq": rng.integers(-127, 128, (H, N, d), dtype=np.int8), "Vh": V, "sQ": s, "sK": s}
-    O = run(ifa, x, B, H, N, d, False).cpu().numpy().reshape(H, N, d)
+    O = heads(x, False)
     assert np.allclose(O, V.astype(np.float64).mean(axis=1, keepdims=True), atol=2e-5)
-    Oc = run(ifa, x, B, H, N, d, True).cpu().numpy().reshape(H, N, d)
+    Oc = heads(x, True)
     pre = np.cumsum(V.astype(np.float64), axis=1) / np.arange(1, N + 1)[None, :, None]
     assert np.allclose(Oc, pre, atol=2e-5)
     # one dominant key per row: O is that row of V, exactly
@@ -158,7 +177,7 @@ def test_degenerate_inputs(ifa):
     Kq = np.zeros((H, N, d), np.int8); Kq[:, 77, 0] = 100
     sd = np.full((H, N), np.sqrt(40.0 / 10000.0), np.float32)
     x = {"Qq": Qq, "Kq": Kq, "Vh": V, "sQ": sd, "sK": sd}
-    O = run(ifa, x, B, H, N, d, False).cpu().numpy().reshape(H, N, d)
+    O = heads(x, False)
     assert np.array_equal(O, np.repeat(V[:, 77:78].astype(np.float32), N, axis=1))
     check(ifa, O.reshape(-1, d), x, False, d, label="dominant key")
 
@@ -166,12 +185,14 @@ def test_degenerate_inputs(ifa):
 @pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("N,d", [(1, 128), (33, 64), (127, 128), (129, 64), (200, 128), (515, 128)])
-def test_ragged_lengths_with_two_byte_outputs(ifa, N, d, causal, dtype):
-    # 2-byte outputs leave through the staged row-wise store: rows past N must not be written (canaries on both
+@pytest.mark.parametrize("fused", [False, True])
+def test_ragged_lengths_with_two_byte_outputs(ifa, N, d, causal, dtype, fused):
+    # 2-byte outputs (the long calls' leave through a staged row-wise store): rows past N must not be written (canaries on both
     # sides of O) and the values must be the fp32 result rounded once
-    heads = 3
-    w = workloads.custom("t", 1, heads, N, d, causal, dist="normal", seed=19 * N + d)
-    x = inputs(w)
+    copies = copies_for_the_fused_kernel(3, N, N, d, half=True) if fused else 1
+    heads = 3 * copies
+    w = workloads.custom("t", 1, 3, N, d, causal, dist="normal", seed=19 * N + d)
+    x = wide(inputs(w), copies)
     tdt = getattr(torch, dtype)
     guard = 256
     Obuf = torch.full((guard + heads * N + guard, d), 77.0, dtype=tdt, device="cuda")
@@ -182,8 +203,10 @@ def test_ragged_lengths_with_two_byte_outputs(ifa, N, d, causal, dtype):
     assert torch.equal(O, O32.to(tdt))
 
 
-def test_output_dtypes_and_determinism(ifa):
-    B, H, N, d = 1, 4, 384, 128
+@pytest.mark.parametrize("H", [4, 48])
+def test_output_dtypes_and_determinism(ifa, H):
+    B, N, d = 1, 384, 128
+    assert route(H, N, N, d, half=True) == ("few" if H == 4 else "fused")
     w = workloads.custom("t", B, H, N, d, True, dist="normal", seed=11)
     x = inputs(w)
     O32 = run(ifa, x, B, H, N, d, True, torch.float32)

@@ -14,7 +14,7 @@ import pytest
 
 import oracle
 import workloads
-from helpers import quantized_inputs, random_int8_problem
+from helpers import copies_for_the_fused_kernel, first_copy, many, quantized_inputs, random_int8_problem, route
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -148,9 +148,8 @@ def test_quantize_workload_heads_bit_exact(ifa):
 @pytest.mark.parametrize("B,H,N,d", [(2, 3, 384, 64), (1, 5, 200, 128), (1, 2, 37, 32), (4, 10, 37, 64), (2, 16, 8, 64), (1, 33, 1000, 128), (8, 8, 5, 128)])
 def test_quantize_qkv_equals_the_three_separate_calls(ifa, dtype, B, H, N, d):
     # the fused preparation against the separate entry points, bit for bit, twice in a row into the same buffers (the
-    # second call must not see what the first one left in the slots or in the codes).  With 32 heads or more of at least
-    # 512 elements the absmax pass of V rides in the launch of Q and K and leaves its partial maxima in the tail of V's
-    # codes; with fewer, that launch clears the slots the atomic absmax pass accumulates into.
+    # second call must not see what the first one left in the codes).  V goes whole heads in the launch of Q and K, or in parts that leave
+    # their maxima in V's codes for a second launch (40 heads of 37 x 64 whole, 33 of 1000 x 128 in parts).
     g = torch.Generator(device="cuda").manual_seed(B * 1000 + N + d)
     Q, K, V = (torch.randn((B, H, N, d), generator=g, device="cuda", dtype=torch.float32).to(dtype) for _ in range(3))
     V[0, 0] = 0                                            # an all-zero head: scale 1, codes 0
@@ -237,9 +236,10 @@ def test_int32_accumulators_of_the_production_kernel_bit_exact(ifa, N, d, causal
     for j in range(N // Bc):
         rows = np.arange(N) if not causal else np.arange(j * Bc, N)                     # query blocks that visit block j
         assert np.array_equal(PV[j][rows], PV_ref[j][rows]), f"P V of key block {j}"
-    # and the output of the same launch is the production output
-    O_prod = run_gpu(ifa, Q[None], K[None], V[None], sQ[None], sK[None], sV, 1, 1, causal).cpu().numpy().reshape(N, d)
-    assert np.array_equal(O, O_prod)
+    # and the output of the same launch is the production output, the fused kernel's and that of the kernel that takes one head
+    for copies in (1, copies_for_the_fused_kernel(1, N, N, d)):
+        O_prod = run_gpu(ifa, *many(copies, Q[None], K[None], V[None], sQ[None], sK[None], sV), 1, copies, causal)
+        assert np.array_equal(O, first_copy(O_prod, copies).reshape(N, d)), copies
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -311,19 +311,22 @@ def test_small_workloads_every_element(ifa, name, scaled):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,H,N,d", [(1, 1, 128, 128), (1, 3, 256, 64), (2, 4, 384, 128), (1, 5, 640, 128), (1, 8, 512, 64)])
 @pytest.mark.parametrize("dist", ["normal", "uniform_outlier", "student_t3"])
-def test_shapes_masks_distributions(ifa, B, H, N, d, causal, dist):
-    # several key blocks, head counts that are and are not multiples of the XCD count, both head dims
+@pytest.mark.parametrize("fused", [False, True])
+def test_shapes_masks_distributions(ifa, B, H, N, d, causal, dist, fused):
+    # several key blocks, head counts that are and are not multiples of the XCD count, both head dims; `fused`: with as many copies
+    # of the heads as the fused kernel wants
     w = workloads.custom("t", B, H, N, d, causal, dist=dist, seed=B * 1000 + N + d)
     x = quantized_inputs(w, scaled=True)
-    O = run_gpu(ifa, x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], B, H, causal).cpu().numpy()
+    copies = copies_for_the_fused_kernel(B * H, N, N, d) if fused else 1
+    O = first_copy(run_gpu(ifa, *many(copies, x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"]), copies * B, H, causal), copies)
     check_against_oracle(ifa, O.reshape(-1, d), x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], causal,
                          label=f"{B}x{H}x{N}x{d} causal={causal} {dist}")
 
 
-@pytest.mark.parametrize("B,H", [(5, 8), (3, 8), (9, 8), (1, 7), (3, 3), (1, 16)])
+@pytest.mark.parametrize("B,H", [(5, 8), (3, 8), (9, 8), (1, 7), (3, 3), (1, 16), (13, 5), (1, 71)])   # from 65 heads on the fused kernel
 def test_head_counts_and_grid_shapes(ifa, B, H):
     # head counts that fill the XCD groups exactly, leave a short last group (padding workgroups), or are not a
-    # multiple of 8 at all (plain grid); every head must come out, each exactly once
+    # multiple of 8 at all; every head must come out, each exactly once
     N, d = 256, 64
     w = workloads.custom("t", B, H, N, d, True, dist="normal", seed=31 * B + H)
     x = quantized_inputs(w, scaled=True)
@@ -351,28 +354,33 @@ def test_head_group_sizes_sampled_rows(ifa, B, H, N, d, causal):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("N,d", [(1, 128), (37, 64), (127, 128), (129, 128), (200, 64), (333, 128), (1000, 128), (515, 64)])
-def test_ragged_sequence_lengths(ifa, N, d, causal):
+@pytest.mark.parametrize("fused", [False, True])
+def test_ragged_sequence_lengths(ifa, N, d, causal, fused):
     # N not a multiple of the 128-key block: keys >= N are masked in the last block, rows >= N are not stored
+    copies = copies_for_the_fused_kernel(3, N, N, d) if fused else 1
+    if copies is None:
+        return                                               # at most 64 queries at d = 64: never the fused kernel's
     w = workloads.custom("t", 1, 3, N, d, causal, dist="normal", seed=N + d)
     x = quantized_inputs(w, scaled=True)
-    heads = 3
+    heads = 3 * copies
     sh = (1, heads, N, d)
     guard = 64                                               # canary rows after O: must stay untouched
     Obuf = torch.full((heads * N + guard, d), 12345.0, dtype=torch.float32, device="cuda")
     O = Obuf[:heads * N].view(sh)
-    ifa.int_flash_attn_fwd(dev(x["Qq"].reshape(sh)), dev(x["Kq"].reshape(sh)), dev(x["Vq"].reshape(sh)),
-                           dev(x["sQ"].reshape(1, heads, N)), dev(x["sK"].reshape(1, heads, N)),
-                           dev(x["sV"].reshape(1, heads)), causal=causal, out=O)
+    Qq, Kq, Vq, sQ, sK, sV = many(copies, x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"])
+    ifa.int_flash_attn_fwd(dev(Qq.reshape(sh)), dev(Kq.reshape(sh)), dev(Vq.reshape(sh)), dev(sQ.reshape(1, heads, N)),
+                           dev(sK.reshape(1, heads, N)), dev(sV.reshape(1, heads)), causal=causal, out=O)
     torch.cuda.synchronize()
     assert bool((Obuf[heads * N:] == 12345.0).all())
-    check_against_oracle(ifa, O.cpu().numpy().reshape(-1, d), x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], causal,
-                         label=f"ragged N={N} d={d} causal={causal}")
+    check_against_oracle(ifa, first_copy(O, copies).reshape(-1, d), x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], causal,
+                         label=f"ragged N={N} d={d} causal={causal} fused={fused}")
 
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Nq,Nk,d", [(1, 1000, 128), (1, 128, 64), (128, 512, 128), (100, 333, 128), (256, 1024, 64),
                                      (37, 37, 128), (130, 131, 128), (64, 4096, 128), (300, 200, 128), (513, 640, 64)])
-def test_rectangular_problems(ifa, Nq, Nk, d, causal):
+@pytest.mark.parametrize("fused", [False, True])
+def test_rectangular_problems(ifa, Nq, Nk, d, causal, fused):
     # Nq query rows against Nk keys: a chunk of queries against a longer sequence, or one query.  Under the mask
     # the queries are the last Nq positions (query i sees keys <= i + Nk - Nq), so the diagonal crosses key blocks
     # at any offset; Nk < Nq is allowed without the mask only.
@@ -384,31 +392,35 @@ def test_rectangular_problems(ifa, Nq, Nk, d, causal):
         rc = ifa.lib().int_flash_attn_fwd_rect(p(z8), p(z8), p(z8), p(zf), p(zf), p(zf), 1, 1, Nq, Nk, d, 1, p(O), 1, None)
         assert rc == -4
         return
-    H = 3
+    copies = copies_for_the_fused_kernel(3, Nq, Nk, d) if fused else 1
+    if copies is None:
+        return                                               # up to 32 queries: the fused kernel has short keys at d = 128 only
+    H = 3 * copies
     rng = np.random.default_rng(Nq * 7 + Nk + d)
-    Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, max(Nq, Nk), d, score_sigma=2.0)
+    Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, 3, max(Nq, Nk), d, score_sigma=2.0)
     Qq, sQ = np.ascontiguousarray(Qq[:, :Nq]), np.ascontiguousarray(sQ[:, :Nq])
     Kq, Vq, sK = np.ascontiguousarray(Kq[:, :Nk]), np.ascontiguousarray(Vq[:, :Nk]), np.ascontiguousarray(sK[:, :Nk])
     guard = 64
     Obuf = torch.full((H * Nq + guard, d), 12345.0, dtype=torch.float32, device="cuda")
     O = Obuf[:H * Nq].view(1, H, Nq, d)
-    ifa.int_flash_attn_fwd(dev(Qq[None]), dev(Kq[None]), dev(Vq[None]), dev(sQ[None]), dev(sK[None]), dev(sV[None]),
-                           causal=causal, out=O)
+    ifa.int_flash_attn_fwd(*[dev(t[None]) for t in many(copies, Qq, Kq, Vq, sQ, sK, sV)], causal=causal, out=O)
     torch.cuda.synchronize()
     assert bool((Obuf[H * Nq:] == 12345.0).all())
-    check_against_oracle(ifa, O.cpu().numpy().reshape(-1, d), Qq, Kq, Vq, sQ, sK, sV, causal,
-                         label=f"rect Nq={Nq} Nk={Nk} d={d} causal={causal}")
+    check_against_oracle(ifa, first_copy(O, copies).reshape(-1, d), Qq, Kq, Vq, sQ, sK, sV, causal,
+                         label=f"rect Nq={Nq} Nk={Nk} d={d} causal={causal} fused={fused}")
 
 
 @pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("N,d", [(1, 128), (33, 64), (127, 128), (129, 64), (200, 128), (515, 128)])
-def test_ragged_lengths_with_two_byte_outputs(ifa, N, d, causal, dtype):
-    # 2-byte outputs leave through the staged row-wise store: rows past N must not be written (canaries on both
-    # sides of O) and the values must be the fp32 result rounded once
-    heads = 3
-    w = workloads.custom("t", 1, heads, N, d, causal, dist="normal", seed=17 * N + d)
-    x = quantized_inputs(w, scaled=True)
+@pytest.mark.parametrize("fused", [False, True])
+def test_ragged_lengths_with_two_byte_outputs(ifa, N, d, causal, dtype, fused):
+    # 2-byte outputs (the fused kernel's leave through its staged row-wise store): rows past N must not be written (canaries on
+    # both sides of O) and the values must be the fp32 result rounded once
+    copies = copies_for_the_fused_kernel(3, N, N, d) if fused else 1
+    heads = 3 * copies
+    w = workloads.custom("t", 1, 3, N, d, causal, dist="normal", seed=17 * N + d)
+    x = dict(zip(("Qq", "Kq", "Vq", "sQ", "sK", "sV"), many(copies, *[quantized_inputs(w, scaled=True)[k] for k in ("Qq", "Kq", "Vq", "sQ", "sK", "sV")])))
     sh = (1, heads, N, d)
     tdt = getattr(torch, dtype)
     guard = 256
@@ -438,16 +450,19 @@ def _random_shapes(n, seed):
 
 @pytest.mark.parametrize("H,Nq,Nk,d,causal", _random_shapes(24, 2024))
 def test_seeded_random_shapes(ifa, H, Nq, Nk, d, causal):
-    # a fixed, seeded sample of odd shapes: any head count, any Nq, Nk (ragged in both), both head dims, both masks
+    # a fixed, seeded sample of odd shapes: any head count, any Nq, Nk (ragged in both), both head dims, both masks; as it is, and with
+    # as many copies of the heads as the fused kernel wants
     rng = np.random.default_rng(H * 1000003 + Nq * 1009 + Nk)
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, max(Nq, Nk), d, score_sigma=float(rng.uniform(0.5, 6.0)))
     Qq, sQ = np.ascontiguousarray(Qq[:, :Nq]), np.ascontiguousarray(sQ[:, :Nq])
     Kq, Vq, sK = np.ascontiguousarray(Kq[:, :Nk]), np.ascontiguousarray(Vq[:, :Nk]), np.ascontiguousarray(sK[:, :Nk])
-    O = ifa.int_flash_attn_fwd(dev(Qq[None]), dev(Kq[None]), dev(Vq[None]), dev(sQ[None]), dev(sK[None]), dev(sV[None]),
-                               causal=causal, out_dtype=torch.float32)
-    torch.cuda.synchronize()
-    check_against_oracle(ifa, O.cpu().numpy().reshape(-1, d), Qq, Kq, Vq, sQ, sK, sV, causal,
-                         label=f"random H={H} Nq={Nq} Nk={Nk} d={d} causal={causal}")
+    for copies in (1, copies_for_the_fused_kernel(H, Nq, Nk, d)):
+        if copies is None:
+            continue
+        O = ifa.int_flash_attn_fwd(*[dev(t[None]) for t in many(copies, Qq, Kq, Vq, sQ, sK, sV)], causal=causal, out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        check_against_oracle(ifa, first_copy(O, copies).reshape(-1, d), Qq, Kq, Vq, sQ, sK, sV, causal,
+                             label=f"random H={H} Nq={Nq} Nk={Nk} d={d} causal={causal} copies={copies}")
 
 
 def ctypes_ptr(t):
@@ -456,8 +471,15 @@ def ctypes_ptr(t):
 
 
 def test_rectangular_rows_equal_the_square_kernel_rows(ifa):
-    # the last Nq rows of the square causal problem, computed as a rectangular call: same bits
-    H, N, Nq, d = 4, 1024, 200, 128
+    # the last Nq rows of the square causal problem, computed as a rectangular call: same bits.  A few heads (the few-query kernel on
+    # the rectangular side) and more (the fused kernel on both)
+    for H, kernel in ((18, "few"), (80, "fused")):
+        N, Nq, d = 1024, 200, 128
+        assert route(H, N, N, d) == "fused" and route(H, Nq, N, d) == kernel
+        _rectangular_rows(ifa, H, N, Nq, d)
+
+
+def _rectangular_rows(ifa, H, N, Nq, d):
     rng = np.random.default_rng(77)
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, N, d, score_sigma=2.0)
     args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sV[None]))
@@ -476,7 +498,8 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
     # A call with a few queries per head (a decode step, a short chunk) runs a kernel of its own that splits every key
     # block over the wavefronts of a workgroup; it performs the arithmetic of the square kernel on the same operands, so
     # its rows are the last Nq rows of the square problem bit for bit, with and without the mask, on a ragged length.
-    H, N = 5, 1231
+    H, N = 15, 1231
+    assert route(H, N, N, d) == "fused" and route(H, Nq, N, d) == "few"
     rng = np.random.default_rng(Nq * 131 + d)
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, N, d, score_sigma=2.0)
     args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sV[None]))
@@ -492,7 +515,8 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
 @pytest.mark.parametrize("Nq", [1, 7, 33, 64])
 def test_few_query_calls_with_blockwise_v_scales_equal_the_square_kernel_rows(ifa, Nq, d):
     # the same with one V scale per key block (the running output is carried in units of the current block's scale)
-    H, N = 3, 1231
+    H, N = 15, 1231
+    assert route(H, N, N, d) == "fused" and route(H, Nq, N, d) == "few"
     rng = np.random.default_rng(Nq * 17 + d)
     Qq, Kq, Vq, sQ, sK, _ = random_int8_problem(rng, H, N, d, score_sigma=2.0)
     sVb = rng.uniform(0.005, 0.05, (H, -(-N // ifa.block_cols(d, True)))).astype(np.float32)
@@ -531,13 +555,15 @@ def test_few_query_calls_against_the_oracle(ifa, Nq, Nk, d, causal):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq,Nk,H", [(1, 16384, 8), (1, 1, 3), (1, 129, 1), (3, 1000, 5), (8, 4097, 8), (5, 300, 16), (2, 20000, 2), (8, 8, 4),
                                       (9, 4097, 8), (32, 16384, 2), (20, 1000, 5), (32, 32, 3), (17, 300, 16), (12, 500, 100),
-                                      (8, 258, 16), (32, 1026, 4)])   # the last run of key blocks is masked entirely for the early queries
+                                      (8, 258, 16), (32, 1026, 4),
+                                      # split, and the last run of key blocks is masked entirely for the early queries
+                                      (8, 2306, 16), (32, 3074, 4), (3, 5000, 5), (5, 2049, 16), (20, 3001, 5), (17, 2300, 16), (12, 2500, 30)])
 def test_key_split_calls_equal_the_sequential_walk(ifa, Nq, Nk, H, d):
     # The key-split path forms P on the grid of the running maximum of the sequential walk (it knows every block's
     # maximum before it forms any P), so it differs from the one-workgroup-per-head kernel only by the order of the
     # fp32 additions of lines 12-13: a few ulp of O, far inside the parity bar (up to 8 queries per head the scores go
-    # through the workspace, from 9 to 32 the second pass recomputes them -- or, with 96 heads or more, the call runs
-    # the one-workgroup-per-head kernel itself).  Checked against that kernel (tight)
+    # through the workspace, from 9 to 32 the second pass recomputes them; up to 2048 keys, or with many heads, the call
+    # does not split and the workspace stays as it was).  Checked against that kernel (tight)
     # and against the oracle (the strict bar), with canary rows behind the output and a workspace of exactly the size
     # the library asks for, poisoned with NaN (nothing may be read before it is written).
     for causal in (False, True):
@@ -555,6 +581,7 @@ def test_key_split_calls_equal_the_sequential_walk(ifa, Nq, Nk, H, d):
         ifa.int_flash_attn_fwd_splitk(*args, causal=causal, out=O, workspace=ws[:need // 4].view(torch.uint8))
         torch.cuda.synchronize()
         assert bool((Obuf[H * Nq:] == 12345.0).all()) and bool(torch.isnan(ws[need // 4:]).all())
+        assert bool(torch.isnan(ws).all()) == (Nk <= 2048), "split or not"
         scale = float(seq.abs().max())
         diff = float((O - seq).abs().max())
         assert diff <= 4e-6 * scale, (Nq, Nk, H, d, causal, diff, scale)
@@ -582,16 +609,18 @@ def test_random_int8_grid_inputs_wide_scores(ifa, causal):
     rng = np.random.default_rng(5)
     for sigma in (0.3, 2.0, 12.0):
         Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, 8, 256, 128, score_sigma=sigma)
-        O = run_gpu(ifa, Qq, Kq, Vq, sQ, sK, sV, 2, 4, causal).cpu().numpy()
-        check_against_oracle(ifa, O.reshape(-1, 128), Qq, Kq, Vq, sQ, sK, sV, causal, label=f"int8 sigma={sigma}")
+        for copies in (1, copies_for_the_fused_kernel(8, 256, 256, 128)):
+            O = first_copy(run_gpu(ifa, *many(copies, Qq, Kq, Vq, sQ, sK, sV), 2 * copies, 4, causal), copies)
+            check_against_oracle(ifa, O.reshape(-1, 128), Qq, Kq, Vq, sQ, sK, sV, causal, label=f"int8 sigma={sigma} copies={copies}")
 
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("causal", [False, True])
-def test_accumulator_extremes_through_the_fused_kernel(ifa, d, causal):
+@pytest.mark.parametrize("fused", [True, False])
+def test_accumulator_extremes_through_the_fused_kernel(ifa, d, causal, fused):
     # Every entry is -128 or 127 and some keys repeat (or negate) a query's sign pattern, so Q K^T reaches
     # +-d * 128 * 128 (2^21 at d = 128) and, with V = -128 columns under flat rows, P V reaches -127 * 128 * B_c:
-    # the int32 sums at the ends of their range must still come out exact.
+    # the int32 sums at the ends of their range must still come out exact (and through the few-query kernel, which takes two heads).
     rng = np.random.default_rng(77 + d)
     heads, N = 2, 384
     pick = lambda shape: np.where(rng.random(shape) < 0.5, -128, 127).astype(np.int8)
@@ -606,8 +635,9 @@ def test_accumulator_extremes_through_the_fused_kernel(ifa, d, causal):
     sQ = np.full((heads, N), np.sqrt(span), np.float32) * rng.uniform(0.9, 1.1, (heads, N)).astype(np.float32)
     sK = np.full((heads, N), np.sqrt(span), np.float32) * rng.uniform(0.9, 1.1, (heads, N)).astype(np.float32)
     sV = np.array([0.01, 0.02], np.float32)
-    O = run_gpu(ifa, Qq, Kq, Vq, sQ, sK, sV, 1, heads, causal).cpu().numpy().reshape(-1, d)
-    check_against_oracle(ifa, O, Qq, Kq, Vq, sQ, sK, sV, causal, label=f"extremes d={d} causal={causal}")
+    copies = copies_for_the_fused_kernel(heads, N, N, d) if fused else 1
+    O = first_copy(run_gpu(ifa, *many(copies, Qq, Kq, Vq, sQ, sK, sV), copies, heads, causal), copies).reshape(-1, d)
+    check_against_oracle(ifa, O, Qq, Kq, Vq, sQ, sK, sV, causal, label=f"extremes d={d} causal={causal} fused={fused}")
     flat = O.reshape(heads, N, d)[:, 130:140]
     if not causal:                                             # flat rows: O = s_V * column mean of V, exactly -128 / 127 s_V
         assert np.allclose(flat[:, :, 3], -128.0 * sV[:, None], rtol=1e-6) and np.allclose(flat[:, :, 4], 127.0 * sV[:, None], rtol=1e-6)
@@ -625,40 +655,48 @@ def test_very_long_ragged_sequences_sampled_rows(ifa, H, N, d, causal):
                          label=f"long N={N} d={d} causal={causal}")
 
 
-def test_degenerate_inputs(ifa):
+@pytest.mark.parametrize("fused", [False, True])
+def test_degenerate_inputs(ifa, fused):
     rng = np.random.default_rng(6)
     N, d = 256, 128
+    copies = copies_for_the_fused_kernel(1, N, N, d) if fused else 1
+
+    def one_head(Qq, Kq, Vq, sQ, sK, sV, causal):
+        return first_copy(run_gpu(ifa, *many(copies, Qq, Kq, Vq, sQ, sK, sV), 1, copies, causal), copies).reshape(N, d)
+
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, 1, N, d)
     # all-zero Q: every score is 0, every P is 127, O is the (prefix) mean of V
     Z = np.zeros_like(Qq)
     for causal in (False, True):
-        O = run_gpu(ifa, Z, Kq, Vq, sQ, sK, sV, 1, 1, causal).cpu().numpy().reshape(N, d)
+        O = one_head(Z, Kq, Vq, sQ, sK, sV, causal)
         Vh = Vq[0].astype(np.float64) * float(sV[0])
         ref = np.cumsum(Vh, 0) / np.arange(1, N + 1)[:, None] if causal else np.broadcast_to(Vh.mean(0), (N, d))
         assert np.allclose(O, ref, rtol=1e-5, atol=1e-7)
     # all-zero V gives exactly zero
-    O = run_gpu(ifa, Qq, Kq, np.zeros_like(Vq), sQ, sK, sV, 1, 1, False).cpu().numpy()
+    O = one_head(Qq, Kq, np.zeros_like(Vq), sQ, sK, sV, False)
     assert not O.any()
     # one dominant key (a one-hot softmax row): O is that value row exactly
     Q1 = np.zeros_like(Qq); Q1[0, :, 0] = 100
     K1 = np.zeros_like(Kq); K1[0, 3, 0] = 100
     s = np.full((1, N), 0.03, np.float32)
-    O = run_gpu(ifa, Q1, K1, Vq, s, s, sV, 1, 1, False).cpu().numpy().reshape(N, d)
+    O = one_head(Q1, K1, Vq, s, s, sV, False)
     assert np.allclose(O, np.broadcast_to(Vq[0, 3].astype(np.float32) * sV[0], (N, d)), rtol=3e-7, atol=0)
     # causal row 0 sees key 0 only
-    O = run_gpu(ifa, Qq, Kq, Vq, sQ, sK, sV, 1, 1, True).cpu().numpy().reshape(N, d)
+    O = one_head(Qq, Kq, Vq, sQ, sK, sV, True)
     assert np.allclose(O[0], Vq[0, 0].astype(np.float32) * sV[0], rtol=3e-7, atol=0)
     # tiny and huge scales stay finite
-    O = run_gpu(ifa, Qq, Kq, Vq, sQ * np.float32(1e-6), sK, sV * np.float32(1e4), 1, 1, False).cpu().numpy()
+    O = one_head(Qq, Kq, Vq, sQ * np.float32(1e-6), sK, sV * np.float32(1e4), False)
     assert np.all(np.isfinite(O))
-    check_against_oracle(ifa, run_gpu(ifa, Qq, Kq, Vq, sQ * 40, sK, sV, 1, 1, True).cpu().numpy().reshape(N, d),  # x40: sharp rows
+    check_against_oracle(ifa, one_head(Qq, Kq, Vq, sQ * 40, sK, sV, True),  # x40: sharp rows
                          Qq, Kq, Vq, sQ * 40, sK, sV, True, label="sharp")
 
 
-def test_output_dtypes_and_determinism(ifa):
-    w = workloads.custom("t", 1, 8, 512, 128, True, seed=77)
+@pytest.mark.parametrize("H", [8, 40])
+def test_output_dtypes_and_determinism(ifa, H):
+    assert route(H, 512, 512, 128) == ("few" if H == 8 else "fused")
+    w = workloads.custom("t", 1, H, 512, 128, True, seed=77)
     x = quantized_inputs(w, scaled=True)
-    args = (x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], 1, 8, True)
+    args = (x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], 1, H, True)
     O32 = run_gpu(ifa, *args, out_dtype=torch.float32).cpu().numpy()
     O32b = run_gpu(ifa, *args, out_dtype=torch.float32).cpu().numpy()
     assert np.array_equal(O32, O32b)                                      # same input twice: identical bits
@@ -667,14 +705,14 @@ def test_output_dtypes_and_determinism(ifa):
     Ob = run_gpu(ifa, *args, out_dtype=torch.bfloat16).float().cpu().numpy()
     assert np.array_equal(Ob, bf16_round(O32))
     # the 12-argument spec entry point writes fp16 on the stream given to ifa_set_stream
-    sh = (1, 8, 512, 128)
+    sh = (1, H, 512, 128)
     out = torch.empty(sh, dtype=torch.float16, device="cuda")
     import ctypes
     t = [dev(x["Qq"].reshape(sh)), dev(x["Kq"].reshape(sh)), dev(x["Vq"].reshape(sh)),
-         dev(x["sQ"].reshape(1, 8, 512)), dev(x["sK"].reshape(1, 8, 512)), dev(x["sV"].reshape(1, 8))]
+         dev(x["sQ"].reshape(1, H, 512)), dev(x["sK"].reshape(1, H, 512)), dev(x["sV"].reshape(1, H))]
     L = ifa.lib()
     L.ifa_set_stream(ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-    assert L.int_flash_attn_fwd(*[ctypes.c_void_p(a.data_ptr()) for a in t], 1, 8, 512, 128, 1,
+    assert L.int_flash_attn_fwd(*[ctypes.c_void_p(a.data_ptr()) for a in t], 1, H, 512, 128, 1,
                                 ctypes.c_void_p(out.data_ptr())) == 0
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), O16)
@@ -698,18 +736,19 @@ def test_quantize_blockwise_bit_exact(ifa, dtype, N, d):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,H,N,d,dist", [(1, 2, 128, 128, "normal"), (2, 4, 512, 128, "student_t3"), (1, 8, 640, 64, "uniform_outlier"),
                                           (1, 3, 333, 128, "student_t3"), (1, 8, 2048, 128, "student_t3")])
-def test_attention_with_blockwise_v_scales(ifa, B, H, N, d, dist, causal):
+@pytest.mark.parametrize("fused", [False, True])
+def test_attention_with_blockwise_v_scales(ifa, B, H, N, d, dist, causal, fused):
     w = workloads.custom("t", B, H, N, d, causal, dist=dist, seed=N + d + B)
     x = quantized_inputs(w, scaled=True)
     Bc = ifa.block_cols(d, causal)
     Vq, sVb = oracle.quantize_blockwise(x["V"], Bc)           # oracle-side inputs, as everywhere
     sh = (B, H, N, d)
-    O = ifa.int_flash_attn_fwd(dev(x["Qq"].reshape(sh)), dev(x["Kq"].reshape(sh)), dev(Vq.reshape(sh)),
-                               dev(x["sQ"].reshape(B, H, N)), dev(x["sK"].reshape(B, H, N)),
-                               dev(sVb.reshape(B, H, -1)), causal=causal, out_dtype=torch.float32)
+    copies = copies_for_the_fused_kernel(B * H, N, N, d) if fused else 1
+    O = ifa.int_flash_attn_fwd(*[dev(t[None]) for t in many(copies, x["Qq"], x["Kq"], Vq, x["sQ"], x["sK"], sVb)], causal=causal,
+                               out_dtype=torch.float32)
     torch.cuda.synchronize()
-    check_against_oracle(ifa, O.cpu().numpy().reshape(-1, d), x["Qq"], x["Kq"], Vq, x["sQ"], x["sK"], sVb, causal,
-                         label=f"block-V {B}x{H}x{N}x{d} {dist} causal={causal}")
+    check_against_oracle(ifa, first_copy(O, copies).reshape(-1, d), x["Qq"], x["Kq"], Vq, x["sQ"], x["sK"], sVb, causal,
+                         label=f"block-V {B}x{H}x{N}x{d} {dist} causal={causal} fused={fused}")
     # and the GPU quantizer feeds it the same thing
     gq, gs = ifa.quantize_blockwise(dev(x["V"].reshape(sh)), Bc)
     assert np.array_equal(gq.cpu().numpy().reshape(Vq.shape), Vq) and np.array_equal(gs.cpu().numpy().reshape(sVb.shape), sVb)
@@ -717,20 +756,22 @@ def test_attention_with_blockwise_v_scales(ifa, B, H, N, d, dist, causal):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Nq,Nk,d", [(1, 1000, 128), (128, 512, 128), (100, 333, 128), (256, 1024, 64), (130, 131, 128), (37, 700, 64)])
-def test_rectangular_problems_with_blockwise_v_scales(ifa, Nq, Nk, d, causal):
+@pytest.mark.parametrize("fused", [False, True])
+def test_rectangular_problems_with_blockwise_v_scales(ifa, Nq, Nk, d, causal, fused):
     # N_q != N_k together with one V scale per key block: chunked prefill / decode against per-block-quantized V
     B, H = 1, 3
+    copies = copies_for_the_fused_kernel(H, Nq, Nk, d) if fused else 1
+    if copies is None:
+        return
     w = workloads.custom("t", B, H, Nk, d, causal, dist="student_t3", seed=Nq + Nk + d)
     x = quantized_inputs(w, scaled=True)
     Bc = ifa.block_cols(d, causal)
     Vq, sVb = oracle.quantize_blockwise(x["V"], Bc)
     Qq, sQ = x["Qq"][:, Nk - Nq:], x["sQ"][:, Nk - Nq:]       # the last Nq positions as queries
-    O = ifa.int_flash_attn_fwd(dev(Qq.reshape(B, H, Nq, d)), dev(x["Kq"].reshape(B, H, Nk, d)), dev(Vq.reshape(B, H, Nk, d)),
-                               dev(sQ.reshape(B, H, Nq)), dev(x["sK"].reshape(B, H, Nk)), dev(sVb.reshape(B, H, -1)),
-                               causal=causal, out_dtype=torch.float32)
+    O = ifa.int_flash_attn_fwd(*[dev(t[None]) for t in many(copies, Qq, x["Kq"], Vq, sQ, x["sK"], sVb)], causal=causal, out_dtype=torch.float32)
     torch.cuda.synchronize()
-    check_against_oracle(ifa, O.cpu().numpy().reshape(-1, d), Qq, x["Kq"], Vq, sQ, x["sK"], sVb, causal,
-                         label=f"block-V rect {Nq}x{Nk}x{d} causal={causal}")
+    check_against_oracle(ifa, first_copy(O, copies).reshape(-1, d), Qq, x["Kq"], Vq, sQ, x["sK"], sVb, causal,
+                         label=f"block-V rect {Nq}x{Nk}x{d} causal={causal} fused={fused}")
 
 
 def test_blockwise_v_scales_improve_heavy_tailed_accuracy(ifa):
@@ -778,7 +819,7 @@ def _full_size(ifa, name, scaled, full_heads, rows_per_head, vblock=False):
         sQd[b, hh].copy_(torch.from_numpy(sq[0])); sKd[b, hh].copy_(torch.from_numpy(x["sK"][0]))
         sVd[b, hh] = torch.from_numpy(np.asarray(sv[0], np.float32))
         kept[h] = (x["Qq"][0], x["Kq"][0], Vq[0], sq[0], x["sK"][0], np.asarray(sv[0], np.float32))
-    out_dtype = torch.float32                                  # parity on the fp32 result; casts are tested above
+    out_dtype = torch.float32                                  # parity on the fp32 result; casts are tested above, on both kernels
     O = ifa.int_flash_attn_fwd(Qd, Kd, Vd, sQd, sKd, sVd, causal=w.causal, out_dtype=out_dtype)
     torch.cuda.synchronize()
     assert bool(torch.isfinite(O).all())

@@ -1,13 +1,15 @@
 """Seeded random shapes through every attention entry point, every row compared with the oracle at the strict bar
 (and, in the second test, through every quantizer entry point, bit for bit):
 the fused kernel (square and N_q != N_k), the few-query kernel, per-block V scales, the key-split path and the
-half-INT8 variant; d in {64, 128}, 1-8 heads, ragged N_q, N_k up to 1500, with and without the causal mask, flat
-to peaked score distributions.  The committed parity cases fix their shapes by hand; this one draws them."""
+half-INT8 variant; d in {64, 128}, 1-8 heads (or copies of them, as many as the fused kernel wants), ragged N_q, N_k up to 1500 (key-split
+calls up to 6000), with and without the causal mask, flat to peaked score distributions.  The committed parity cases fix their
+shapes by hand; this one draws them."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
+from helpers import copies_for_the_fused_kernel, first_copy, many, route
 
 pytestmark = pytest.mark.gpu
 
@@ -29,6 +31,8 @@ def _draw(rng, ifa):
     kind = str(rng.choice(KINDS))
     causal = bool(rng.integers(0, 2))
     Nk = int(rng.choice([rng.integers(1, 140), rng.integers(140, 700), rng.integers(700, 1500)]))
+    if kind == "splitk" and rng.random() < 0.75:
+        Nk = int(rng.integers(2049, 6000))                          # up to 2048 keys such a call does not split
     if kind in ("square", "vblock", "half") and rng.integers(0, 2):
         Nq = Nk
     elif kind == "few":
@@ -55,22 +59,32 @@ def _draw(rng, ifa):
 def test_random_shapes_meet_the_strict_bar_on_every_row(ifa, seed):
     rng = np.random.default_rng(seed)
     dev = lambda a: torch.from_numpy(a).cuda()[None]
+    reached = {}
     for case in range(60):
         desc, (Qq, Kq, Vq, sQ, sK, sV), Bc = _draw(rng, ifa)
-        d, causal = desc["d"], desc["causal"]
-        if desc["kind"] == "half":
+        d, causal, half, split = desc["d"], desc["causal"], desc["kind"] == "half", desc["kind"] == "splitk"
+        copies = (copies_for_the_fused_kernel(desc["H"], desc["Nq"], desc["Nk"], d, half) or 1) if not split and rng.integers(0, 2) else 1
+        desc["kernel"] = "split" if split else route(copies * desc["H"], desc["Nq"], desc["Nk"], d, half)
+        reached[half, desc["kernel"]] = reached.get((half, desc["kernel"]), 0) + 1
+        if half:
             Vh = (Vq.astype(np.float32) * 0.01).astype(np.float16)
-            O = ifa.int_flash_attn_fwd_half(dev(Qq), dev(Kq), dev(Vh), dev(sQ), dev(sK), causal=causal, out_dtype=torch.float32)
+            O = ifa.int_flash_attn_fwd_half(*[dev(t) for t in many(copies, Qq, Kq, Vh, sQ, sK)], causal=causal, out_dtype=torch.float32)
             ref = oracle.int_flash_attn_fwd_half(Qq, Kq, Vh, sQ, sK, causal, ifa.block_cols_half(d, causal))["O"]
-            got = O[0].reshape(-1, d).cpu().numpy()
+            got = first_copy(O, copies).reshape(-1, d)
             assert np.abs(got - ref).max() <= 1e-3 * np.abs(ref).max(), (seed, case, desc)
             continue
-        fn = ifa.int_flash_attn_fwd_splitk if desc["kind"] == "splitk" else ifa.int_flash_attn_fwd
-        O = fn(dev(Qq), dev(Kq), dev(Vq), dev(sQ), dev(sK), dev(sV), causal=causal, out_dtype=torch.float32)
-        got = O[0].reshape(-1, d).cpu().numpy()
+        if split:
+            ws = torch.full((ifa.splitk_workspace_bytes(1, desc["H"], desc["Nq"], desc["Nk"], d) // 4,), float("nan"), device="cuda")
+            O = ifa.int_flash_attn_fwd_splitk(dev(Qq), dev(Kq), dev(Vq), dev(sQ), dev(sK), dev(sV), causal=causal, out_dtype=torch.float32,
+                                              workspace=ws.view(torch.uint8))
+            assert bool(torch.isnan(ws).all()) == (desc["Nk"] <= 2048), (seed, case, desc)      # the passes ran, or not
+        else:
+            O = ifa.int_flash_attn_fwd(*[dev(t) for t in many(copies, Qq, Kq, Vq, sQ, sK, sV)], causal=causal, out_dtype=torch.float32)
+        got = first_copy(O, copies).reshape(-1, d)
         assert np.isfinite(got).all(), (seed, case, desc)
         res = oracle.compare_up_to_ties(got, Qq, Kq, Vq, sQ, sK, sV, causal, Bc)
         assert np.all(res["err"] <= 1e-3 * res["scale"]), (seed, case, desc, float((res["err"] / res["scale"]).max()))
+    assert set(reached) >= {(False, "fused"), (False, "few"), (False, "packed"), (False, "split"), (True, "fused"), (True, "few")}, reached
 
 
 def _widen(t):
