@@ -390,13 +390,14 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
 // ---- few queries, many keys -------------------------------------------------------------------------------------
 // The half-INT8 counterpart of the few-query kernel of intfa_attention_fewq.hip: the wavefronts of a workgroup share one
 // group of 32 queries and take FEW_NB key blocks of 64 keys at a time, in two roles that run one group of blocks apart.
-//   2 FEW_NB S wavefronts (block b of the group, key tile t): lines 9-11 for that tile and its part of l.  A wavefront copies the
+//   2 FEW_NB S wavefronts (block b of the group, key tile t): lines 9-11 for that tile.  A wavefront copies the
 //       K rows it reads itself, two groups ahead, and holds the operands of the next group in registers; the extrema of the tiles
 //       meet in LDS (first barrier), then the weights go to LDS (second barrier);
-//   four PV wavefronts (d tile): O = alpha O + P~ V for the group before, block by block in order, on weights and V^T operands
+//   four PV wavefronts (d tile): O = alpha O + P~ V and l for the group before, block by block in order, on weights and V^T operands
 //       they have taken to registers by the first barrier; they also copy V, a group ahead.
-// The running maximum in front of each block of 64 keys is that of the sequential walk, so the fp16 weights are those of the
-// kernel above; only l is added up in another order.
+// The running maximum in front of each block of 64 keys is that of the sequential walk and a lane's weights and sums are those of a lane
+// of the kernel above, so the rows are the same, bit for bit: what a head gives does not depend on how many heads the call has.  (l in
+// the S wavefronts, each its tile's part, was another order of that sum, and 32 x 1 x 4099 29.0 us against 27.0.)
 // What bounds it is what one CU takes in (about 60 GB/s: 48 KB per group in 0.8 us at d = 128) and the chain of a group next to
 // it.  Three blocks per group fill LDS and measure 4-8 % slower from 128 heads on.  DS = 2 (d = 128): two workgroups per query
 // group, each with half of the d columns, as in the INT8 kernel (32 KB per group and CU).  One query against 4096 keys: 128
@@ -503,7 +504,6 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
         __builtin_amdgcn_sched_barrier(0);
         read_group(0);
         wait_lds();
-        float l = 0.0f, m_own = -INFINITY;                       // this wavefront's part of l and the maximum it refers to
         for (int gi = 0; gi < ngroups; ++gi) {
             v16i sacc = bias;
 #pragma unroll
@@ -540,17 +540,10 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
 #pragma unroll
             for (int b = 1; b < NB; ++b) mb = blk == b ? m.v[b] : mb;
             h2 ph[8];
-            float psum = 0.0f;
-            const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const h2 w = {(_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(a[2 * c], sq2, -mb)),
-                              (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(a[2 * c + 1], sq2, -mb))};
-                ph[c] = w;
-                psum = __builtin_amdgcn_fdot2(w, ones, psum, false);
-            }
-            l = __builtin_fmaf(l, __builtin_amdgcn_exp2f(m_own - mb), psum);
-            m_own = mb;
+            for (int c = 0; c < 8; ++c)
+                ph[c] = h2{(_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(a[2 * c], sq2, -mb)),
+                           (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(a[2 * c + 1], sq2, -mb))};
 #pragma unroll
             for (int s_ = 0; s_ < 2; ++s_) {
                 const h8 pb = {ph[4 * s_][0], ph[4 * s_][1], ph[4 * s_ + 1][0], ph[4 * s_ + 1][1], ph[4 * s_ + 2][0], ph[4 * s_ + 2][1], ph[4 * s_ + 3][0], ph[4 * s_ + 3][1]};
@@ -560,10 +553,6 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
             __syncthreads();
         }
         wait_all_memory();                                       // requests past the last group: nothing of mine stays in flight
-        // this wavefront's l on the final maximum; the K rows are free (its own part of them) for the sums
-        l *= __builtin_amdgcn_exp2f(m_own - m2);
-        l += swap32(l);
-        if (g == 0) *reinterpret_cast<LDS_AS float *>(kbuf + t * (32 * D) + 4 * r) = l;
         __syncthreads();                                         // the PV wavefronts' last group
         return;
     }
@@ -602,8 +591,16 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
     for (int v = 0; v < 16; ++v) o[v] = 0.0f;
     const bool works = dt < PIECES;                              // two d tiles in a half (or D = 64): the other wavefronts only copy
     h8 vop[NB][4], pf[NB][4];
+    float l = 0.0f;                                              // of this lane's keys, added up in the order of the kernel above
+    const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
     auto block = [&](int b, float m_prev, float m_new) {         // (a block past the last one: the maximum stays, the weights are 0)
         const float alpha = __builtin_amdgcn_exp2f(m_prev - m_new);
+        float psum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) psum = __builtin_amdgcn_fdot2(h2{pf[b][i][2 * j], pf[b][i][2 * j + 1]}, ones, psum, false);
+        l = __builtin_fmaf(l, alpha, psum);
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[v] *= alpha;
 #pragma unroll
@@ -643,10 +640,7 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
     wait_all_memory();
 
     if (q_head < Nq && works) {
-        float l = 0.0f;
-#pragma unroll
-        for (int w = 0; w < FEW_S_WAVES; ++w) l += *reinterpret_cast<const float *>(&sm.k[0][w >> 1][(w & 1) * (32 * D) + 4 * r]);
-        const float f = 1.0f / l;
+        const float f = 1.0f / (l + swap32(l));
         OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + col0 + 32 * dt + 4 * g;
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
