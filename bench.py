@@ -58,7 +58,7 @@ def decode_bench(args, torch, ifa):
     need = ifa.splitk_workspace_bytes(B, H, Nq, Nk, d)
     if need == 0:
         sys.exit("bench.py --decode: the key-split path takes at most 32 queries per head and d in {64, 128}")
-    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    ws = torch.full((need,), 255, dtype=torch.uint8, device=dev)      # (every word a NaN: a call that does not split leaves it so)
     calls = {"one_workgroup_per_head": lambda: ifa.int_flash_attn_fwd(Qq, Kq, Vq, sQ, sK, sV, causal=True, out=O1),
              "key_split": lambda: ifa.int_flash_attn_fwd_splitk(Qq, Kq, Vq, sQ, sK, sV, causal=True, out=O2, workspace=ws)}
     ms = {}
@@ -77,6 +77,7 @@ def decode_bench(args, torch, ifa):
         torch.cuda.synchronize()
         ms[name] = (time.perf_counter() - t0) * 1e3 / args.steps
     heads = B * H
+    split = not bool((ws == 255).all())
     algo_bytes = heads * (2 * Nk * d + 4 * Nk + Nq * d + 4 * Nq + 2 * Nq * d) + 4 * heads   # K, V, s_K; Q, s_Q, O; s_V
     ops = 4.0 * heads * d * sum(Nk - Nq + i + 1 for i in range(Nq))
     result = {"metric": "decode_attention_kv_stream", "value": round(algo_bytes / (ms["key_split"] * 1e-3) / 1e9, 1), "unit": "GB/s",
@@ -84,9 +85,10 @@ def decode_bench(args, torch, ifa):
               "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int8", "data": "synthetic",
               "config": {"workload": f"decode: B={B} H={H} Nq={Nq} Nk={Nk} d={d} causal, N(0,1) fp16 activations quantized beforehand; "
                                      "step = one attention call on the quantized cache", "workspace_bytes": need, "int8_ops_per_step": ops},
-              "ms_one_workgroup_per_head": round(ms["one_workgroup_per_head"], 4),
-              "roofline": {"bound": "hbm", "kernel": "splitk_scores_kernel + splitk_pv_kernel + splitk_combine_kernel, or int_flash_attn_fwd_narrow_kernel "
-                                                  "with many heads (one call)",
+              # the plain attention call on the same inputs; without a split the two are the same launch
+              "key_axis_split": split, "ms_one_workgroup_per_head": round(ms["one_workgroup_per_head"], 4),
+              "roofline": {"bound": "hbm", "kernel": (f"splitk_scores_kernel + {'splitk_pv_kernel' if Nq <= 8 else 'splitk_pv_recompute_kernel'} + "
+                                                      "splitk_combine_kernel (one call)") if split else "the kernel of int_flash_attn_fwd_rect",
                            "achieved": round(algo_bytes / (ms["key_split"] * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
                            "frac": round(algo_bytes / (ms["key_split"] * 1e-3) / 8e12, 4), "traffic": None,
                            "note": "algorithmic bytes: K, V int8 and s_K read once, Q, s_Q, s_V read, O written; the scores that pass "

@@ -152,6 +152,8 @@ int int_flash_attn_fwd_ex(const signed char *Q_i8, const signed char *K_i8, cons
  *   causal = 1: the queries are the LAST Nq positions of the key sequence, i.e. query i sees keys
  *   j <= i + (Nk - Nq); needs Nk >= Nq (else IFA_ERR_UNSUPPORTED: some query would see no key).
  * Everything else as int_flash_attn_fwd_ex, which is this call with Nq = Nk.
+ * Several kernels stand behind this call (by the number of heads, Nq, Nk and d); a row's result does not depend on which of them ran,
+ * nor on the other heads or rows of the call, bit for bit.
  */
 int int_flash_attn_fwd_rect(const signed char *Q_i8, const signed char *K_i8, const signed char *V_i8,
                             const float *s_Q, const float *s_K, const float *s_V,
@@ -166,8 +168,8 @@ int int_flash_attn_fwd_rect(const signed char *Q_i8, const signed char *K_i8, co
  * walk of Algorithm 1 would have at that block: P and the int32 P V are those of int_flash_attn_fwd_rect bit for bit,
  * and O differs from its result only by the order of the fp32 additions of lines 12-13 (the partial (m, l, O) of the
  * parts are merged with e^{m_part - m}, once per part instead of once per block).  With many heads (from 64 to 160 on,
- * by Nq and d; half as many up to 4096 keys) or at most 2048 keys the split does not pay and the call runs the kernel
- * of int_flash_attn_fwd_rect.
+ * by Nq, Nk and d; half as many up to 4096 keys) or at most 2048 keys the split does not pay and the call is
+ * int_flash_attn_fwd_rect.
  *   workspace         device memory, 256-byte aligned, at least ifa_splitk_workspace_bytes(B, H, Nq, Nk, d) bytes
  *                     (else IFA_ERR_WORKSPACE); owned by the caller, contents undefined before and after, must not be
  *                     shared by calls that may overlap.  At most three kernel launches on hip_stream, nothing is allocated.
@@ -225,6 +227,9 @@ int int_flash_attn_fwd_vblock(const signed char *Q_i8, const signed char *K_i8, 
 /*
  * The same for N_q query rows against N_k keys: shapes and mask rule of int_flash_attn_fwd_rect, per-block V scales
  * s_Vb [B, H, ceil(Nk / ifa_block_cols(d, causal))] of int_flash_attn_fwd_vblock (blocks count from key 0).
+ * As there, a row's result does not depend on the kernel that ran or on the other heads.  With the mask its last bits (2^-21 of the
+ * value) may depend on Nq: rows go in groups of 32 from the first query on, the output of a group is carried in units of the current
+ * block's scale, and a block that one row of the group sees changes the unit for all of them.
  */
 int int_flash_attn_fwd_vblock_rect(const signed char *Q_i8, const signed char *K_i8, const signed char *V_i8,
                                    const float *s_Q, const float *s_K, const float *s_Vb,
@@ -245,8 +250,8 @@ int int_flash_attn_fwd_half(const signed char *Q_i8, const signed char *K_i8, co
                             const float *s_Q, const float *s_K,
                             int B, int H, int N, int d, int causal, void *O, int o_dtype, void *hip_stream);
 
-/* The half-INT8 variant for N_q query rows against N_k keys; shapes and the causal convention as in
- * int_flash_attn_fwd_rect (V_f16 is [B, H, Nk, d]).  int_flash_attn_fwd_half is this call with Nq = Nk. */
+/* The half-INT8 variant for N_q query rows against N_k keys; shapes, the causal convention and what a row's result does not depend on
+ * as in int_flash_attn_fwd_rect (V_f16 is [B, H, Nk, d]; a 32-key tile of V that no row of a group of 32 sees is not looked at).  int_flash_attn_fwd_half is this call with Nq = Nk. */
 int int_flash_attn_fwd_half_rect(const signed char *Q_i8, const signed char *K_i8, const void *V_f16,
                                  const float *s_Q, const float *s_K,
                                  int B, int H, int Nq, int Nk, int d, int causal, void *O, int o_dtype, void *hip_stream);

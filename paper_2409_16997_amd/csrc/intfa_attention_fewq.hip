@@ -5,7 +5,7 @@
 //                                      the calls of ifa_packed_queries();
 //   int_flash_attn_fwd_narrow_kernel   one or two workgroups per head and group of 32 queries, the key blocks split over
 //                                      their wavefronts; bit-identical to the fused kernel's rows, needs no memory
-//                                      beyond inputs and outputs; what int_flash_attn_fwd_rect runs by ifa_few_queries();
+//                                      beyond inputs and outputs; the calls of ifa_few_queries();
 //   splitk_*                           the key axis of a head split over many workgroups, exactly: lines 9-10 for every
 //                                      block first, then lines 11-13 on the known running maximum, then a merge;
 //                                      int_flash_attn_fwd_splitk (caller's workspace) and _splitk_static (built in).
@@ -44,7 +44,9 @@ using namespace ifa_tiles;
 // 16384 (DS = 1) 95 us = 5.7 TB/s (the packed kernel 148), 512 of 4096 91 us = 5.9 TB/s (131).
 // Every number is computed by the same instruction sequence on the same operands as in the fused kernel (the
 // integer sums are exact, the extremum is order-independent, the row sum l is taken over the same P dwords), so
-// the output is bit-identical to the corresponding rows of a square call: still Algorithm 1 at B_c = 128.
+// the rows are bit-identical to those of the same call on the fused kernel, and with one V scale per head to the
+// corresponding rows of any other call: still Algorithm 1 at B_c = 128.  (With per-block V scales and the mask a row goes
+// through the scale of a block that only other rows of its group of 32 see; which rows those are depends on N_q.)
 constexpr int NARROW_BR = 32;      // queries per workgroup
 constexpr int NARROW_NB = 2;       // key blocks per group
 constexpr int NARROW_S_WAVES = 4 * NARROW_NB;
@@ -1039,7 +1041,7 @@ int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
     // K and V with the non-temporal hint where one workgroup reads each byte, and reads it once, and there are more of them than the
     // caches could keep for the next call; such a call runs with DS = 1.  (With the hint and DS = 2 the second workgroup of a pair may
-    // find a line gone: right after K and V were written that costs the memory traffic twice.)  128 heads x 1 x 16384, 537 MB, us, after
+    // find a line gone: right after K and V were written the call below fetched 730 - 790 MB, 545 with DS = 1.)  128 heads x 1 x 16384, 537 MB, us, after
     // the same call / after a read of 512 MB elsewhere / after a copy of 512 MB / right after K and V were quantized:
     //   hint, DS = 1 94 / 95 / 112 / 108;  hint, DS = 2 89 / 91 / 109 / 139;  no hint, DS = 2 100 / 100 / 120 / 122;  key split 100 / 103 / 112 / 112.
     // Below the line, 64 x 1 x 4096, 67 MB: hint, DS = 1 22.9 / 27.3 / 27.8 / 23.5; no hint, DS = 2 20.0 / 27.4 / 32.4 / 22.5.
