@@ -15,6 +15,8 @@ SOURCES = ["intfa_attention.hip", "intfa_attention_fewq.hip", "intfa_attention_h
 # Loops start at multiples of 32 bytes: where the 4 KB body of the fused kernel's key loop lies relative to the
 # instruction fetch is worth 4 % (32 heads x 8192 x 128 causal, start moved in steps of 4 bytes: 348 - 363 us, with a
 # period of 32 bytes; 350 at a multiple), and without the flag every change in front of a loop moves it.
+# It helps two workgroups that share a CU (32 x 8192 x 128 without the mask, half-INT8 942 -> 918 us; INT8 64 x 4096 339 -> 334) and costs one
+# that is alone on it, i.e. calls whose last wave leaves most CUs half empty (half-INT8 36 x 4096 308 -> 319, INT8 12 x 8192 269 -> 275 - 283).
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-ffp-contract=off", "-falign-loops=32", "-Wall", "-Wno-unused-command-line-argument"]
