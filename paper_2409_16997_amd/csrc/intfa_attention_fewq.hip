@@ -1,8 +1,9 @@
 // INT-FlashAttention forward (Algorithm 1) for gfx950: calls with few queries per head (a decode step, a few draft
-// tokens, a short chunk of a prefill).  Three families, all built from the tile code of the fused kernel
+// tokens, a short chunk of a prefill).  Four families, all built from the tile code of the fused kernel
 // (intfa_attention_tiles.h: same LDS layout, same MFMA operand order, same staging copies) and the same arithmetic:
 //   int_flash_attn_fwd_packed_kernel   one workgroup of four wavefronts per head and group of 32 queries, one key block at a time;
 //                                      the calls of ifa_packed_queries();
+//   int_flash_attn_fwd_pair_kernel     one workgroup of twelve wavefronts for two groups of 32 queries of a head; the calls of ifa_pair_queries();
 //   int_flash_attn_fwd_narrow_kernel   one or two workgroups per head and group of 32 queries, the key blocks split over
 //                                      their wavefronts; bit-identical to the fused kernel's rows, needs no memory
 //                                      beyond inputs and outputs; the calls of ifa_few_queries();
@@ -312,6 +313,324 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
                 *reinterpret_cast<uint2 *>(orow + 8 * vq) = Pack4<OutT>::pack(o[4 * vq] * f, o[4 * vq + 1] * f, o[4 * vq + 2] * f, o[4 * vq + 3] * f);
             } else {
                 *reinterpret_cast<v4f *>(orow + 8 * vq) = v4f{o[4 * vq] * f, o[4 * vq + 1] * f, o[4 * vq + 2] * f, o[4 * vq + 3] * f};
+            }
+        }
+    }
+#endif
+}
+
+// ---- more query groups than CUs: two groups of 32 queries per workgroup ------------------------------------------
+// The kernel above leaves each of its roles idle for half of a step: the S wavefronts wait for the PV wavefronts to take V and P, the PV
+// wavefronts for the next P.  With more groups of queries than CUs a workgroup therefore takes TWO groups, A and B, half a
+// step apart, on the same K and V, each copied and read from LDS once for both.  A step (PAIR_NB = 2 key blocks) has two half steps:
+//     S wavefronts    even: line 9 of A, lines 10-11 of B for the blocks before      odd: lines 10-11 of A, line 9 of B
+//     PV wavefronts   even: lines 12-13 of A for the blocks before                   odd: lines 12-13 of B
+// Neither part of a half step waits for the other: P of one group forms under the MFMAs of the other's scores, and a PV wavefront folds
+// the half step before while its operands come in from LDS.  One barrier ends a half step: what it leaves in LDS -- extrema, P
+// bytes, their sums, the factors alpha -- is read in the next.
+// What bounds it: a half step takes about 1950 cycles, of which the vector ALU of a SIMD issues in 1500 (350 instructions of its three
+// wavefronts, an MFMA every fifth) and LDS is busy for 680 + 300 of copies; the rest is waits for LDS and the barrier.  The copies spread between the
+// vector instructions, a higher priority for either role, and 10 % fewer vector instructions all measured the same within 2 %.
+// 32 heads x 512 queries x 8192 keys 60 us = 1110 TOP/s (79 on the kernel above, 106 on the fused one); 65 x 128 x 1500 25 -> 17, 4 x 8192 x 8192 causal 107 -> 69.
+// Rows are bit-identical to the other kernels'.  Where the lines lie: ifa_pair_queries().
+constexpr int PAIR_NB = 2;         // key blocks per step
+constexpr int PAIR_BR = 64;        // queries per workgroup
+
+template <int D> struct SmemPair {
+    alignas(4096) int8_t k[2][PAIR_NB][BC * D];
+    alignas(4096) int8_t v[2][PAIR_NB][BC * D];
+    alignas(256) float sk[2][PAIR_NB * 4][64];            // per S wavefront: the 32 s_K of its key tile (+ 32 unused)
+    alignas(16) v4i p[2][PAIR_NB][4][64];                 // per query group, block, key tile and lane: the 16 P bytes of that lane
+    alignas(16) int ps[2][PAIR_NB][64][4];                // per query group, block, lane and key tile: their sum
+    alignas(16) float ext[2][PAIR_NB][32][4];             // per query group, block, query and key tile: the extremum (line 10)
+    alignas(16) float alpha[2][PAIR_NB][32];              // per query group, block and query: e^(m_old - m)
+};
+static_assert(sizeof(SmemPair<128>) <= 160 * 1024 && offsetof(SmemPair<64>, v) % 4096 == 0, "LDS budget and tile bases");
+
+template <int D, bool CAUSAL, bool VB, typename OutT>
+__global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_pair_kernel(
+    const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
+    const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
+    int heads, int Nq, int Nk, int head_group, OutT *__restrict__ O) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __shared__ SmemPair<D> sm;
+    constexpr int KS = D / 32, NB = PAIR_NB;
+
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T_c = (Nk + BC - 1) / BC, T_r = (Nq + PAIR_BR - 1) / PAIR_BR;
+    const int shift = CAUSAL ? Nk - Nq : 0;
+    int head, qord;
+    map_workgroup(blockIdx.x, heads, T_r, head_group, CAUSAL, head, qord, false);
+    const int first_q = (CAUSAL ? T_r - 1 - qord : qord) * PAIR_BR;
+    // query group x (0: A, 1: B): queries first_q + 32 x + r.  Rows past Nq: a clamped copy, never stored
+    int blocks[2];                                               // key blocks of either group, up to the last key it sees
+    float nq2[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        blocks[x] = CAUSAL ? min(Nk - 1, min(first_q + 32 * x + 32, Nq) - 1 + shift) / BC + 1 : T_c;
+        nq2[x] = sQ[static_cast<long>(head) * Nq + min(first_q + 32 * x + r, Nq - 1)] * (-LOG2E * ACC_UNIT);
+    }
+    const int nblocks = blocks[1];                               // (of the later queries: no fewer than blocks[0])
+    const int nsteps = (nblocks + NB - 1) / NB;
+
+    v16i acc0;                                                   // what both accumulations start from
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc0[v] = ACC_START_I;
+
+    if (wave < NARROW_S_WAVES) {
+        // ---- S wavefront: key tile t of block `blk` of every step, for both query groups
+        constexpr int PER_STEP = KS + 1;                         // copy instructions per step
+        const int t = wave & 3, blk = wave >> 2;
+        const BufRsrc rK = make_rsrc(K + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+        const BufRsrc rSK = make_rsrc(sK + static_cast<long>(head) * Nk, static_cast<unsigned>(Nk) * 4);
+        const lds_ptr kbuf = (lds_ptr)(&sm.k[0][blk][0]);
+        const lds_ptr skbuf = (lds_ptr)(&sm.sk[0][wave][0]);
+        const LaneOffsets<D> lo(lane, t);
+        // line 8: this wavefront's 32 rows of K and their s_K, which it alone reads, so that its own counted wait orders the two.
+        // A block past the last one is requested nowhere, so that every step costs PER_STEP copies.
+        auto stage_step = [&](int n) {
+            const int jb = n * NB + blk;
+            const bool real = jb < nblocks;
+            const Prefetch pf = {rK, rK, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE, kbuf + (n & 1) * (NB * BC * D), kbuf,
+                                 skbuf + (n & 1) * (NB * 4 * 256)};
+#pragma unroll
+            for (int i = 0; i < KS; ++i) prefetch_k_piece<D>(pf, lo, t, i);
+            lds_copy4(pf.sk, pf.lsk, 4 * r + 128 * t, pf.skoff);
+        };
+        stage_step(0);
+        stage_step(1);
+        v4i qf[2][KS];                                           // line 5
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int8_t *qptr = Q + (static_cast<long>(head) * Nq + min(first_q + 32 * x + r, Nq - 1)) * D + 16 * g;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) qf[x][kk] = *reinterpret_cast<const v4i *>(qptr + 32 * kk);
+        }
+        // landed BEFORE the loop as far as the compiler is concerned: a wait of its own inside the loop would be a wait for
+        // the staged copies as well
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[x][kk]));
+        asm volatile("" : "+v"(nq2[0]), "+v"(nq2[1]));
+        v4i kop[KS];
+        v4f skv[4];
+        auto read_k = [&](int n) {
+            const lds_ptr ks = kbuf + (n & 1) * (NB * BC * D);
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) kop[kk] = *reinterpret_cast<LDS_AS const v4i *>(k_operand<D>(ks, lo, kk) + 32 * t * D);
+        };
+        auto read_sk = [&](int n) {
+            const lds_ptr sk = skbuf + (n & 1) * (NB * 4 * 256);
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) skv[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + lo.sk + 32 * vq);
+        };
+        v16i sacc;
+        float a[2][16];
+        // line 9 of group x, integer part
+        auto gemm = [&](int x) {
+            sacc = acc0;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[kk], qf[x][kk], sacc, 0, 0, 0);
+        };
+        // line 9, fp32 part, and the extrema; kept keys: index inside the block <= klimit (the causal diagonal, the
+        // ragged end of the sequence, a block past the last one)
+        auto scores = [&](int x, int n) {
+            const int j0 = (n * NB + blk) * BC, fq = first_q + 32 * x;
+            const int tail = Nk - 1 - j0;
+            const int klimit = CAUSAL ? min(fq + r + shift - j0, tail) : tail;
+            const bool masked = CAUSAL ? (j0 + BC - 1 > min(fq + shift, Nk - 1)) : (tail < BC - 1);   // wave-uniform
+            float bmin = INFINITY;
+            auto scale = [&](auto with_mask) {
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float y = (ACC_START_F - __int_as_float(sacc[4 * vq + e])) * skv[vq][e];
+                        if (decltype(with_mask)::value && (32 * t + 8 * vq + 4 * g + e > klimit)) y = INFINITY;
+                        a[x][4 * vq + e] = y;
+                        bmin = fminf(bmin, y);
+                    }
+            };
+            if (masked) scale(std::true_type{});
+            else scale(std::false_type{});
+            bmin = pair_min(bmin);
+            if (g == 0) sm.ext[x][blk][r][t] = bmin;
+        };
+        // lines 10, 11 of group x; every wavefront follows the running maximum through both blocks of the step
+        float m2[2] = {-INFINITY, -INFINITY};                    // line 6
+        auto weights = [&](int x) {
+            float before = m2[x], m = m2[x];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const v4f e = *reinterpret_cast<const v4f *>(&sm.ext[x][b][r][0]);
+                m2[x] = fmaxf(m2[x], min4(e) * nq2[x]);
+                if (b == blk) m = m2[x];
+                if (b < blk) before = m2[x];
+            }
+            if (t == 0 && g == 0) sm.alpha[x][blk][r] = __builtin_amdgcn_exp2f(before - m);
+            const float mm = m - LOG2_R_NORM;
+            v4i pw;
+            uint32_t psum = 0;
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                float e[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[x][4 * vq + i], nq2[x], -mm));
+                const uint32_t w = pack_p4(e);
+                psum = __builtin_amdgcn_sad_u8(w, 0u, psum);
+                pw[vq] = static_cast<int>(w);
+            }
+            sm.p[x][blk][t][lane] = pw;
+            sm.ps[x][blk][lane][t] = static_cast<int>(psum);
+        };
+        wait_vmcnt<PER_STEP>();                                  // step 0 has landed
+        __builtin_amdgcn_sched_barrier(0);
+        read_k(0);
+        read_sk(0);
+        wait_lds();
+        for (int n = 0; n < nsteps; ++n) {                       // line 7
+            gemm(0);
+            __builtin_amdgcn_sched_barrier(0);
+            stage_step(n + 2);                                   // into the place step n has left
+            __builtin_amdgcn_sched_barrier(0);
+            if (n > 0) weights(1);
+            scores(0, n);
+            wait_lds();
+            __syncthreads();
+            gemm(1);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_vmcnt<PER_STEP>();                              // step n + 1 has landed (step n + 2 may be in flight)
+            __builtin_amdgcn_sched_barrier(0);
+            read_k(n + 1);
+            weights(0);
+            scores(1, n);
+            read_sk(n + 1);
+            wait_lds();
+            __syncthreads();
+        }
+        weights(1);
+        wait_all_memory();                                       // requests past the last step: nothing of mine stays in flight
+        __syncthreads();
+        return;
+    }
+
+    // ---- PV wavefront: d tile dt of O^T = V^T P^T
+    const int dt = wave - NARROW_S_WAVES;
+    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+    const lds_ptr vbuf = (lds_ptr)(&sm.v[0][0][0]);
+    const LaneOffsets<D> lo(lane, dt);
+    // V of step n (this wavefront's quarter of every block); a block past the last one is requested nowhere and comes as zeros
+    auto stage_step = [&](int n) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int jb = n * NB + b;
+            const Prefetch pf = {rV, rV, rV, jb < nblocks ? jb * BC * D : NOWHERE, NOWHERE, vbuf, vbuf + ((n & 1) * NB + b) * (BC * D), vbuf};
+#pragma unroll
+            for (int i = 0; i < KS; ++i) prefetch_v_piece<D>(pf, lo, dt, i);
+        }
+    };
+    float l[2] = {0.0f, 0.0f}, o[2][16];                         // this d tile of the running output (units of 2^26), l of the whole row
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[x][v] = 0.0f;
+    // s_V: one scalar per head, or (VB) one per key block of this head, read through the scalar cache
+    const float *sVh = VB ? sV + static_cast<long>(head) * T_c : sV + head;
+    float sv_prev[2] = {1.0f, 1.0f};
+    const bool works = dt < KS;                                  // two d tiles at D = 64: the other wavefronts only copy
+    v4i vop[NB][4];
+    v16i pacc[NB];
+    float alpha[NB];
+    int psum[NB];
+    // lines 12, 13 of group x for step n, block by block in order, from what gemm() left.  (A block past the last one: the maximum
+    // stays, P is 0, nothing changes.)
+    auto fold = [&](int x, int n) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int jb = n * NB + b;
+            float alpha_o = alpha[b];
+            if (VB && jb < blocks[x]) {                          // one V scale per key block: the running output is kept in units of the current block's
+                const float sv_j = uniform(sVh[jb]);
+                alpha_o = alpha[b] * uniform(sv_prev[x] * __builtin_amdgcn_rcpf(sv_j));
+                sv_prev[x] = sv_j;
+            }
+            l[x] = __builtin_fmaf(l[x], alpha[b], static_cast<float>(psum[b]));
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[x][v] = __builtin_fmaf(o[x][v], alpha_o, -(ACC_START_F - __int_as_float(pacc[b][v])));
+        }
+    };
+    // line 13, integer part, of group x for step n, and what its fold will take; `before` runs while the operands come in from LDS
+    auto gemm = [&](int x, int n, auto before) {
+        v4i pf[NB][4], ps[NB];
+        float al[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) pf[b][mt] = sm.p[x][b][mt][lane];
+            ps[b] = *reinterpret_cast<const v4i *>(&sm.ps[x][b][lane][0]);
+            al[b] = sm.alpha[x][b][r];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        before();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) pacc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop[b][mt], pf[b][mt], mt == 0 ? acc0 : pacc[b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            alpha[b] = al[b];
+            psum[b] = ps[b][0] + ps[b][1] + ps[b][2] + ps[b][3];
+        }
+    };
+    stage_step(0);
+    stage_step(1);
+    __syncthreads();                                             // half step 0: nothing to do yet
+    wait_vmcnt<NB * KS>();                                       // my part of V of step 0 has landed (step 1 may be in flight)
+    __syncthreads();
+    for (int n = 0; n < nsteps; ++n) {
+        if (works) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const lds_ptr vs = vbuf + ((n & 1) * NB + b) * (BC * D);
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) {
+                    const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, dt) + 32 * mt * D));
+                    const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(v_operand<D>(vs, lo, dt) + 16 * D + 32 * mt * D));
+                    vop[b][mt] = v4i{t0[0], t0[1], t1[0], t1[1]};
+                }
+            }
+            gemm(0, n, [&]() { if (n > 0) fold(1, n - 1); });
+        }
+        wait_lds();
+        __syncthreads();                                         // V of step n is in registers, P of group B in LDS
+        stage_step(n + 2);
+        if (works) gemm(1, n, [&]() { fold(0, n); });
+        if (n + 1 < nsteps) {
+            wait_vmcnt<NB * KS>();                               // my part of V of step n + 1 has landed (step n + 2 may be in flight)
+            __syncthreads();                                     // everyone's has, and P of group A is in LDS
+        }
+    }
+    if (works) fold(1, nsteps - 1);
+    wait_all_memory();
+
+    // lines 15-17 for d tile dt (d = 32 * dt + 8 * (v / 4) + 4 * g + v % 4 of query r)
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const float lt = l[x] + swap32(l[x]);
+        const float f = (VB ? sv_prev[x] : sVh[0]) * ACC_UNIT / lt;
+        const int q_head = first_q + 32 * x + r;
+        if (q_head < Nq && works) {
+            OutT *orow = O + (static_cast<long>(head) * Nq + q_head) * D + 32 * dt + 4 * g;
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                if constexpr (sizeof(OutT) == 2) {
+                    *reinterpret_cast<uint2 *>(orow + 8 * vq) = Pack4<OutT>::pack(o[x][4 * vq] * f, o[x][4 * vq + 1] * f, o[x][4 * vq + 2] * f, o[x][4 * vq + 3] * f);
+                } else {
+                    *reinterpret_cast<v4f *>(orow + 8 * vq) = v4f{o[x][4 * vq] * f, o[x][4 * vq + 1] * f, o[x][4 * vq + 2] * f, o[x][4 * vq + 3] * f};
+                }
             }
         }
     }
@@ -1037,6 +1356,12 @@ int launch_packed(const int8_t *Q, const int8_t *K, const int8_t *V, const float
 template <int D, bool CAUSAL, bool VB, typename OutT>
 int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
+    if (ifa_pair_queries(heads, Nq, Nk, D, CAUSAL)) {
+        const int T_r = (Nq + PAIR_BR - 1) / PAIR_BR;
+        hipLaunchKernelGGL((int_flash_attn_fwd_pair_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(static_cast<long>(heads) * T_r)),
+                           dim3(NARROW_THREADS), 0, st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, head_group_for(CAUSAL, 2L * Nk * D, T_r), static_cast<OutT *>(O));
+        return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+    }
     if (ifa_packed_queries(heads, Nq, Nk, D)) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
     // K and V with the non-temporal hint where one workgroup reads each byte, and reads it once, and there are more of them than the

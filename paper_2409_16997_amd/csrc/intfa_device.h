@@ -65,12 +65,12 @@ inline int head_group_for(bool causal, long kv_bytes_per_head, int T_r) {
 // 1024 and 128 x 600 3 % slower.)
 //   Before, causal calls with heads & 7 were dealt out head by head, uneven work on the CUs, and nothing went backwards, d = 128:
 // 36 x 4096 200.7 -> 118.7 us, 12 x 16384 683 -> 582, 4 x 16384 289 -> 236, 36 x 1777 37.4 -> 33.9; 8 x 8192 134 -> 122,
-// 64 x 1024 25.6 -> 22.0.
-__host__ __device__ __forceinline__ void map_workgroup(int L, int heads, int T_r, int head_group, bool causal, int &head, int &qord) {
+// 64 x 1024 25.6 -> 22.0.  `paired`: a kernel of which two workgroups share a CU.
+__host__ __device__ __forceinline__ void map_workgroup(int L, int heads, int T_r, int head_group, bool causal, int &head, int &qord, bool paired = true) {
     const int x = L & 7, hpx = heads >> 3, rem = heads & 7;          // whole heads per XCD, heads shared out
     if (!causal && rem && T_r >= 16) { head = L / T_r; qord = L % T_r; return; }
     int s = L >> 3;
-    if (causal && s >= 32 && heads * T_r <= 512) s = ((heads * T_r - x + 7) >> 3) + 31 - s;
+    if (paired && causal && s >= 32 && heads * T_r <= 512) s = ((heads * T_r - x + 7) >> 3) + 31 - s;
     const int nfull = hpx > 0 ? (hpx - 1) / head_group : 0;          // groups before the last
     const int per_group = head_group * T_r, base = nfull * head_group;
     if (s < nfull * per_group) {
@@ -192,6 +192,14 @@ __device__ __forceinline__ float pair_max(float x) {
 __device__ __forceinline__ float pair_min(float x) {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fminf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+}
+
+// minimum of four values that come out of minima (through LDS): two instructions, none to quiet NaNs that are quiet already
+__device__ __forceinline__ float min4(const v4f &e) {
+    float m;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(e[0]), "v"(e[1]), "v"(e[2]));
+    asm("v_min_f32 %0, %1, %2" : "=v"(m) : "v"(m), "v"(e[3]));
+    return m;
 }
 
 #endif  // __HIP_DEVICE_COMPILE__

@@ -21,7 +21,7 @@ constexpr long IFA_FEW_MAX_GROUPS = 5L << 20;
 //   more, up to 32 queries per head  the fused kernel has a wavefront in four busy, but twice the workgroups on a CU and less to start:
 //                                    up to `short_keys` keys it wins (INT8: 512 x 32 x 256 14.4 / 12.8, 1000 x 1 x 256 23.8 / 22.1, x 384 28.4 / 28.2,
 //                                    x 512 31.3 / 34.2; 4096 x 1 x 128 70 / 42), beyond it does not (1000 x 1 x 1024 48 / 56, 768 x 32 x 1024 41 / 52)
-//   more, longer ones                two waves win on long key sequences (32 x 512 x 8192 79 / 106, 256 x 64 x 2048 37 / 37) and lose on short ones
+//   more, longer ones                (those that ifa_pair_queries() leaves) two waves win on long key sequences (2 x 5000 x 5000 33 / 65) and lose on short ones
 //                                    (64 x 200 x 200 7.5 / 5.9), more lose (32 x 700 x 8192 120 / 107, 512 x 64 x 2048 71 / 59)
 static inline long ifa_query_groups(int heads, int Nq) { return static_cast<long>(heads) * ((Nq + 31) / 32); }
 static inline bool ifa_few_queries(int heads, int Nq, int Nk, int d, bool half) {
@@ -45,7 +45,26 @@ static inline bool ifa_packed_queries(int heads, int Nq, int Nk, int d) {
     return Nq <= 32 ? Nk <= (groups <= 512 ? 1280 : 1024) : Nq <= 64 && groups <= 512 && Nk >= 128 && Nk < 2048;
 }
 
-// The packed or the twelve-wavefront few-query kernel of intfa_attention_fewq.hip, for the dispatcher of the entry points in
+// Which INT8 calls the two-group kernel takes before all of them: more groups of 32 queries than CUs, two of one head to a workgroup.
+// It walks 256 keys of 64 queries in 1.7 - 1.9 us, one workgroup per CU; the few-query kernel takes 1.15 for 32 queries, a fused workgroup of 128
+// alone on its CU 3.3, two 5.1.  Before (which kernel) / now, us, d = 128 unless stated:
+//   up to 256 workgroups, one wave  32 heads x 512 queries x 8192 keys 79 (few-query) / 60, 65 x 128 x 3000 45 (few-query) / 26, 32 x 512 x 1500 25 (fused) / 18,
+//                                   x 700 15.1 (fused) / 12.4; d = 64, 256 x 64 x 1000 14.9 (packed) / 11.5.  On fewer keys start and end outweigh it:
+//                                   32 x 448 x 448 10.6 (fused) / 10.8, 160 x 64 x 300 10.0 / 10.8; d = 64, 24 x 384 x 450 9.7 / 7.8, 130 x 64 x 300 7.2 / 7.5.
+//                                   Half of the key blocks masked: the heaviest workgroup decides, and the two waves of the few-query kernel, which
+//                                   takes such calls from 2048 keys on, even out: 2 x 5000 33 (few-query) / 37, 1 x 14000 87 / 89; but 3 x 5000 45 / 38, 8 x 2048 22.8 / 20.4
+//   more, half of the blocks masked twice as many and smaller workgroups than the fused kernel's even out better: 8 x 4096 56 (fused) / 41, 4 x 8192 107 / 69,
+//                                   1 x 32768 410 / 236, 16 x 2048 x 2048 30.7 / 27.8, 5 x 8192 115 / 99; then not: 20 x 1600 25.8 / 25.9, 12 x 3200 45.5 / 45.5, 7 x 8192 112 / 119
+//   more, all blocks visible        two waves of workgroups against one of the fused kernel's: 48 x 512 x 8192 107 (fused) / 111
+static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causal) {
+    if (Nq <= 32 || ifa_query_groups(heads, Nq) <= 256) return false;
+    const long wgs = static_cast<long>(heads) * ((Nq + 63) / 64);
+    const bool uneven = causal && 2L * Nq >= Nk;
+    if (wgs <= 256) return Nk >= (d == 128 ? 512 : 384) && !(uneven && Nk >= 2048 && (heads == 1 || wgs <= 192));
+    return uneven && Nk >= 2048 && wgs <= (heads <= 8 ? 768 : 512);
+}
+
+// The packed, the two-group or the few-query kernel of intfa_attention_fewq.hip, for the dispatcher of the entry points in
 // intfa_attention.hip; arguments already validated.
 int ifa_launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads,
                       int Nq, int Nk, int d, int causal, int vblock, void *O, int o_dtype, hipStream_t st);
