@@ -443,10 +443,12 @@ int launch_tokenwise(const TokenJob &j0, const TokenJob &j1, int jobs, long rows
 }
 
 // Whole heads or parts.  From 96 heads on, whole heads keep enough workgroups busy and the second read of V is partly a
-// cache hit (Q, K, V of 96 x 2048 x 128 fp16: 47 us whole, 55 in parts; 128 x 4096 x 128: 124 and 145; 64 x 4096 x 128, below
-// the line: 81 and 73).  With fewer heads one workgroup walks its head at about 40 GB/s next to the fixed 4 us, and what
+// cache hit (Q, K, V of 96 x 2048 x 128 fp16: 47 us whole, 55 in parts; 128 x 4096 x 128: 124 and 145).  With fewer heads one workgroup walks its head at about 40 GB/s next to the fixed 4 us, and what
 // the second launch costs (2.5 us) only buys the chip's bandwidth for heads that are long: 4 heads of 256 KB 10.7 us whole
 // and 7.6 in parts, 64 heads of 128 KB 10.2 and 12.0.
+// Next to the rows of Q and K the line lies lower for heads of up to 1 MB, which an extra launch delays more than it speeds up (Q, K, V in rotation, parts /
+// whole, us: 64 x 1777 x 128 fp16 34.5 / 27.4, 64 x 4096 x 128 72.5 / 68.2, 64 x 6000 x 64 53 / 43.6, 80 x 2600 x 128 56.5 / 49.4, 80 x 1300 x 128 fp32 45.3 / 37.3;
+// beyond it 64 x 8192 x 128 fp16 147 / 160, and below 64 heads or, in fp32, 80 they even out: 48 x 1777 x 128 fp16 27.7 / 29.7, 64 x 1777 x 128 fp32 48.1 / 51.7).
 // `alone`: no rows of Q and K to fill in around the heads, so long heads that leave CUs without one (256 take a head each, then the
 // next 256) go in parts as well.  V alone, whole / in parts, us, repeated and with inputs in rotation: 96 x 8192 x 128 fp16 101, 121 / 84, 103, fp32 220, 232 /
 // 174, 186; 128 x 4096 x 128 fp32 108, 127 / 95, 108; 260 x 2048 x 128 fp16 60, 71 / 56, 66, fp32 121, 135 / 105, 121; 300 x 8192 x 64 fp16 155, 166 / 149, 157;
@@ -455,7 +457,8 @@ HeadJob plan_heads(const void *X, long heads, long per_head, int elem_bytes, int
     HeadJob hj = {X, Xq, scale, per_head, static_cast<int>(heads), 0, 0, 0, 0};
     const long head_bytes = per_head * elem_bytes, rounds = (heads + 255) / 256;
     const bool uneven = alone && 8 * heads < 5 * 256 * rounds && head_bytes > (heads > 256 ? 256L << 10 : 1L << 20);
-    if ((heads >= 96 && per_head < (1L << 29) && !uneven) || head_bytes <= (64L << 10) + (heads < 96 ? heads * (4L << 10) : 0)) return hj;
+    const bool beside = !alone && heads >= (elem_bytes == 2 ? 64 : 80) && head_bytes <= (1L << 20);
+    if (beside || (heads >= 96 && per_head < (1L << 29) && !uneven) || head_bytes <= (64L << 10) + (heads < 96 ? heads * (4L << 10) : 0)) return hj;
     const long chunks = per_head / 8;
     auto split = [&](long want, long &per) {             // at most `want` pieces of at least HEAD_THREADS chunks
         long n = chunks / HEAD_THREADS < want ? chunks / HEAD_THREADS : want;
