@@ -1,7 +1,9 @@
-"""ctypes binding of include/intfa.h.  Argument marshalling only."""
+"""Binding of include/intfa.h: ctypes, and for the plain calls a host module (csrc/intfa_host.cpp).  Argument marshalling only."""
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -65,6 +67,28 @@ def lib():
     return _lib
 
 
+_native = None
+_NATIVE_PATH = os.path.join(_HERE, "_intfa_host.so")
+
+
+def _load_native():
+    """csrc/intfa_host.cpp: the plain calls without Python between the tensors and the C ABI.  Its functions return None for whatever
+    is not a plain call, and the code behind them here takes over."""
+    global _native
+    import torch  # noqa: F401  (the module's symbols are torch's)
+    if not os.path.exists(_NATIVE_PATH):
+        raise IntfaError(f"{_NATIVE_PATH} is missing: build it with `python -m paper_2409_16997_amd.build` or __graft_entry__.build()")
+    loader = importlib.machinery.ExtensionFileLoader("_intfa_host", _NATIVE_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_intfa_host", loader))
+    loader.exec_module(module)
+    module.init(*(ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value for name in (
+        "quantize_tokenwise_ex", "quantize_headwise_ex", "quantize_qkv", "quantize_qk", "int_flash_attn_fwd_rect",
+        "int_flash_attn_fwd_vblock_rect", "int_flash_attn_fwd_half_rect", "int_flash_attn_fwd_splitk", "int_flash_attn_fwd_splitk_static",
+        "ifa_block_cols")))
+    _native = module
+    return module
+
+
 def status_str(code: int) -> str:
     return lib().ifa_status_str(int(code)).decode()
 
@@ -74,9 +98,8 @@ def _check(code: int, what: str):
         raise IntfaError(f"{what}: {status_str(code)} ({code})")
 
 
-# What a call costs the host is most of what a short one takes, so the helpers below are kept to the attribute reads they
-# need: pointers go to ctypes as plain integers (an int8 [1, 32, 1, 128] query quantized and attended to: 25 us of Python
-# and launches with c_void_p objects, torch.cuda.current_stream() and torch.empty; 13 us like this).
+# What a call costs the host is most of what a short one takes: the plain calls go through _load_native()'s module, and the helpers below, which
+# serve every other, are kept to the attribute reads they need.
 
 def _dtype_enum(t):
     import torch
@@ -121,6 +144,10 @@ def _scales(X, shape):
 def quantize_tokenwise(X, scale_mul=1.0, hadamard=False):
     """X [..., d] fp32/fp16/bf16 on the GPU -> (int8 [..., d], fp32 scale [...] times scale_mul).
     hadamard=True quantizes the Walsh-Hadamard transform H_d x of every row instead of x."""
+    if not hadamard:
+        r = (_native or _load_native()).tokenwise(X, scale_mul)
+        if r is not None:
+            return r
     x = _dev(X)
     shape = X.shape
     d = shape[-1]
@@ -133,6 +160,10 @@ def quantize_tokenwise(X, scale_mul=1.0, hadamard=False):
 
 def quantize_headwise(X, global_scale=False):
     """X [B, H, N, d] (or [heads, N, d]) -> (int8 same shape, fp32 scale [B, H] (or [heads]))."""
+    if not global_scale:
+        r = (_native or _load_native()).headwise(X)
+        if r is not None:
+            return r
     x = _dev(X)
     shape = X.shape
     N, d = shape[-2], shape[-1]
@@ -147,6 +178,10 @@ def quantize_qkv(Q, K, V, s_Q_mul=1.0, out=None):
     """The input preparation of one attention call in one or two launches: Q, K token-level, V tensor-level.
     Q, K, V [B, H, N, d] -> (Q_i8, K_i8, V_i8, s_Q [B, H, N] (times s_Q_mul), s_K [B, H, N], s_V [B, H]);
     out: optional tuple of those six tensors to write into."""
+    if out is None:
+        r = (_native or _load_native()).qkv(Q, K, V, s_Q_mul)
+        if r is not None:
+            return r
     import torch
     shape = Q.shape
     assert shape == K.shape == V.shape and Q.dtype == K.dtype == V.dtype
@@ -168,6 +203,10 @@ def quantize_qkv(Q, K, V, s_Q_mul=1.0, out=None):
 def quantize_qk(Q, K, s_Q_mul=1.0, hadamard=False, out=None):
     """Q and K token-level in one launch.  Q, K [..., d] of one shape -> (Q_i8, K_i8, s_Q [...] (times s_Q_mul), s_K [...]);
     out: optional tuple of those four tensors to write into."""
+    if out is None:
+        r = (_native or _load_native()).qk(Q, K, s_Q_mul, hadamard)
+        if r is not None:
+            return r
     import torch
     shape = Q.shape
     assert shape == K.shape and Q.dtype == K.dtype
@@ -202,6 +241,10 @@ def int_flash_attn_fwd(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out_dtype=
     """Algorithm 1 on int8 tensors Q [B, H, Nq, d], K, V [B, H, Nk, d] (Nq = Nk in the paper; under the causal mask
     the queries are the last Nq positions).  Returns O [B, H, Nq, d] (fp16 unless out_dtype/out says otherwise).
     s_V [B, H] is the tensor-level scale of V; a 3-d s_V [B, H, ceil(N/B_c)] selects the per-block V scales."""
+    if out is None:
+        r = (_native or _load_native()).fwd(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal, out_dtype)
+        if r is not None:
+            return r
     import torch
     B, H, N, d = Q_i8.shape
     Nk = K_i8.shape[2]
@@ -235,6 +278,11 @@ def int_flash_attn_fwd_splitk(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out
     whole chip: same shapes and mask convention as int_flash_attn_fwd.  `workspace`: a uint8 device tensor of at least
     splitk_workspace_bytes(...) bytes (allocated here if not given), or the string "static": the library's built-in
     16 MiB workspace (no allocation at all; calls that overlap on one GPU must not share it)."""
+    static = isinstance(workspace, str) and workspace == "static"
+    if out is None and (static or not isinstance(workspace, (str, type(None)))):
+        r = (_native or _load_native()).splitk(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal, out_dtype, None if static else workspace)
+        if r is not None:
+            return r
     import torch
     B, H, N, d = Q_i8.shape
     Nk = K_i8.shape[2]
@@ -269,6 +317,10 @@ def block_cols(d: int, causal: bool) -> int:
 def int_flash_attn_fwd_half(Q_i8, K_i8, V_f16, s_Q, s_K, causal=False, out_dtype=None, out=None):
     """Half-INT8 variant: int8 Q [B, H, Nq, d], K [B, H, Nk, d] with token-level scales, fp16 V [B, H, Nk, d] as is
     (Nq = Nk in the paper; under the mask the queries are the last Nq positions).  Returns O [B, H, Nq, d]."""
+    if out is None:
+        r = (_native or _load_native()).half(Q_i8, K_i8, V_f16, s_Q, s_K, causal, out_dtype)
+        if r is not None:
+            return r
     import torch
     B, H, N, d = Q_i8.shape
     ptrs = (_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_f16, torch.float16),

@@ -1,4 +1,4 @@
-"""Builds libintfa.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Builds libintfa.so (hand-written HIP for gfx950) with hipcc and the binding's host module with the host compiler, in-tree."""
 from __future__ import annotations
 
 import os
@@ -22,7 +22,28 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-ffp-contract=off", "-falign-loops=32", "-Wall", "-Wno-unused-command-line-argument"]
 
 
+# The binding's plain calls (host code only): a CPython module on torch's C++ interface.
+HOST_SRC = os.path.join(CSRC, "intfa_host.cpp")
+HOST_LIB = os.path.join(_HERE, "_intfa_host.so")
+
+
+def _host_command():
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")))
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE, "-isystem", os.path.join(root, "include"),
+            "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"], "-Wall", HOST_SRC, "-o", HOST_LIB,
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
+    """libintfa.so and, beside it, the host module."""
+    host_cmd = _host_command()
+    if verbose:
+        print(" ".join(host_cmd), flush=True)
+    host = subprocess.Popen(host_cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *HIPCC_FLAGS, *extra_flags, "-I", INCLUDE, "-I", CSRC,
            *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
@@ -30,10 +51,13 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(ln for ln in res.stdout.splitlines() if "packed-fp32-ops" not in ln)
+    host_out = host.communicate()[0]
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + out)
-    if verbose and out.strip():
-        print(out)
+    if host.returncode != 0:
+        raise RuntimeError(f"{host_cmd[0]} failed:\n" + host_out)
+    if verbose and (out + host_out).strip():
+        print(out + host_out)
     return LIB
 
 

@@ -1,0 +1,84 @@
+"""The plain calls of the binding, which go through its native module, and the same calls on the general path behind it: the same
+results and the same refusals.  (An active torch function mode sends every call the general way.)"""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def general(f):
+    with torch.device("cuda"):                                   # a torch function mode
+        return f()
+
+
+def tensors(r):
+    return r if isinstance(r, tuple) else (r,)
+
+
+def calls(B, H, Nq, Nk, d, dtype):
+    import paper_2409_16997_amd as ifa
+    g = torch.Generator(device="cuda").manual_seed(Nk)
+    mk = lambda n, t=dtype: torch.randn((B, H, n, d), generator=g, device="cuda").to(t)
+    Q, K, V, W = mk(Nq), mk(Nk), mk(Nk), mk(Nk, torch.float16)
+    q8, sq = ifa.quantize_tokenwise(Q, scale_mul=d ** -0.5)
+    k8, sk = ifa.quantize_tokenwise(K)
+    v8, sv = ifa.quantize_headwise(V)
+    vb, svb = ifa.quantize_blockwise(V, ifa.block_cols(d, True))
+    ws = torch.empty(max(ifa.splitk_workspace_bytes(B, H, Nq, Nk, d), 256), dtype=torch.uint8, device="cuda")
+    out = [lambda: ifa.quantize_tokenwise(Q, scale_mul=2), lambda: ifa.quantize_headwise(V), lambda: ifa.quantize_qkv(K, V, K, s_Q_mul=0.5),
+           lambda: ifa.quantize_qk(K, V), lambda: ifa.quantize_qk(K, V, hadamard=True)]
+    for causal in (True, False):
+        for dt in (None, torch.float32, torch.bfloat16):
+            out += [lambda c=causal, t=dt: ifa.int_flash_attn_fwd(q8, k8, v8, sq, sk, sv, causal=c, out_dtype=t),
+                    lambda c=causal, t=dt: ifa.int_flash_attn_fwd(q8, k8, vb, sq, sk, svb, causal=c, out_dtype=t),
+                    lambda c=causal, t=dt: ifa.int_flash_attn_fwd_half(q8, k8, W, sq, sk, causal=c, out_dtype=t)]
+            if Nq <= 32:
+                out += [lambda c=causal, t=dt, w=w: ifa.int_flash_attn_fwd_splitk(q8, k8, v8, sq, sk, sv, causal=c, out_dtype=t, workspace=w) for w in (ws, "static", None)]
+    return out
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1, 64), (2, 3, 5, 300, 128), (1, 2, 129, 129, 64), (2, 5, 32, 2100, 128)])
+def test_both_paths_agree(shape, dtype):
+    for f in calls(*shape, dtype):
+        a, b = tensors(f()), tensors(general(f))
+        assert len(a) == len(b)
+        for x, y in zip(a, b):
+            assert x.dtype is y.dtype and x.shape == y.shape and x.stride() == y.stride() and torch.equal(x, y)
+    side = torch.cuda.Stream()                                   # ... and on a stream other than the default one
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        got = [tensors(f()) for f in calls(*shape, dtype)[:6]]
+    torch.cuda.current_stream().wait_stream(side)
+    for x, f in zip(got, calls(*shape, dtype)[:6]):
+        assert all(torch.equal(p, q) for p, q in zip(x, tensors(f())))
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def test_refusals_are_those_of_the_general_path():
+    import paper_2409_16997_amd as ifa
+    X = torch.randn((1, 2, 64, 64), device="cuda").half()
+    q8, k8, v8, sq, sk, sv = ifa.quantize_qkv(X, X, X)
+    fwd, cut = ifa.int_flash_attn_fwd, torch.zeros((1, 2, 65, 64), dtype=torch.int8, device="cuda")
+    bad = [lambda: ifa.quantize_tokenwise(X.cpu()), lambda: ifa.quantize_tokenwise(X.transpose(2, 3)), lambda: ifa.quantize_tokenwise(X.double()),
+           lambda: ifa.quantize_tokenwise(X, scale_mul=0.0), lambda: ifa.quantize_tokenwise(X, scale_mul="x"), lambda: ifa.quantize_tokenwise(X[:0]), lambda: ifa.quantize_tokenwise(None),
+           lambda: ifa.quantize_headwise(X[0, 0, 0]), lambda: ifa.quantize_qkv(X, X, X[:, :1]), lambda: ifa.quantize_qk(X, X.float()),
+           lambda: fwd(q8, k8, v8, sq, sk, sv[:, :1].expand(1, 2)), lambda: fwd(q8, k8, v8, sq[:, :1], sk, sv), lambda: fwd(X, k8, v8, sq, sk, sv),
+           lambda: fwd(cut, k8, v8, torch.ones((1, 2, 65), device="cuda"), sk, sv, causal=True), lambda: fwd(q8, k8, v8, sq, sk, sv.view(1, 2, 1).repeat(1, 1, 2)),
+           lambda: fwd(q8, k8, v8, sq, sk, sv, out_dtype=torch.float64), lambda: fwd(q8[0], k8[0], v8[0], sq[0], sk[0], sv[0]),
+           lambda: ifa.int_flash_attn_fwd_half(q8, k8, X.float(), sq, sk), lambda: ifa.int_flash_attn_fwd_splitk(q8, k8, v8, sq, sk, sv, workspace="static"),
+           lambda: ifa.int_flash_attn_fwd_splitk(q8[:, :, :2].contiguous(), k8, v8, sq[:, :, :2].contiguous(), sk, sv, workspace=torch.empty(8, dtype=torch.uint8, device="cuda"))]
+    for i, f in enumerate(bad):
+        seen = []
+        for path in (lambda: f(), lambda: general(f)):
+            with pytest.raises(Exception) as e:
+                path()
+            seen.append((e.type, str(e.value)))
+        assert seen[0] == seen[1], i
+    for f in (lambda x: ifa.quantize_tokenwise(x), lambda x: ifa.quantize_headwise(x)):       # accepted before, accepted still
+        assert all(torch.equal(a, b) for a, b in zip(f(X.as_subclass(Sub)), f(X)))
+    assert torch.equal(fwd(q8, k8, v8, sq, sk, sv, causal=1), fwd(q8, k8, v8, sq, sk, sv, causal=True))
