@@ -43,6 +43,10 @@ using namespace ifa_tiles;
 // read twice, by CUs of one XCD at about the same time, and each CU takes in 48 KB per group.
 // 32 heads of 4099 keys, one query: 21 us (without DS = 2 23.7, the packed kernel 42.5); K and V not in the caches: 128 heads of
 // 16384 (DS = 1) 95 us = 5.7 TB/s (the packed kernel 148), 512 of 4096 91 us = 5.9 TB/s (131).
+// LATE (d = 64, where the copies of a group take half as long and the PV wavefronts' way to the first barrier decides): they only
+// bring P and V to registers and fold the group before while those come in; their MFMAs follow the barrier, and the S wavefronts, which hold
+// P anyway, sum it up.  8 heads x 300 queries x 3000 keys 13.8 -> 12.8 us, 32 x 1 x 4099 17.8 -> 16.5, 64 x 4 x 8000 32.3 -> 30.0; at d = 128 the
+// same measures 2 % faster to 2 % slower (32 x 1 x 4099 20.9 -> 21.2).
 // Every number is computed by the same instruction sequence on the same operands as in the fused kernel (the
 // integer sums are exact, the extremum is order-independent, the row sum l is taken over the same P dwords), so
 // the rows are bit-identical to those of the same call on the fused kernel, and with one V scale per head to the
@@ -58,6 +62,7 @@ template <int D, int DS> struct SmemNarrow {
     alignas(4096) int8_t v[2][NARROW_NB][BC * (D / DS)];
     alignas(256) float sk[2][NARROW_NB * 4][64];          // per S wavefront: the 32 s_K of its key tile (+ 32 unused)
     alignas(16) v4i p[NARROW_NB][4][64];                  // per block, key tile and lane: the 16 P bytes of that lane (line 11)
+    alignas(16) int ps[D == 64 ? NARROW_NB : 1][64][4];   // (LATE) per block, lane and key tile: their sum (line 12)
     alignas(16) float ext[2][NARROW_NB][32][4];           // per block, query and key tile: the extremum of a (line 10)
 };
 static_assert(sizeof(SmemNarrow<128, 1>) <= 160 * 1024, "LDS budget");
@@ -70,6 +75,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
 #if defined(__HIP_DEVICE_COMPILE__)
     __shared__ SmemNarrow<D, DS> sm;
     constexpr int KS = D / 32, NB = NARROW_NB, DV = D / DS;
+    constexpr bool LATE = D == 64;                               // (see above)
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -96,7 +102,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const v4f e = *reinterpret_cast<const v4f *>(&sm.ext[parity][b][r][0]);
-            m2 = fmaxf(m2, fminf(fminf(e[0], e[1]), fminf(e[2], e[3])) * nq2);
+            m2 = fmaxf(m2, min4(e) * nq2);
             m.v[b] = m2;
         }
         return m;
@@ -189,14 +195,18 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
             read_group(gi + 1);
             const float mm = (blk ? m.v[1] : m.v[0]) - LOG2_R_NORM;
             v4i pw;
+            uint32_t psum = 0;
 #pragma unroll
             for (int vq = 0; vq < 4; ++vq) {
                 float x[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[4 * vq + e], nq2, -mm));
-                pw[vq] = static_cast<int>(pack_p4(x));
+                const uint32_t w = pack_p4(x);
+                if (LATE) psum = __builtin_amdgcn_sad_u8(w, 0u, psum);
+                pw[vq] = static_cast<int>(w);
             }
             sm.p[blk][t][lane] = pw;
+            if constexpr (LATE) sm.ps[blk][lane][t] = static_cast<int>(psum);
             wait_lds();                                          // (the operands of group gi + 1 are in registers too)
             __syncthreads();
         }
@@ -244,15 +254,42 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
     float sv_prev = 1.0f;
     const bool works = dt < PIECES;                              // two d tiles in a half (or D = 64): the other wavefronts only copy
     stage_group(0);
+    v16i pacc[NB];
+    float alpha[NB], psum[NB];
+    // lines 12, 13 of group gi, block by block in order.  (A block past the last one: the maximum stays, P is 0, nothing changes.)
+    auto fold = [&](int gi) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int jb = gi * NB + b;
+            float alpha_o = alpha[b];
+            if (VB && jb < nblocks) {                            // one V scale per key block: the running output is kept in units of the current block's
+                const float sv_j = uniform(sVh[jb]);
+                alpha_o = alpha[b] * uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j));
+                sv_prev = sv_j;
+            }
+            l = __builtin_fmaf(l, alpha[b], psum[b]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[b][v])));
+        }
+    };
     for (int gi = 0; gi <= ngroups; ++gi) {
         // Everything group gi - 1 needs goes to registers first, so that its place in LDS is free after the first barrier.
-        // (A block past the last one: the maximum stays, P is 0, nothing changes.)
         const float m_before = m2;
         Maxima m = {};
-        v16i pacc[NB];
-        uint32_t psum[NB] = {};
+        v4i pf[NB][4], vop[NB][4], ps[NB];
+        auto products = [&]() {
+            m = maxima((gi - 1) & 1);
+            if (!LATE) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) pacc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop[b][mt], pf[b][mt], mt == 0 ? acc0 : pacc[b], 0, 0, 0);
+        };
+        auto alphas = [&]() {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) alpha[b] = __builtin_amdgcn_exp2f((b == 0 ? m_before : m.v[b == 0 ? 0 : b - 1]) - m.v[b]);
+        };
         if (gi > 0 && works) {
-            v4i pf[NB][4], vop[NB][4];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const lds_ptr vs = vbuf + (((gi - 1) & 1) * NB + b) * (BC * DV);
@@ -263,36 +300,35 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
                     vop[b][mt] = v4i{t0[0], t0[1], t1[0], t1[1]};
                     pf[b][mt] = sm.p[b][mt][lane];
                 }
+                if constexpr (LATE) ps[b] = *reinterpret_cast<const v4i *>(&sm.ps[b][lane][0]);
             }
-            m = maxima((gi - 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (LATE) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (gi > 1) fold(gi - 2);
+                __builtin_amdgcn_sched_barrier(0);
+                wait_lds();
+            } else {
+                products();
 #pragma unroll
-            for (int b = 0; b < NB; ++b) pacc[b] = acc0;
+                for (int b = 0; b < NB; ++b) {
+                    uint32_t sum = 0;
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) pacc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vop[b][mt], pf[b][mt], pacc[b], 0, 0, 0);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) psum[b] = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[b][i >> 2][i & 3]), 0u, psum[b]);
+                    for (int i = 0; i < 16; ++i) sum = __builtin_amdgcn_sad_u8(static_cast<uint32_t>(pf[b][i >> 2][i & 3]), 0u, sum);
+                    psum[b] = static_cast<float>(sum);
+                }
+            }
         }
         __syncthreads();
         if (gi < ngroups) stage_group(gi + 1);
         if (gi > 0 && works) {
+            if constexpr (LATE) {
+                products();
+                alphas();
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int jb = (gi - 1) * NB + b;
-                const float alpha = __builtin_amdgcn_exp2f((b == 0 ? m_before : m.v[b == 0 ? 0 : b - 1]) - m.v[b]);
-                float alpha_o = alpha;
-                if (VB && jb < nblocks) {                        // one V scale per key block: the running output is kept in units of the current block's
-                    const float sv_j = uniform(sVh[jb]);
-                    alpha_o = alpha * uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j));
-                    sv_prev = sv_j;
-                }
-                l = __builtin_fmaf(l, alpha, static_cast<float>(psum[b]));            // line 12
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[v] = __builtin_fmaf(o[v], alpha_o, -(ACC_START_F - __int_as_float(pacc[b][v])));   // line 13
+                for (int b = 0; b < NB; ++b) psum[b] = static_cast<float>(ps[b][0] + ps[b][1] + ps[b][2] + ps[b][3]);
+            } else {
+                alphas();
+                fold(gi - 1);
             }
         }
         if (gi < ngroups) {
@@ -300,6 +336,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
             __syncthreads();                                     // everyone's has, and P of group gi is in LDS
         }
     }
+    if (LATE && works) fold(ngroups - 1);
     wait_all_memory();
 
     // lines 15-17 for d tile dt (d = 32 * dt + 8 * (v / 4) + 4 * g + v % 4 of query r)
