@@ -365,8 +365,8 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
 // Neither part of a half step waits for the other: P of one group forms under the MFMAs of the other's scores, and a PV wavefront folds
 // the half step before while its operands come in from LDS.  One barrier ends a half step: what it leaves in LDS -- extrema, P
 // bytes, their sums, the factors alpha -- is read in the next.
-// What bounds it: a half step takes about 1950 cycles, of which the vector ALU of a SIMD issues in 1500 (350 instructions of its three
-// wavefronts, an MFMA every fifth) and LDS is busy for 680 + 300 of copies; the rest is waits for LDS and the barrier.  The copies spread between the
+// What bounds it: a half step takes 1985 cycles, of which the wavefronts of a SIMD issue vector instructions in 1440 (326 of them, 16
+// MFMAs) and LDS is busy for 660 beside the copies; the rest is waits for LDS and the barrier.  The copies spread between the
 // vector instructions, a higher priority for either role, and 10 % fewer vector instructions all measured the same within 2 %.
 // 32 heads x 512 queries x 8192 keys 60 us = 1110 TOP/s (79 on the kernel above, 106 on the fused one); 65 x 128 x 1500 25 -> 17, 4 x 8192 x 8192 causal 107 -> 69.
 // Rows are bit-identical to the other kernels'.  Where the lines lie: ifa_pair_queries().
