@@ -60,11 +60,11 @@ signed char *i8(const at::Tensor &t) { return static_cast<signed char *>(t.data_
 float *f32(const at::Tensor &t) { return static_cast<float *>(t.data_ptr()); }
 at::Tensor codes(const at::Tensor &x) { return at::empty_like(x, x.options().dtype(at::kChar)); }
 at::Tensor scales(const at::Tensor &x, at::IntArrayRef shape) { return at::empty(shape, at::TensorOptions().dtype(at::kFloat).device(x.device())); }
-template <typename F> int unlocked(F f) {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f();
-    Py_END_ALLOW_THREADS
+// One call of the C ABI (which does not throw) without the GIL.  The arguments, data_ptr() among them, which can throw, are evaluated before it is released.
+template <typename... P, typename... A> int unlocked(int (*fn)(P...), A... a) {
+    PyThreadState *const state = PyEval_SaveThread();
+    const int rc = fn(a...);
+    PyEval_RestoreThread(state);
     return rc;
 }
 // C++ exceptions end here: the general path meets the same condition and says so
@@ -107,7 +107,7 @@ PyObject *tokenwise(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const long d = shape.back();
         at::Tensor q = codes(*x), s = scales(*x, shape.slice(0, shape.size() - 1));
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] { return abi.tokenwise(x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / d, static_cast<int>(d), i8(q), f32(s), static_cast<float>(mul), st); });
+        const int rc = unlocked(abi.tokenwise, x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / d, static_cast<int>(d), i8(q), f32(s), static_cast<float>(mul), st);
         return rc == IFA_OK ? tuple({q, s}) : nullptr;
     });
 }
@@ -121,7 +121,7 @@ PyObject *headwise(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const long d = shape.back(), N = shape[shape.size() - 2];
         at::Tensor q = codes(*x), s = scales(*x, shape.slice(0, shape.size() - 2));
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] { return abi.headwise(x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / (N * d), N, d, i8(q), f32(s), 0, st); });
+        const int rc = unlocked(abi.headwise, x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / (N * d), N, d, i8(q), f32(s), 0, st);
         return rc == IFA_OK ? tuple({q, s}) : nullptr;
     });
 }
@@ -139,7 +139,7 @@ PyObject *qkv(PyObject *, PyObject *const *a, Py_ssize_t n) {
         at::Tensor q8 = codes(*q), k8 = codes(*q), v8 = codes(*q);
         at::Tensor sq = scales(*q, shape.slice(0, shape.size() - 1)), sk = scales(*q, shape.slice(0, shape.size() - 1)), sv = scales(*q, shape.slice(0, shape.size() - 2));
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] { return abi.qkv(q->data_ptr(), k->data_ptr(), v->data_ptr(), dt, q->numel() / (N * d), N, static_cast<int>(d), i8(q8), i8(k8), i8(v8), f32(sq), f32(sk), f32(sv), static_cast<float>(mul), st); });
+        const int rc = unlocked(abi.qkv, q->data_ptr(), k->data_ptr(), v->data_ptr(), dt, q->numel() / (N * d), N, static_cast<int>(d), i8(q8), i8(k8), i8(v8), f32(sq), f32(sk), f32(sv), static_cast<float>(mul), st);
         return rc == IFA_OK ? tuple({q8, k8, v8, sq, sk, sv}) : nullptr;
     });
 }
@@ -156,7 +156,7 @@ PyObject *qk(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const long d = shape.back();
         at::Tensor q8 = codes(*q), k8 = codes(*q), sq = scales(*q, shape.slice(0, shape.size() - 1)), sk = scales(*q, shape.slice(0, shape.size() - 1));
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] { return abi.qk(q->data_ptr(), k->data_ptr(), dt, q->numel() / d, static_cast<int>(d), i8(q8), i8(k8), f32(sq), f32(sk), static_cast<float>(mul), had, st); });
+        const int rc = unlocked(abi.qk, q->data_ptr(), k->data_ptr(), dt, q->numel() / d, static_cast<int>(d), i8(q8), i8(k8), f32(sq), f32(sk), static_cast<float>(mul), had, st);
         return rc == IFA_OK ? tuple({q8, k8, sq, sk}) : nullptr;
     });
 }
@@ -195,7 +195,7 @@ PyObject *fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
             if (bc <= 0 || c.sv->size(0) != c.B || c.sv->size(1) != c.H || c.sv->size(2) != (c.Nk + bc - 1) / bc) return nullptr;
         }
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] { return (vb ? abi.vblock : abi.fwd)(i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st); });
+        const int rc = unlocked(vb ? abi.vblock : abi.fwd, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
         return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;
     });
 }
@@ -206,7 +206,7 @@ PyObject *half(PyObject *, PyObject *const *a, Py_ssize_t n) {
         Call c;
         if (n != 7 || !c.take(a, dev, at::kHalf, nullptr, a[5], a[6])) return nullptr;
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] { return abi.half(i8(*c.q), i8(*c.k), c.v->data_ptr(), f32(*c.sq), f32(*c.sk), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st); });
+        const int rc = unlocked(abi.half, i8(*c.q), i8(*c.k), c.v->data_ptr(), f32(*c.sq), f32(*c.sk), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
         return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;
     });
 }
@@ -219,10 +219,8 @@ PyObject *splitk(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (n != 9 || (a[8] != Py_None && (!(ws = plain(a[8], dev)) || ws->scalar_type() != at::kByte))) return nullptr;
         if (!c.take(a, dev, at::kChar, a[5], a[6], a[7]) || c.sv->dim() != 2 || c.sv->size(0) != c.B || c.sv->size(1) != c.H) return nullptr;
         const hipStream_t st = stream(dev);
-        const int rc = unlocked([&] {
-            return ws ? abi.splitk(i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, ws->data_ptr(), ws->numel(), st)
-                      : abi.splitk_static(i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
-        });
+        const int rc = ws ? unlocked(abi.splitk, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, ws->data_ptr(), ws->numel(), st)
+                          : unlocked(abi.splitk_static, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
         return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;
     });
 }

@@ -82,3 +82,16 @@ def test_refusals_are_those_of_the_general_path():
     for f in (lambda x: ifa.quantize_tokenwise(x), lambda x: ifa.quantize_headwise(x)):       # accepted before, accepted still
         assert all(torch.equal(a, b) for a, b in zip(f(X.as_subclass(Sub)), f(X)))
     assert torch.equal(fwd(q8, k8, v8, sq, sk, sv, causal=1), fwd(q8, k8, v8, sq, sk, sv, causal=True))
+
+
+def test_a_tensor_whose_address_cannot_be_had_is_refused():
+    # data_ptr() raises for it (C++ exception inside the module): the call ends in the same error on both paths, and the process goes on
+    import paper_2409_16997_amd as ifa
+    bad = torch.randn((1, 2, 64, 64), device="cuda").half()
+    torch._C._set_throw_on_mutable_data_ptr(bad)
+    for f in (lambda: ifa.quantize_tokenwise(bad), lambda: ifa.quantize_headwise(bad), lambda: ifa.quantize_qkv(bad, bad, bad), lambda: ifa.quantize_qk(bad, bad)):
+        for path in (lambda: f(), lambda: general(f)):
+            with pytest.raises(RuntimeError, match="data pointer"):
+                path()
+    good = torch.randn((1, 2, 64, 64), device="cuda").half()
+    assert ifa.quantize_tokenwise(good)[0].shape == good.shape
