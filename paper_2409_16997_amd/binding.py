@@ -113,13 +113,15 @@ def _dtype_enum(t):
     raise IntfaError(f"unsupported dtype {dt}")
 
 
-def _dev(t, dtype=None):
-    """Address of a contiguous tensor in GPU memory, of the given dtype if one is named."""
+def _dev(t, dtype=None, least=0):
+    """Address of a contiguous tensor in GPU memory, of the given dtype if one is named, with at least `least` elements."""
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
         raise IntfaError("expected a contiguous tensor in GPU memory")
     if dtype is not None and t.dtype is not dtype:
         raise IntfaError(f"expected dtype {dtype}, got {t.dtype}")
+    if t.numel() < least:
+        raise IntfaError(f"expected at least {least} elements, got {t.numel()}")
     return t.data_ptr()
 
 
@@ -249,7 +251,7 @@ def int_flash_attn_fwd(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out_dtype=
     B, H, N, d = Q_i8.shape
     Nk = K_i8.shape[2]
     args = (_dev(Q_i8, torch.int8), _dev(K_i8, torch.int8), _dev(V_i8, torch.int8),
-            _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32))
+            _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32, B * H))     # (a scale of every head is read)
     if out is None:
         out = torch.empty_like(Q_i8, dtype=out_dtype or torch.float16)
     tail = (d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())

@@ -193,7 +193,7 @@ PyObject *fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (vb) {
             const int bc = abi.block_cols(c.d, c.causal);
             if (bc <= 0 || c.sv->size(0) != c.B || c.sv->size(1) != c.H || c.sv->size(2) != (c.Nk + bc - 1) / bc) return nullptr;
-        }
+        } else if (c.sv->numel() < static_cast<int64_t>(c.B) * c.H) return nullptr;              // a scale of every head is read
         const hipStream_t st = stream(dev);
         const int rc = unlocked(vb ? abi.vblock : abi.fwd, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
         return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;

@@ -1,0 +1,53 @@
+"""What the binding's general path refuses before the C ABI is reached, on host tensors with a stand-in for the library."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2409_16997_amd import binding
+
+
+class Library:
+    """Every function of it succeeds and is noted."""
+    def __init__(self):
+        self.called = []
+
+    def __getattr__(self, name):
+        def call(*args):
+            if not name.startswith("ifa_"):
+                self.called.append(name)
+            return {"ifa_block_cols": 128, "ifa_splitk_workspace_bytes": 256}.get(name, 0)
+        return call
+
+
+class NoModule:
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+@pytest.fixture
+def library(monkeypatch):
+    stand_in = Library()
+    monkeypatch.setattr(torch.Tensor, "is_cuda", True, raising=False)
+    monkeypatch.setattr(binding, "lib", lambda: stand_in)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    monkeypatch.setattr(binding, "_native", NoModule())
+    return stand_in
+
+
+def operands(B=2, H=3, Nq=5, Nk=7, d=64):
+    i8 = lambda n: torch.zeros((B, H, n, d), dtype=torch.int8)
+    return i8(Nq), i8(Nk), i8(Nk), torch.ones((B, H, Nq)), torch.ones((B, H, Nk))
+
+
+# s_V is read at every head: a tensor with fewer scales than heads would be read past its end
+@pytest.mark.parametrize("shape,taken", [((2, 3), True), ((6,), True), ((2, 3, 1), True), ((2, 3, 1, 1), True), ((1,), False), ((), False), ((2, 2), False),
+                                         ((5,), False), ((2, 3, 2), False), ((1, 1, 1), False)])
+def test_v_scales_of_every_head(library, shape, taken):
+    call = lambda: binding.int_flash_attn_fwd(*operands(), torch.ones(shape))
+    if taken:
+        call()
+        assert len(library.called) == 1
+    else:
+        with pytest.raises(binding.IntfaError):
+            call()
+        assert not library.called

@@ -69,6 +69,7 @@ def test_refusals_are_those_of_the_general_path():
            lambda: ifa.quantize_headwise(X[0, 0, 0]), lambda: ifa.quantize_qkv(X, X, X[:, :1]), lambda: ifa.quantize_qk(X, X.float()),
            lambda: fwd(q8, k8, v8, sq, sk, sv[:, :1].expand(1, 2)), lambda: fwd(q8, k8, v8, sq[:, :1], sk, sv), lambda: fwd(X, k8, v8, sq, sk, sv),
            lambda: fwd(cut, k8, v8, torch.ones((1, 2, 65), device="cuda"), sk, sv, causal=True), lambda: fwd(q8, k8, v8, sq, sk, sv.view(1, 2, 1).repeat(1, 1, 2)),
+           lambda: fwd(q8, k8, v8, sq, sk, sv[:, :1].contiguous()), lambda: fwd(q8, k8, v8, sq, sk, sv[0, 0]), lambda: fwd(q8, k8, v8, sq, sk, sv[0, :1]),
            lambda: fwd(q8, k8, v8, sq, sk, sv, out_dtype=torch.float64), lambda: fwd(q8[0], k8[0], v8[0], sq[0], sk[0], sv[0]),
            lambda: ifa.int_flash_attn_fwd_half(q8, k8, X.float(), sq, sk), lambda: ifa.int_flash_attn_fwd_splitk(q8, k8, v8, sq, sk, sv, workspace="static"),
            lambda: ifa.int_flash_attn_fwd_splitk(q8[:, :, :2].contiguous(), k8, v8, sq[:, :, :2].contiguous(), sk, sv, workspace=torch.empty(8, dtype=torch.uint8, device="cuda"))]
@@ -81,6 +82,7 @@ def test_refusals_are_those_of_the_general_path():
         assert seen[0] == seen[1], i
     for f in (lambda x: ifa.quantize_tokenwise(x), lambda x: ifa.quantize_headwise(x)):       # accepted before, accepted still
         assert all(torch.equal(a, b) for a, b in zip(f(X.as_subclass(Sub)), f(X)))
+    assert torch.equal(fwd(q8, k8, v8, sq, sk, sv[0]), fwd(q8, k8, v8, sq, sk, sv))
     assert torch.equal(fwd(q8, k8, v8, sq, sk, sv, causal=1), fwd(q8, k8, v8, sq, sk, sv, causal=True))
 
 
