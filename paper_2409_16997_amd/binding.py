@@ -196,8 +196,9 @@ def quantize_qkv(Q, K, V, s_Q_mul=1.0, out=None):
         sk = torch.empty_like(sq)
     else:
         q8, k8, v8, sq, sk, sv = out
-    _check(lib().quantize_qkv(q, k, v, _dtype_enum(Q), heads, N, d, _dev(q8, torch.int8), _dev(k8, torch.int8),
-                              _dev(v8, torch.int8), _dev(sq, torch.float32), _dev(sk, torch.float32), _dev(sv, torch.float32),
+    rows, n = heads * N, heads * N * d
+    _check(lib().quantize_qkv(q, k, v, _dtype_enum(Q), heads, N, d, _dev(q8, torch.int8, n), _dev(k8, torch.int8, n),
+                              _dev(v8, torch.int8, n), _dev(sq, torch.float32, rows), _dev(sk, torch.float32, rows), _dev(sv, torch.float32, heads),
                               float(s_Q_mul), _stream()), "quantize_qkv")
     return q8, k8, v8, sq, sk, sv
 
@@ -221,8 +222,8 @@ def quantize_qk(Q, K, s_Q_mul=1.0, hadamard=False, out=None):
         sk = torch.empty_like(sq)
     else:
         q8, k8, sq, sk = out
-    _check(lib().quantize_qk(q, k, _dtype_enum(Q), rows, d, _dev(q8, torch.int8), _dev(k8, torch.int8),
-                             _dev(sq, torch.float32), _dev(sk, torch.float32), float(s_Q_mul), int(bool(hadamard)), _stream()),
+    _check(lib().quantize_qk(q, k, _dtype_enum(Q), rows, d, _dev(q8, torch.int8, rows * d), _dev(k8, torch.int8, rows * d),
+                             _dev(sq, torch.float32, rows), _dev(sk, torch.float32, rows), float(s_Q_mul), int(bool(hadamard)), _stream()),
            "quantize_qk")
     return q8, k8, sq, sk
 
@@ -254,7 +255,7 @@ def int_flash_attn_fwd(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out_dtype=
             _dev(s_Q, torch.float32), _dev(s_K, torch.float32), _dev(s_V, torch.float32, B * H))     # (a scale of every head is read)
     if out is None:
         out = torch.empty_like(Q_i8, dtype=out_dtype or torch.float16)
-    tail = (d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
+    tail = (d, int(bool(causal)), _dev(out, None, B * H * N * d), _dtype_enum(out), _stream())
     if K_i8.shape != (B, H, Nk, d) or V_i8.shape != K_i8.shape or s_K.shape != (B, H, Nk) or s_Q.shape != (B, H, N):
         raise IntfaError("Q/K/V/scale shapes do not agree")
     if s_V.dim() == 3:
@@ -301,12 +302,12 @@ def int_flash_attn_fwd_splitk(Q_i8, K_i8, V_i8, s_Q, s_K, s_V, causal=False, out
     if isinstance(workspace, str):
         if workspace != "static":
             raise IntfaError("workspace: a uint8 device tensor, None or 'static'")
-        code = lib().int_flash_attn_fwd_splitk_static(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
+        code = lib().int_flash_attn_fwd_splitk_static(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out, None, B * H * N * d), _dtype_enum(out), _stream())
         _check(code, "int_flash_attn_fwd_splitk_static")
         return out
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=Q_i8.device)
-    code = lib().int_flash_attn_fwd_splitk(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out),
+    code = lib().int_flash_attn_fwd_splitk(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out, None, B * H * N * d), _dtype_enum(out),
                                            _dev(workspace, torch.uint8), workspace.numel(), _stream())
     _check(code, "int_flash_attn_fwd_splitk")
     return out
@@ -332,7 +333,7 @@ def int_flash_attn_fwd_half(Q_i8, K_i8, V_f16, s_Q, s_K, causal=False, out_dtype
     Nk = K_i8.shape[2]
     if K_i8.shape != (B, H, Nk, d) or V_f16.shape != K_i8.shape or s_K.shape != (B, H, Nk) or s_Q.shape != (B, H, N):
         raise IntfaError("Q/K/V/scale shapes do not agree")
-    code = lib().int_flash_attn_fwd_half_rect(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out), _dtype_enum(out), _stream())
+    code = lib().int_flash_attn_fwd_half_rect(*ptrs, B, H, N, Nk, d, int(bool(causal)), _dev(out, None, B * H * N * d), _dtype_enum(out), _stream())
     _check(code, "int_flash_attn_fwd_half")
     return out
 

@@ -51,3 +51,27 @@ def test_v_scales_of_every_head(library, shape, taken):
         with pytest.raises(binding.IntfaError):
             call()
         assert not library.called
+
+
+# an `out` with fewer elements than the call writes would be written past its end
+def test_outputs_have_room(library):
+    q, k, v, sq, sk = operands(Nq=5, Nk=5)
+    sv = torch.ones((2, 3))
+    X = torch.zeros((2, 3, 5, 64), dtype=torch.float16)
+    small, room, flat = torch.empty((2, 3, 4, 64)), torch.empty((2, 3, 5, 64)), torch.empty(2 * 3 * 5 * 64)
+    for fn, args in ((binding.int_flash_attn_fwd, (q, k, v, sq, sk, sv)), (binding.int_flash_attn_fwd_half, (q, k, X, sq, sk)),
+                     (binding.int_flash_attn_fwd_splitk, (q, k, v, sq, sk, sv))):
+        for out in (room, flat):
+            assert fn(*args, out=out) is out
+        before = len(library.called)
+        with pytest.raises(binding.IntfaError):
+            fn(*args, out=small)
+        assert len(library.called) == before
+    codes, rows = torch.empty((2, 3, 5, 64), dtype=torch.int8), torch.empty((2, 3, 5))
+    for fn, args, outs in ((binding.quantize_qkv, (X, X, X), [codes, codes, codes, rows, rows, sv]), (binding.quantize_qk, (X, X), [codes, codes, rows, rows])):
+        fn(*args, out=tuple(outs))
+        before = len(library.called)
+        for i, t in enumerate(outs):
+            with pytest.raises(binding.IntfaError):
+                fn(*args, out=tuple(outs[:i] + [t.flatten()[:-1]] + outs[i + 1:]))
+        assert len(library.called) == before
