@@ -69,6 +69,13 @@ def lib():
 
 _native = None
 _NATIVE_PATH = os.path.join(_HERE, "_intfa_host.so")
+# the functions of the C ABI that the module calls, in its order
+_NATIVE_CALLS = ("quantize_tokenwise_ex", "quantize_headwise_ex", "quantize_qkv", "quantize_qk", "int_flash_attn_fwd_rect", "int_flash_attn_fwd_vblock_rect",
+                 "int_flash_attn_fwd_half_rect", "int_flash_attn_fwd_splitk", "int_flash_attn_fwd_splitk_static", "ifa_block_cols")
+
+
+def _address(fn):
+    return ctypes.cast(fn, ctypes.c_void_p).value
 
 
 def _load_native():
@@ -81,10 +88,7 @@ def _load_native():
     loader = importlib.machinery.ExtensionFileLoader("_intfa_host", _NATIVE_PATH)
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_intfa_host", loader))
     loader.exec_module(module)
-    module.init(*(ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value for name in (
-        "quantize_tokenwise_ex", "quantize_headwise_ex", "quantize_qkv", "quantize_qk", "int_flash_attn_fwd_rect",
-        "int_flash_attn_fwd_vblock_rect", "int_flash_attn_fwd_half_rect", "int_flash_attn_fwd_splitk", "int_flash_attn_fwd_splitk_static",
-        "ifa_block_cols")))
+    module.init(_check, *(_address(getattr(lib(), name)) for name in _NATIVE_CALLS))
     _native = module
     return module
 

@@ -3,9 +3,9 @@
 // arguments taken apart and the seven outputs allocated in Python, 13.6 like this, of which 9 are GPU time; a first pass on new inputs 38 and 24).
 //
 // Every function returns None for anything but the plain case -- a tensor subclass, an active torch function or dispatch mode, a tensor
-// that is not contiguous, not on the current device or of another type, shapes that do not agree, any error of the C ABI -- and
-// the binding then takes its general path, which handles or refuses it.  The C ABI is reached through the addresses that init() is
-// given, those of the library the binding has loaded.  The GIL is released around a call, as ctypes does.
+// that is not contiguous, not on the current device or of another type, shapes that do not agree, a call that the C ABI refuses -- and
+// the binding then takes its general path, which handles or refuses it.  An error of the HIP runtime is raised from here.  The C ABI is
+// reached through the addresses that init() is given, those of the library the binding has loaded.  The GIL is released around a call, as ctypes does.
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -35,15 +35,19 @@ struct Abi {
     decltype(&::ifa_block_cols) block_cols;
 } abi;
 constexpr int ABI_FUNCTIONS = sizeof(Abi) / sizeof(void *);
+PyObject *check = nullptr;                                       // the binding's: check(status, name of the call) raises what such a status raises
 
+// init(check, address of every function of Abi)
 PyObject *init(PyObject *, PyObject *const *args, Py_ssize_t n) {
-    if (n != ABI_FUNCTIONS) { PyErr_SetString(PyExc_TypeError, "init: one address per function of the C ABI"); return nullptr; }
+    if (n != 1 + ABI_FUNCTIONS) { PyErr_SetString(PyExc_TypeError, "init: check() and one address per function of the C ABI"); return nullptr; }
     void *p[ABI_FUNCTIONS];
     for (int i = 0; i < ABI_FUNCTIONS; ++i) {
-        p[i] = PyLong_AsVoidPtr(args[i]);
+        p[i] = PyLong_AsVoidPtr(args[1 + i]);
         if (!p[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "init: null address"); return nullptr; }
     }
     memcpy(&abi, p, sizeof p);
+    Py_INCREF(args[0]);
+    Py_XSETREF(check, args[0]);
     Py_RETURN_NONE;
 }
 
@@ -66,6 +70,12 @@ template <typename... P, typename... A> int unlocked(int (*fn)(P...), A... a) {
     const int rc = fn(a...);
     PyEval_RestoreThread(state);
     return rc;
+}
+// False for a refusal, which comes before anything is enqueued and which the general path repeats and reports; a HIP error is raised at once:
+// the runtime has forgotten it by the time of a second call, which would enqueue again what the first one has.
+bool succeeded(int rc, const char *what) {
+    if (rc == IFA_ERR_HIP) Py_XDECREF(PyObject_CallFunction(check, "is", rc, what));
+    return rc == IFA_OK;
 }
 // C++ exceptions end here: the general path meets the same condition and says so
 template <typename F> PyObject *guarded(F f) {
@@ -108,7 +118,7 @@ PyObject *tokenwise(PyObject *, PyObject *const *a, Py_ssize_t n) {
         at::Tensor q = codes(*x), s = scales(*x, shape.slice(0, shape.size() - 1));
         const hipStream_t st = stream(dev);
         const int rc = unlocked(abi.tokenwise, x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / d, static_cast<int>(d), i8(q), f32(s), static_cast<float>(mul), st);
-        return rc == IFA_OK ? tuple({q, s}) : nullptr;
+        return succeeded(rc, "quantize_tokenwise") ? tuple({q, s}) : nullptr;
     });
 }
 
@@ -122,7 +132,7 @@ PyObject *headwise(PyObject *, PyObject *const *a, Py_ssize_t n) {
         at::Tensor q = codes(*x), s = scales(*x, shape.slice(0, shape.size() - 2));
         const hipStream_t st = stream(dev);
         const int rc = unlocked(abi.headwise, x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / (N * d), N, d, i8(q), f32(s), 0, st);
-        return rc == IFA_OK ? tuple({q, s}) : nullptr;
+        return succeeded(rc, "quantize_headwise_ex") ? tuple({q, s}) : nullptr;
     });
 }
 
@@ -140,7 +150,7 @@ PyObject *qkv(PyObject *, PyObject *const *a, Py_ssize_t n) {
         at::Tensor sq = scales(*q, shape.slice(0, shape.size() - 1)), sk = scales(*q, shape.slice(0, shape.size() - 1)), sv = scales(*q, shape.slice(0, shape.size() - 2));
         const hipStream_t st = stream(dev);
         const int rc = unlocked(abi.qkv, q->data_ptr(), k->data_ptr(), v->data_ptr(), dt, q->numel() / (N * d), N, static_cast<int>(d), i8(q8), i8(k8), i8(v8), f32(sq), f32(sk), f32(sv), static_cast<float>(mul), st);
-        return rc == IFA_OK ? tuple({q8, k8, v8, sq, sk, sv}) : nullptr;
+        return succeeded(rc, "quantize_qkv") ? tuple({q8, k8, v8, sq, sk, sv}) : nullptr;
     });
 }
 
@@ -157,7 +167,7 @@ PyObject *qk(PyObject *, PyObject *const *a, Py_ssize_t n) {
         at::Tensor q8 = codes(*q), k8 = codes(*q), sq = scales(*q, shape.slice(0, shape.size() - 1)), sk = scales(*q, shape.slice(0, shape.size() - 1));
         const hipStream_t st = stream(dev);
         const int rc = unlocked(abi.qk, q->data_ptr(), k->data_ptr(), dt, q->numel() / d, static_cast<int>(d), i8(q8), i8(k8), f32(sq), f32(sk), static_cast<float>(mul), had, st);
-        return rc == IFA_OK ? tuple({q8, k8, sq, sk}) : nullptr;
+        return succeeded(rc, "quantize_qk") ? tuple({q8, k8, sq, sk}) : nullptr;
     });
 }
 
@@ -196,7 +206,7 @@ PyObject *fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
         } else if (c.sv->numel() < static_cast<int64_t>(c.B) * c.H) return nullptr;              // a scale of every head is read
         const hipStream_t st = stream(dev);
         const int rc = unlocked(vb ? abi.vblock : abi.fwd, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
-        return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;
+        return succeeded(rc, "int_flash_attn_fwd") ? THPVariable_Wrap(c.out) : nullptr;
     });
 }
 
@@ -207,7 +217,7 @@ PyObject *half(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (n != 7 || !c.take(a, dev, at::kHalf, nullptr, a[5], a[6])) return nullptr;
         const hipStream_t st = stream(dev);
         const int rc = unlocked(abi.half, i8(*c.q), i8(*c.k), c.v->data_ptr(), f32(*c.sq), f32(*c.sk), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
-        return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;
+        return succeeded(rc, "int_flash_attn_fwd_half") ? THPVariable_Wrap(c.out) : nullptr;
     });
 }
 
@@ -221,7 +231,7 @@ PyObject *splitk(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const hipStream_t st = stream(dev);
         const int rc = ws ? unlocked(abi.splitk, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, ws->data_ptr(), ws->numel(), st)
                           : unlocked(abi.splitk_static, i8(*c.q), i8(*c.k), i8(*c.v), f32(*c.sq), f32(*c.sk), f32(*c.sv), c.B, c.H, c.Nq, c.Nk, c.d, c.causal, c.out.data_ptr(), c.o_dtype, st);
-        return rc == IFA_OK ? THPVariable_Wrap(c.out) : nullptr;
+        return succeeded(rc, ws ? "int_flash_attn_fwd_splitk" : "int_flash_attn_fwd_splitk_static") ? THPVariable_Wrap(c.out) : nullptr;
     });
 }
 

@@ -97,3 +97,32 @@ def test_a_tensor_whose_address_cannot_be_had_is_refused():
                 path()
     good = torch.randn((1, 2, 64, 64), device="cuda").half()
     assert ifa.quantize_tokenwise(good)[0].shape == good.shape
+
+
+def test_a_hip_error_is_raised_and_the_call_not_repeated():
+    # a stand-in for the C ABI whose every launch fails once behind the module; the library on the general path would succeed
+    import ctypes
+    from paper_2409_16997_amd import binding
+    ifa = binding
+    B, H, N, d = 1, 2, 64, 64
+    X = torch.randn((B, H, N, d), device="cuda").half()
+    q8, k8, v8, sq, sk, sv = ifa.quantize_qkv(X, X, X)
+    svb = ifa.quantize_blockwise(X, 128)[1]
+    ws = torch.empty(ifa.splitk_workspace_bytes(B, H, 8, N, d), dtype=torch.uint8, device="cuda")
+    few = (q8[:, :, :8].contiguous(), k8, v8, sq[:, :, :8].contiguous(), sk, sv)
+    calls = [lambda: ifa.quantize_tokenwise(X), lambda: ifa.quantize_headwise(X), lambda: ifa.quantize_qkv(X, X, X), lambda: ifa.quantize_qk(X, X),
+             lambda: ifa.int_flash_attn_fwd(q8, k8, v8, sq, sk, sv), lambda: ifa.int_flash_attn_fwd(q8, k8, v8, sq, sk, svb),
+             lambda: ifa.int_flash_attn_fwd_half(q8, k8, X, sq, sk), lambda: ifa.int_flash_attn_fwd_splitk(*few, workspace=ws),
+             lambda: ifa.int_flash_attn_fwd_splitk(*few, workspace="static")]
+    fail = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: -5)            # IFA_ERR_HIP
+    module = binding._load_native()
+    addresses = [binding._address(getattr(binding.lib(), name)) for name in binding._NATIVE_CALLS]
+    try:
+        module.init(binding._check, *([binding._address(fail)] * (len(addresses) - 1) + addresses[-1:]))
+        for i, f in enumerate(calls):
+            with pytest.raises(binding.IntfaError, match="IFA_ERR_HIP"):
+                f()
+    finally:
+        module.init(binding._check, *addresses)
+    for f in calls:
+        f()
