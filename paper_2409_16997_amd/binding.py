@@ -5,6 +5,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libintfa.so")
@@ -78,17 +79,29 @@ def _address(fn):
     return ctypes.cast(fn, ctypes.c_void_p).value
 
 
+class _NoNative:
+    """In place of a module that cannot be had: every call is left to the general path."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_native():
     """csrc/intfa_host.cpp: the plain calls without Python between the tensors and the C ABI.  Its functions return None for whatever
-    is not a plain call, and the code behind them here takes over."""
+    is not a plain call, and the code behind them here takes over; it serves every call, 8 to 13 us slower, where the module is missing
+    or was built for another torch or another binding."""
     global _native
-    import torch  # noqa: F401  (the module's symbols are torch's)
-    if not os.path.exists(_NATIVE_PATH):
-        raise IntfaError(f"{_NATIVE_PATH} is missing: build it with `python -m paper_2409_16997_amd.build` or __graft_entry__.build()")
-    loader = importlib.machinery.ExtensionFileLoader("_intfa_host", _NATIVE_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_intfa_host", loader))
-    loader.exec_module(module)
-    module.init(_check, *(_address(getattr(lib(), name)) for name in _NATIVE_CALLS))
+    import torch
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_intfa_host", _NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_intfa_host", loader))
+        loader.exec_module(module)
+        if module.torch_version != torch.__version__:
+            raise ImportError(f"it was built for torch {module.torch_version}")
+        module.init(_check, *(_address(getattr(lib(), name)) for name in _NATIVE_CALLS))
+    except (ImportError, AttributeError, TypeError) as e:
+        warnings.warn(f"{_NATIVE_PATH} cannot be used ({e}): calls go through ctypes and take longer on the host; build it with "
+                      "`python -m paper_2409_16997_amd.build` or __graft_entry__.build()", RuntimeWarning, stacklevel=3)
+        module = _NoNative()
     _native = module
     return module
 

@@ -33,7 +33,7 @@ def _host_command():
     root = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")))
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE, "-isystem", os.path.join(root, "include"),
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DINTFA_TORCH_VERSION="{torch.__version__}"', "-I", INCLUDE, "-isystem", os.path.join(root, "include"),
             "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"], "-Wall", HOST_SRC, "-o", HOST_LIB,
             "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
 

@@ -241,4 +241,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_intfa_host", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__intfa_host() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__intfa_host() {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", INTFA_TORCH_VERSION) < 0) Py_CLEAR(m);      // the one whose internals it was built for
+    return m;
+}

@@ -1,4 +1,7 @@
 """What the binding's general path refuses before the C ABI is reached, on host tensors with a stand-in for the library."""
+import os
+import warnings
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -19,18 +22,13 @@ class Library:
         return call
 
 
-class NoModule:
-    def __getattr__(self, name):
-        return lambda *args: None
-
-
 @pytest.fixture
 def library(monkeypatch):
     stand_in = Library()
     monkeypatch.setattr(torch.Tensor, "is_cuda", True, raising=False)
     monkeypatch.setattr(binding, "lib", lambda: stand_in)
     monkeypatch.setattr(binding, "_stream", lambda: 0)
-    monkeypatch.setattr(binding, "_native", NoModule())
+    monkeypatch.setattr(binding, "_native", binding._NoNative())
     return stand_in
 
 
@@ -75,3 +73,25 @@ def test_outputs_have_room(library):
             with pytest.raises(binding.IntfaError):
                 fn(*args, out=tuple(outs[:i] + [t.flatten()[:-1]] + outs[i + 1:]))
         assert len(library.called) == before
+
+
+# Without a host module that fits (none, one that does not load, one built for another torch) the general path serves every call.
+@pytest.mark.parametrize("fault", ["missing", "broken", "other torch"])
+def test_calls_without_the_host_module(monkeypatch, tmp_path, fault):
+    monkeypatch.setattr(binding, "_native", None)
+    if fault == "other torch":
+        if not os.path.exists(binding._NATIVE_PATH):
+            pytest.skip("not built")
+        monkeypatch.setattr(torch, "__version__", "1.0.0")
+    else:
+        path = tmp_path / "_intfa_host.so"
+        if fault == "broken":
+            path.write_bytes(b"not a library")
+        monkeypatch.setattr(binding, "_NATIVE_PATH", str(path))
+    with pytest.warns(RuntimeWarning, match="cannot be used"):
+        with pytest.raises(binding.IntfaError, match="contiguous tensor in GPU memory"):
+            binding.quantize_tokenwise(torch.zeros((4, 64)))
+    with warnings.catch_warnings():                              # said once
+        warnings.simplefilter("error")
+        with pytest.raises(binding.IntfaError, match="contiguous tensor in GPU memory"):
+            binding.quantize_headwise(torch.zeros((4, 64)))

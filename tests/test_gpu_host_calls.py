@@ -41,6 +41,8 @@ def calls(B, H, Nq, Nk, d, dtype):
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("shape", [(1, 1, 1, 1, 64), (2, 3, 5, 300, 128), (1, 2, 129, 129, 64), (2, 5, 32, 2100, 128)])
 def test_both_paths_agree(shape, dtype):
+    from paper_2409_16997_amd import binding
+    assert not isinstance(binding._load_native(), binding._NoNative)
     for f in calls(*shape, dtype):
         a, b = tensors(f()), tensors(general(f))
         assert len(a) == len(b)
