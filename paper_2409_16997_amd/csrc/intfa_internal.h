@@ -54,14 +54,18 @@ static inline bool ifa_packed_queries(int heads, int Nq, int Nk, int d) {
 //                                   Half of the key blocks masked: the heaviest workgroup decides, and the two waves of the few-query kernel, which
 //                                   takes such calls from 2048 keys on, even out: 2 x 5000 33 (few-query) / 37, 1 x 14000 87 / 89; but 3 x 5000 45 / 38, 8 x 2048 22.8 / 20.4
 //   more, half of the blocks masked twice as many and smaller workgroups than the fused kernel's even out better: 8 x 4096 56 (fused) / 41, 4 x 8192 107 / 69,
-//                                   1 x 32768 410 / 236, 16 x 2048 x 2048 30.7 / 27.8, 5 x 8192 115 / 99; then not: 20 x 1600 25.8 / 25.9, 12 x 3200 45.5 / 45.5, 7 x 8192 112 / 119
+//                                   1 x 32768 410 / 236, 16 x 2048 x 2048 30.7 / 27.8, 5 x 8192 115 / 99; then not: 20 x 1600 25.8 / 25.9, 12 x 3200 45.5 / 45.5, 7 x 8192 112 / 119.
+//                                   From 513 workgroups on the gain is spent the sooner the more keys lie in front of the queries, where all blocks are visible
+//                                   (fused -> this one, d = 128 / 64): 8 x 6124 x 6124 84.0 -> 82.9 / 68.9 -> 65.3, 8 x 5612 x 7015 101.6 -> 102.2 / 81.5 -> 81.3; beyond `keys`
+//                                   8 x 5612 x 8418 126 -> 127 / 99 -> 101, 8 x 6124 x 12248 195 -> 206 / 147 -> 161, 4 x 12268 x 24536 382 -> 394 / 287 -> 310
 //   more, all blocks visible        two waves of workgroups against one of the fused kernel's: 48 x 512 x 8192 107 (fused) / 111
 static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causal) {
     if (Nq <= 32 || ifa_query_groups(heads, Nq) <= 256) return false;
     const long wgs = static_cast<long>(heads) * ((Nq + 63) / 64);
     const bool uneven = causal && 2L * Nq >= Nk;
     if (wgs <= 256) return Nk >= (d == 128 ? 512 : 384) && !(uneven && Nk >= 2048 && (heads == 1 || wgs <= 192));
-    return uneven && Nk >= 2048 && wgs <= (heads <= 8 ? 768 : 512);
+    const long keys = 56L << 10;                                 // of all heads
+    return uneven && Nk >= 2048 && (wgs <= 512 || (heads <= 8 && wgs <= 768 && heads * static_cast<long>(Nk) <= keys));
 }
 
 // The packed, the two-group or the few-query kernel of intfa_attention_fewq.hip, for the dispatcher of the entry points in
