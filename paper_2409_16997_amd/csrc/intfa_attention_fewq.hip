@@ -895,7 +895,7 @@ constexpr int SPLIT_MAX_Q = 8;       // queries per head up to which the scores 
 constexpr int SPLIT_MAX_Q_RECOMPUTE = 32;   // ... and up to which the second pass recomputes them from K instead (one column tile)
 constexpr int SPLIT_NSTAGE_K = 4;    // pass 1: ring of K blocks, filled three ahead
 constexpr int SPLIT_NSTAGE_V = 3;    // pass 2: ring of V blocks, filled two ahead
-constexpr int SPLIT_NSTAGE_KV = 2;   // pass 2 with K: ring of K and V blocks, filled one ahead
+constexpr int SPLIT_LONG_RUN = 9;    // pass 2 with K, d = 64: blocks of a run from which the ring holds three blocks of K and V instead of two
 [[maybe_unused]] constexpr bool SPLIT_NT = true;      // staging copies carry the non-temporal hint: every byte is read once (measured +7 % at 537 MB of K and V)
 
 template <int D> struct SmemSplitK {
@@ -915,18 +915,20 @@ static_assert(offsetof(SmemSplitV<64>, v) % 4096 == 0 && (BC * 64) % 4096 == 0, 
 
 // Second pass for 9 .. 32 queries per head: the scores would be as many bytes as K and V, so they are not stored;
 // the pass streams K once more and recomputes line 9 (same MFMA chain, same scaling: the same numbers).  A key tile is one chain from
-// its scores to its share of O, so what a CU gets done is the wavefronts it holds: a ring of two blocks, filled one ahead, leaves
+// its scores to its share of O, so what a CU gets done is the wavefronts it holds: at d = 128 a ring of NS = 2 blocks, filled one ahead, leaves
 // room for two workgroups (64 KB of copies in flight either way; with a ring of three, one per CU, half of a call's 512 workgroups
-// waited for the other half).  Whole call, us, before / now: 32 heads x 16 queries x 8192 keys 32.1 / 27.6, 60 x 16 x 8192 59 / 49, 32 x 32 x 32768
-// 100 / 90, 8 x 16 x 16384 20.1 / 19.2, d = 64, 32 x 16 x 8192 18.5 / 17.7.
-template <int D> struct SmemSplitKV {
-    alignas(4096) int8_t k[SPLIT_NSTAGE_KV][BC * D];
-    alignas(4096) int8_t v[SPLIT_NSTAGE_KV][BC * D];
-    alignas(256) float sk[SPLIT_NSTAGE_KV][4][64];
-    alignas(1024) float tmin[SPLIT_NSTAGE_KV][4][256];           // per wavefront: the block's [query][tile] minima (512 B, + 512 unused)
+// waited for the other half).  Whole call, us, ring of three / two: 32 heads x 16 queries x 8192 keys 32.1 / 27.6, 60 x 16 x 8192 59 / 49, 32 x 32 x 32768
+// 100 / 90, 8 x 16 x 16384 20.1 / 19.2.  At d = 64 two workgroups share a CU with either ring.  The smaller one starts sooner, the larger one
+// has more in flight: runs of 4 blocks 24 x 9 x 16384 24.0 / 20.6, 32 x 16 x 8192 18.5 / 17.7, of 8 even (64 x 16 x 16384 45.3 / 45.4), of 13 24 x 9 x 65536 62.6 / 64.8, of
+// 25 48 x 16 x 65536 120 / 128.
+template <int D, int NS> struct SmemSplitKV {
+    alignas(4096) int8_t k[NS][BC * D];
+    alignas(4096) int8_t v[NS][BC * D];
+    alignas(256) float sk[NS][4][64];
+    alignas(1024) float tmin[NS][4][256];                       // per wavefront: the block's [query][tile] minima (512 B, + 512 unused)
     alignas(16) float pre[SPLIT_MAX_Q_RECOMPUTE];
 };
-static_assert(2 * sizeof(SmemSplitKV<128>) <= 160 * 1024, "two workgroups per CU");
+static_assert(2 * sizeof(SmemSplitKV<128, 2>) <= 160 * 1024 && 2 * sizeof(SmemSplitKV<64, 3>) <= 160 * 1024, "two workgroups per CU");
 
 // Layout of the workspace (fp32 words), shared by the host code and the kernels (MAXQ = 8 or 32, by Nq):
 //   scores  [heads, T_c, 4 tiles, Nq, 32]     a of line 9 (masked keys: +inf); Nq <= 8 only
@@ -1191,14 +1193,16 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_kernel(
 }
 
 // Second pass for 9 .. 32 queries per head (see SmemSplitKV): lines 9-13 per key tile with m known beforehand.
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, int NS>
 __global__ __launch_bounds__(THREADS, 2) void splitk_pv_recompute_kernel(
     const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V, const float *__restrict__ sQ,
     const float *__restrict__ sK, int Nq, int Nk, int cb, int nchunks, const float *__restrict__ tminG,
     const float *__restrict__ cminG, float *__restrict__ part_o, float *__restrict__ part_ml) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __shared__ SmemSplitKV<D> sm;
+    using Smem = SmemSplitKV<D, NS>;
+    __shared__ Smem sm;
     constexpr int KS = D / 32, DT = D / 32, MAXQ = SPLIT_MAX_Q_RECOMPUTE;
+    constexpr int PER_BLOCK = KS + DT + 2;                       // copy instructions per wavefront and block
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T_c = (Nk + BC - 1) / BC;
@@ -1218,7 +1222,7 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_recompute_kernel(
     const LaneOffsets<D> lo(lane, wave);
     // this wavefront's key tile of K_j and V_j, its 32 s_K, and the block's 128 tile minima (lanes 32-63 repeat 0-31)
     auto stage_block = [&](int jb) {
-        const int st = (jb - jb0) % SPLIT_NSTAGE_KV;
+        const int st = (jb - jb0) % NS;
         const bool real = jb < jb1;
         const Prefetch pf = {rK, rV, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE,
                              kbuf + st * BC * D, vbuf + st * BC * D, skbuf + (st * 4 + wave) * 256};
@@ -1230,6 +1234,7 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_recompute_kernel(
         lds_copy16(rT, tbuf + (st * 4 + wave) * 1024, 16 * r, real ? jb * (MAXQ * 4 * 4) : NOWHERE);
     };
     stage_block(jb0);
+    if (NS > 2) stage_block(jb0 + 1);
 
     const int8_t *qptr = Q + (static_cast<long>(head) * Nq + rq) * D + 16 * g;
     v4i qf[KS];
@@ -1263,9 +1268,9 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_recompute_kernel(
     }
 
     for (int jb = jb0; jb < jb1; ++jb) {
-        const int st = (jb - jb0) % SPLIT_NSTAGE_KV, j0 = jb * BC;
-        wait_vmcnt<0>();                                         // block jb has landed
-        stage_block(jb + 1);                                     // into the stage of block jb - 1, which this wavefront has left
+        const int st = (jb - jb0) % NS, j0 = jb * BC;
+        wait_vmcnt<(NS - 2) * PER_BLOCK>();                      // block jb has landed (NS = 3: block jb + 1 may be in flight)
+        stage_block(jb + NS - 1);                                // into the stage of block jb - 1, which this wavefront has left
         const lds_ptr ks = kbuf + st * BC * D, vs = vbuf + st * BC * D;
         // line 9 for key tile `wave`, as in the first pass
         v4i kop[KS];
@@ -1318,7 +1323,7 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_recompute_kernel(
     wait_all_memory();
     // The four wavefronts hold partials of the same run at the same m: their sum is the workgroup's partial.  The K
     // and V rings (contiguous) are free once every wavefront has left the loop; [wavefront][query][d] floats go through them.
-    static_assert(offsetof(SmemSplitKV<D>, v) == sizeof(SmemSplitKV<D>::k) && 4 * MAXQ * D * 4 <= 2 * SPLIT_NSTAGE_KV * BC * D, "exchange area");
+    static_assert(offsetof(Smem, v) == sizeof(Smem::k) && 4 * MAXQ * D * 4 <= 2 * NS * BC * D, "exchange area");
     const float lt = l + swap32(l);
     __syncthreads();
     float *xo = reinterpret_cast<float *>(&sm.k[0][0]);
@@ -1438,8 +1443,14 @@ int launch_splitk(const int8_t *Q, const int8_t *K, const int8_t *V, const float
     } else {
         hipLaunchKernelGGL((splitk_scores_kernel<D, CAUSAL, SPLIT_MAX_Q_RECOMPUTE, false>), grid, dim3(THREADS), 0, st, Q, K, sK, Nq, Nk, p.cb,
                            p.nchunks, scores, tmin, cmin);
-        hipLaunchKernelGGL((splitk_pv_recompute_kernel<D, CAUSAL>), grid, dim3(THREADS), 0, st, Q, K, V, sQ, sK, Nq, Nk, p.cb, p.nchunks, tmin,
-                           cmin, part_o, part_ml);
+        auto launch = [&](auto ns) {
+            hipLaunchKernelGGL((splitk_pv_recompute_kernel<D, CAUSAL, decltype(ns)::value>), grid, dim3(THREADS), 0, st, Q, K, V, sQ, sK, Nq, Nk, p.cb,
+                               p.nchunks, tmin, cmin, part_o, part_ml);
+        };
+        if constexpr (D == 64) {
+            if (p.cb >= SPLIT_LONG_RUN) launch(std::integral_constant<int, 3>{});
+            else launch(std::integral_constant<int, 2>{});
+        } else launch(std::integral_constant<int, 2>{});
     }
     hipLaunchKernelGGL((splitk_combine_kernel<D, OutT>), dim3(static_cast<unsigned>(heads * Nq)), dim3(THREADS), 0, st, part_o, part_ml, sV,
                        Nq, p.parts, static_cast<OutT *>(O));
