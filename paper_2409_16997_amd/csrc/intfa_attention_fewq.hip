@@ -1467,23 +1467,6 @@ int launch_splitk_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const
     }
 }
 
-// Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  The
-// few-query kernel walks 1000 keys of every head in 4.4 us (d = 64: 3.5) however many heads there are, until the chip is full; the split
-// passes stream K, V and the scores (or K twice) of all heads at 5 - 6 TB/s, in three launches that take 15 us together on short
-// sequences.  Without / with the split, us, after the same call and (beyond 4096 keys) after a read of 512 MB elsewhere, d = 128 unless
-// stated:
-//   up to 2048 keys  8 heads x 1 x 2048 11.4 / 17.0, 64 x 8 x 2048 12.7 / 18.2, 128 x 1 x 2048 13.9 / 27.0; d = 64, 8 x 1 x 2048 10.3 / 17.5
-//   up to 4096 keys  half as many heads do as further on: 57 x 1 x 4096 22 / 28, 49 x 8 21 / 28, 33 x 16 20 / 28; 32 x 1 20 / 18; d = 64, 81 x 1 18 / 19.
-//                    (After a copy of 512 MB, which leaves the caches to write back, 64 x 4 x 4096 36 / 32.)
-//   many heads       1 query: 112 x 16384 90, 92 / 90, 99, 128 x 16384 93, 95 / 97, 103; 5: 96 x 16384 87, 90 / 91, 95, 96 x 32768 171, 174 / 174, 179; 9: 64 x 16384
-//                    82, 85 / 83, 87, 72 x 32768 164, 166 / 165, 168; d = 64, 160 x 1 x 16384 64, 66 / 75, 82, 112 x 5 x 16384 60, 63 / 67, 71, 96 x 16 60, 64 / 124, 125
-//   below the line   96 x 1 x 16384 82 / 76, 80 x 5 x 16384 85, 87 / 80, 83, 64 x 9 x 32768 162, 164 / 146, 150; d = 64, 128 x 1 x 16384 65, 65 / 58, 65,
-//                    96 x 5 x 32768 117, 121 / 106, 110, 80 x 9 x 16384 60, 62 / 54, 59
-inline bool narrow_beats_split(int heads, int Nq, int Nk, int d) {
-    const int enough = Nq > SPLIT_MAX_Q ? (d == 128 ? (Nk <= 16384 ? 64 : 72) : 96) : Nq > 4 ? (d == 128 ? 96 : 112) : (d == 128 ? 112 : 160);
-    return heads >= enough || Nk <= 2048 || (Nk <= 4096 && heads > enough / 2);
-}
-
 // argument checks of the key-split path that do not concern the workspace
 int splitk_args(const signed char *Q_i8, const signed char *K_i8, const signed char *V_i8, const float *s_Q, const float *s_K,
                 const float *s_V, int B, int H, int Nq, int Nk, int d, int causal, const void *O, int o_dtype) {
@@ -1511,7 +1494,7 @@ int splitk_dispatch(const signed char *Q_i8, const signed char *K_i8, const sign
     const int8_t *K = reinterpret_cast<const int8_t *>(K_i8);
     const int8_t *V = reinterpret_cast<const int8_t *>(V_i8);
     const int hd = B * H;
-    if (narrow_beats_split(hd, Nq, Nk, d)) return ifa_launch_fwd(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, d, causal, O, o_dtype, st);
+    if (ifa_unsplit_queries(hd, Nq, Nk, d)) return ifa_launch_fwd(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, d, causal, O, o_dtype, st);
     if (d == 128)
         return causal ? launch_splitk_dtype<128, true>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, ws, st)
                       : launch_splitk_dtype<128, false>(Q, K, V, s_Q, s_K, s_V, hd, Nq, Nk, O, o_dtype, ws, st);

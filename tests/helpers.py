@@ -50,6 +50,15 @@ def route(heads, Nq, Nk, d, half=False):
     return "fused"
 
 
+def unsplit(heads, Nq, Nk, d):
+    """Whether a call of the key-split entry points runs the kernel of the plain call.  tests/test_routes.py holds this to the library's own rule."""
+    if Nq <= 8:
+        E, S, H = (2048, 1536, 134 - 5 * Nq) if d == 128 else (1024, 1536, 146 - 7 * Nq)
+    else:
+        E, S, H = 1024, 2304, (104 if d == 128 else 122) - Nq
+    return Nk <= 2048 or heads * (Nk + E) >= H * (Nk - S)
+
+
 def copies_for_the_fused_kernel(heads, Nq, Nk, d, half=False):
     """How many copies of these heads make a call that runs the fused kernel; None if no number does."""
     copies = -(-513 // (heads * -(-Nq // 32)))

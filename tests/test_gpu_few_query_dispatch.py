@@ -9,7 +9,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle
-from helpers import route
+from helpers import route, unsplit
 
 pytestmark = pytest.mark.gpu
 
@@ -79,16 +79,18 @@ def test_half_int8_kernels_agree(heads, N, d, causal):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("d,Nq,heads", [(128, 1, 112), (128, 8, 96), (128, 32, 64), (64, 4, 160), (64, 5, 112), (64, 9, 96)])
-def test_key_split_entry_point_on_both_sides_of_its_rule(d, Nq, heads, causal):
-    # `heads` is the number from which the entry point runs the few-query kernel at any length (d = 128 and more than 8 queries: up
-    # to 16384 keys, 72 heads beyond): the same result, bit for bit.
-    # Below it, and with more than 2048 keys, the split passes run, which add up O in another order (a few ulp of the
+@pytest.mark.parametrize("d,Nq", [(128, 1), (128, 8), (128, 9), (128, 32), (64, 1), (64, 4), (64, 8), (64, 9), (64, 32)])
+def test_key_split_entry_point_on_both_sides_of_its_rule(d, Nq, causal):
+    # With many heads, and up to 2048 keys, the entry point runs the kernel of the plain call: the same result, bit for bit.
+    # Otherwise the split passes run, which add up O in another order (a few ulp of the
     # largest value; in the last case the last run of key blocks is masked for the early queries).
     import paper_2409_16997_amd as ifa
-    for H, Nk, same in ((heads, 4099, True), (heads - 1, 4097, False), (heads - 1, 4096, True), (heads // 2, 4096, False),
-                        (heads // 2 + 1, 2049, True), (3, 2048, True), (3, 2049, False), (2, 4098, False)) + (
-            ((64, 16384, True), (64, 16385, False), (71, 16500, False), (72, 16385, True)) if (d, Nq) == (128, 32) else ()):
+    cases = [(3, 2048), (3, 2049), (2, 4098)]
+    for Nk in (2305, 4096, 4099, 8193) + ((16385,) if Nq in (9, 32) else ()):
+        many = next(H for H in range(1, 200) if unsplit(H, Nq, Nk, d))
+        cases += [(many, Nk), (max(many - 1, 1), Nk)]
+    seen = set()
+    for H, Nk in cases:
         q8, k8, v8, sq, sk = problem(H, Nk, d, H + Nk)
         q8, sq = q8[:, :, Nk - Nq:].contiguous(), sq[:, :, Nk - Nq:].contiguous()
         sv = 0.005 + 0.02 * torch.rand((1, H), device="cuda", generator=torch.Generator(device="cuda").manual_seed(Nk))
@@ -96,11 +98,14 @@ def test_key_split_entry_point_on_both_sides_of_its_rule(d, Nq, heads, causal):
         need = ifa.splitk_workspace_bytes(1, H, Nq, Nk, d)
         ws = torch.full((need // 4,), float("nan"), device="cuda").view(torch.uint8)
         out = ifa.int_flash_attn_fwd_splitk(q8, k8, v8, sq, sk, sv, causal=causal, out_dtype=torch.float32, workspace=ws)
+        same = unsplit(H, Nq, Nk, d)
+        seen.add((Nk > 2048, same))
+        assert bool(torch.isnan(ws.view(torch.float32)).all()) == same, (H, Nk)          # the passes ran, or not
         if same:
             assert torch.equal(out, ref), (H, Nk)
         else:
-            assert not bool(torch.isnan(ws.view(torch.float32)).all()), (H, Nk)      # the passes ran
             assert float((out - ref).abs().max()) <= 4e-6 * float(ref.abs().max()), (H, Nk)
+    assert seen == {(False, True), (True, True), (True, False)}
 
 
 @pytest.mark.parametrize("d", [64, 128])
