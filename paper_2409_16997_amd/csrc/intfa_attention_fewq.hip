@@ -1399,15 +1399,15 @@ int launch_packed(const int8_t *Q, const int8_t *K, const int8_t *V, const float
 }
 
 template <int D, bool CAUSAL, bool VB, typename OutT>
-int launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
+int launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
-    if (ifa_pair_queries(heads, Nq, Nk, D, CAUSAL)) {
+    if (kernel == IFA_KERNEL_PAIR) {
         const int T_r = (Nq + PAIR_BR - 1) / PAIR_BR;
         hipLaunchKernelGGL((int_flash_attn_fwd_pair_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(static_cast<long>(heads) * T_r)),
                            dim3(NARROW_THREADS), 0, st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, head_group_for(CAUSAL, 2L * Nk * D, T_r), static_cast<OutT *>(O));
         return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
     }
-    if (ifa_packed_queries(heads, Nq, Nk, D)) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
+    if (kernel == IFA_KERNEL_PACKED) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
     // K and V with the non-temporal hint where one workgroup reads each byte, and reads it once, and there are more of them than the
     // caches could keep for the next call; such a call runs with DS = 1.  (With the hint and DS = 2 the second workgroup of a pair may
@@ -1505,15 +1505,15 @@ int splitk_dispatch(const signed char *Q_i8, const signed char *K_i8, const sign
 }  // namespace
 
 // The narrow kernel for the dispatcher of the fused kernel's entry points (arguments already validated there).
-int ifa_launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads,
+int ifa_launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads,
                       int Nq, int Nk, int d, int causal, int vblock, void *O, int o_dtype, hipStream_t st) {
     auto by_dtype = [&](auto D_, auto C_, auto VB_) {
         constexpr int D = decltype(D_)::value;
         constexpr bool C = decltype(C_)::value, VB = decltype(VB_)::value;
         switch (o_dtype) {
-        case IFA_F32: return launch_narrow<D, C, VB, float>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
-        case IFA_F16: return launch_narrow<D, C, VB, __half>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
-        default: return launch_narrow<D, C, VB, __hip_bfloat16>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
+        case IFA_F32: return launch_narrow<D, C, VB, float>(kernel, Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
+        case IFA_F16: return launch_narrow<D, C, VB, __half>(kernel, Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
+        default: return launch_narrow<D, C, VB, __hip_bfloat16>(kernel, Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
         }
     };
     using I64 = std::integral_constant<int, 64>;

@@ -89,9 +89,16 @@ static inline bool ifa_unsplit_queries(int heads, int Nq, int Nk, int d) {
     return Nk <= 2048 || heads * (Nk + E) >= H * (Nk - S);
 }
 
-// The packed, the two-group or the few-query kernel of intfa_attention_fewq.hip, for the dispatcher of the entry points in
+// The kernel of an INT8 call
+enum IfaKernel { IFA_KERNEL_FUSED, IFA_KERNEL_PAIR, IFA_KERNEL_PACKED, IFA_KERNEL_FEW };
+static inline IfaKernel ifa_fwd_kernel(int heads, int Nq, int Nk, int d, bool causal) {
+    return ifa_pair_queries(heads, Nq, Nk, d, causal) ? IFA_KERNEL_PAIR : ifa_packed_queries(heads, Nq, Nk, d) ? IFA_KERNEL_PACKED :
+           ifa_few_queries(heads, Nq, Nk, d, false) ? IFA_KERNEL_FEW : IFA_KERNEL_FUSED;
+}
+
+// One of the kernels of intfa_attention_fewq.hip (not IFA_KERNEL_FUSED), for the dispatcher of the entry points in
 // intfa_attention.hip; arguments already validated.
-int ifa_launch_narrow(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads,
+int ifa_launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads,
                       int Nq, int Nk, int d, int causal, int vblock, void *O, int o_dtype, hipStream_t st);
 
 // That dispatcher, one V scale per head: the kernel int_flash_attn_fwd_rect runs; arguments already validated.

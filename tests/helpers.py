@@ -36,11 +36,20 @@ def random_int8_problem(rng, heads, N, d, score_sigma=1.0):
     return Qq, Kq, Vq, sQ, sK, sV
 
 
-def route(heads, Nq, Nk, d, half=False):
-    """Which kernel a plain attention call runs: "fused", "few" (twelve wavefronts per 32 queries, half-INT8 eight) or "packed".
-    tests/test_routes.py holds this to the library's own rule."""
+def route(heads, Nq, Nk, d, causal=None, half=False):
+    """Which kernel a plain attention call runs: "fused", "few" (twelve wavefronts per 32 queries, half-INT8 eight), "packed" or "pair" (two groups of 32
+    queries).  `causal` decides nothing for half-INT8.  tests/test_routes.py holds this to the library's own rule."""
     groups = heads * -(-Nq // 32)
     if not half:
+        assert causal is not None
+        if Nq > 32 and groups > 256:
+            wgs, uneven = heads * -(-Nq // 64), causal and 2 * Nq >= Nk
+            if wgs <= 256:
+                pair = Nk >= (512 if d == 128 else 384) and not (uneven and Nk >= 2048 and (heads == 1 or wgs <= 192))
+            else:
+                pair = uneven and Nk >= 2048 and (wgs <= 512 or heads <= 8 and wgs <= 768 and heads * Nk <= 56 << 10)
+            if pair:
+                return "pair"
         if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (1280 if groups <= 512 else 1024) if Nq <= 32 else
                                                         Nq <= 64 and groups <= 512 and 128 <= Nk < 2048):
             return "packed"
@@ -59,10 +68,14 @@ def unsplit(heads, Nq, Nk, d):
     return Nk <= 2048 or heads * (Nk + E) >= H * (Nk - S)
 
 
-def copies_for_the_fused_kernel(heads, Nq, Nk, d, half=False):
-    """How many copies of these heads make a call that runs the fused kernel; None if no number does."""
-    copies = -(-513 // (heads * -(-Nq // 32)))
-    return copies if route(heads * copies, Nq, Nk, d, half) == "fused" else None
+def copies_for(kernel, heads, Nq, Nk, d, causal=None, half=False):
+    """How many copies of these heads make a call that runs `kernel`, "fused" or "pair"; None if no number does."""
+    first = -(-(513 if kernel == "fused" else 257) // (heads * -(-Nq // 32)))
+    return next((c for c in range(first, 4 * first + 1) if route(heads * c, Nq, Nk, d, causal, half) == kernel), None)
+
+
+def copies_for_the_fused_kernel(heads, Nq, Nk, d, causal=None, half=False):
+    return copies_for("fused", heads, Nq, Nk, d, causal, half)
 
 
 def many(copies, *arrays):

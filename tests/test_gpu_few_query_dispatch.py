@@ -32,7 +32,7 @@ def problem(heads, N, d, seed):
 @pytest.mark.parametrize("heads,N", SHAPES)
 def test_both_kernels_give_the_same_rows(heads, N, d, causal, vblock):
     import paper_2409_16997_amd as ifa
-    assert route(heads, N, N, d) == "fused" and route(5, N, N, d) == ("packed" if N <= 128 else "few")
+    assert route(heads, N, N, d, causal) == "fused" and route(5, N, N, d, causal) == ("packed" if N <= 128 else "few")
     q8, k8, v8, sq, sk = problem(heads, N, d, heads + N)
     Bc = ifa.block_cols(d, causal)
     g = torch.Generator(device="cuda").manual_seed(N)
@@ -163,7 +163,7 @@ def test_few_queries_of_more_heads_than_cus(d, Nk, causal, vblock):
     sv = 0.005 + 0.02 * torch.rand((1, heads) + ((-(-Nk // Bc),) if vblock else ()), generator=g, device="cuda")
     call = lambda q, a, n: ifa.int_flash_attn_fwd(q[:, :n].contiguous(), k8[:, :n], v8[:, :n], a[:, :n].contiguous(), sk[:, :n], sv[:, :n],
                                                   causal=causal, out_dtype=torch.float32)
-    assert route(heads, N, Nk, d) == ("packed" if d == 64 and N <= 64 else "fused")
+    assert route(heads, N, Nk, d, causal) == ("packed" if d == 64 and N <= 64 else "fused")
     full = call(q8, sq, heads)
     for n, nq in ((heads, 1), (heads, 8), (heads, 32), (257, 32), (257, 31), (256, 32), (256, 33), (140, 64), (140, 40), (7, 1), (3, 33), (2, 128)):
         if nq > N:
@@ -199,7 +199,7 @@ def test_few_queries_of_more_heads_than_cus_half_int8(d, Nk, causal):
 def test_long_caches_are_read_past_the_caches(variant, heads, Nk, d):
     import paper_2409_16997_amd as ifa
     half = variant == "half"
-    assert heads * Nk * d * (3 if half else 2) > 64 << 20 and route(heads, 1, Nk, d, half) == "few"
+    assert heads * Nk * d * (3 if half else 2) > 64 << 20 and route(heads, 1, Nk, d, True, half) == "few"
     q8, k8, v8, sq, sk = problem(heads, Nk, d, heads)
     q8, sq = q8[:, :, 1:2].contiguous(), sq[:, :, 1:2].contiguous()
     sv = 0.005 + 0.02 * torch.rand((1, heads), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))

@@ -1,16 +1,12 @@
 """The two-group kernel (two groups of 32 queries of a head per workgroup): the rows of the other kernels, bit for bit, and the
 calls its rule takes."""
-import os
-import subprocess
-
 import pytest
 
 torch = pytest.importorskip("torch")
 
 import oracle
+from helpers import route
 from test_gpu_few_query_dispatch import problem
-
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # (heads, Nq, Nk): an odd number of key blocks and a ragged one, a last workgroup without its second group (Nq = 33, 65, 96: all but or half
 # empty), more than one query per key block of the mask, and (the last two, under the mask only) more workgroups than CUs
@@ -18,27 +14,7 @@ SHAPES = [(129, 64, 512), (130, 33, 513), (90, 65, 640), (65, 96, 1023), (37, 20
 
 
 def taken(heads, Nq, Nk, d, causal):
-    if Nq <= 32 or heads * -(-Nq // 32) <= 256:
-        return False
-    wgs, uneven = heads * -(-Nq // 64), causal and 2 * Nq >= Nk
-    if wgs <= 256:
-        return Nk >= (512 if d == 128 else 384) and not (uneven and Nk >= 2048 and (heads == 1 or wgs <= 192))
-    return uneven and Nk >= 2048 and (wgs <= 512 or heads <= 8 and wgs <= 768 and heads * Nk <= 56 << 10)
-
-
-def test_rule_is_the_librarys(tmp_path):
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    if not os.path.exists(hipcc):
-        pytest.skip("no hipcc")
-    src, exe = tmp_path / "pair.hip", tmp_path / "pair"
-    src.write_text('#include "intfa_internal.h"\n#include <cstdio>\nint main() { int h, q, k, d, c; '
-                   'while (scanf("%d %d %d %d %d", &h, &q, &k, &d, &c) == 5) puts(ifa_pair_queries(h, q, k, d, c) ? "1" : "0"); }\n')
-    subprocess.run([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
-                    os.path.join(ROOT, "paper_2409_16997_amd", "csrc"), str(src), "-o", str(exe)], check=True)
-    cases = [(h, q, k, d, c) for h in (1, 2, 8, 9, 64, 65, 128, 129, 256, 257, 5 << 20) for q in (1, 32, 33, 64, 65, 2000, 4100, 6000, 8192, 16384, 24000, 32768, 48000)
-             for k in (64, 383, 384, 511, 512, 2047, 2048, 4000, 4001, 7168, 7169, 16384, 28672, 28673, 32768, 57344, 57345) for d in (64, 128) for c in (0, 1)]
-    out = subprocess.run([str(exe)], input="".join("%d %d %d %d %d\n" % c for c in cases), stdout=subprocess.PIPE, text=True, check=True).stdout.split()
-    assert out == ["01"[taken(*c)] for c in cases]
+    return route(heads, Nq, Nk, d, causal) == "pair"
 
 
 @pytest.mark.gpu

@@ -237,7 +237,7 @@ def test_int32_accumulators_of_the_production_kernel_bit_exact(ifa, N, d, causal
         rows = np.arange(N) if not causal else np.arange(j * Bc, N)                     # query blocks that visit block j
         assert np.array_equal(PV[j][rows], PV_ref[j][rows]), f"P V of key block {j}"
     # and the output of the same launch is the production output, the fused kernel's and that of the kernel that takes one head
-    for copies in (1, copies_for_the_fused_kernel(1, N, N, d)):
+    for copies in (1, copies_for_the_fused_kernel(1, N, N, d, causal)):
         O_prod = run_gpu(ifa, *many(copies, Q[None], K[None], V[None], sQ[None], sK[None], sV), 1, copies, causal)
         assert np.array_equal(O, first_copy(O_prod, copies).reshape(N, d)), copies
 
@@ -317,7 +317,7 @@ def test_shapes_masks_distributions(ifa, B, H, N, d, causal, dist, fused):
     # of the heads as the fused kernel wants
     w = workloads.custom("t", B, H, N, d, causal, dist=dist, seed=B * 1000 + N + d)
     x = quantized_inputs(w, scaled=True)
-    copies = copies_for_the_fused_kernel(B * H, N, N, d) if fused else 1
+    copies = copies_for_the_fused_kernel(B * H, N, N, d, causal) if fused else 1
     O = first_copy(run_gpu(ifa, *many(copies, x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"]), copies * B, H, causal), copies)
     check_against_oracle(ifa, O.reshape(-1, d), x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], causal,
                          label=f"{B}x{H}x{N}x{d} causal={causal} {dist}")
@@ -357,7 +357,7 @@ def test_head_group_sizes_sampled_rows(ifa, B, H, N, d, causal):
 @pytest.mark.parametrize("fused", [False, True])
 def test_ragged_sequence_lengths(ifa, N, d, causal, fused):
     # N not a multiple of the 128-key block: keys >= N are masked in the last block, rows >= N are not stored
-    copies = copies_for_the_fused_kernel(3, N, N, d) if fused else 1
+    copies = copies_for_the_fused_kernel(3, N, N, d, causal) if fused else 1
     if copies is None:
         return                                               # at most 64 queries at d = 64: never the fused kernel's
     w = workloads.custom("t", 1, 3, N, d, causal, dist="normal", seed=N + d)
@@ -392,7 +392,7 @@ def test_rectangular_problems(ifa, Nq, Nk, d, causal, fused):
         rc = ifa.lib().int_flash_attn_fwd_rect(p(z8), p(z8), p(z8), p(zf), p(zf), p(zf), 1, 1, Nq, Nk, d, 1, p(O), 1, None)
         assert rc == -4
         return
-    copies = copies_for_the_fused_kernel(3, Nq, Nk, d) if fused else 1
+    copies = copies_for_the_fused_kernel(3, Nq, Nk, d, causal) if fused else 1
     if copies is None:
         return                                               # up to 32 queries: the fused kernel has short keys at d = 128 only
     H = 3 * copies
@@ -417,7 +417,7 @@ def test_rectangular_problems(ifa, Nq, Nk, d, causal, fused):
 def test_ragged_lengths_with_two_byte_outputs(ifa, N, d, causal, dtype, fused):
     # 2-byte outputs (the fused kernel's leave through its staged row-wise store): rows past N must not be written (canaries on
     # both sides of O) and the values must be the fp32 result rounded once
-    copies = copies_for_the_fused_kernel(3, N, N, d) if fused else 1
+    copies = copies_for_the_fused_kernel(3, N, N, d, causal) if fused else 1
     heads = 3 * copies
     w = workloads.custom("t", 1, 3, N, d, causal, dist="normal", seed=17 * N + d)
     x = dict(zip(("Qq", "Kq", "Vq", "sQ", "sK", "sV"), many(copies, *[quantized_inputs(w, scaled=True)[k] for k in ("Qq", "Kq", "Vq", "sQ", "sK", "sV")])))
@@ -456,7 +456,7 @@ def test_seeded_random_shapes(ifa, H, Nq, Nk, d, causal):
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, max(Nq, Nk), d, score_sigma=float(rng.uniform(0.5, 6.0)))
     Qq, sQ = np.ascontiguousarray(Qq[:, :Nq]), np.ascontiguousarray(sQ[:, :Nq])
     Kq, Vq, sK = np.ascontiguousarray(Kq[:, :Nk]), np.ascontiguousarray(Vq[:, :Nk]), np.ascontiguousarray(sK[:, :Nk])
-    for copies in (1, copies_for_the_fused_kernel(H, Nq, Nk, d)):
+    for copies in (1, copies_for_the_fused_kernel(H, Nq, Nk, d, causal)):
         if copies is None:
             continue
         O = ifa.int_flash_attn_fwd(*[dev(t[None]) for t in many(copies, Qq, Kq, Vq, sQ, sK, sV)], causal=causal, out_dtype=torch.float32)
@@ -475,7 +475,7 @@ def test_rectangular_rows_equal_the_square_kernel_rows(ifa):
     # the rectangular side) and more (the fused kernel on both)
     for H, kernel in ((18, "few"), (80, "fused")):
         N, Nq, d = 1024, 200, 128
-        assert route(H, N, N, d) == "fused" and route(H, Nq, N, d) == kernel
+        assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == kernel for c in (False, True))
         _rectangular_rows(ifa, H, N, Nq, d)
 
 
@@ -499,7 +499,7 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
     # block over the wavefronts of a workgroup; it performs the arithmetic of the square kernel on the same operands, so
     # its rows are the last Nq rows of the square problem bit for bit, with and without the mask, on a ragged length.
     H, N = 15, 1231
-    assert route(H, N, N, d) == "fused" and route(H, Nq, N, d) == "few"
+    assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == "few" for c in (False, True))
     rng = np.random.default_rng(Nq * 131 + d)
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, N, d, score_sigma=2.0)
     args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sV[None]))
@@ -516,7 +516,7 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
 def test_few_query_calls_with_blockwise_v_scales_equal_the_square_kernel_rows(ifa, Nq, d):
     # the same with one V scale per key block (the running output is carried in units of the current block's scale)
     H, N = 15, 1231
-    assert route(H, N, N, d) == "fused" and route(H, Nq, N, d) == "few"
+    assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == "few" for c in (False, True))
     rng = np.random.default_rng(Nq * 17 + d)
     Qq, Kq, Vq, sQ, sK, _ = random_int8_problem(rng, H, N, d, score_sigma=2.0)
     sVb = rng.uniform(0.005, 0.05, (H, -(-N // ifa.block_cols(d, True)))).astype(np.float32)
@@ -609,7 +609,7 @@ def test_random_int8_grid_inputs_wide_scores(ifa, causal):
     rng = np.random.default_rng(5)
     for sigma in (0.3, 2.0, 12.0):
         Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, 8, 256, 128, score_sigma=sigma)
-        for copies in (1, copies_for_the_fused_kernel(8, 256, 256, 128)):
+        for copies in (1, copies_for_the_fused_kernel(8, 256, 256, 128, causal)):
             O = first_copy(run_gpu(ifa, *many(copies, Qq, Kq, Vq, sQ, sK, sV), 2 * copies, 4, causal), copies)
             check_against_oracle(ifa, O.reshape(-1, 128), Qq, Kq, Vq, sQ, sK, sV, causal, label=f"int8 sigma={sigma} copies={copies}")
 
@@ -635,7 +635,7 @@ def test_accumulator_extremes_through_the_fused_kernel(ifa, d, causal, fused):
     sQ = np.full((heads, N), np.sqrt(span), np.float32) * rng.uniform(0.9, 1.1, (heads, N)).astype(np.float32)
     sK = np.full((heads, N), np.sqrt(span), np.float32) * rng.uniform(0.9, 1.1, (heads, N)).astype(np.float32)
     sV = np.array([0.01, 0.02], np.float32)
-    copies = copies_for_the_fused_kernel(heads, N, N, d) if fused else 1
+    copies = copies_for_the_fused_kernel(heads, N, N, d, causal) if fused else 1
     O = first_copy(run_gpu(ifa, *many(copies, Qq, Kq, Vq, sQ, sK, sV), copies, heads, causal), copies).reshape(-1, d)
     check_against_oracle(ifa, O, Qq, Kq, Vq, sQ, sK, sV, causal, label=f"extremes d={d} causal={causal} fused={fused}")
     flat = O.reshape(heads, N, d)[:, 130:140]
@@ -659,7 +659,7 @@ def test_very_long_ragged_sequences_sampled_rows(ifa, H, N, d, causal):
 def test_degenerate_inputs(ifa, fused):
     rng = np.random.default_rng(6)
     N, d = 256, 128
-    copies = copies_for_the_fused_kernel(1, N, N, d) if fused else 1
+    copies = copies_for_the_fused_kernel(1, N, N, d, causal=True) if fused else 1      # (so few keys: the mask decides nothing)
 
     def one_head(Qq, Kq, Vq, sQ, sK, sV, causal):
         return first_copy(run_gpu(ifa, *many(copies, Qq, Kq, Vq, sQ, sK, sV), 1, copies, causal), copies).reshape(N, d)
@@ -693,7 +693,7 @@ def test_degenerate_inputs(ifa, fused):
 
 @pytest.mark.parametrize("H", [8, 40])
 def test_output_dtypes_and_determinism(ifa, H):
-    assert route(H, 512, 512, 128) == ("few" if H == 8 else "fused")
+    assert route(H, 512, 512, 128, True) == ("few" if H == 8 else "fused")
     w = workloads.custom("t", 1, H, 512, 128, True, seed=77)
     x = quantized_inputs(w, scaled=True)
     args = (x["Qq"], x["Kq"], x["Vq"], x["sQ"], x["sK"], x["sV"], 1, H, True)
@@ -743,7 +743,7 @@ def test_attention_with_blockwise_v_scales(ifa, B, H, N, d, dist, causal, fused)
     Bc = ifa.block_cols(d, causal)
     Vq, sVb = oracle.quantize_blockwise(x["V"], Bc)           # oracle-side inputs, as everywhere
     sh = (B, H, N, d)
-    copies = copies_for_the_fused_kernel(B * H, N, N, d) if fused else 1
+    copies = copies_for_the_fused_kernel(B * H, N, N, d, causal) if fused else 1
     O = ifa.int_flash_attn_fwd(*[dev(t[None]) for t in many(copies, x["Qq"], x["Kq"], Vq, x["sQ"], x["sK"], sVb)], causal=causal,
                                out_dtype=torch.float32)
     torch.cuda.synchronize()
@@ -760,7 +760,7 @@ def test_attention_with_blockwise_v_scales(ifa, B, H, N, d, dist, causal, fused)
 def test_rectangular_problems_with_blockwise_v_scales(ifa, Nq, Nk, d, causal, fused):
     # N_q != N_k together with one V scale per key block: chunked prefill / decode against per-block-quantized V
     B, H = 1, 3
-    copies = copies_for_the_fused_kernel(H, Nq, Nk, d) if fused else 1
+    copies = copies_for_the_fused_kernel(H, Nq, Nk, d, causal) if fused else 1
     if copies is None:
         return
     w = workloads.custom("t", B, H, Nk, d, causal, dist="student_t3", seed=Nq + Nk + d)

@@ -1,7 +1,7 @@
 """Seeded random shapes through every attention entry point, every row compared with the oracle at the strict bar
 (and, in the second test, through every quantizer entry point, bit for bit):
 the fused kernel (square and N_q != N_k), the few-query kernel, per-block V scales, the key-split path and the
-half-INT8 variant; d in {64, 128}, 1-8 heads (or copies of them, as many as the fused kernel wants), ragged N_q, N_k up to 1500 (key-split
+half-INT8 variant; d in {64, 128}, 1-8 heads (or copies of them, as many as the fused or the two-group kernel wants), ragged N_q, N_k up to 1500 (key-split
 calls up to 6000), with and without the causal mask, flat to peaked score distributions.  The committed parity cases fix their
 shapes by hand; this one draws them."""
 import numpy as np
@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import oracle
-from helpers import copies_for_the_fused_kernel, first_copy, many, route, unsplit
+from helpers import copies_for, first_copy, many, route, unsplit
 
 pytestmark = pytest.mark.gpu
 
@@ -63,8 +63,11 @@ def test_random_shapes_meet_the_strict_bar_on_every_row(ifa, seed):
     for case in range(60):
         desc, (Qq, Kq, Vq, sQ, sK, sV), Bc = _draw(rng, ifa)
         d, causal, half, split = desc["d"], desc["causal"], desc["kind"] == "half", desc["kind"] == "splitk"
-        copies = (copies_for_the_fused_kernel(desc["H"], desc["Nq"], desc["Nk"], d, half) or 1) if not split and rng.integers(0, 2) else 1
-        desc["kernel"] = "split" if split else route(copies * desc["H"], desc["Nq"], desc["Nk"], d, half)
+        shape = (desc["H"], desc["Nq"], desc["Nk"], d, causal, half)
+        copies = 1
+        if not split and rng.integers(0, 2):
+            copies = copies_for(str(rng.choice(["fused", "pair"])), *shape) or copies_for("fused", *shape) or 1
+        desc["kernel"] = "split" if split else route(copies * desc["H"], *shape[1:])
         reached[half, desc["kernel"]] = reached.get((half, desc["kernel"]), 0) + 1
         if half:
             Vh = (Vq.astype(np.float32) * 0.01).astype(np.float16)
@@ -84,7 +87,7 @@ def test_random_shapes_meet_the_strict_bar_on_every_row(ifa, seed):
         assert np.isfinite(got).all(), (seed, case, desc)
         res = oracle.compare_up_to_ties(got, Qq, Kq, Vq, sQ, sK, sV, causal, Bc)
         assert np.all(res["err"] <= 1e-3 * res["scale"]), (seed, case, desc, float((res["err"] / res["scale"]).max()))
-    assert set(reached) >= {(False, "fused"), (False, "few"), (False, "packed"), (False, "split"), (True, "fused"), (True, "few")}, reached
+    assert set(reached) >= {(False, "fused"), (False, "few"), (False, "packed"), (False, "pair"), (False, "split"), (True, "fused"), (True, "few")}, reached
 
 
 def _widen(t):
