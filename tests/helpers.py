@@ -51,7 +51,7 @@ def route(heads, Nq, Nk, d, causal=None, half=False):
             if pair:
                 return "pair"
         if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (1280 if groups <= 512 else 1024) if Nq <= 32 else
-                                                        Nq <= 64 and groups <= 512 and 128 <= Nk < 2048):
+                                                        Nq <= 64 and groups <= 512 and 128 <= Nk < 384):
             return "packed"
     short_keys = {(True, 128): 256, (True, 64): 64, (False, 128): 384, (False, 64): 0}[half, d]
     if groups <= 5 << 20 and (groups <= 256 or (Nk > short_keys if Nq <= 32 else groups <= 512 and Nk >= 2048)):

@@ -146,11 +146,11 @@ def test_more_heads_than_one_few_query_launch_holds(variant, heads):
 
 @pytest.mark.parametrize("vblock", [False, True])
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("d,Nk", [(64, 1), (64, 66), (64, 128), (64, 129), (64, 1023), (64, 1024), (64, 1025), (64, 1280), (64, 1281), (64, 2047), (64, 2048),
+@pytest.mark.parametrize("d,Nk", [(64, 1), (64, 66), (64, 128), (64, 129), (64, 257), (64, 383), (64, 384), (64, 1023), (64, 1024), (64, 1025), (64, 1280), (64, 1281), (64, 2047), (64, 2048),
                                   (128, 1), (128, 66), (128, 128), (128, 129), (128, 384), (128, 385), (128, 700)])
 def test_few_queries_of_more_heads_than_cus(d, Nk, causal, vblock):
     # More than 256 groups of 32 queries: up to 32 queries per head the packed kernel (d = 64) or the fused one (d = 128) takes short
-    # key sequences, the twelve-wavefront kernel the rest; d = 64 and 33 to 64 queries the packed kernel between 128 and 2048 keys.
+    # key sequences, the twelve-wavefront kernel the rest; d = 64 and 33 to 64 queries the packed kernel between 128 and 383 keys, the two-group one beyond.
     # One to 256 groups and at most 128 keys: the packed kernel.  All against the rows of a call with more than 64 queries and more
     # than 512 groups, which is the fused kernel's.
     import paper_2409_16997_amd as ifa
@@ -164,15 +164,18 @@ def test_few_queries_of_more_heads_than_cus(d, Nk, causal, vblock):
     call = lambda q, a, n: ifa.int_flash_attn_fwd(q[:, :n].contiguous(), k8[:, :n], v8[:, :n], a[:, :n].contiguous(), sk[:, :n], sv[:, :n],
                                                   causal=causal, out_dtype=torch.float32)
     assert route(heads, N, Nk, d, causal) == ("packed" if d == 64 and N <= 64 else "fused")
-    full = call(q8, sq, heads)
+    full, reached = call(q8, sq, heads), set()
     for n, nq in ((heads, 1), (heads, 8), (heads, 32), (257, 32), (257, 31), (256, 32), (256, 33), (140, 64), (140, 40), (7, 1), (3, 33), (2, 128)):
         if nq > N:
             continue
+        reached.add((nq > 32, route(n, nq, Nk, d, causal)))
         out, ref = call(q8[:, :, N - nq:], sq[:, :, N - nq:], n), full[:, :n, N - nq:]
         if vblock and causal:                                    # as above
             assert bool(((out - ref).abs() <= 2.0 ** -21 * ref.abs()).all()), (n, nq)
         else:
             assert torch.equal(out, ref), (n, nq)
+    if d == 64 and Nk > 128:
+        assert (True, "packed" if Nk < 384 else "pair") in reached and (False, "packed" if Nk <= 1024 else "few") in reached
     h = lambda t, n=1: t[0, :n].cpu().numpy()
     res = oracle.compare_up_to_ties(h(full)[0], h(q8), h(k8), h(v8), h(sq), h(sk), h(sv), causal, Bc)
     assert float(res["err"].max()) <= 1e-3 * float(res["scale"])
