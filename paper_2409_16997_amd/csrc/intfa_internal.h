@@ -34,15 +34,16 @@ static inline bool ifa_few_queries(int heads, int Nq, int Nk, int d, bool half) 
 
 // Which INT8 calls the packed kernel takes before either of them, us (calls in a graph, K and V in rotation):
 //   one key block                    packed / few-query: 32 x 1 x 128 4.3 / 4.9, 128 x 32 x 64 5.0 / 5.8; d = 64, 32 x 1 x 128 3.7 / 4.3
-//   d = 64, more than 256 workgroups and up to 1024 or 1280 keys, packed / few-query / fused: 264 x 1 x 256 6.7 / 8.5 / 7.5, 512 x 32 x 128
-//                                    5.9 / 9.4 / 6.8, 1000 x 1 x 512 20.5 / 24.1 / 22.8, 4096 x 1 x 128 30 / 62 / 33, 400 x 8 x 1025 16.8 / 18.4 / 20;
-//                                    beyond that 400 x 8 x 1500 21.6 / 19.7 / 27.6, 768 x 32 x 1024 26.3 / 25.4 / 33.  With 33 to 64 queries packed / fused: 256 x 33 x 128 5.2 / 5.7,
+//   d = 64, more than 256 workgroups and up to 768 keys (1152 from 1025 on), packed / few-query: 400 x 8 x 768 13.0 / 13.4, 1000 x 1 x 640 22.7 / 24.2,
+//                                    1500 x 1 x 1152 47.9 / 47.6, 2000 x 32 x 1024 60.1 / 60.9; and fused, on the same K and V: 260 x 1 x 256 5.1 / 6.6 / 6.3, 512 x 32 x 128 4.5 / 7.6 /
+//                                    5.6, 1000 x 1 x 512 18.7 / 20.9 / 21.6.  Beyond that 600 x 1 x 900 23.5 / 20.8, 512 x 32 x 1280 21.0 / 19.1, 1000 x 1 x 1280
+//                                    36.7 / 33.4, 2000 x 8 x 1280 69.0 / 64.3.  With 33 to 64 queries packed / fused: 256 x 33 x 128 5.2 / 5.7,
 //                                    but 140 x 64 x 64 4.9 / 4.5 and above 512 workgroups 300 x 64 x 512 15.2 / 11.7; from 384 keys on the two-group kernel's
 static inline bool ifa_packed_queries(int heads, int Nq, int Nk, int d) {
     const long groups = ifa_query_groups(heads, Nq);
     if (groups <= 256) return Nk <= 128;
     if (d != 64) return false;
-    return Nq <= 32 ? Nk <= (groups <= 512 ? 1280 : 1024) : Nq <= 64 && groups <= 512 && Nk >= 128 && Nk < 384;
+    return Nq <= 32 ? Nk <= (groups <= 1024 ? 768 : 1152) : Nq <= 64 && groups <= 512 && Nk >= 128 && Nk < 384;
 }
 
 // Which INT8 calls the two-group kernel takes before all of them: more groups of 32 queries than CUs, two of one head to a workgroup.

@@ -50,7 +50,7 @@ def route(heads, Nq, Nk, d, causal=None, half=False):
                 pair = uneven and Nk >= 2048 and (wgs <= 512 or heads <= 8 and wgs <= 768 and heads * Nk <= 56 << 10)
             if pair:
                 return "pair"
-        if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (1280 if groups <= 512 else 1024) if Nq <= 32 else
+        if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (768 if groups <= 1024 else 1152) if Nq <= 32 else
                                                         Nq <= 64 and groups <= 512 and 128 <= Nk < 384):
             return "packed"
     short_keys = {(True, 128): 256, (True, 64): 64, (False, 128): 384, (False, 64): 0}[half, d]

@@ -36,8 +36,8 @@ def library_says(tmp_path, program, cases):
 
 def test_helpers_route_is_the_librarys_rule(tmp_path):
     cases = [(heads, Nq, Nk, d, causal, half) for d in (64, 128) for causal, half in ((0, 0), (1, 0), (0, 1)) for Nq in (1, 31, 32, 33, 64, 65, 127, 128, 1000, 4100, 8192)
-             for heads in (1, 2, 4, 8, 9, 64, 65, 128, 129, 171, 256, 257, 300, 512, 513, 1000, 5 << 20, (5 << 20) + 1)
-             for Nk in (1, 64, 65, 127, 128, 129, 256, 257, 383, 384, 385, 511, 512, 1024, 1025, 1280, 1281, 2047, 2048, 7168, 7169, 16384, 28672, 28673)]
+             for heads in (1, 2, 4, 8, 9, 64, 65, 128, 129, 171, 256, 257, 300, 512, 513, 1000, 1024, 1025, 5 << 20, (5 << 20) + 1)
+             for Nk in (1, 64, 65, 127, 128, 129, 256, 257, 383, 384, 385, 511, 512, 768, 769, 1024, 1025, 1152, 1153, 1280, 1281, 2047, 2048, 7168, 7169, 16384, 28672, 28673)]
     assert library_says(tmp_path, PROGRAM, cases) == [route(*c) for c in cases]
 
 
