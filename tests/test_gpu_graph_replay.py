@@ -92,3 +92,45 @@ def test_a_captured_key_split_call_on_the_static_workspace_replays_to_the_eager_
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(O, want), (Nq, Nk, rep)
+
+
+def test_calls_that_allocate_their_outputs_in_a_captured_step(ifa, monkeypatch):
+    # no `out`: the binding's native module allocates, from the graph's pool, and launches on the capturing stream
+    from paper_2409_16997_amd import binding
+    shape, Nk, d = (1, 8, 4, 128), 2500, 128
+    kv = (1, 8, Nk, d)
+
+    def step(Q, K, V, q, ws):
+        t = ifa.quantize_qkv(K, K, V, s_Q_mul=0.1)
+        q8, sq = ifa.quantize_tokenwise(q, scale_mul=0.1)
+        v8, sv = ifa.quantize_headwise(V)
+        r = ifa.quantize_qk(K, V)
+        return [*t, ifa.int_flash_attn_fwd(*t, causal=True), q8, sq, v8, sv, *r, ifa.int_flash_attn_fwd_half(q8, t[1], V, sq, t[4], causal=True),
+                ifa.int_flash_attn_fwd_splitk(q8, t[1], v8, sq, t[4], sv, causal=True, workspace=ws),
+                ifa.int_flash_attn_fwd_splitk(q8, t[1], v8, sq, t[4], sv, causal=True, workspace="static")]
+
+    def inputs(seed):
+        g = torch.Generator(device="cpu").manual_seed(seed)
+        return [torch.randn(s, generator=g).to(torch.float16).cuda() for s in (kv, kv, kv, shape)]
+
+    ws = torch.empty(ifa.splitk_workspace_bytes(1, 8, 4, Nk, d), dtype=torch.uint8, device="cuda")
+    static, kept = inputs(1), []
+
+    def fn():
+        kept[:] = step(*static, ws)
+
+    def refuse(*a):
+        raise AssertionError("the general path")
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_dev", refuse)
+        graph = _capture(fn)
+    for seed in (2, 3, 2):
+        cur = inputs(seed)
+        want = step(*cur, ws)
+        torch.cuda.synchronize()
+        for a, b in zip(static, cur):
+            a.copy_(b)
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(kept, want)):
+            assert torch.equal(a, b), (seed, i)

@@ -128,3 +128,26 @@ def test_a_hip_error_is_raised_and_the_call_not_repeated():
         module.init(binding._check, *addresses)
     for f in calls:
         f()
+
+
+def test_calls_run_on_the_current_stream():
+    # the inputs are written by the side stream after a wait of some milliseconds; a launch on another stream would find what was there before
+    import paper_2409_16997_amd as ifa
+    torch.manual_seed(5)
+    new = torch.randn((1, 4, 300, 128), device="cuda").half()
+    want = ifa.quantize_qkv(new, new, new)
+    want_O = ifa.int_flash_attn_fwd(*want, causal=True)
+    X, side = torch.zeros_like(new), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(10_000_000)
+        X.copy_(new)
+        got = ifa.quantize_qkv(X, X, X) + ifa.quantize_tokenwise(X) + ifa.quantize_headwise(X) + ifa.quantize_qk(X, X)
+        O = [ifa.int_flash_attn_fwd(*got[:6], causal=True), ifa.int_flash_attn_fwd_half(got[0], got[1], X, got[3], got[4], causal=True),
+             ifa.int_flash_attn_fwd_splitk(got[0][:, :, -8:].contiguous(), *got[1:3], got[3][:, :, -8:].contiguous(), *got[4:6], causal=True, workspace="static")]
+    torch.cuda.synchronize()
+    q8, k8, v8, sq, sk, sv = want
+    for a, b in zip(got, (q8, k8, v8, sq, sk, sv, q8, sq, v8, sv, q8, k8, sq, sk)):
+        assert torch.equal(a, b)
+    assert torch.equal(O[0], want_O) and torch.equal(O[1], ifa.int_flash_attn_fwd_half(q8, k8, new, sq, sk, causal=True))
+    assert torch.equal(O[2], want_O[:, :, -8:])

@@ -1,4 +1,4 @@
-"""The fused kernels' mapping of workgroups to (head, query block), compiled for the host: every pair exactly once, the whole
+"""The mapping of workgroups of the fused kernels (two of which share a CU) and the two-group kernel (one to a CU) to (head, query block), compiled for the host: every pair exactly once, the whole
 heads of a call on one XCD each, and the order that the mask asks for."""
 import os
 import subprocess
@@ -11,19 +11,19 @@ PROGRAM = r"""
 #include "intfa_device.h"
 #include <cstdio>
 #include <vector>
-static int check(int heads, int T_r, int group, bool causal) {
+static int check(int heads, int T_r, int group, bool causal, bool paired) {
     const int W = heads * T_r;
     std::vector<int> seen(W, 0), last(8, -1);
     for (int L = 0; L < W; ++L) {
         int h = -1, q = -1;
-        ifa_dev::map_workgroup(L, heads, T_r, group, causal, h, q);
+        ifa_dev::map_workgroup(L, heads, T_r, group, causal, h, q, paired);
         if (h < 0 || h >= heads || q < 0 || q >= T_r || seen[h * T_r + q]++) return 1;
         const bool dealt = !causal && (heads & 7) && T_r >= 16;
         if (!dealt && h < heads / 8 * 8 && (h & 7) != (L & 7)) return 2;
         // one group: the ranks of an XCD never fall, except in the backward half of a call that starts all at once, where they never rise
         if (causal && heads / 8 <= group) {
-            const bool back = W <= 512 && (L >> 3) > 32;
-            if ((L >> 3) != 32 && (back ? q > last[L & 7] : q < last[L & 7])) return 3;
+            const bool back = paired && W <= 512 && (L >> 3) > 32;
+            if ((!paired || (L >> 3) != 32) && (back ? q > last[L & 7] : q < last[L & 7])) return 3;
         }
         last[L & 7] = q;
     }
@@ -35,7 +35,8 @@ int main() {
         for (int T_r : ranks)
             for (int group : {1, 2, 4, 8})
                 for (int causal = 0; causal < 2; ++causal)
-                    if (int rc = check(heads, T_r, group, causal)) { printf("heads %d blocks %d group %d causal %d: %d\n", heads, T_r, group, causal, rc); return 1; }
+                    for (int paired = 0; paired < 2; ++paired)
+                        if (int rc = check(heads, T_r, group, causal, paired)) { printf("heads %d blocks %d group %d causal %d paired %d: %d\n", heads, T_r, group, causal, paired, rc); return 1; }
     return 0;
 }
 """
