@@ -1,6 +1,6 @@
 // The Python binding's plain calls, natively: take the tensors apart, allocate the outputs, call the C ABI on torch's current stream.
 // What such a call costs the host bounds every small shape (quantize Q, K, V of one 128 x 64 head and attend: 26.1 us a pass with the
-// arguments taken apart and the seven outputs allocated in Python, 13.6 like this, of which 9 are GPU time; a first pass on new inputs 38 and 24).
+// arguments taken apart and the seven outputs allocated in Python, 13.6 like this, of which the two kernels take 6.6; a first pass on new inputs 38 and 24).
 //
 // Every function returns None for anything but the plain case -- a tensor subclass, an active torch function or dispatch mode, a tensor
 // that is not contiguous, not on the current device or of another type, shapes that do not agree, a call that the C ABI refuses -- and
