@@ -7,6 +7,7 @@ torch = pytest.importorskip("torch")
 import oracle
 from helpers import route
 from test_gpu_few_query_dispatch import problem
+from test_routes import library_says
 
 # (heads, Nq, Nk): an odd number of key blocks and a ragged one, a last workgroup without its second group (Nq = 33, 65, 96: all but or half
 # empty), more than one query per key block of the mask, exactly as many workgroups as CUs (8 x 2048) and, under the mask only, more (9 x 1999)
@@ -15,6 +16,14 @@ SHAPES = [(129, 64, 512), (130, 33, 513), (90, 65, 640), (90, 96, 1023), (37, 20
 
 def taken(heads, Nq, Nk, d, causal):
     return route(heads, Nq, Nk, d, causal) == "pair"
+
+
+def test_rule_is_the_librarys(tmp_path):
+    program = ('#include "intfa_internal.h"\n#include <cstdio>\nint main() { int h, q, k, d, c; '
+               'while (scanf("%d %d %d %d %d", &h, &q, &k, &d, &c) == 5) puts(ifa_pair_queries(h, q, k, d, c) ? "1" : "0"); }\n')
+    cases = [(h, q, k, d, c) for h in (1, 2, 8, 9, 64, 65, 128, 129, 256, 257, 5 << 20) for q in (1, 32, 33, 64, 65, 2000, 4100, 6000, 8192, 16384, 24000, 32768, 48000)
+             for k in (64, 383, 384, 511, 512, 2047, 2048, 4000, 4001, 7168, 7169, 16384, 28672, 28673, 32768, 57344, 57345) for d in (64, 128) for c in (0, 1)]
+    assert library_says(tmp_path, program, cases) == ["01"[taken(*c)] for c in cases]
 
 
 def test_every_shape_is_the_kernels():
