@@ -63,13 +63,21 @@ namespace {
 
 using namespace ifa_tiles;
 
-template <int D> struct Smem {
+// W wavefronts per SIMD, two or (d = 64) three.  With two, matrix and vector instructions take turns (d = 64: 512 + 1500 cycles per wavefront and
+// block, 2000 measured): one wavefront in its MFMAs leaves the other to issue vector instructions alone, at half of the rate two reach.  For three,
+// 168 registers hold the block: Q comes from LDS every block (8 registers less) and V1 keeps the s_K of one key tile, reloaded as they
+// are used (16 less).  Two / three, us: 128 x 4096 causal 289 / 263, 32 x 9974 causal 377 / 346, 256 x 1398 131 / 121, 96 x 1024 28.5 / 25.8, 600 x 128
+// causal 8.0 / 6.0, 90 x 700 22.5 / 19.1.  Which calls take three: launch_fwd().
+template <int D, int W> struct Smem {
     alignas(4096) int8_t k[2][BC * D];   // K_j, row = key, 16-byte slots XOR-swizzled by row
     alignas(1024) int8_t v[2][BC * D];   // V_j, row = key, 16-byte slots XOR-swizzled by row
     alignas(512) float sk[2][BC];        // s_K of the block
+    alignas(16) v4i q[W == 3 ? 4 * (D / 32) * 64 : 1];   // [wavefront][k-step][lane]: the Q operands, where they don't stay in registers
 };
 // lds_xor() wants every K / V tile at a multiple of 4096 bytes
-static_assert((BC * 64) % 4096 == 0 && offsetof(Smem<64>, v) % 4096 == 0 && offsetof(Smem<128>, v) % 4096 == 0, "tile bases");
+static_assert(3 * sizeof(Smem<64, 3>) <= 160 * 1024 && 2 * sizeof(Smem<128, 2>) <= 160 * 1024, "workgroups per CU");
+template <typename S> constexpr bool tile_bases = offsetof(S, v) % 4096 == 0;
+static_assert((BC * 64) % 4096 == 0 && tile_bases<Smem<64, 2>> && tile_bases<Smem<64, 3>> && tile_bases<Smem<128, 2>>, "tile bases");
 
 // Test hook: where the int32 accumulators and the packed P of every key block go (null: not written), and an
 // optional P to use in place of the computed one.  Only the DBG instantiation of the kernel reads this.
@@ -83,6 +91,13 @@ struct DebugDump {
 
 #if defined(__HIP_DEVICE_COMPILE__)   // device-only code: buffer resources and LDS builtins do not exist in the host pass
 // ---- the fused kernel ---------------------------------------------------------------------------
+// The lane's index, computed anew (volatile: not moved ahead of where it stands), so that nothing is kept for it through the key loop
+__device__ __forceinline__ int lane_index() {
+    int x;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(x));
+    return x;
+}
+
 // Online-softmax state of one lane: one query row, half of the keys of every block.
 template <int D> struct RowState {
     float m2;             // running max in log2 units (identical in lanes r and r + 32)
@@ -103,12 +118,13 @@ template <int D> struct RowState {
 // after the barrier so that their LDS latency is covered by V3.  `kfirst` holds those operands on entry and on
 // exit.  DIAG blocks leave staging and barriers to the caller: a wavefront whose rows see none of a masked block
 // skips it altogether.  In !DIAG blocks the issue order is pinned (sched_group_barrier) to the one written here.
-template <int D, bool DIAG, bool VB, bool DBG>
+template <int D, int W, bool DIAG, bool VB, bool DBG>
 __device__ __forceinline__ void process_block(lds_ptr ks, lds_ptr vs, lds_ptr sk, lds_ptr ks_next, const LaneOffsets<D> &lo,
-                                              const v4i (&qf)[D / 32], float nq2, int wave, int lane, int klimit, int last_tile, int clear_tiles,
+                                              v4i (&qf)[D / 32], lds_ptr qs, float nq2, int wave, int lane, int klimit, int last_tile, int clear_tiles,
                                               int g, float oscale, const float *sv_next_ptr, float &sv_next, const Prefetch &nx, bool preload_next,
                                               v4i (&kfirst)[D / 32], RowState<D> &st, const DebugDump &dbg, long dbg_row, int dbg_j0, int dbg_jb, int dbg_nq) {
     constexpr int KS = D / 32, DT = D / 32;
+    constexpr bool ONE_SK = W == 3 && !DIAG;  // V1 keeps the s_K of one key tile only
     const int last = DIAG ? last_tile : 3;           // last active 32-key tile (wave-uniform)
 
     auto load_k = [&](v4i (&dst)[KS], lds_ptr base, int mt) {
@@ -120,13 +136,20 @@ __device__ __forceinline__ void process_block(lds_ptr ks, lds_ptr vs, lds_ptr sk
         for (int vq = 0; vq < 4; ++vq) dst[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + lo.sk + 128 * mt + 32 * vq);
     };
 
+    auto load_q = [&]() {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<LDS_AS const v4i *>(qs + 1024 * kk);
+    };
+
     // ---- M1: S^T = K Q^T, all four key tiles back to back (line 9, integer part).  The K operands of tile mt+1
     // are requested before the MFMAs of tile mt are issued; the staging copies of the next block go out here too.
     v16i sacc[4];
     v4i kop[2][KS];
     v4f skr[2][4];
-    if (DIAG) load_k(kop[0], ks, 0);
-    else {
+    if (DIAG) {
+        load_k(kop[0], ks, 0);
+        if (W == 3) load_q();
+    } else {
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) kop[0][kk] = kfirst[kk];
     }
@@ -135,15 +158,15 @@ __device__ __forceinline__ void process_block(lds_ptr ks, lds_ptr vs, lds_ptr sk
         if (mt <= last) {
             if (mt + 1 <= last) load_k(kop[(mt + 1) & 1], ks, mt + 1);
             // the scales of the first two key tiles are requested under the last MFMAs, so that V1 starts on data
-            if (DIAG ? mt == last : mt == 2) load_sk(skr[0], 0);
-            if (DIAG ? (mt == last && last >= 1) : mt == 3) load_sk(skr[1], 1);
+            if (DIAG ? mt == last : mt == (ONE_SK ? 3 : 2)) load_sk(skr[0], 0);
+            if (!ONE_SK && (DIAG ? (mt == last && last >= 1) : mt == 3)) load_sk(skr[1], 1);
             sacc[mt] = mfma_i8_start(kop[mt & 1][0], qf[0]);
 #pragma unroll
             for (int kk = 1; kk < KS; ++kk)
                 sacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[mt & 1][kk], qf[kk], sacc[mt], 0, 0, 0);
             if (!DIAG) {                                                    // issue order: operand reads, then this tile's MFMAs
                 if (mt < 2) __builtin_amdgcn_sched_group_barrier(0x100, KS, 0);
-                else if (mt == 2) __builtin_amdgcn_sched_group_barrier(0x100, KS + 4, 0);
+                else if (mt == 2) __builtin_amdgcn_sched_group_barrier(0x100, KS + (ONE_SK ? 0 : 4), 0);
                 else __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, KS - 1, 0);     // (the chain start is an asm statement, not counted)
             }
@@ -169,20 +192,32 @@ __device__ __forceinline__ void process_block(lds_ptr ks, lds_ptr vs, lds_ptr sk
     // the extremum, so the block maximum of line 10 is a minimum here and a masked key is +infinity.
     float a[4][16];
     float bmin = INFINITY;
+    auto scale_quad = [&](int mt, int vq, const v4f &skq, auto masked) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float x = (ACC_START_F - __int_as_float(sacc[mt][4 * vq + e])) * skq[e];
+            if (decltype(masked)::value && (32 * mt + 8 * vq + 4 * g + e > klimit)) x = INFINITY;       // masked key
+            a[mt][4 * vq + e] = x;
+            bmin = fminf(bmin, x);
+        }
+    };
     auto scale_elems = [&](int mt, const v4f (&skv)[4], auto masked) {
 #pragma unroll
-        for (int vq = 0; vq < 4; ++vq)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float x = (ACC_START_F - __int_as_float(sacc[mt][4 * vq + e])) * skv[vq][e];
-                if (decltype(masked)::value && (32 * mt + 8 * vq + 4 * g + e > klimit)) x = INFINITY;   // masked key
-                a[mt][4 * vq + e] = x;
-                bmin = fminf(bmin, x);
-            }
+        for (int vq = 0; vq < 4; ++vq) scale_quad(mt, vq, skv[vq], masked);
     };
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
-        if (mt <= last) {
+        if (ONE_SK) {                                            // four scales of the next tile as soon as four have been used
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                scale_quad(mt, vq, skr[0][vq], std::false_type{});
+                __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
+                if (mt < 3) {
+                    skr[0][vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + lo.sk + 128 * (mt + 1) + 32 * vq);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+            }
+        } else if (mt <= last) {
             // only the tiles the mask boundary crosses pay for the comparisons (wave-uniform choice)
             if (DIAG && mt >= clear_tiles) scale_elems(mt, skr[mt & 1], std::true_type{});
             else scale_elems(mt, skr[mt & 1], std::false_type{});
@@ -286,6 +321,7 @@ __device__ __forceinline__ void process_block(lds_ptr ks, lds_ptr vs, lds_ptr sk
         __syncthreads();                                         // everyone's has, and the current buffers are free again
         if (VB) asm volatile("" : "+s"(sv_next));
         if (preload_next) load_k(kfirst, ks_next, 0);
+        if (W == 3) load_q();                            // (unconditional: no earlier value stays live)
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -314,13 +350,13 @@ __device__ __forceinline__ void process_block(lds_ptr ks, lds_ptr vs, lds_ptr sk
 
 #endif  // __HIP_DEVICE_COMPILE__
 
-template <int D, bool CAUSAL, bool VB, typename OutT, bool DBG = false>
-__global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
+template <int D, int W, bool CAUSAL, bool VB, typename OutT, bool DBG = false>
+__global__ __launch_bounds__(THREADS, W) void int_flash_attn_fwd_kernel(
     const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
     const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
     int heads, int Nq, int Nk, int head_group, OutT *__restrict__ O, DebugDump dbg) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __shared__ Smem<D> sm;
+    __shared__ Smem<D, W> sm;
     constexpr int DT = D / 32;
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
@@ -354,10 +390,17 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
     const BufRsrc rSK = make_rsrc(sKh, static_cast<unsigned>(Nk) * 4);
 
     // line 5: Q_i and s_Q,i.  B operand: lane (r, g) holds bytes d = 32*kk + 16*g .. +15 of query r.
-    const int8_t *qptr = Q + qrow * D + 16 * g;
     v4i qf[D / 32];
+    const lds_ptr qbuf = (lds_ptr)(&sm.q[0]) + wave * (D / 32) * 1024;    // (W = 3) each lane reads back what it has copied
+    if constexpr (W == 3) {
+        const int rows = min(BR, Nq - qb * BR);
+        const BufRsrc rQ = make_rsrc(Q + (static_cast<long>(head) * Nq + qb * BR) * D, static_cast<unsigned>(rows) * D);
 #pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 32 * kk);
+        for (int kk = 0; kk < D / 32; ++kk) lds_copy16(rQ, qbuf + 1024 * kk, min(q_local, rows - 1) * D + 16 * g, 32 * kk);
+    } else {
+#pragma unroll
+        for (int kk = 0; kk < D / 32; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(Q + qrow * D + 16 * g + 32 * kk);
+    }
     const float nq2 = sQ[qrow] * (-LOG2E * ACC_UNIT);        // line 9's s_Q, log2 e, the accumulator unit and the sign of a
     const LaneOffsets<D> lo(lane, wave);
     {                                                            // line 8 for block 0
@@ -392,7 +435,10 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
     if (VB) asm volatile("" : "+s"(sv_cur));
     v4i kfirst[D / 32];                                          // K operands of the first key tile of the coming block
 #pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) kfirst[kk] = *reinterpret_cast<LDS_AS const v4i *>(k_operand<D>(kbuf, lo, kk));
+    for (int kk = 0; kk < D / 32; ++kk) {
+        kfirst[kk] = *reinterpret_cast<LDS_AS const v4i *>(k_operand<D>(kbuf, lo, kk));
+        if (W == 3) qf[kk] = *reinterpret_cast<LDS_AS const v4i *>(qbuf + 16 * lane + 1024 * kk);
+    }
 
     for (int jb = 0; jb < nfull; ++jb) {                         // line 7
         const int cur = jb & 1, nxt = cur ^ 1;
@@ -404,7 +450,7 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
         const Prefetch pf = {rK, rV, rSK, more ? j1 * D : NOWHERE, more ? j1 * 4 : NOWHERE, kbuf + nxt * BC * D,
                              vbuf + nxt * BC * D, skbuf + nxt * BC * 4};
         // the staged copies are awaited and the workgroup barrier is met inside, between the second GEMM and the fold
-        process_block<D, false, VB, DBG>(kbuf + cur * BC * D, vbuf + cur * BC * D, skbuf + cur * BC * 4, kbuf + nxt * BC * D, lo, qf, nq2,
+        process_block<D, W, false, VB, DBG>(kbuf + cur * BC * D, vbuf + cur * BC * D, skbuf + cur * BC * 4, kbuf + nxt * BC * D, lo, qf, qbuf + 16 * lane, nq2,
                                          wave, lane, 0, 3, 4, g, oscale, sVh + (VB ? min(jb + 1, T_c - 1) : 0), sv_cur, pf, jb + 1 < nfull, kfirst, st, dbg,
                                          dbg_row, jb * BC, jb, Nq);
     }
@@ -416,7 +462,8 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
         // kept keys of this block: index inside the block <= klimit (may be negative: none).  Tiles after tile
         // wlim / 32 hold no kept key for any lane of this wavefront.
         const int tail = Nk - 1 - j0;
-        const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;
+        const int lane = lane_index(), g = lane >> 5;
+        const int klimit = CAUSAL ? min(first_q + 32 * wave + (lane & 31) + shift - j0, tail) : tail;
         const int wlim = CAUSAL ? min(first_q + 32 * wave + 31 + shift - j0, tail) : tail;
         const int wmin = CAUSAL ? min(first_q + 32 * wave + shift - j0, tail) : tail;   // klimit of the wavefront's first row
         if (wlim >= 0) {                                         // wave-uniform: this wavefront sees part of the block
@@ -424,7 +471,7 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
             const float sv_j = VB ? (jb == nfull ? sv_cur : uniform(sVh[jb])) : 1.0f;
             const float oscale = VB ? uniform(sv_prev * __builtin_amdgcn_rcpf(sv_j)) : 1.0f;
             sv_prev = sv_j;
-            process_block<D, true, VB, DBG>(kbuf + cur * BC * D, vbuf + cur * BC * D, skbuf + cur * BC * 4, kbuf, lo, qf, nq2, wave, lane,
+            process_block<D, W, true, VB, DBG>(kbuf + cur * BC * D, vbuf + cur * BC * D, skbuf + cur * BC * 4, kbuf, lo, qf, qbuf + 16 * lane, nq2, wave, lane,
                                             klimit, min(3, wlim >> 5), max(0, (wmin + 1) >> 5), g, oscale, sVh, sv_cur, none, false, kfirst, st, dbg,
                                             dbg_row, j0, jb, Nq);
         }
@@ -455,7 +502,7 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_kernel(
     const lds_ptr stage = (wave < 2 ? kbuf : vbuf) + freeb * BC * D + (wave & 1) * (64 * D);
     const int row0 = qb * BR + 32 * wave;                        // first query row of this wavefront
     OutT *orow0 = O + (static_cast<long>(head) * Nq + row0) * D;
-    store_tile_staged<D, OutT>(stage, orow0, Nq - row0, lane, [&](int dt, int v) { return st.o[dt][v] * f; });
+    store_tile_staged<D, OutT>(stage, orow0, Nq - row0, lane_index(), [&](int dt, int v) { return st.o[dt][v] * f; });
 #endif
 }
 
@@ -465,10 +512,23 @@ hipStream_t g_stream = nullptr;
 template <int D, bool CAUSAL, bool VB, typename OutT>
 int launch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                int heads, int Nq, int Nk, void *O, hipStream_t st) {
-    const long wgs = static_cast<long>(heads) * ((Nq + BR - 1) / BR);
-    hipLaunchKernelGGL((int_flash_attn_fwd_kernel<D, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,
-                       st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, head_group_for(CAUSAL, 2L * Nk * D, (Nq + BR - 1) / BR), static_cast<OutT *>(O),
-                       DebugDump{nullptr, nullptr, nullptr, nullptr, 0});
+    const int T_r = (Nq + BR - 1) / BR;
+    const long wgs = static_cast<long>(heads) * T_r;
+    auto launch = [&](auto w) {
+        hipLaunchKernelGGL((int_flash_attn_fwd_kernel<D, decltype(w)::value, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,
+                           st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, head_group_for(CAUSAL, 2L * Nk * D, T_r), static_cast<OutT *>(O),
+                           DebugDump{nullptr, nullptr, nullptr, nullptr, 0});
+    };
+    if constexpr (D == 64) {
+        // Three wavefronts per SIMD where a third workgroup per CU has something to do.  If a little more than 512 are uneven, all of them start at
+        // once and the heaviest decide; with two to a CU the light ones start where a CU has become free.  Two / three, us: 96 x 800 causal
+        // 16.9 / 20.0 (672 workgroups), 100 x 900 20.2 / 23.3 (800), 14 x 7800 103 / 112 (854); but 110 x 1024 25.6 / 25.1 (880), 90 x 1300 32.5 /
+        // 29.0 (990), and with three query blocks a head and fewer 300 x 250 9.5 / 8.6 (600), 230 x 300 11.3 / 9.5 (690), 280 x 300 12.9 / 11.8 (840).
+        // Up to 512 the shorter way to the operands is worth 1 - 2 %: 100 x 512 10.5 / 10.8.
+        const bool uneven = CAUSAL && 2L * Nq >= Nk && T_r > 3;
+        if (wgs > (uneven ? 864 : 512)) launch(std::integral_constant<int, 3>{});
+        else launch(std::integral_constant<int, 2>{});
+    } else launch(std::integral_constant<int, 2>{});
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 
@@ -588,7 +648,7 @@ extern "C" int int_flash_attn_fwd(const signed char *Q_i8, const signed char *K_
 template <int D, bool CAUSAL>
 static int launch_debug(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int N,
                  const DebugDump &dbg, float *O, hipStream_t st) {
-    hipLaunchKernelGGL((int_flash_attn_fwd_kernel<D, CAUSAL, false, float, true>), dim3(N / BR), dim3(THREADS), 0, st, Q, K, V, sQ, sK,
+    hipLaunchKernelGGL((int_flash_attn_fwd_kernel<D, 2, CAUSAL, false, float, true>), dim3(N / BR), dim3(THREADS), 0, st, Q, K, V, sQ, sK,
                        sV, 1, N, N, 1, O, dbg);
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
