@@ -91,13 +91,6 @@ struct DebugDump {
 
 #if defined(__HIP_DEVICE_COMPILE__)   // device-only code: buffer resources and LDS builtins do not exist in the host pass
 // ---- the fused kernel ---------------------------------------------------------------------------
-// The lane's index, computed anew (volatile: not moved ahead of where it stands), so that nothing is kept for it through the key loop
-__device__ __forceinline__ int lane_index() {
-    int x;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(x));
-    return x;
-}
-
 // Online-softmax state of one lane: one query row, half of the keys of every block.
 template <int D> struct RowState {
     float m2;             // running max in log2 units (identical in lanes r and r + 32)

@@ -277,10 +277,129 @@ __device__ __forceinline__ void process_block_half(lds_ptr ks, lds_ptr vs, lds_p
     }
 }
 
+// The same block, same results, in registers for three wavefronts per SIMD (d = 64: four), for calls with enough workgroups.  Two wavefronts
+// take turns at matrix and vector instructions and wait out each other's row maximum, LDS reads and barrier, every 64 keys; a third one fills in.  166
+// registers (d = 64: 114) hold the block without the 16 the S^T accumulators start from (the MFMA's inline constant; a is carried in units of
+// 2^26, a power of two, so the numbers are the same), with the scores in the accumulators' place and the s_K of one key tile, reloaded as
+// they are used.  Two / three or four, us: d = 64, 32 x 8192 causal 350 / 302, 64 x 4096 340 / 303, 128 x 4096 causal 359 / 326, 300 x 200 12.7 / 10.2;
+// d = 128, 32 x 16384 causal 1874 / 1811, 96 x 1724 154 / 151, 300 x 200 18.0 / 15.6, 600 x 128 causal 15.0 / 12.5.  With few workgroups the order of the function
+// above is faster, which has all of its LDS operands requested earlier: 24 x 1400 at d = 128 36.8 / 38.5.
+template <int D, bool MASKED>
+__device__ __forceinline__ void process_block_half_lean(lds_ptr ks, lds_ptr vs, lds_ptr sk, const LaneOffsetsH<D> &lo,
+                                                        const v4i (&qf)[D / 32], float sq2, int klimit, int last_tile, int clear_tiles, int g,
+                                                        RowStateH<D> &st) {
+    constexpr int KS = D / 32, DT = D / 32;
+    const int last = MASKED ? last_tile : NT - 1;
+    v16i sacc[NT];
+    float a[NT][16];
+    float bmax = -INFINITY;
+    v4i kop[NT][KS];
+    v4f skr[4];
+    auto load_k = [&](int mt) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) kop[mt][kk] = *reinterpret_cast<LDS_AS const v4i *>(lds_xor(ks, 32 * kk, lo.k0) + 32 * mt * D);
+    };
+    auto load_sk = [&](int mt, int vq) { skr[vq] = *reinterpret_cast<LDS_AS const v4f *>(sk + 16 * g + 128 * mt + 32 * vq); };
+
+    // ---- S^T = K Q^T, tile by tile
+    load_k(0);
+#pragma unroll
+    for (int mt = 0; mt < NT; ++mt) {
+        if (mt <= last) {
+            if (mt + 1 <= last) load_k(mt + 1);
+            if (mt == last) {
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq) load_sk(0, vq);
+            }
+            sacc[mt] = mfma_i8_start(kop[mt][0], qf[0]);
+#pragma unroll
+            for (int kk = 1; kk < KS; ++kk) sacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kop[mt][kk], qf[kk], sacc[mt], 0, 0, 0);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // line 9, fp32 part, in place: a = acc * s_K in units of 2^26
+#pragma unroll
+    for (int mt = 0; mt < NT; ++mt) {
+        if (mt <= last) {
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float x = (__int_as_float(sacc[mt][4 * vq + e]) - ACC_START_F) * skr[vq][e];
+                    if (MASKED && mt >= clear_tiles && 32 * mt + 8 * vq + 4 * g + e > klimit) x = -INFINITY;
+                    a[mt][4 * vq + e] = x;
+                    bmax = fmaxf(bmax, x);
+                }
+                if (mt + 1 <= last) load_sk(mt + 1, vq);
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) a[mt][v] = -INFINITY;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    bmax = pair_max(bmax);
+    const float m_new = fmaxf(st.m2, bmax * sq2);                 // finite from the first block on (key 0 is never masked)
+    const float alpha = __builtin_amdgcn_exp2f(st.m2 - m_new);    // exp2(-inf) = 0 on the first block
+    st.m2 = m_new;
+
+    // ---- P~ = fp16(2^(a s_Q' - m)), two keys per register in accumulator order; l sums the rounded values
+    h2 ph[NT][8];
+    float psum = 0.0f;
+    const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
+    auto p_pair = [&](int mt, int c) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(a[mt][2 * c], sq2, -m_new));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(a[mt][2 * c + 1], sq2, -m_new));
+        const h2 w = {(_Float16)p0, (_Float16)p1};
+        ph[mt][c] = w;
+        psum = __builtin_amdgcn_fdot2(w, ones, psum, false);
+    };
+    h8 vt[DT][2];
+    auto load_v1 = [&](int mt, int dt, int s_) {
+        const int koff = (32 * mt + 16 * s_) * (2 * D);
+        const h4 t0 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + koff)));
+        const h4 t1 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_AS s4 *>(lds_xor(vs, 64 * dt, lo.v0) + 8 * (2 * D) + koff)));
+        vt[dt][s_] = h8{t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
+    };
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) { load_v1(0, dt, 0); load_v1(0, dt, 1); }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) p_pair(0, c);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int mt = 0; mt < NT; ++mt) {
+        if (mt <= last) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                if (mt == 0) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) st.o[dt][v] *= alpha;
+                }
+#pragma unroll
+                for (int s_ = 0; s_ < 2; ++s_) {
+                    const h8 pb = {ph[mt][4 * s_][0], ph[mt][4 * s_][1], ph[mt][4 * s_ + 1][0], ph[mt][4 * s_ + 1][1],
+                                   ph[mt][4 * s_ + 2][0], ph[mt][4 * s_ + 2][1], ph[mt][4 * s_ + 3][0], ph[mt][4 * s_ + 3][1]};
+                    st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vt[dt][s_], pb, st.o[dt], 0, 0, 0);
+                    if (mt + 1 <= last) load_v1(mt + 1, dt, s_);
+                }
+                if (mt + 1 <= last) {
+#pragma unroll
+                    for (int q = 0; q < 8 / DT; ++q) p_pair(mt + 1, dt * (8 / DT) + q);
+                }
+            }
+        }
+    }
+    __builtin_amdgcn_s_setprio(0);
+    st.l = __builtin_fmaf(st.l, alpha, psum);
+}
+
 #endif  // __HIP_DEVICE_COMPILE__
 
-template <int D, bool CAUSAL, typename OutT>
-__global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
+// W wavefronts per SIMD: 2, or as many as the lean form of a block allows
+template <int D, int W, bool CAUSAL, typename OutT>
+__global__ __launch_bounds__(THREADS, W) void int_flash_attn_fwd_half_kernel(
     const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const _Float16 *__restrict__ V,
     const float *__restrict__ sQ, const float *__restrict__ sK, int heads, int Nq, int Nk, int head_group, OutT *__restrict__ O) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -320,17 +439,19 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk)
         qf[kk] = *reinterpret_cast<const v4i *>(Q + qrow * D + 32 * kk + 16 * g);
-    const float sq2 = sQ[qrow] * LOG2E;
+    const float sq2 = sQ[qrow] * (W == 2 ? LOG2E : LOG2E * ACC_UNIT);
     const LaneOffsetsH<D> lo(lane, wave);
     {
         const PrefetchH first = {rK, rV, rSK, 0, 0, 0, kbuf, vbuf, skbuf};
         prefetch_block<D>(first, lo, wave, lane);
     }
 
-    v16i bias;                                                   // constant registers the S^T accumulators start from
+    [[maybe_unused]] v16i bias;                                  // (W = 2) constant registers the S^T accumulators start from
 #pragma unroll
     for (int v = 0; v < 16; ++v) bias[v] = ACC_BIAS_I;
-    asm volatile("" : "+v"(bias));                               // opaque: kept in registers, not re-materialised per use
+    if constexpr (W == 2) asm volatile("" : "+v"(bias));                               // opaque: kept in registers, not re-materialised per use
+
+    auto lane_late = [&]() { return W == 2 ? lane : lane_index(); };   // after the loop over the unmasked blocks
 
     RowStateH<D> st;
     st.m2 = -INFINITY;
@@ -356,23 +477,28 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
     for (int jb = 0; jb < nfull; ++jb) {
         const int cur = jb & 1;
         prefetch_block<D>(next_block(jb), lo, wave, lane);
-        process_block_half<D, false>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
-                                     0, NT - 1, NT, g, bias, st);
+        if constexpr (W == 2) process_block_half<D, false>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
+                                                           0, NT - 1, NT, g, bias, st);
+        else process_block_half_lean<D, false>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2, 0, NT - 1, NT, g, st);
         wait_all_memory();                                       // my part of the next block has landed in LDS
         __syncthreads();                                         // everyone's has, and `cur` is free again
     }
     for (int jb = nfull; jb < nblocks; ++jb) {
         const int cur = jb & 1;
-        prefetch_block<D>(next_block(jb), lo, wave, lane);
+        prefetch_block<D>(next_block(jb), lo, wave, lane_late());
         const int j0 = jb * BCH;
         const int tail = Nk - 1 - j0;                                              // last valid key of the block
-        const int klimit = CAUSAL ? min(q_head + shift - j0, tail) : tail;         // < 0: nothing kept
+        const int ln = lane_late(), g = ln >> 5;
+        const int klimit = CAUSAL ? min(first_q + 32 * wave + (ln & 31) + shift - j0, tail) : tail;     // < 0: nothing kept
         const int wlim = CAUSAL ? min(wave_last_q + shift - j0, tail) : tail;
         const int last_tile = wlim < 0 ? -1 : min(NT - 1, wlim >> 5);
         const int wmin = CAUSAL ? min(wave_last_q - 31 + shift - j0, tail) : tail;   // klimit of the wavefront's first row
-        if (last_tile >= 0)                                                        // wave-uniform
-            process_block_half<D, true>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
-                                        klimit, last_tile, max(0, (wmin + 1) >> 5), g, bias, st);
+        if (last_tile >= 0) {                                                      // wave-uniform
+            if constexpr (W == 2) process_block_half<D, true>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
+                                                              klimit, last_tile, max(0, (wmin + 1) >> 5), g, bias, st);
+            else process_block_half_lean<D, true>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
+                                                  klimit, last_tile, max(0, (wmin + 1) >> 5), g, st);
+        }
         wait_all_memory();
         __syncthreads();
     }
@@ -383,7 +509,7 @@ __global__ __launch_bounds__(THREADS, 2) void int_flash_attn_fwd_half_kernel(
     // 64 D bytes of the V buffers and stores whole (fp32: half) rows.
     const int row0 = qb * BR + 32 * wave;                        // first query row of this wavefront
     OutT *orow0 = O + (static_cast<long>(head) * Nq + row0) * D;
-    store_tile_staged<D, OutT>(vbuf + wave * (64 * D), orow0, Nq - row0, lane, [&](int dt, int v) { return st.o[dt][v] * f; });
+    store_tile_staged<D, OutT>(vbuf + wave * (64 * D), orow0, Nq - row0, lane_late(), [&](int dt, int v) { return st.o[dt][v] * f; });
 #endif
 }
 
@@ -678,10 +804,22 @@ int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float
         } else launch(std::integral_constant<int, 1>{});
         return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
     }
-    const long wgs = static_cast<long>(heads) * ((Nq + BR - 1) / BR);
-    // T_r = 0: under the mask this kernel keeps 4 heads per group (8 measured 4-17 % slower here at N = 1280 .. 2048)
-    hipLaunchKernelGGL((int_flash_attn_fwd_half_kernel<D, CAUSAL, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,
-                       st, Q, K, V, sQ, sK, heads, Nq, Nk, head_group_for(CAUSAL, 3L * Nk * D, 0), static_cast<OutT *>(O));
+    const int T_r = (Nq + BR - 1) / BR;
+    const long wgs = static_cast<long>(heads) * T_r;
+    auto launch = [&](auto w) {
+        // T_r = 0: under the mask this kernel keeps 4 heads per group (8 measured 4-17 % slower here at N = 1280 .. 2048)
+        hipLaunchKernelGGL((int_flash_attn_fwd_half_kernel<D, decltype(w)::value, CAUSAL, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,
+                           st, Q, K, V, sQ, sK, heads, Nq, Nk, head_group_for(CAUSAL, 3L * Nk * D, 0), static_cast<OutT *>(O));
+    };
+    // More wavefronts per SIMD where there are workgroups for them: 768 (d = 64: 1024) then start at once instead of 512.  Uneven ones even out better
+    // two to a CU while there are few (two / more, us: d = 128, 70 x 1000 causal 30.4 / 33.8 = 560 workgroups, 16 x 6656 174 / 188 = 832, 192 x 668
+    // 39.3 / 43.0 = 1152, 87 x 3837 313 / 332 = 2610; 267 x 768 61.0 / 58.8 = 1602, 222 x 2204 310 / 295 = 3996; d = 64, 130 x 1000 36.9 / 39.7 = 1040,
+    // 144 x 1152 47.4 / 41.1 = 1296), and at d = 128 769 to 1024 even ones, which start in two waves of 512, would do so in two waves of
+    // 768 (71 x 1792 3 % slower, 20 x 5120 4 %; 32 x 5120 11 % faster).
+    const bool uneven = CAUSAL && 2L * Nq >= Nk && T_r > 3;
+    const bool more = uneven ? wgs > (D == 64 ? 1024 : T_r <= 10 ? 1250 : 2700) : wgs > 512 && !(D == 128 && T_r > 3 && wgs > 768 && wgs <= 1024);
+    if (more) launch(std::integral_constant<int, D == 64 ? 4 : 3>{});
+    else launch(std::integral_constant<int, 2>{});
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 

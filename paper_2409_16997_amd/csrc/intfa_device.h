@@ -149,6 +149,13 @@ __device__ __forceinline__ lds_ptr lds_xor(lds_ptr base, unsigned step, unsigned
     return reinterpret_cast<lds_ptr>(static_cast<uintptr_t>(a));
 }
 
+// The lane's index, computed anew (volatile: not moved ahead of where it stands), so that nothing is kept for it through the key loop
+__device__ __forceinline__ int lane_index() {
+    int x;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(x));
+    return x;
+}
+
 // every outstanding memory operation of this wavefront has completed (vmcnt = expcnt = lgkmcnt = 0)
 __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0); }
 

@@ -29,18 +29,19 @@ def _regs(text):
 
 
 @pytest.mark.timeout(600)
-def test_nothing_but_the_next_mfma_of_its_chain_touches_a_chain_start_result():
+@pytest.mark.parametrize("source,kernel,least", [("intfa_attention.hip", "int_flash_attn_fwd_kernel", 8 * 36), ("intfa_attention_half.hip", "int_flash_attn_fwd_half_kernel", 4 * 12)])
+def test_nothing_but_the_next_mfma_of_its_chain_touches_a_chain_start_result(source, kernel, least):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not os.path.exists(hipcc):
         pytest.skip("no hipcc")
     flags = [f for f in hip_build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "attn.s")
-        src = os.path.join(hip_build.CSRC, "intfa_attention.hip")
+        src = os.path.join(hip_build.CSRC, source)
         subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-I", hip_build.INCLUDE, "-I", hip_build.CSRC, src, "-o", out],
                        check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
         lines = open(out).read().splitlines()
-    # Only the fused kernel writes its chain starts as assembly; in the other kernels of the file an MFMA with the same
+    # Only the fused kernels (half-INT8: its lean form) write their chain starts as assembly; in the other kernels an MFMA with the same
     # inline constant is the compiler's own (it folds a single-use splat) and carries the compiler's hazard handling.
     func, owner = None, []
     for ln in lines:
@@ -49,8 +50,8 @@ def test_nothing_but_the_next_mfma_of_its_chain_touches_a_chain_start_result():
             func = m.group(1)
         owner.append(func)
     starts = [i for i, ln in enumerate(lines) if "v_mfma_i32_32x32x32_i8" in ln and ln.rstrip().endswith("0.15915494")
-              and owner[i] and "int_flash_attn_fwd_kernel" in owner[i]]
-    assert len(starts) >= 8 * 24, f"expected the chain starts of every instantiation, found {len(starts)}"
+              and owner[i] and kernel in owner[i]]
+    assert len(starts) >= least, f"expected the chain starts of every instantiation, found {len(starts)}"
     for i in starts:
         dst_txt = lines[i].split("v_mfma_i32_32x32x32_i8")[1].split(",")[0]
         dst = _regs(dst_txt)
