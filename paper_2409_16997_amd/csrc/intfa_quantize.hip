@@ -179,7 +179,8 @@ __global__ __launch_bounds__(256) void quantize_tokenwise_kernel(TokenJob j0, To
 }
 
 // ---- tensor-level, one scale per head ----------------------------------------------------------
-// A head's absmax has to be known before its first code.  Two ways, neither with atomics or slots to clear:
+// A head's absmax has to be known before its first code.  Three ways, none with atomics or slots to clear:
+//   shares several workgroups per head take the absmax of all of it, each writes the codes of its share; one launch;
 //   whole  one workgroup of HEAD_THREADS takes the whole head, keeps its first KEEP_BYTES in registers and reads the rest a
 //          second time right after the first, out of the caches; one launch;
 //   parts  `parts` workgroups per head leave the absmax of their part (fp32 bits) at the START of each of the `regions`
@@ -193,8 +194,9 @@ struct HeadJob {
     int8_t *Xq;
     float *scale;                  // [heads]
     long per_head;
-    int heads, parts, regions;     // parts = 0: whole heads
-    long chunks_per_part, chunks_per_region;   // in chunks of 8 elements; the last part and region take the remainder
+    int heads, parts, regions;     // parts = 0: whole heads, by `shares` workgroups each
+    int shares;
+    long chunks_per_part, chunks_per_region;   // in chunks of 8 elements; the last part and region take the remainder (shares: chunks_per_region each)
 };
 
 template <int THREADS> __device__ __forceinline__ float workgroup_max(float a) {
@@ -269,6 +271,58 @@ template <typename T, int THREADS> __device__ __forceinline__ void head_whole(co
         }
 }
 
+// shares > 1: every one of a head's workgroups takes the absmax of the whole head, beginning with the share whose codes it writes, which stays in
+// registers.  They run on one XCD (8 apart), so what one brings in the others find in its L2: a CU takes in 59 GB/s from beyond it, 120 - 140 out of it.
+// (What it measures: plan_heads().)
+template <typename T> __device__ __forceinline__ void head_share(const HeadJob &hj, long head, int share) {
+    constexpr int KEEP = sizeof(T) == 2 ? KEEP_BYTES / 16384 : KEEP_BYTES / 32768;   // chunks per thread
+    constexpr int U = LOADS_IN_FLIGHT<T>;
+    const T *X = static_cast<const T *>(hj.X) + head * hj.per_head;
+    int8_t *Xq = hj.Xq + head * hj.per_head;
+    const int chunks = static_cast<int>(hj.per_head / 8), tid = threadIdx.x, size = static_cast<int>(hj.chunks_per_region);
+    const int c0 = share * size, c1 = min(chunks, c0 + size);
+    Raw8<T> keep[KEEP];
+    float a = 0.0f, x[8];
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (c0 + tid + i * HEAD_THREADS < c1) keep[i].load(X, 8 * (c0 + tid + i * HEAD_THREADS));
+    // the rest of the head, from the end of the share on and round to its beginning
+    const int rest = chunks - (c1 - c0);
+    auto place = [&](int j) { return c1 + j < chunks ? c1 + j : c1 + j - chunks; };
+    int j = tid;
+    for (; j + (U - 1) * HEAD_THREADS < rest; j += U * HEAD_THREADS) {
+        Raw8<T> r[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) r[i].load(X, 8 * place(j + i * HEAD_THREADS));
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            r[i].widen(x);
+            a = fmaxf(a, absmax8(x));
+        }
+    }
+    for (; j < rest; j += HEAD_THREADS) {
+        load8<T>(X, 8 * place(j), x);
+        a = fmaxf(a, absmax8(x));
+    }
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (c0 + tid + i * HEAD_THREADS < c1) {
+            keep[i].widen(x);
+            a = fmaxf(a, absmax8(x));
+        }
+    a = workgroup_max<HEAD_THREADS>(a);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) keep[i].hold();
+    const float inv = (a == 0.0f) ? 0.0f : 127.0f / a;
+    if (share == 0 && tid == 0) hj.scale[head] = (a == 0.0f) ? 1.0f : a / 127.0f;
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (c0 + tid + i * HEAD_THREADS < c1) {
+            keep[i].widen(x);
+            *reinterpret_cast<uint2 *>(Xq + 8 * (c0 + tid + i * HEAD_THREADS)) = quant8(x, inv);
+        }
+}
+
 template <typename T> __device__ __forceinline__ void head_part_absmax(const HeadJob &hj, long head, int part) {
     constexpr int U = LOADS_IN_FLIGHT<T>;
     const long base = head * hj.per_head, chunks = hj.per_head / 8;
@@ -294,10 +348,12 @@ template <typename T> __device__ __forceinline__ void head_part_absmax(const Hea
         reinterpret_cast<float *>(hj.Xq + base + 8 * r * hj.chunks_per_region)[part] = a;
 }
 
-// What workgroup `wg` of a launch does for V before any row of Q and K is touched; the number of such workgroups is
-// heads (whole) or heads * parts.
+// What workgroup `wg` of a launch does for V before any row of Q and K is touched; the number of such workgroups is head_workgroups().
 template <typename T> __device__ __forceinline__ void head_first_pass(const HeadJob &hj, int wg) {
-    if (hj.parts == 0) head_whole<T, HEAD_THREADS>(hj, wg);
+    if (hj.shares > 1) {
+        const int unit = wg >> 3, head = unit / hj.shares * 8 + (wg & 7);
+        if (head < hj.heads) head_share<T>(hj, head, unit % hj.shares);
+    } else if (hj.parts == 0) head_whole<T, HEAD_THREADS>(hj, wg);
     else head_part_absmax<T>(hj, wg / hj.parts, wg % hj.parts);
 }
 template <typename T> __global__ __launch_bounds__(HEAD_THREADS, 8) void head_first_pass_kernel(HeadJob hj) {
@@ -442,7 +498,7 @@ int launch_tokenwise(const TokenJob &j0, const TokenJob &j1, int jobs, long rows
     });
 }
 
-// Whole heads or parts.  From 96 heads on, whole heads keep enough workgroups busy and the second read of V is partly a
+// Shares, whole heads or parts.  From 96 heads on, whole heads keep enough workgroups busy and the second read of V is partly a
 // cache hit (Q, K, V of 96 x 2048 x 128 fp16: 47 us whole, 55 in parts; 128 x 4096 x 128: 124 and 145).  With fewer heads one workgroup walks its head at about 40 GB/s next to the fixed 4 us, and what
 // the second launch costs (2.5 us) only buys the chip's bandwidth for heads that are long: 4 heads of 256 KB 10.7 us whole
 // and 7.6 in parts, 64 heads of 128 KB 10.2 and 12.0.
@@ -454,8 +510,23 @@ int launch_tokenwise(const TokenJob &j0, const TokenJob &j1, int jobs, long rows
 // 174, 186; 128 x 4096 x 128 fp32 108, 127 / 95, 108; 260 x 2048 x 128 fp16 60, 71 / 56, 66, fp32 121, 135 / 105, 121; 300 x 8192 x 64 fp16 155, 166 / 149, 157;
 // on the other side 128 x 4096 x 128 fp16 49, 67 / 54, 62, 128 x 1024 x 128 fp32 19, 27 / 25, 28, 160 x 4096 x 128 fp16 59, 78 / 66, 78, 256 x 4096 x 128 fp16 101, 117 / 118, 133.
 HeadJob plan_heads(const void *X, long heads, long per_head, int elem_bytes, int8_t *Xq, float *scale, bool alone) {
-    HeadJob hj = {X, Xq, scale, per_head, static_cast<int>(heads), 0, 0, 0, 0};
+    HeadJob hj = {X, Xq, scale, per_head, static_cast<int>(heads), 0, 0, 1, 0, 0};
     const long head_bytes = per_head * elem_bytes, rounds = (heads + 255) / 256;
+    // Up to 64 heads of up to 256 KB (fp32, or 8 to 48 heads beside the rows of Q and K: 384 KB): in shares, one launch instead of two, or of 16 KB and more
+    // per share instead of a whole head, and about as many workgroups as CUs.  Before (whole or parts) / shares, us, Q, K, V in rotation, fp16: 1 x 96 KB
+    // 5.6 / 3.8, 4 x 128 6.8 / 4.9, 8 x 64 5.3 / 4.1, 8 x 192 7.5 / 6.0, 16 x 128 8.8 / 5.5, 32 x 192 13.9 / 9.2, 32 x 384 18.2 / 15.8, 48 x 256 18.7 / 14.6, 64 x 256 20.3 / 18.7; beyond
+    // 1 x 384 7.3 / 7.9, 4 x 384 8.3 / 8.6, 64 x 384 24.2 / 26.9, 80 x 256 20.8 / 22.0.  V alone: 8 x 96 5.5 / 3.8, 32 x 128 8.4 / 5.1, 48 x 256 13.2 / 9.0; 16 x 384 8.2 / 8.7.
+    const long share_limit = elem_bytes == 4 || (!alone && heads >= 8 && heads <= 48) ? 384L << 10 : 256L << 10;
+    if (heads <= 64 && head_bytes <= share_limit) {
+        long n = head_bytes / (16L << 10);
+        if (n > 12) n = 12;
+        if (n > 224 / heads) n = 224 / heads;
+        if (n >= 2 && head_bytes <= n * KEEP_BYTES) {
+            hj.shares = static_cast<int>(n);
+            hj.chunks_per_region = (per_head / 8 + n - 1) / n;
+            return hj;
+        }
+    }
     const bool uneven = alone && 8 * heads < 5 * 256 * rounds && head_bytes > (heads > 256 ? 256L << 10 : 1L << 20);
     const bool beside = !alone && heads >= (elem_bytes == 2 ? 64 : 80) && head_bytes <= (1L << 20);
     if (beside || (heads >= 96 && per_head < (1L << 29) && !uneven) || head_bytes <= (64L << 10) + (heads < 96 ? heads * (4L << 10) : 0)) return hj;
@@ -470,7 +541,10 @@ HeadJob plan_heads(const void *X, long heads, long per_head, int elem_bytes, int
     hj.regions = split((1024 + heads - 1) / heads, hj.chunks_per_region);   // 8 KB of codes or more: the words of 64 parts fit
     return hj;
 }
-int head_workgroups(const HeadJob &hj) { return hj.parts == 0 ? hj.heads : hj.heads * hj.parts; }
+int head_workgroups(const HeadJob &hj) {
+    if (hj.shares > 1) return (hj.heads + 7) / 8 * 8 * hj.shares;
+    return hj.parts == 0 ? hj.heads : hj.heads * hj.parts;
+}
 
 template <typename T> int launch_head_second(const HeadJob &hj, hipStream_t st) {
     if (hj.parts > 0)

@@ -47,3 +47,17 @@ def test_headwise_codes_and_scales(heads, N, d, dtype):
     for x, c, sc in ((Q, out[0], out[3]), (K, out[1], out[4])):
         rq, rs = ifa.quantize_tokenwise(x)
         assert torch.equal(c, rq) and torch.equal(sc, rs)
+
+
+# In shares: 32 KB a head (two shares) up to 256 or 384 KB (twelve), 64 heads; shares that do not divide the head, ends of the registers (96 KB a share
+# with 64 heads of 256 KB + and 48 of 384), head counts that fill no round of eight, and the sizes on the other side of each line.
+SHARES = [
+    (1, 127, 128), (1, 128, 128), (1, 255, 64), (1, 256, 64), (3, 129, 128), (8, 131, 128), (9, 1023, 128), (1, 1024, 128), (1, 1025, 128),
+    (7, 1537, 64), (8, 1536, 128), (8, 1537, 128), (16, 769, 64), (31, 333, 128), (48, 768, 128), (48, 1536, 128), (49, 1023, 64), (63, 512, 128), (64, 511, 128),
+    (64, 1024, 128), (65, 512, 128), (64, 1025, 64)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("heads,N,d", SHARES)
+def test_heads_in_shares(heads, N, d, dtype):
+    test_headwise_codes_and_scales(heads, N, d, dtype)
