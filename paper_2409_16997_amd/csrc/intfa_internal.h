@@ -54,9 +54,14 @@ static inline bool ifa_packed_queries(int heads, int Nq, int Nk, int d) {
 //                                   32 x 448 x 448 10.6 (fused) / 10.8, 160 x 64 x 300 10.0 / 10.8; d = 64, 24 x 384 x 450 9.7 / 7.8, 130 x 64 x 300 7.2 / 7.5.
 //                                   Half of the key blocks masked: the heaviest workgroup decides, and the two waves of the few-query kernel, which
 //                                   takes such calls from 2048 keys on, even out: 2 x 5000 33 (few-query) / 37, 1 x 14000 87 / 89; but 3 x 5000 45 / 38, 8 x 2048 22.8 / 20.4
-//   more, half of the blocks masked twice as many and smaller workgroups than the fused kernel's even out better: 8 x 4096 56 (fused) / 41, 4 x 8192 107 / 69,
-//                                   1 x 32768 410 / 236, 16 x 2048 x 2048 30.7 / 27.8, 5 x 8192 115 / 99; then not: 20 x 1600 25.8 / 25.9, 12 x 3200 45.5 / 45.5, 7 x 8192 112 / 119.
-//                                   From 513 workgroups on the gain is spent the sooner the more keys lie in front of the queries, where all blocks are visible
+//   more, some of the blocks masked twice as many and smaller workgroups than the fused kernel's even out better, up to 512 of them the sooner the fewer they are: the
+//                                   other one's heaviest workgroup decides, this one's second wave is light and short.  The line (key sequences from
+//                                   4 w - 100 keys on, d = 64 3 w - 200, w workgroups) fitted to 2035 calls: of the kernels it takes one 0.4 % slower on average than the fastest
+//                                   (from 2048 keys on and with at most twice as many keys as queries only, 3.9 %).  Before (fused) / this one: 10 x 1996 d = 64 24.5 / 15.5,
+//                                   12 x 1518 d = 64 19.3 / 12.6, 12 x 1444 22.8 / 17.6, 3 x 5898 x 14531 187 / 132, 8 x 3084 x 7287 d = 64 82 / 67, 8 x 4096 56 / 41, 4 x 8192 107 / 69;
+//                                   not 24 x 757 14.3 / 15.9, 24 x 732 x 1629 25.8 / 28.7, 32 x 892 x 1979 31.5 / 33.6.
+//                                   Beyond 512, half of the blocks masked: 1 x 32768 410 / 236, 5 x 8192 115 / 99, 10 x 3380 d = 64 39.9 / 32.8; then not: 20 x 1600 25.8 / 25.9, 12 x 3200
+//                                   45.5 / 45.5, 7 x 8192 112 / 119.  The gain is spent the sooner the more keys lie in front of the queries, where all blocks are visible
 //                                   (fused -> this one, d = 128 / 64): 8 x 6124 x 6124 84.0 -> 82.9 / 68.9 -> 65.3, 8 x 5612 x 7015 101.6 -> 102.2 / 81.5 -> 81.3; beyond `keys`
 //                                   8 x 5612 x 8418 126 -> 127 / 99 -> 101, 8 x 6124 x 12248 195 -> 206 / 147 -> 161, 4 x 12268 x 24536 382 -> 394 / 287 -> 310
 //   more, all blocks visible        two waves of workgroups against one of the fused kernel's: 48 x 512 x 8192 107 (fused) / 111
@@ -65,8 +70,10 @@ static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causa
     const long wgs = static_cast<long>(heads) * ((Nq + 63) / 64);
     const bool uneven = causal && 2L * Nq >= Nk;
     if (wgs <= 256) return Nk >= (d == 128 ? 512 : 384) && !(uneven && Nk >= 2048 && (heads == 1 || wgs <= 192));
+    if (!causal || 4L * Nq < Nk) return false;
+    if (wgs <= 512) return Nk >= (d == 128 ? 4 * wgs - 100 : 3 * wgs - 200) && (uneven || Nk >= (d == 128 ? 3000 : 2048));
     const long keys = 56L << 10;                                 // of all heads
-    return uneven && Nk >= 2048 && (wgs <= 512 || (heads <= 8 && wgs <= 768 && heads * static_cast<long>(Nk) <= keys));
+    return uneven && Nk >= 2048 && heads * static_cast<long>(Nk) <= keys && ((heads <= 8 && wgs <= 768) || (wgs <= 576 && Nk >= (d == 128 ? 4000 : 3000)));
 }
 
 // Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  The

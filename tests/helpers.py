@@ -47,7 +47,11 @@ def route(heads, Nq, Nk, d, causal=None, half=False):
             if wgs <= 256:
                 pair = Nk >= (512 if d == 128 else 384) and not (uneven and Nk >= 2048 and (heads == 1 or wgs <= 192))
             else:
-                pair = uneven and Nk >= 2048 and (wgs <= 512 or heads <= 8 and wgs <= 768 and heads * Nk <= 56 << 10)
+                line = 4 * wgs - 100 if d == 128 else 3 * wgs - 200
+                if wgs <= 512:
+                    pair = causal and 4 * Nq >= Nk >= line and (uneven or Nk >= (3000 if d == 128 else 2048))
+                else:
+                    pair = uneven and Nk >= 2048 and heads * Nk <= 56 << 10 and (heads <= 8 and wgs <= 768 or wgs <= 576 and Nk >= (4000 if d == 128 else 3000))
             if pair:
                 return "pair"
         if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (768 if groups <= 1024 else 1152) if Nq <= 32 else

@@ -88,6 +88,15 @@ def test_rows_of_calls_with_more_workgroups_than_cus(heads, Nq, Nk, d, vblock):
         assert bool(((out - ref).abs() <= 2.0 ** -21 * ref.abs()).all()) if vblock else torch.equal(out, ref), (a, b)
 
 
+# ... on fewer keys, the sooner the fewer workgroups, with up to four times as many keys as queries, and a little beyond 512 of them
+@pytest.mark.gpu
+@pytest.mark.parametrize("vblock", [False, True])
+@pytest.mark.parametrize("heads,Nq,Nk,d", [(12, 1444, 1444, 128), (10, 1996, 1996, 64), (26, 659, 659, 64), (19, 1000, 1117, 128), (3, 5898, 14531, 128), (8, 2050, 8200, 64),
+                                           (10, 3380, 3380, 64), (9, 4010, 4010, 128)])
+def test_rows_of_calls_with_a_short_second_wave(heads, Nq, Nk, d, vblock):
+    test_rows_of_calls_with_more_workgroups_than_cus(heads, Nq, Nk, d, vblock)
+
+
 # 2-byte outputs are the fp32 rows rounded once, and nothing around O is written
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])

@@ -498,7 +498,7 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
     # A call with a few queries per head (a decode step, a short chunk) runs a kernel of its own that splits every key
     # block over the wavefronts of a workgroup; it performs the arithmetic of the square kernel on the same operands, so
     # its rows are the last Nq rows of the square problem bit for bit, with and without the mask, on a ragged length.
-    H, N = 15, 1231
+    H, N = 30, 1231
     assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == "few" for c in (False, True))
     rng = np.random.default_rng(Nq * 131 + d)
     Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, N, d, score_sigma=2.0)
@@ -515,7 +515,7 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
 @pytest.mark.parametrize("Nq", [1, 7, 33, 64])
 def test_few_query_calls_with_blockwise_v_scales_equal_the_square_kernel_rows(ifa, Nq, d):
     # the same with one V scale per key block (the running output is carried in units of the current block's scale)
-    H, N = 15, 1231
+    H, N = 30, 1231
     assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == "few" for c in (False, True))
     rng = np.random.default_rng(Nq * 17 + d)
     Qq, Kq, Vq, sQ, sK, _ = random_int8_problem(rng, H, N, d, score_sigma=2.0)
