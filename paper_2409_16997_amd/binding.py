@@ -71,7 +71,7 @@ def lib():
 _native = None
 _NATIVE_PATH = os.path.join(_HERE, "_intfa_host.so")
 # the functions of the C ABI that the module calls, in its order
-_NATIVE_CALLS = ("quantize_tokenwise_ex", "quantize_headwise_ex", "quantize_qkv", "quantize_qk", "int_flash_attn_fwd_rect", "int_flash_attn_fwd_vblock_rect",
+_NATIVE_CALLS = ("quantize_tokenwise_ex", "quantize_headwise_ex", "quantize_blockwise", "quantize_qkv", "quantize_qk", "int_flash_attn_fwd_rect", "int_flash_attn_fwd_vblock_rect",
                  "int_flash_attn_fwd_half_rect", "int_flash_attn_fwd_splitk", "int_flash_attn_fwd_splitk_static", "ifa_block_cols")
 
 
@@ -247,6 +247,9 @@ def quantize_qk(Q, K, s_Q_mul=1.0, hadamard=False, out=None):
 
 def quantize_blockwise(X, block_keys):
     """X [B, H, N, d] (or [heads, N, d]) -> (int8 same shape, fp32 scale [B, H, ceil(N/block_keys)])."""
+    r = (_native or _load_native()).blockwise(X, block_keys)
+    if r is not None:
+        return r
     x = _dev(X)
     shape = X.shape
     N, d = shape[-2], shape[-1]

@@ -35,7 +35,7 @@ def _host_command():
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DINTFA_TORCH_VERSION="{torch.__version__}"', "-I", INCLUDE, "-isystem", os.path.join(root, "include"),
             "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"], "-Wall", HOST_SRC, "-o", HOST_LIB,
-            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10", "-lc10_hip"]
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:

@@ -1,6 +1,6 @@
 // The Python binding's plain calls, natively: take the tensors apart, allocate the outputs, call the C ABI on torch's current stream.
 // What such a call costs the host bounds every small shape (quantize Q, K, V of one 128 x 64 head and attend: 26.1 us a pass with the
-// arguments taken apart and the seven outputs allocated in Python, 13.6 like this, of which the two kernels take 6.6; a first pass on new inputs 38 and 24).
+// arguments taken apart and the seven outputs allocated in Python, 11.1 like this, of which the two kernels take 6.6; a first pass on new inputs 38 and 24).
 //
 // Every function returns None for anything but the plain case -- a tensor subclass, an active torch function or dispatch mode, a tensor
 // that is not contiguous, not on the current device or of another type, shapes that do not agree, a call that the C ABI refuses -- and
@@ -9,8 +9,7 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/PythonTorchFunctionTLS.h>
-#include <ATen/ops/empty.h>
-#include <ATen/ops/empty_like.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
@@ -25,6 +24,7 @@ namespace {
 struct Abi {
     decltype(&::quantize_tokenwise_ex) tokenwise;
     decltype(&::quantize_headwise_ex) headwise;
+    decltype(&::quantize_blockwise) blockwise;
     decltype(&::quantize_qkv) qkv;
     decltype(&::quantize_qk) qk;
     decltype(&::int_flash_attn_fwd_rect) fwd;
@@ -62,8 +62,11 @@ bool modes() { return at::impl::torch_function_mode_enabled() || c10::impl::Torc
 int dtype_enum(at::ScalarType t) { return t == at::kFloat ? IFA_F32 : t == at::kHalf ? IFA_F16 : t == at::kBFloat16 ? IFA_BF16 : -1; }
 signed char *i8(const at::Tensor &t) { return static_cast<signed char *>(t.data_ptr()); }
 float *f32(const at::Tensor &t) { return static_cast<float *>(t.data_ptr()); }
-at::Tensor codes(const at::Tensor &x) { return at::empty_like(x, x.options().dtype(at::kChar)); }
-at::Tensor scales(const at::Tensor &x, at::IntArrayRef shape) { return at::empty(shape, at::TensorOptions().dtype(at::kFloat).device(x.device())); }
+// Outputs, straight from the caching allocator: nothing between here and there (autograd of integers, a mode, a subclass) has anything to do for a
+// plain call, and every output is written whole.  The six outputs of quantize_qkv: 2.9 us of host, 4.9 through the dispatcher.
+at::Tensor like(const at::Tensor &x, at::ScalarType dtype) { return at::detail::empty_strided_cuda(x.sizes(), x.strides(), dtype, x.device()); }
+at::Tensor codes(const at::Tensor &x) { return like(x, at::kChar); }
+at::Tensor scales(const at::Tensor &x, at::IntArrayRef shape) { return at::detail::empty_cuda(shape, at::kFloat, x.device(), std::nullopt); }
 // One call of the C ABI (which does not throw) without the GIL.  The arguments, data_ptr() among them, which can throw, are evaluated before it is released.
 template <typename... P, typename... A> int unlocked(int (*fn)(P...), A... a) {
     PyThreadState *const state = PyEval_SaveThread();
@@ -136,6 +139,26 @@ PyObject *headwise(PyObject *, PyObject *const *a, Py_ssize_t n) {
     });
 }
 
+// quantize_blockwise(X, block_keys)
+PyObject *blockwise(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    return guarded([&](c10::DeviceIndex dev) -> PyObject * {
+        const at::Tensor *x = n == 2 ? plain(a[0], dev) : nullptr;
+        if (!x || x->dim() < 2 || dtype_enum(x->scalar_type()) < 0 || !PyLong_CheckExact(a[1])) return nullptr;
+        int overflow = 0;
+        const long block = PyLong_AsLongAndOverflow(a[1], &overflow);
+        if (overflow || block <= 0 || block > INT_MAX) return nullptr;
+        const auto shape = x->sizes();
+        const long d = shape.back(), N = shape[shape.size() - 2];
+        if (d > INT_MAX) return nullptr;
+        c10::SmallVector<int64_t, 5> sshape(shape.begin(), shape.end() - 1);
+        sshape.back() = (N + block - 1) / block;
+        at::Tensor q = codes(*x), s = scales(*x, sshape);
+        const hipStream_t st = stream(dev);
+        const int rc = unlocked(abi.blockwise, x->data_ptr(), dtype_enum(x->scalar_type()), x->numel() / (N * d), N, static_cast<int>(d), static_cast<int>(block), i8(q), f32(s), st);
+        return succeeded(rc, "quantize_blockwise") ? tuple({q, s}) : nullptr;
+    });
+}
+
 // quantize_qkv(Q, K, V, s_Q_mul)
 PyObject *qkv(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return guarded([&](c10::DeviceIndex dev) -> PyObject * {
@@ -189,7 +212,7 @@ struct Call {
         causal = causal_ == Py_True;
         const at::ScalarType ot = out_dtype == Py_None ? at::kHalf : THPDtype_Check(out_dtype) ? reinterpret_cast<THPDtype *>(out_dtype)->scalar_type : at::kChar;
         if ((o_dtype = dtype_enum(ot)) < 0) return false;
-        out = at::empty_like(*q, q->options().dtype(ot));
+        out = like(*q, ot);
         return true;
     }
 };
@@ -236,7 +259,7 @@ PyObject *splitk(PyObject *, PyObject *const *a, Py_ssize_t n) {
 }
 
 #define FASTCALL(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {FASTCALL(init), FASTCALL(tokenwise), FASTCALL(headwise), FASTCALL(qkv), FASTCALL(qk), FASTCALL(fwd), FASTCALL(half), FASTCALL(splitk), {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {FASTCALL(init), FASTCALL(tokenwise), FASTCALL(headwise), FASTCALL(blockwise), FASTCALL(qkv), FASTCALL(qk), FASTCALL(fwd), FASTCALL(half), FASTCALL(splitk), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_intfa_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -151,3 +151,20 @@ def test_calls_run_on_the_current_stream():
         assert torch.equal(a, b)
     assert torch.equal(O[0], want_O) and torch.equal(O[1], ifa.int_flash_attn_fwd_half(q8, k8, new, sq, sk, causal=True))
     assert torch.equal(O[2], want_O[:, :, -8:])
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("shape,block", [((2, 3, 300, 128), 128), ((1, 1, 1, 64), 64), ((5, 129, 64), 128), ((7, 8, 32), 3), ((2, 2, 2, 33, 64), 256), ((4, 100, 8), 100)])
+def test_quantize_blockwise_on_both_paths(shape, block, dtype):
+    import paper_2409_16997_amd as ifa
+    from paper_2409_16997_amd import binding
+    X = torch.randn(shape, device="cuda").to(dtype)
+    if len(shape) == 4:
+        X = X.transpose(0, 1).contiguous().transpose(0, 1) if shape[0] == 1 or shape[1] == 1 else X      # (a stride of a dimension of one kept as it is)
+    a, b = ifa.quantize_blockwise(X, block), general(lambda: ifa.quantize_blockwise(X, block))
+    for x, y in zip(a, b):
+        assert x.dtype is y.dtype and x.shape == y.shape and x.stride() == y.stride() and torch.equal(x, y)
+    for bad in (0, -1, 1 << 40):                                 # the same refusals
+        for path in (lambda f: f(), general):
+            with pytest.raises((binding.IntfaError, ZeroDivisionError, RuntimeError)):
+                path(lambda: ifa.quantize_blockwise(X, bad))
