@@ -1,5 +1,5 @@
 // INT-FlashAttention forward (Algorithm 1) for gfx950: calls with few queries per head (a decode step, a few draft
-// tokens, a short chunk of a prefill).  Four families, all built from the tile code of the fused kernel
+// tokens, a short chunk of a prefill).  Five families, all built from the tile code of the fused kernel
 // (intfa_attention_tiles.h: same LDS layout, same MFMA operand order, same staging copies) and the same arithmetic:
 //   int_flash_attn_fwd_packed_kernel   one workgroup of four wavefronts per head and group of 32 queries, one key block at a time;
 //                                      the calls of ifa_packed_queries();
@@ -7,6 +7,8 @@
 //   int_flash_attn_fwd_narrow_kernel   one or two workgroups per head and group of 32 queries, the key blocks split over
 //                                      their wavefronts; bit-identical to the fused kernel's rows, needs no memory
 //                                      beyond inputs and outputs; the calls of ifa_few_queries();
+//   int_flash_attn_fwd_decode_kernel   two or four workgroups per head with one query, 16 key blocks at a time; the calls of the few-query kernel
+//                                      that ifa_decode_query() names;
 //   splitk_*                           the key axis of a head split over many workgroups, exactly: lines 9-10 for every
 //                                      block first, then lines 11-13 on the known running maximum, then a merge;
 //                                      int_flash_attn_fwd_splitk (caller's workspace) and _splitk_static (built in).
@@ -16,6 +18,7 @@
 #include <stdint.h>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include "intfa.h"
 #include "intfa_internal.h"
@@ -869,6 +872,274 @@ __global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_packed_kernel(
 #endif
 }
 
+// ---- one query per head (a decode step) ---------------------------------------------------------------------------
+// The few-query kernel forms P for 32 queries two key blocks at a time, with two barriers and the chain MFMA - scale - exchange - exp - exchange - MFMA in
+// each such step (1.0 us), also where there is one query.  Here a workgroup takes a WINDOW of 16 key blocks at once, one to each of its 16 wavefronts, and
+// a wavefront does everything for its own block:
+//   line 9 key tile by key tile, the integer sums of the one query to LDS; then, four keys to a lane, their scaling and the extremum of the
+//   block; (barrier) the running maximum in front of it from the extrema of all, P, alpha and row sum; P V of the block, its sums to LDS;
+//   (barrier) a thread per output column folds the blocks of the window in order: lines 12 and 13.
+// Two barriers per 2048 keys.  K and V come through a ring per wavefront, ordered by its counted waits, which runs on through the barriers.  Four (d = 64: two)
+// workgroups per head, on one XCD, have 32 columns of V and O each; all read K, each beginning with another of a wavefront's tiles: what one
+// brings in, the others find in L2 (a CU takes in 59 GB/s from beyond it and 120 - 140 out of it).
+// What bounds it is the chain of a wavefront through a window, 5 us at d = 128 (4.9 with the next entry of the ring requested before the operands of this one are read,
+// as it is; 5.9 with the place of this one refilled once they are read, twice as much in flight; with products of 32 x 32 x 32, whose chains are
+// twice as long, 5.9 and 6.2; eight wavefronts with two blocks each and 32 x 32 x 32 6.4), beside 2.3 us that 320 KB take at best.  Few-query kernel / this one, us, in a graph:
+// 32 heads x 4099 keys 20.7 / 14.6, 8 x 2603 13.1 / 8.9, 64 x 579 6.3 / 4.9, 16 x 16384 64.8 / 42.1, 64 x 18595 97.6 / 79; d = 64, 32 x 4099 16.2 / 11.0, 64 x 32768 109 / 74.
+// The numbers are those of the other kernels: integer sums, the maximum is order-independent, the row sum is kept per half of the keys (bit 2 of the key's index)
+// as their lanes do, and the fp32 folds are the same, block by block.
+constexpr int DEC_WAVES = 16, DEC_THREADS = DEC_WAVES * 64;      // wavefronts = key blocks per window
+template <int D, int DS> struct DecodePlan {
+    static constexpr int DV = D / DS;
+    static constexpr int VE = 4 / DS;                            // ring entries (32 D bytes) of V, 32 DS keys each, behind four key tiles of K
+    static constexpr int EPW = 4 + VE;                           // ... per window
+    static constexpr int R = D == 128 ? 2 : 4;                   // entries of the ring, one of them being read
+    static constexpr int copies(int k) { return D / 32 + (k % EPW == 0 ? 2 : 0); }   // of entry k (the first of a window brings the s_K)
+    static constexpr int behind(int k) { int n = 0; for (int j = 1; j < R - 1; ++j) n += copies(k + j); return n; }   // in flight behind entry k
+};
+template <int D, int DS> struct SmemDecode {
+    using P = DecodePlan<D, DS>;
+    alignas(4096) int8_t ring[DEC_WAVES][P::R][32 * D];
+    alignas(16) int s[DEC_WAVES][BC];                            // Q K^T of the wavefront's block; then its P bytes (8 dwords per key tile)
+    alignas(256) float sk[2][DEC_WAVES][BC];                     // of this window and the next
+    alignas(16) float pv[DEC_WAVES][P::DV];                      // minus P V, units of 2^26
+    alignas(16) float ext[DEC_WAVES];                            // extremum of a per block (line 10)
+    alignas(16) float alpha[DEC_WAVES];                          // e^(m_old - m)
+    alignas(16) float psum[DEC_WAVES][2];                        // the row sums over either half of the keys
+};
+static_assert(sizeof(SmemDecode<128, 4>) <= 160 * 1024 && sizeof(SmemDecode<64, 2>) <= 160 * 1024, "LDS budget");
+
+template <typename F, int... I> __device__ __forceinline__ void for_each_int(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int CTRL> __device__ __forceinline__ unsigned dpp(unsigned old, unsigned x) {
+    return static_cast<unsigned>(__builtin_amdgcn_update_dpp(static_cast<int>(old), static_cast<int>(x), CTRL, 0xf, 0xf, false));
+}
+constexpr int ROW_SHR = 0x110, ROW_ROR = 0x120;
+// minimum over the 32 lanes of a half wavefront; sum over those of them of one parity
+__device__ __forceinline__ float half_min(float x) {
+    for_each_int([&](auto i) {
+        const unsigned u = __float_as_uint(x);
+        x = fminf(x, __uint_as_float(dpp<ROW_ROR | (1 << decltype(i)::value)>(u, u)));
+    }, std::make_integer_sequence<int, 4>{});
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fminf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+}
+__device__ __forceinline__ unsigned parity_sum(unsigned x) {
+    x += dpp<ROW_ROR | 8>(x, x);
+    x += dpp<ROW_ROR | 4>(x, x);
+    x += dpp<ROW_ROR | 2>(x, x);
+    const auto sw = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return sw[0] + sw[1];
+}
+__device__ __forceinline__ float lane_value(float x, int lane) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), lane)); }
+#endif
+
+template <int D, int DS>
+__global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_decode_kernel(
+    const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
+    const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
+    int heads, int Nk, int vblock, int o_dtype, void *__restrict__ O) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using P = DecodePlan<D, DS>;
+    __shared__ SmemDecode<D, DS> sm;
+    constexpr int KS = D / 32, KK = D / 64, DV = P::DV, VE = P::VE, EPW = P::EPW, R = P::R;
+    static_assert(DV == 32, "one d tile");
+
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, c = lane & 15, G = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T_c = (Nk + BC - 1) / BC, windows = (T_c + DEC_WAVES - 1) / DEC_WAVES;
+    int head, qg, part;
+    if (!map_query_group<DS>(blockIdx.x, heads, 1, head, qg, part)) return;
+    const int col0 = part * DV;                                  // first column of V and O
+
+    const BufRsrc rK = make_rsrc(K + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+    const BufRsrc rSK = make_rsrc(sK + static_cast<long>(head) * Nk, static_cast<unsigned>(Nk) * 4);
+    const LaneOffsets<D> lo(lane, 0);
+    const lds_ptr ring = (lds_ptr)(&sm.ring[wave][0][0]), skbuf = (lds_ptr)(&sm.sk[0][wave][0]);
+    const unsigned gv = (lane / (DV / 16)) * D + col0 + 16 * (lane % (DV / 16));    // V: whole rows of DV bytes, which the transposing reads take without conflicts
+    const int turn = part * (4 / DS);                            // which of its key tiles a wavefront begins with
+    int in = 0, slot = 0;                                                // of the ring: the oldest entry's
+    // entry k of window w into the ring; what lies past the end comes as zeros, what is past the last window is requested nowhere: the counts stay valid
+    auto issue = [&](auto k_, int w) {
+        constexpr int k = decltype(k_)::value % EPW;
+        const int key0 = (w * DEC_WAVES + wave) * BC;            // first key of this wavefront's block
+        const lds_ptr dst = ring + in * (32 * D);
+        in = in + 1 == R ? 0 : in + 1;
+        if constexpr (k < 4) {
+            const int key = key0 + 32 * ((k + turn) & 3), off = key < Nk ? key * D : NOWHERE;
+#pragma unroll
+            for (int i = 0; i < KS; ++i) lds_copy16(rK, dst + 1024 * i, lo.gk, off + 1024 * i);
+            if constexpr (k == 0) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) lds_copy4(rSK, skbuf + (w & 1) * (DEC_WAVES * BC * 4) + 256 * i, 4 * lane, key0 + 64 * i < Nk ? (key0 + 64 * i) * 4 : NOWHERE);
+            }
+        } else {
+            const int key = key0 + 32 * DS * (k - 4), off = key < Nk ? key * D : NOWHERE;
+#pragma unroll
+            for (int i = 0; i < KS; ++i) lds_copy16(rV, dst + 1024 * i, gv, off + i * (1024 / DV) * D);
+        }
+    };
+    for_each_int([&](auto k) { issue(k, 0); }, std::make_integer_sequence<int, R - 1>{});
+
+    // line 5, in every column of the operand.  The products are 16 x 16 x 64: half of the work of 32 x 32 x 32 goes to columns that nobody asked for, and
+    // their chains are half as long.  Lane (c, G) = (lane % 16, lane / 16) holds 16 bytes from 16 G on of row c, and of the result rows 4 G .. 4 G + 3 of column c.
+    const int8_t *qptr = Q + static_cast<long>(head) * D + 16 * G;
+    v4i qf[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 64 * kk);
+    float nq2 = sQ[head] * (-LOG2E * ACC_UNIT);
+    // landed BEFORE the loop as far as the compiler is concerned: a wait of its own inside would be a wait for the copies as well
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qf[kk]));
+    asm volatile("" : "+v"(nq2));
+    const v4i acc0 = {ACC_START_I, ACC_START_I, ACC_START_I, ACC_START_I};   // what both accumulations start from
+    const unsigned k0 = c * D + 16 * (G ^ k_swz<D>(c));          // K operand (see LaneOffsets): the next 64 columns at k0 ^ 64, the next 16 keys, which the swizzle does not see, at + 16 D
+    // transposing read of V, keys 16 G .. 16 G + 7 of 64: lane i of the group addresses row i / 2, byte half i % 2, and receives column i
+    const unsigned v0 = (16 * G + (c >> 1)) * DV + 8 * (c & 1);
+
+    const float *sVh = vblock ? sV + static_cast<long>(head) * T_c : sV + head;
+    float carry = -INFINITY;                                     // m in front of the window (line 6)
+    float o = 0.0f, l0 = 0.0f, l1 = 0.0f, sv_prev = 1.0f;        // of column tid
+    int *const pbytes = &sm.s[wave][0];
+
+    for (int w = 0; w < windows; ++w) {
+        const bool mine = w * DEC_WAVES + wave < T_c;            // (wave-uniform) the last window may have no block for this wavefront
+        // the coming entry has landed; the one R - 1 further on goes into the place of the last one; take(where it is) reads it
+        auto advance = [&](auto k_, auto take) {
+            constexpr int k = decltype(k_)::value;
+            wait_vmcnt<P::behind(k)>();
+            __builtin_amdgcn_sched_barrier(0);
+            issue(std::integral_constant<int, k + R - 1>{}, w + (k + R - 1) / EPW);
+            __builtin_amdgcn_sched_barrier(0);
+            take(ring + slot * (32 * D));
+            slot = slot + 1 == R ? 0 : slot + 1;
+        };
+        float a[4], bmin = INFINITY;
+        if (mine) {
+        // line 9, integer part, key tile by key tile; the lanes of one column hand the sums on
+        for_each_int([&](auto k) {
+            const int tile = (decltype(k)::value + turn) & 3;
+            v4i kop[2][KK], sacc[2];
+            advance(k, [&](lds_ptr ks) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk) kop[h][kk] = *reinterpret_cast<LDS_AS const v4i *>(lds_xor(ks, 64 * kk, k0) + 16 * D * h);
+            });
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) sacc[h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kop[h][kk], qf[kk], kk == 0 ? acc0 : sacc[h], 0, 0, 0);
+            if (c == 0) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) *reinterpret_cast<v4i *>(&sm.s[wave][32 * tile + 16 * h + 4 * G]) = sacc[h];
+            }
+        }, std::make_integer_sequence<int, 4>{});
+        // line 9, fp32 part, and the extremum of the block: keys 4 r .. 4 r + 3 of it (lanes 32 - 63 repeat lanes 0 - 31); the one query sees every key there is
+        const int left = Nk - ((w * DEC_WAVES + wave) * BC + 4 * r);
+        const v4f skv = *reinterpret_cast<const v4f *>(&sm.sk[w & 1][wave][4 * r]);
+        const v4i acc = *reinterpret_cast<const v4i *>(&sm.s[wave][4 * r]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float x = (ACC_START_F - __int_as_float(acc[e])) * skv[e];
+            if (e >= left) x = INFINITY;
+            a[e] = x;
+            bmin = fminf(bmin, x);
+        }
+        bmin = half_min(bmin);
+        }
+        if (lane == 0) sm.ext[wave] = bmin;
+        __syncthreads();
+        // lines 10, 11 and the row sums of 12
+        const float x = sm.ext[lane & 15];
+        float upto = x;                                          // extremum over the blocks up to this one
+        for_each_int([&](auto i) {
+            constexpr int n = 1 << decltype(i)::value;
+            upto = fminf(upto, __uint_as_float(dpp<ROW_SHR | n>(0x7f800000u, __float_as_uint(upto))));
+        }, std::make_integer_sequence<int, 4>{});
+        const float m_old = wave ? fmaxf(carry, lane_value(upto, wave - 1) * nq2) : carry, m = fmaxf(m_old, lane_value(x, wave) * nq2), mm = m - LOG2_R_NORM;
+        carry = fmaxf(carry, lane_value(upto, 15) * nq2);
+        if (mine) {
+        float y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[e], nq2, -mm));
+        const uint32_t p = pack_p4(y);
+        pbytes[r] = static_cast<int>(p);
+        const unsigned sum = parity_sum(__builtin_amdgcn_sad_u8(p, 0u, 0u));
+        if (lane < 2) sm.psum[wave][lane] = static_cast<float>(sum);
+        if (lane == 0) sm.alpha[wave] = __builtin_amdgcn_exp2f(m_old - m);
+        // line 13, P V of the block
+        v4i pacc[2];
+        for_each_int([&](auto e_) {
+            constexpr int e = decltype(e_)::value, N64 = DS / 2; // runs of 64 keys in an entry
+            v4i vop[N64][2], pf[N64];
+            advance(std::integral_constant<int, 4 + e>{}, [&](lds_ptr vs) {
+#pragma unroll
+                for (int t = 0; t < N64; ++t) {
+#pragma unroll
+                    for (int dt = 0; dt < 2; ++dt) {
+                        const lds_ptr va = vs + v0 + 64 * t * DV + 16 * dt;
+                        const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(va));
+                        const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(va + 8 * DV));
+                        vop[t][dt] = v4i{t0[0], t0[1], t1[0], t1[1]};
+                    }
+                    pf[t] = *reinterpret_cast<const v4i *>(&pbytes[16 * (e * N64 + t) + 4 * G]);
+                }
+            });
+#pragma unroll
+            for (int t = 0; t < N64; ++t)
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt) pacc[dt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vop[t][dt], pf[t], e + t == 0 ? acc0 : pacc[dt], 0, 0, 0);
+        }, std::make_integer_sequence<int, VE>{});
+        if (c == 0) {
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt) {
+                v4f t;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] = ACC_START_F - __int_as_float(pacc[dt][i]);
+                *reinterpret_cast<v4f *>(&sm.pv[wave][16 * dt + 4 * G]) = t;
+            }
+        }
+        }
+        __syncthreads();
+        // lines 12, 13: the blocks of the window in order
+        if (tid < DV) {
+            float t[DEC_WAVES], al[DEC_WAVES], ps[DEC_WAVES][2];
+#pragma unroll
+            for (int b = 0; b < DEC_WAVES; ++b) { t[b] = sm.pv[b][tid]; al[b] = sm.alpha[b]; ps[b][0] = sm.psum[b][0]; ps[b][1] = sm.psum[b][1]; }
+#pragma unroll
+            for (int b = 0; b < DEC_WAVES; ++b) {
+                const int jb = w * DEC_WAVES + b;
+                if (jb < T_c) {
+                    float alpha_o = al[b];
+                    if (vblock) {                                // one V scale per key block: the running output is kept in units of the current block's
+                        const float sv_j = sVh[jb];
+                        alpha_o = al[b] * (sv_prev * __builtin_amdgcn_rcpf(sv_j));
+                        sv_prev = sv_j;
+                    }
+                    l0 = __builtin_fmaf(l0, al[b], ps[b][0]);
+                    l1 = __builtin_fmaf(l1, al[b], ps[b][1]);
+                    o = __builtin_fmaf(o, alpha_o, -t[b]);
+                }
+            }
+        }
+    }
+    wait_all_memory();                                           // requests past the last window: nothing of mine stays in flight
+
+    // lines 15-17
+    if (tid < DV) {
+        const float f = (vblock ? sv_prev : sVh[0]) * ACC_UNIT / (l0 + l1);
+        float y = o * f;
+        asm volatile("" : "+v"(y));                              // the fp32 product, rounded once more below
+        const long at = static_cast<long>(head) * D + col0 + tid;
+        if (o_dtype == IFA_F32) static_cast<float *>(O)[at] = y;
+        else if (o_dtype == IFA_F16) static_cast<uint16_t *>(O)[at] = static_cast<uint16_t>(Pack4<__half>::pack(y, 0.0f, 0.0f, 0.0f).x & 0xffffu);
+        else static_cast<uint16_t *>(O)[at] = static_cast<uint16_t>(Pack4<__hip_bfloat16>::pack(y, 0.0f, 0.0f, 0.0f).x & 0xffffu);
+    }
+#endif
+}
+
 // ---- few queries, many keys, any number of heads: the key axis split across workgroups, exactly ----------------
 // The narrow kernel cannot fill the chip when there are few heads, and walks a long key sequence at what one or two CUs take
 // in.  Splitting the keys of a head over workgroups is not Algorithm 1 as
@@ -1398,6 +1669,15 @@ int launch_packed(const int8_t *Q, const int8_t *K, const int8_t *V, const float
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 
+template <int D>
+int launch_decode(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, long heads, int Nk,
+                  int vblock, int o_dtype, void *O, hipStream_t st) {
+    constexpr int DS = D / 32;
+    hipLaunchKernelGGL((int_flash_attn_fwd_decode_kernel<D, DS>), dim3(static_cast<unsigned>((heads + 7) / 8 * 8 * DS)), dim3(DEC_THREADS), 0, st,
+                       Q, K, V, sQ, sK, sV, static_cast<int>(heads), Nk, vblock, o_dtype, O);
+    return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
+}
+
 template <int D, bool CAUSAL, bool VB, typename OutT>
 int launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV,
                   int heads, int Nq, int Nk, void *O, hipStream_t st) {
@@ -1409,6 +1689,8 @@ int launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8
     }
     if (kernel == IFA_KERNEL_PACKED) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
+    if (ifa_decode_query(heads, Nq, D))
+        return launch_decode<D>(Q, K, V, sQ, sK, sV, heads, Nk, VB, sizeof(OutT) == 4 ? IFA_F32 : std::is_same_v<OutT, __half> ? IFA_F16 : IFA_BF16, O, st);
     // K and V with the non-temporal hint where one workgroup reads each byte, and reads it once, and there are more of them than the
     // caches could keep for the next call; such a call runs with DS = 1.  (With the hint and DS = 2 the second workgroup of a pair may
     // find a line gone: right after K and V were written the call below fetched 730 - 790 MB, 545 with DS = 1.)  128 heads x 1 x 16384, 537 MB, us, after

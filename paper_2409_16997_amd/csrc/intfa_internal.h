@@ -32,6 +32,11 @@ static inline bool ifa_few_queries(int heads, int Nq, int Nk, int d, bool half) 
     return Nq <= 32 ? Nk > short_keys : groups <= 512 && Nk >= 2048;
 }
 
+// Which of the few-query kernel's INT8 calls the decode kernel takes: one query per head, as long as its workgroups (four per head, d = 64: two) each have a
+// CU of their own.  Few-query / decode kernel, us, K and V in rotation: 1 x 300 keys 5.2 / 3.9, 32 x 1024 8.1 / 6.5, 64 x 1500 .88 of the time, 64 x 32800 .81, 8 x 24600 .58; d = 64,
+// 128 x 200 .94, 128 x 4100 .90, 128 x 16500 .80.  Beyond the line, at d = 128: 65 heads x 257 1.21, x 4100 1.38, 128 x 1024 1.32.
+static inline bool ifa_decode_query(long heads, int Nq, int d) { return Nq == 1 && heads <= (d == 128 ? 64 : 128); }
+
 // Which INT8 calls the packed kernel takes before either of them, us (calls in a graph, K and V in rotation):
 //   one key block                    packed / few-query: 32 x 1 x 128 4.3 / 4.9, 128 x 32 x 64 5.0 / 5.8; d = 64, 32 x 1 x 128 3.7 / 4.3
 //   d = 64, more than 256 workgroups and up to 768 keys (1152 from 1025 on), packed / few-query: 400 x 8 x 768 13.0 / 13.4, 1000 x 1 x 640 22.7 / 24.2,
@@ -90,7 +95,10 @@ static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causa
 //             88 30.5 / 30.4;  72 x 8 x 16384 56.9 / 53.1, 80 57.2 / 58.2;  72 x 9 x 8192 30.9 / 29.6, 80 31.4 / 32.7;  80 x 16 x 16384 57.9 / 55.3, 88 58.2 / 59.0;  80 x 32 x 32768
 //             112 / 109, 88 114 / 118
 // Off by most: 8 x 16 x 2500 at d = 128 (12.5 us split, 15.7 taken; in rotation 15.1 and 15.8), 32 x 16 x 4096 (18.4 split, 19.8 taken).
+// One query: the decode kernel's own line, decode kernel / split, K and V in rotation: 1 x 3000 .97 of the time, x 4100 1.26; 16 x 4100 .97, x 6200 1.19; 32 x 6200 1.01; 56 x 6200 .96,
+// x 8200 1.09; 64 x 8200 .92; d = 64, 1 x 3000 .87, x 4100 1.21; 32 x 6200 .91, x 8200 1.26; 64 x 6200 .87, x 8200 1.08; 96 x 8200 1.00; 128 x 4100 .75, x 32800 .93.
 static inline bool ifa_unsplit_queries(int heads, int Nq, int Nk, int d) {
+    if (ifa_decode_query(heads, Nq, d)) return Nk <= 3000 + 75 * heads || heads >= 120;
     const bool stored = Nq <= 8;                                 // the scores go through memory (more queries: K is read again)
     const long E = stored && d == 128 ? 2048 : 1024, S = stored ? 1536 : 2304;
     const long H = stored ? (d == 128 ? 134 - 5 * Nq : 146 - 7 * Nq) : (d == 128 ? 104 : 122) - Nq;
