@@ -7,8 +7,8 @@
 //   int_flash_attn_fwd_narrow_kernel   one or two workgroups per head and group of 32 queries, the key blocks split over
 //                                      their wavefronts; bit-identical to the fused kernel's rows, needs no memory
 //                                      beyond inputs and outputs; the calls of ifa_few_queries();
-//   int_flash_attn_fwd_decode_kernel   two or four workgroups per head with one query, 16 key blocks at a time; the calls of the few-query kernel
-//                                      that ifa_decode_query() names;
+//   int_flash_attn_fwd_decode_kernel   two or four workgroups per head with one query (.._draft_kernel: two to eight), 16 key blocks at a time; the calls
+//                                      of the few-query kernel that ifa_decode_query() names;
 //   splitk_*                           the key axis of a head split over many workgroups, exactly: lines 9-10 for every
 //                                      block first, then lines 11-13 on the known running maximum, then a merge;
 //                                      int_flash_attn_fwd_splitk (caller's workspace) and _splitk_static (built in).
@@ -889,16 +889,16 @@ __global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_packed_kernel(
 // The numbers are those of the other kernels: integer sums, the maximum is order-independent, the row sum is kept per half of the keys (bit 2 of the key's index)
 // as their lanes do, and the fp32 folds are the same, block by block.
 constexpr int DEC_WAVES = 16, DEC_THREADS = DEC_WAVES * 64;      // wavefronts = key blocks per window
-template <int D, int DS> struct DecodePlan {
+template <int D, int DS, int RING> struct DecodePlan {
     static constexpr int DV = D / DS;
     static constexpr int VE = 4 / DS;                            // ring entries (32 D bytes) of V, 32 DS keys each, behind four key tiles of K
     static constexpr int EPW = 4 + VE;                           // ... per window
-    static constexpr int R = D == 128 ? 2 : 4;                   // entries of the ring, one of them being read
+    static constexpr int R = RING;                               // entries of the ring, one of them being read
     static constexpr int copies(int k) { return D / 32 + (k % EPW == 0 ? 2 : 0); }   // of entry k (the first of a window brings the s_K)
     static constexpr int behind(int k) { int n = 0; for (int j = 1; j < R - 1; ++j) n += copies(k + j); return n; }   // in flight behind entry k
 };
 template <int D, int DS> struct SmemDecode {
-    using P = DecodePlan<D, DS>;
+    using P = DecodePlan<D, DS, D == 128 ? 2 : 4>;
     alignas(4096) int8_t ring[DEC_WAVES][P::R][32 * D];
     alignas(16) int s[DEC_WAVES][BC];                            // Q K^T of the wavefront's block; then its P bytes (8 dwords per key tile)
     alignas(256) float sk[2][DEC_WAVES][BC];                     // of this window and the next
@@ -940,7 +940,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_decode_kern
     const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
     int heads, int Nk, int vblock, int o_dtype, void *__restrict__ O) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    using P = DecodePlan<D, DS>;
+    using P = typename SmemDecode<D, DS>::P;
     __shared__ SmemDecode<D, DS> sm;
     constexpr int KS = D / 32, KK = D / 64, DV = P::DV, VE = P::VE, EPW = P::EPW, R = P::R;
     static_assert(DV == 32, "one d tile");
@@ -1133,6 +1133,246 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_decode_kern
         float y = o * f;
         asm volatile("" : "+v"(y));                              // the fp32 product, rounded once more below
         const long at = static_cast<long>(head) * D + col0 + tid;
+        if (o_dtype == IFA_F32) static_cast<float *>(O)[at] = y;
+        else if (o_dtype == IFA_F16) static_cast<uint16_t *>(O)[at] = static_cast<uint16_t>(Pack4<__half>::pack(y, 0.0f, 0.0f, 0.0f).x & 0xffffu);
+        else static_cast<uint16_t *>(O)[at] = static_cast<uint16_t>(Pack4<__hip_bfloat16>::pack(y, 0.0f, 0.0f, 0.0f).x & 0xffffu);
+    }
+#endif
+}
+
+// ---- two to eight queries per head (a few draft tokens) ------------------------------------------------------------
+// The decode kernel with the queries in the columns of its products: a lane (c, G) holds the scores of query c for 32 of the block's keys, and P in the order in which
+// the second product takes it, so neither goes through LDS.  A window takes 5.3 us (the decode kernel's 4.9), with eight queries as with two.  Few-query kernel / this
+// one, us: 32 heads x 5 queries x 4900 keys 23.9 / 19.1, 8 x 8 x 2048 10.8 / 8.1, 32 x 8 x 16384 75 / 51; d = 64, 64 x 8 x 4900 20.3 / 15.2, 32 x 2 x 16384 56 / 37.
+constexpr int DRAFT_MAX_Q = 8;
+template <int D, int DS> struct SmemDraft {
+    using P = DecodePlan<D, DS, D == 128 ? 2 : 3>;
+    alignas(4096) int8_t ring[DEC_WAVES][P::R][32 * D];
+    alignas(256) float sk[DEC_WAVES][BC];
+    alignas(16) float pv[DEC_WAVES][DRAFT_MAX_Q][P::DV];         // minus P V, units of 2^26
+    alignas(16) float ext[DEC_WAVES][16];                        // extremum of a per block and query (line 10)
+    alignas(16) float alpha[DRAFT_MAX_Q][DEC_WAVES];             // e^(m_old - m)
+    alignas(16) float psum[DRAFT_MAX_Q][DEC_WAVES][2];           // the row sums over either half of the keys
+};
+// (the s_K of the next window are asked for with the first entry of V at the earliest, when those of this one have been used)
+static_assert(sizeof(SmemDraft<128, 4>) <= 160 * 1024 && SmemDraft<128, 4>::P::EPW - SmemDraft<128, 4>::P::R + 1 >= 4 && SmemDraft<64, 2>::P::EPW - SmemDraft<64, 2>::P::R + 1 >= 4, "LDS, ring");
+
+template <int D, int DS>
+__global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_draft_kernel(
+    const int8_t *__restrict__ Q, const int8_t *__restrict__ K, const int8_t *__restrict__ V,
+    const float *__restrict__ sQ, const float *__restrict__ sK, const float *__restrict__ sV,
+    int heads, int Nq, int Nk, int causal, int vblock, int o_dtype, void *__restrict__ O) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using P = typename SmemDraft<D, DS>::P;
+    __shared__ SmemDraft<D, DS> sm;
+    constexpr int KS = D / 32, KK = D / 64, DV = P::DV, VE = P::VE, EPW = P::EPW, R = P::R, NQ = DRAFT_MAX_Q;
+    static_assert(DV == 32, "two d tiles of 16");
+
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, G = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T_c = (Nk + BC - 1) / BC, windows = (T_c + DEC_WAVES - 1) / DEC_WAVES;
+    int head, qg, part;
+    if (!map_query_group<DS>(blockIdx.x, heads, 1, head, qg, part)) return;
+    const int col0 = part * DV;                                  // first column of V and O
+
+    const BufRsrc rK = make_rsrc(K + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+    const BufRsrc rV = make_rsrc(V + static_cast<long>(head) * Nk * D, static_cast<unsigned>(Nk) * D);
+    const BufRsrc rSK = make_rsrc(sK + static_cast<long>(head) * Nk, static_cast<unsigned>(Nk) * 4);
+    const LaneOffsets<D> lo(lane, 0);
+    const lds_ptr ring = (lds_ptr)(&sm.ring[wave][0][0]), skbuf = (lds_ptr)(&sm.sk[wave][0]);
+    const unsigned gv = (lane / (DV / 16)) * D + col0 + 16 * (lane % (DV / 16));
+    const int turn = part * (4 / DS);                            // which of its key tiles a wavefront begins with: step k is tile (k + turn) % 4 throughout
+    int in = 0, slot = 0;
+    auto issue = [&](auto k_, int w) {
+        constexpr int k = decltype(k_)::value % EPW;
+        const int key0 = (w * DEC_WAVES + wave) * BC;            // first key of this wavefront's block
+        const lds_ptr dst = ring + in * (32 * D);
+        in = in + 1 == R ? 0 : in + 1;
+        if constexpr (k < 4) {
+            const int key = key0 + 32 * ((k + turn) & 3), off = key < Nk ? key * D : NOWHERE;
+#pragma unroll
+            for (int i = 0; i < KS; ++i) lds_copy16(rK, dst + 1024 * i, lo.gk, off + 1024 * i);
+            if constexpr (k == 0) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) lds_copy4(rSK, skbuf + 256 * i, 4 * lane, key0 + 64 * i < Nk ? (key0 + 64 * i) * 4 : NOWHERE);
+            }
+        } else {                                                 // (d = 64: the half of the block that the steps began with first)
+            const int key = key0 + (VE == 2 ? (32 * DS * (k - 4) + 32 * turn) & (BC - 1) : 0), off = key < Nk ? key * D : NOWHERE;
+#pragma unroll
+            for (int i = 0; i < KS; ++i) lds_copy16(rV, dst + 1024 * i, gv, off + i * (1024 / DV) * D);
+        }
+    };
+    for_each_int([&](auto k) { issue(k, 0); }, std::make_integer_sequence<int, R - 1>{});
+
+    // line 5: column c is query c (past the last one: a copy of it, never stored)
+    const int q = min(c, Nq - 1);
+    const int8_t *qptr = Q + (static_cast<long>(head) * Nq + q) * D + 16 * G;
+    v4i qf[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const v4i *>(qptr + 64 * kk);
+    float nq2 = sQ[static_cast<long>(head) * Nq + q] * (-LOG2E * ACC_UNIT);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qf[kk]));
+    asm volatile("" : "+v"(nq2));
+    const int first_limit = causal ? Nk - Nq : Nk - 1, klimit = causal ? q + Nk - Nq : Nk - 1;   // last key that the first query, that this one sees
+    const v4i acc0 = {ACC_START_I, ACC_START_I, ACC_START_I, ACC_START_I};
+    const unsigned k0 = c * D + 16 * (G ^ k_swz<D>(c));
+    // transposing read of V, keys 4 G .. 4 G + 3 and 16 + 4 G .. of a key tile: the order in which a lane holds P
+    const unsigned v0 = (16 * (c >> 3) + 4 * G + ((c >> 1) & 3)) * DV + 8 * (c & 1);
+
+    const float *sVh = vblock ? sV + static_cast<long>(head) * T_c : sV + head;
+    float carry = -INFINITY;                                     // m in front of the window (line 6)
+    float o = 0.0f, l0 = 0.0f, l1 = 0.0f, sv_prev = 1.0f;        // of query tid / DV and column tid % DV
+    const int fq = tid / DV, fc = tid % DV;
+
+    for (int w = 0; w < windows; ++w) {
+        const bool mine = w * DEC_WAVES + wave < T_c;            // (wave-uniform)
+        auto advance = [&](auto k_, auto take) {
+            constexpr int k = decltype(k_)::value;
+            wait_vmcnt<P::behind(k)>();
+            __builtin_amdgcn_sched_barrier(0);
+            issue(std::integral_constant<int, k + R - 1>{}, w + (k + R - 1) / EPW);
+            __builtin_amdgcn_sched_barrier(0);
+            take(ring + slot * (32 * D));
+            slot = slot + 1 == R ? 0 : slot + 1;
+        };
+        v4i sacc[4][2];
+        float a[4][2][4], bmin = INFINITY;
+        if (mine) {
+            // line 9, integer part
+            for_each_int([&](auto k_) {
+                constexpr int k = decltype(k_)::value;
+                v4i kop[2][KK];
+                advance(k_, [&](lds_ptr ks) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int kk = 0; kk < KK; ++kk) kop[h][kk] = *reinterpret_cast<LDS_AS const v4i *>(lds_xor(ks, 64 * kk, k0) + 16 * D * h);
+                });
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) sacc[k][h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kop[h][kk], qf[kk], kk == 0 ? acc0 : sacc[k][h], 0, 0, 0);
+            }, std::make_integer_sequence<int, 4>{});
+            // line 9, fp32 part, and the extremum of the block
+            const int key0 = (w * DEC_WAVES + wave) * BC;
+            const bool masked = key0 + BC - 1 > min(first_limit, Nk - 1);                        // (wave-uniform)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int at = 32 * ((k + turn) & 3) + 16 * h + 4 * G;                       // first of four keys, in the block
+                    const v4f skv = *reinterpret_cast<const v4f *>(&sm.sk[wave][at]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float x = (ACC_START_F - __int_as_float(sacc[k][h][e])) * skv[e];
+                        if (masked && key0 + at + e > klimit) x = INFINITY;
+                        a[k][h][e] = x;
+                        bmin = fminf(bmin, x);
+                    }
+                    if (h) __builtin_amdgcn_sched_barrier(0);
+                }
+            const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(bmin), __float_as_uint(bmin), false, false);
+            bmin = pair_min(fminf(__uint_as_float(sw[0]), __uint_as_float(sw[1])));
+        }
+        if (G == 0) sm.ext[wave][c] = bmin;
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        // lines 10, 11 and the row sums of 12
+        float before = INFINITY, total = INFINITY;               // over the blocks of the window in front of this wavefront's; over all
+#pragma unroll
+        for (int b = 0; b < DEC_WAVES; ++b) {
+            if (b == wave) before = total;
+            total = fminf(total, sm.ext[b][c]);
+        }
+        const float m_old = fmaxf(carry, before * nq2), m = fmaxf(m_old, bmin * nq2), mm = m - LOG2_R_NORM;
+        carry = fmaxf(carry, total * nq2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (mine) {
+            v4i pf[2];                                           // two runs of 64 keys: steps 0 and 1, 2 and 3
+            unsigned sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[k][h][e], nq2, -mm));
+                    const uint32_t p = pack_p4(y);
+                    sum = __builtin_amdgcn_sad_u8(p, 0u, sum);
+                    pf[k >> 1][2 * (k & 1) + h] = static_cast<int>(p);
+                }
+            const auto sw = __builtin_amdgcn_permlane32_swap(sum, sum, false, false);            // lanes G and G + 2 hold the same half of the keys
+            if (c < NQ && G < 2) sm.psum[c][wave][G] = static_cast<float>(sw[0] + sw[1]);
+            if (c < NQ && G == 0) sm.alpha[c][wave] = __builtin_amdgcn_exp2f(m_old - m);
+            // line 13, P V of the block
+            v4i pacc[2];
+            for_each_int([&](auto e_) {
+                constexpr int e = decltype(e_)::value, N64 = DS / 2;                             // runs in an entry
+                v4i vop[N64][2];
+                advance(std::integral_constant<int, 4 + e>{}, [&](lds_ptr vs) {
+#pragma unroll
+                    for (int t = 0; t < N64; ++t)
+#pragma unroll
+                        for (int dt = 0; dt < 2; ++dt) {
+                            // the run's two key tiles (d = 64: the entry holds them in order)
+                            const int ta = VE == 2 ? 0 : (2 * t + turn) & 3, tb = VE == 2 ? 1 : (2 * t + 1 + turn) & 3;
+                            const v2i t0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(vs + v0 + 32 * ta * DV + 16 * dt));
+                            const v2i t1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32(reinterpret_cast<LDS_AS v2i *>(vs + v0 + 32 * tb * DV + 16 * dt));
+                            vop[t][dt] = v4i{t0[0], t0[1], t1[0], t1[1]};
+                        }
+                });
+#pragma unroll
+                for (int t = 0; t < N64; ++t)
+#pragma unroll
+                    for (int dt = 0; dt < 2; ++dt)
+                        pacc[dt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vop[t][dt], pf[e * N64 + t], e + t == 0 ? acc0 : pacc[dt], 0, 0, 0);
+            }, std::make_integer_sequence<int, VE>{});
+            if (c < NQ) {
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt) {
+                    v4f t;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) t[i] = ACC_START_F - __int_as_float(pacc[dt][i]);
+                    *reinterpret_cast<v4f *>(&sm.pv[wave][c][16 * dt + 4 * G]) = t;
+                }
+            }
+        }
+        __syncthreads();
+        // lines 12, 13: the blocks of the window in order
+        if (tid < NQ * DV) {
+#pragma unroll
+            for (int b0 = 0; b0 < DEC_WAVES; b0 += 8) {
+                float t[8], al[8], ps[8][2];
+#pragma unroll
+                for (int b = 0; b < 8; ++b) { t[b] = sm.pv[b0 + b][fq][fc]; al[b] = sm.alpha[fq][b0 + b]; ps[b][0] = sm.psum[fq][b0 + b][0]; ps[b][1] = sm.psum[fq][b0 + b][1]; }
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    const int jb = w * DEC_WAVES + b0 + b;
+                    if (jb < T_c) {
+                        float alpha_o = al[b];
+                        if (vblock) {                            // one V scale per key block: the running output is kept in units of the current block's
+                            const float sv_j = sVh[jb];
+                            alpha_o = al[b] * (sv_prev * __builtin_amdgcn_rcpf(sv_j));
+                            sv_prev = sv_j;
+                        }
+                        l0 = __builtin_fmaf(l0, al[b], ps[b][0]);
+                        l1 = __builtin_fmaf(l1, al[b], ps[b][1]);
+                        o = __builtin_fmaf(o, alpha_o, -t[b]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    wait_all_memory();                                           // requests past the last window: nothing of mine stays in flight
+
+    // lines 15-17
+    if (tid < NQ * DV && fq < Nq) {
+        const float f = (vblock ? sv_prev : sVh[0]) * ACC_UNIT / (l0 + l1);
+        float y = o * f;
+        asm volatile("" : "+v"(y));                              // the fp32 product, rounded once more below
+        const long at = (static_cast<long>(head) * Nq + fq) * D + col0 + fc;
         if (o_dtype == IFA_F32) static_cast<float *>(O)[at] = y;
         else if (o_dtype == IFA_F16) static_cast<uint16_t *>(O)[at] = static_cast<uint16_t>(Pack4<__half>::pack(y, 0.0f, 0.0f, 0.0f).x & 0xffffu);
         else static_cast<uint16_t *>(O)[at] = static_cast<uint16_t>(Pack4<__hip_bfloat16>::pack(y, 0.0f, 0.0f, 0.0f).x & 0xffffu);
@@ -1670,11 +1910,12 @@ int launch_packed(const int8_t *Q, const int8_t *K, const int8_t *V, const float
 }
 
 template <int D>
-int launch_decode(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, long heads, int Nk,
-                  int vblock, int o_dtype, void *O, hipStream_t st) {
+int launch_decode(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK, const float *sV, int heads, int Nq, int Nk,
+                  int causal, int vblock, int o_dtype, void *O, hipStream_t st) {
     constexpr int DS = D / 32;
-    hipLaunchKernelGGL((int_flash_attn_fwd_decode_kernel<D, DS>), dim3(static_cast<unsigned>((heads + 7) / 8 * 8 * DS)), dim3(DEC_THREADS), 0, st,
-                       Q, K, V, sQ, sK, sV, static_cast<int>(heads), Nk, vblock, o_dtype, O);
+    const dim3 grid(static_cast<unsigned>((heads + 7) / 8 * 8 * DS));
+    if (Nq == 1) hipLaunchKernelGGL((int_flash_attn_fwd_decode_kernel<D, DS>), grid, dim3(DEC_THREADS), 0, st, Q, K, V, sQ, sK, sV, heads, Nk, vblock, o_dtype, O);
+    else hipLaunchKernelGGL((int_flash_attn_fwd_draft_kernel<D, DS>), grid, dim3(DEC_THREADS), 0, st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, causal, vblock, o_dtype, O);
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }
 
@@ -1689,8 +1930,8 @@ int launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8
     }
     if (kernel == IFA_KERNEL_PACKED) return launch_packed<D, CAUSAL, VB, OutT>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, O, st);
     const long qgroups = (Nq + NARROW_BR - 1) / NARROW_BR, padded = (heads * qgroups + 7) / 8 * 8;
-    if (ifa_decode_query(heads, Nq, D))
-        return launch_decode<D>(Q, K, V, sQ, sK, sV, heads, Nk, VB, sizeof(OutT) == 4 ? IFA_F32 : std::is_same_v<OutT, __half> ? IFA_F16 : IFA_BF16, O, st);
+    if (ifa_decode_query(heads, Nq, Nk, D))
+        return launch_decode<D>(Q, K, V, sQ, sK, sV, heads, Nq, Nk, CAUSAL, VB, sizeof(OutT) == 4 ? IFA_F32 : std::is_same_v<OutT, __half> ? IFA_F16 : IFA_BF16, O, st);
     // K and V with the non-temporal hint where one workgroup reads each byte, and reads it once, and there are more of them than the
     // caches could keep for the next call; such a call runs with DS = 1.  (With the hint and DS = 2 the second workgroup of a pair may
     // find a line gone: right after K and V were written the call below fetched 730 - 790 MB, 545 with DS = 1.)  128 heads x 1 x 16384, 537 MB, us, after

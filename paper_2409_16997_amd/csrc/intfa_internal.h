@@ -32,10 +32,12 @@ static inline bool ifa_few_queries(int heads, int Nq, int Nk, int d, bool half) 
     return Nq <= 32 ? Nk > short_keys : groups <= 512 && Nk >= 2048;
 }
 
-// Which of the few-query kernel's INT8 calls the decode kernel takes: one query per head, as long as its workgroups (four per head, d = 64: two) each have a
-// CU of their own.  Few-query / decode kernel, us, K and V in rotation: 1 x 300 keys 5.2 / 3.9, 32 x 1024 8.1 / 6.5, 64 x 1500 .88 of the time, 64 x 32800 .81, 8 x 24600 .58; d = 64,
-// 128 x 200 .94, 128 x 4100 .90, 128 x 16500 .80.  Beyond the line, at d = 128: 65 heads x 257 1.21, x 4100 1.38, 128 x 1024 1.32.
-static inline bool ifa_decode_query(long heads, int Nq, int d) { return Nq == 1 && heads <= (d == 128 ? 64 : 128); }
+// Which of the few-query kernel's INT8 calls the decode kernel (one query per head) and its form for two to eight take: as long as its workgroups (four per head,
+// d = 64: two) each have a CU of their own.  Few-query / decode kernel, us, K and V in rotation: 1 x 300 keys 5.2 / 3.9, 32 x 1024 8.1 / 6.5, 64 x 1500 .88 of the time,
+// 64 x 32800 .81, 8 x 24600 .58; d = 64, 128 x 200 .94, 128 x 4100 .90, 128 x 16500 .80.  Beyond the line, at d = 128: 65 heads x 257 1.21, x 4100 1.38, 128 x 1024 1.32.
+// Two to eight queries, repeated: 32 x 4 x 4900 23.9 / 19.1, 8 x 5 x 2048 10.6 / 7.8, 64 x 8 x 16384 81 / 62, 64 x 8 x 600 6.6 / 6.0; d = 64, 64 x 8 x 4900 20.3 / 15.2, 128 x 8 x 600 5.6 /
+// 5.2; on fewer keys all that is there to do is start and end: 64 x 8 x 200 4.7 / 5.0, d = 64 128 x 5 x 200 4.0 / 4.5.
+static inline bool ifa_decode_query(long heads, int Nq, int Nk, int d) { return heads <= (d == 128 ? 64 : 128) && (Nq == 1 || (Nq <= 8 && Nk > 384)); }
 
 // Which INT8 calls the packed kernel takes before either of them, us (calls in a graph, K and V in rotation):
 //   one key block                    packed / few-query: 32 x 1 x 128 4.3 / 4.9, 128 x 32 x 64 5.0 / 5.8; d = 64, 32 x 1 x 128 3.7 / 4.3
@@ -96,9 +98,13 @@ static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causa
 //             112 / 109, 88 114 / 118
 // Off by most: 8 x 16 x 2500 at d = 128 (12.5 us split, 15.7 taken; in rotation 15.1 and 15.8), 32 x 16 x 4096 (18.4 split, 19.8 taken).
 // One query: the decode kernel's own line, decode kernel / split, K and V in rotation: 1 x 3000 .97 of the time, x 4100 1.26; 16 x 4100 .97, x 6200 1.19; 32 x 6200 1.01; 56 x 6200 .96,
-// x 8200 1.09; 64 x 8200 .92; d = 64, 1 x 3000 .87, x 4100 1.21; 32 x 6200 .91, x 8200 1.26; 64 x 6200 .87, x 8200 1.08; 96 x 8200 1.00; 128 x 4100 .75, x 32800 .93.
+// x 8200 1.09; 64 x 8200 .92; d = 64, 1 x 3000 .87, x 4100 1.21; 32 x 6200 .91, x 8200 1.26; 64 x 6200 .87, x 8200 1.08; 96 x 8200 1.00; 112 x 8200 .93, x 16500 .77, x 32800 1.06; 128 x 4100 .75, x 32800 .93.
+// Two to eight: its form's line, the same way: 8 queries x 8 heads x 2100 keys 11.6 / 13.4, 32 x 4100 21.2 / 24.4, x 6200 29.4 / 30.3, x 8200 37.5 / 31.1, 48 x 6200 31.9 / 35.7, x 8200
+// 40.1 / 39.7, 64 x 8200 39.2 / 46.1, x 16500 71.0 / 72.4; 2 queries, 16 x 3000 13.0 / 13.4, 48 x 4100 23.1 / 26.4, x 6200 31.6 / 31.3; d = 64, 2 queries, 64 x 6200 22.1 / 23.6, 96 x 12300 1.06;
+// 8 queries, 64 x 6200 21.9 / 27.2, x 12300 39.6 / 40.5, 96 x 32800 106 / 121.
 static inline bool ifa_unsplit_queries(int heads, int Nq, int Nk, int d) {
-    if (ifa_decode_query(heads, Nq, d)) return Nk <= 3000 + 75 * heads || heads >= 120;
+    if (ifa_decode_query(heads, Nq, Nk, d))
+        return Nq == 1 ? Nk <= 3000 + 75 * heads || heads >= 108 : Nk <= 2000 + (86 + 4 * Nq) * heads || heads >= 120 - 3 * Nq;
     const bool stored = Nq <= 8;                                 // the scores go through memory (more queries: K is read again)
     const long E = stored && d == 128 ? 2048 : 1024, S = stored ? 1536 : 2304;
     const long H = stored ? (d == 128 ? 134 - 5 * Nq : 146 - 7 * Nq) : (d == 128 ? 104 : 122) - Nq;

@@ -65,8 +65,8 @@ def route(heads, Nq, Nk, d, causal=None, half=False):
 
 def unsplit(heads, Nq, Nk, d):
     """Whether a call of the key-split entry points runs the kernel of the plain call.  tests/test_routes.py holds this to the library's own rule."""
-    if Nq == 1 and heads <= (64 if d == 128 else 128):            # the decode kernel's
-        return Nk <= 3000 + 75 * heads or heads >= 120
+    if heads <= (64 if d == 128 else 128) and (Nq == 1 or Nq <= 8 and Nk > 384):      # the decode kernel's
+        return Nk <= 3000 + 75 * heads or heads >= 108 if Nq == 1 else Nk <= 2000 + (86 + 4 * Nq) * heads or heads >= 120 - 3 * Nq
     if Nq <= 8:
         E, S, H = (2048, 1536, 134 - 5 * Nq) if d == 128 else (1024, 1536, 146 - 7 * Nq)
     else:
