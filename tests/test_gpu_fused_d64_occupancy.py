@@ -1,4 +1,4 @@
-"""The fused kernel at d = 64 with three wavefronts per SIMD (calls of more than 512 workgroups, uneven ones of more than 864) against the same
+"""The fused kernel at d = 64 with three wavefronts per SIMD (calls of more than 512 workgroups, uneven ones of more than 864 to 2250) against the same
 heads in a call that has two, bit for bit, and against the oracle."""
 import pytest
 
@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("heads,few,Nq,Nk,causal", [
     (129, 128, 385, 385, False), (129, 128, 512, 511, False), (513, 512, 66, 641, False),         # 516 and 513 workgroups against 512
     (217, 216, 500, 500, True), (173, 172, 513, 513, True),                                        # 868 and 865 against 864 and 860, uneven
+    (188, 187, 1500, 1500, True), (79, 78, 2001, 2001, True),                                      # 2256 against 2244, 1264 against 1248
     (520, 500, 128, 128, True), (172, 170, 257, 300, True), (260, 250, 130, 900, True)])           # one, three and two query blocks a head
 def test_rows_do_not_depend_on_the_wavefronts_per_simd(heads, few, Nq, Nk, causal, vblock):
     import paper_2409_16997_amd as ifa
