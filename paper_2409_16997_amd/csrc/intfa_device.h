@@ -121,22 +121,24 @@ __device__ __forceinline__ BufRsrc make_rsrc(const void *base, unsigned bytes) {
 
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+// (M0 written by a scalar instruction has to be one wait state old when a copy to LDS reads it, or the copy may land where the one before it went.  The
+// compiler's hazard handling does not look inside an assembly statement, so the s_nop stands in each.)
 // 64 lanes x 16 bytes: lane t's bytes [voff, voff + 16) past soff land at LDS address lds + 16 t
 __device__ __forceinline__ void lds_copy16(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
     const v4i rs = {r.w[0], r.w[1], r.w[2], r.w[3]};
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds))), "v"(voff), "s"(rs), "s"(soff) : "m0");
 }
 // the same with the non-temporal hint: for bytes that are read exactly once (the streaming passes of the key-split path)
 __device__ __forceinline__ void lds_copy16_nt(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
     const v4i rs = {r.w[0], r.w[1], r.w[2], r.w[3]};
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
                  :: "s"(static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds))), "v"(voff), "s"(rs), "s"(soff) : "m0");
 }
 // 64 lanes x 4 bytes, lane t's dword lands at lds + 4 t
 __device__ __forceinline__ void lds_copy4(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
     const v4i rs = {r.w[0], r.w[1], r.w[2], r.w[3]};
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
                  :: "s"(static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds))), "v"(voff), "s"(rs), "s"(soff) : "m0");
 }
 #pragma clang diagnostic pop

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # (heads, heads of the call with two, Nq, Nk, causal, d): just beyond a line of the rule and at it or below; whole, ragged and single key blocks
 @pytest.mark.parametrize("heads,few,Nq,Nk,causal,d", [
     (129, 128, 449, 449, False, 64), (513, 512, 65, 640, False, 64), (257, 256, 511, 512, True, 64), (520, 500, 128, 128, True, 64), (600, 512, 100, 127, True, 64),
-    (129, 128, 449, 449, False, 128), (257, 256, 450, 385, False, 128), (513, 512, 66, 641, False, 128), (313, 312, 500, 500, True, 128), (208, 207, 1664, 1664, True, 128), (520, 500, 128, 128, True, 128),
+    (129, 128, 449, 449, False, 128), (257, 256, 450, 385, False, 128), (513, 512, 66, 641, False, 128), (313, 312, 500, 500, True, 128), (208, 207, 1664, 1664, True, 128), (560, 250, 600, 600, True, 128), (209, 208, 768, 768, True, 128), (520, 500, 128, 128, True, 128),
     (172, 170, 257, 300, True, 128), (129, 128, 400, 1000, True, 128)])
 def test_rows_do_not_depend_on_the_wavefronts_per_simd(heads, few, Nq, Nk, causal, d):
     import paper_2409_16997_amd as ifa
