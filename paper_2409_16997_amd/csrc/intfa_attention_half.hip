@@ -279,13 +279,16 @@ __device__ __forceinline__ void process_block_half(lds_ptr ks, lds_ptr vs, lds_p
 }
 
 // The same block, same results, in registers for three wavefronts per SIMD (d = 64: four), for calls with enough workgroups.  Two wavefronts
-// take turns at matrix and vector instructions and wait out each other's row maximum, LDS reads and barrier, every 64 keys; a third one fills in.  166
-// registers (d = 64: 114) hold the block without the 16 the S^T accumulators start from (the MFMA's inline constant; a is carried in units of
-// 2^26, a power of two, so the numbers are the same), with the scores in the accumulators' place and the s_K of one key tile, reloaded as
+// take turns at matrix and vector instructions and wait out each other's row maximum, LDS reads and barrier, every 64 keys; a third one fills in.  168
+// registers (d = 64: 116) hold the block without the 16 the S^T accumulators start from (the MFMA's inline constant; a is carried in units of
+// 2^26, a power of two, so the numbers are the same as long as neither it nor s_Q times that leaves the range: FAR_SQ), with the scores in the accumulators' place and the s_K of one key tile, reloaded as
 // they are used.  Two / three or four, us: d = 64, 32 x 8192 causal 350 / 302, 64 x 4096 340 / 303, 128 x 4096 causal 359 / 326, 300 x 200 12.7 / 10.2;
 // d = 128, 32 x 16384 causal 1874 / 1811, 96 x 1724 154 / 151, 300 x 200 18.0 / 15.6, 600 x 128 causal 15.0 / 12.5.  With few workgroups the order of the function
 // above is faster, which has all of its LDS operands requested earlier: 24 x 1400 at d = 128 36.8 / 38.5.
-template <int D, bool MASKED>
+// FAR: for a wavefront with a row whose s_Q is beyond FAR_SQ: s_Q 2^26 log2 e could be infinite from 2^101 on, and s_K 2^-26 loses bits that such a row can see.
+// Up to FAR_SQ what is lost below 2^-149 is less than 2^-33 of a score.
+constexpr float FAR_SQ = 1.2379400392853803e27f;                 // 2^90
+template <int D, bool MASKED, bool FAR>
 __device__ __forceinline__ void process_block_half_lean(lds_ptr ks, lds_ptr vs, lds_ptr sk, const LaneOffsetsH<D> &lo,
                                                         const v4i (&qf)[D / 32], float sq2, int klimit, int last_tile, int clear_tiles, int g,
                                                         RowStateH<D> &st) {
@@ -326,7 +329,9 @@ __device__ __forceinline__ void process_block_half_lean(lds_ptr ks, lds_ptr vs, 
             for (int vq = 0; vq < 4; ++vq) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    float x = (__int_as_float(sacc[mt][4 * vq + e]) - ACC_START_F) * skr[vq][e];
+                    float x = __int_as_float(sacc[mt][4 * vq + e]) - ACC_START_F;
+                    if (FAR) x *= ACC_UNIT;
+                    x *= skr[vq][e];
                     if (MASKED && mt >= clear_tiles && 32 * mt + 8 * vq + 4 * g + e > klimit) x = -INFINITY;
                     a[mt][4 * vq + e] = x;
                     bmax = fmaxf(bmax, x);
@@ -440,7 +445,9 @@ __global__ __launch_bounds__(THREADS, W) void int_flash_attn_fwd_half_kernel(
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk)
         qf[kk] = *reinterpret_cast<const v4i *>(Q + qrow * D + 32 * kk + 16 * g);
-    const float sq2 = sQ[qrow] * (W == 2 ? LOG2E : LOG2E * ACC_UNIT);
+    const float sq = sQ[qrow];
+    const bool far = W > 2 && __any(sq > FAR_SQ);                // (wave-uniform)
+    const float sq2 = sq * (W == 2 || far ? LOG2E : LOG2E * ACC_UNIT);
     const LaneOffsetsH<D> lo(lane, wave);
     {
         const PrefetchH first = {rK, rV, rSK, 0, 0, 0, kbuf, vbuf, skbuf};
@@ -475,12 +482,14 @@ __global__ __launch_bounds__(THREADS, W) void int_flash_attn_fwd_half_kernel(
         return PrefetchH{rK, rV, rSK, more ? j1 * D : NOWHERE_H, more ? j1 * D * 2 : NOWHERE_H, more ? j1 * 4 : NOWHERE_H,
                          kbuf + nxt * BCH * D, vbuf + nxt * BCH * D * 2, skbuf + nxt * BCH * 4};
     };
+    auto walk = [&](auto far_) {                                 // (as many barriers either way)
+    [[maybe_unused]] constexpr bool FAR = decltype(far_)::value;
     for (int jb = 0; jb < nfull; ++jb) {
         const int cur = jb & 1;
         prefetch_block<D>(next_block(jb), lo, wave, lane);
         if constexpr (W == 2) process_block_half<D, false>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
                                                            0, NT - 1, NT, g, bias, st);
-        else process_block_half_lean<D, false>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2, 0, NT - 1, NT, g, st);
+        else process_block_half_lean<D, false, FAR>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2, 0, NT - 1, NT, g, st);
         wait_all_memory();                                       // my part of the next block has landed in LDS
         __syncthreads();                                         // everyone's has, and `cur` is free again
     }
@@ -497,12 +506,15 @@ __global__ __launch_bounds__(THREADS, W) void int_flash_attn_fwd_half_kernel(
         if (last_tile >= 0) {                                                      // wave-uniform
             if constexpr (W == 2) process_block_half<D, true>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
                                                               klimit, last_tile, max(0, (wmin + 1) >> 5), g, bias, st);
-            else process_block_half_lean<D, true>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
+            else process_block_half_lean<D, true, FAR>(kbuf + cur * BCH * D, vbuf + cur * BCH * D * 2, skbuf + cur * BCH * 4, lo, qf, sq2,
                                                   klimit, last_tile, max(0, (wmin + 1) >> 5), g, st);
         }
         wait_all_memory();
         __syncthreads();
     }
+    };
+    if (W > 2 && far) walk(std::bool_constant<(W > 2)>{});
+    else walk(std::false_type{});
 
     const float l = st.l + swap32(st.l);
     const float f = 1.0f / l;

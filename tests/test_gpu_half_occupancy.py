@@ -34,3 +34,18 @@ def test_rows_do_not_depend_on_the_wavefronts_per_simd(heads, few, Nq, Nk, causa
     n = lambda t: t[0, h:h + 1].cpu().numpy()
     ref = oracle.int_flash_attn_fwd_half(n(q8), n(k8), n(v), n(sq), n(sk), causal, ifa.block_cols_half(d, causal))["O"]
     assert np.abs(full[0, h].cpu().numpy() - ref).max() <= 1e-3 * np.abs(ref).max()
+
+
+# s_Q and s_K are any positive fp32.  A power of two moved from one to the other leaves every product, and so every row, as it is: for all rows, and for one row of a
+# call that alone leaves the range in which the kernels of many workgroups carry the scores.  (s_K is 2^-8.5 at least: at 2^-117 of it still a normal number.)
+@pytest.mark.parametrize("power", [80, 97, 110, 117])
+@pytest.mark.parametrize("d,heads,N,causal", [(128, 260, 400, False), (64, 300, 385, True), (128, 520, 128, True)])
+def test_rows_with_scales_far_from_one(d, heads, N, causal, power):
+    import paper_2409_16997_amd as ifa
+    q8, k8, v8, sq, sk = problem(heads, N, d, power)
+    v = v8.to(torch.float16) / 64
+    call = lambda a, b: ifa.int_flash_attn_fwd_half(q8, k8, v, a, b, causal=causal, out_dtype=torch.float32)
+    ref = call(sq, sk)
+    assert torch.equal(call(sq * 2.0 ** power, sk * 2.0 ** -power), ref)
+    one = torch.where(torch.arange(N, device="cuda") == 77, sq, sq * 2.0 ** -power)     # the other rows see scores of about zero
+    assert torch.equal(call(one * 2.0 ** power, sk * 2.0 ** -power)[:, :, 77], ref[:, :, 77])
