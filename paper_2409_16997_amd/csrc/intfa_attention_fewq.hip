@@ -128,13 +128,8 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
             const bool real = jb < nblocks;
             const Prefetch pf = {rK, rK, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE, kbuf + (gi & 1) * (NB * BC * D), kbuf,
                                  skbuf + (gi & 1) * (NB * 4 * 256)};
-            if (once) {
-#pragma unroll
-                for (int i = 0; i < KS; ++i) prefetch_k_piece<D, true>(pf, lo, t, i);
-            } else {
-#pragma unroll
-                for (int i = 0; i < KS; ++i) prefetch_k_piece<D>(pf, lo, t, i);
-            }
+            if (once) prefetch_k<D, true>(pf, lo, t);
+            else prefetch_k<D>(pf, lo, t);
             lds_copy4(pf.sk, pf.lsk, 4 * r + 128 * t, pf.skoff);
         };
         stage_group(0);
@@ -237,11 +232,10 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_narrow_k
             const int voff = jb < nblocks ? jb * BC * D : NOWHERE;
             const lds_ptr dst = vbuf + ((gi & 1) * NB + b) * (BC * DV);
             const Prefetch pf = {rV, rV, rV, voff, NOWHERE, vbuf, dst, vbuf};
+            if constexpr (DS == 1) prefetch_v<D, decltype(nt)::value>(pf, lo, dt);
+            else {
 #pragma unroll
-            for (int i = 0; i < PIECES; ++i) {
-                if constexpr (DS == 1) prefetch_v_piece<D, decltype(nt)::value>(pf, lo, dt, i);
-                else if constexpr (decltype(nt)::value) lds_copy16_nt(rV, dst + (dt * PIECES + i) * 1024, gvs, voff + i * (1024 / DV) * D);
-                else lds_copy16(rV, dst + (dt * PIECES + i) * 1024, gvs, voff + i * (1024 / DV) * D);
+                for (int i = 0; i < PIECES; ++i) lds_copy16<decltype(nt)::value>(rV, dst + (dt * PIECES + i) * 1024, gvs, voff + i * (1024 / DV) * D);
             }
         }
     };
@@ -434,8 +428,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_pair_ker
             const bool real = jb < nblocks;
             const Prefetch pf = {rK, rK, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE, kbuf + (n & 1) * (NB * BC * D), kbuf,
                                  skbuf + (n & 1) * (NB * 4 * 256)};
-#pragma unroll
-            for (int i = 0; i < KS; ++i) prefetch_k_piece<D>(pf, lo, t, i);
+            prefetch_k<D>(pf, lo, t);
             lds_copy4(pf.sk, pf.lsk, 4 * r + 128 * t, pf.skoff);
         };
         stage_step(0);
@@ -567,8 +560,7 @@ __global__ __launch_bounds__(NARROW_THREADS, 3) void int_flash_attn_fwd_pair_ker
         for (int b = 0; b < NB; ++b) {
             const int jb = n * NB + b;
             const Prefetch pf = {rV, rV, rV, jb < nblocks ? jb * BC * D : NOWHERE, NOWHERE, vbuf, vbuf + ((n & 1) * NB + b) * (BC * D), vbuf};
-#pragma unroll
-            for (int i = 0; i < KS; ++i) prefetch_v_piece<D>(pf, lo, dt, i);
+            prefetch_v<D>(pf, lo, dt);
         }
     };
     float l[2] = {0.0f, 0.0f}, o[2][16];                         // this d tile of the running output (units of 2^26), l of the whole row
@@ -745,8 +737,8 @@ __global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_packed_kernel(
         const bool real = jb < nblocks;
         const Prefetch pf = {rK, rV, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE,
                              kbuf + st * BC * D, vbuf + st * BC * D, skbuf + st * BC * 4};
-#pragma unroll
-        for (int i = 0; i < KS; ++i) { prefetch_k_piece<D>(pf, lo, wave, i); prefetch_v_piece<D>(pf, lo, wave, i); }
+        prefetch_k<D>(pf, lo, wave);
+        prefetch_v<D>(pf, lo, wave);
         lds_copy4(pf.sk, pf.lsk + 256 * (wave & 1), 4 * lane + 256 * (wave & 1), pf.skoff);   // wavefronts 2, 3 repeat 0, 1
     };
     stage_block(0);
@@ -968,8 +960,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_decode_kern
         in = in + 1 == R ? 0 : in + 1;
         if constexpr (k < 4) {
             const int key = key0 + 32 * ((k + turn) & 3), off = key < Nk ? key * D : NOWHERE;
-#pragma unroll
-            for (int i = 0; i < KS; ++i) lds_copy16(rK, dst + 1024 * i, lo.gk, off + 1024 * i);
+            lds_copy16_run<KS>(rK, dst, lo.gk, lo.gk, off);
             if constexpr (k == 0) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) lds_copy4(rSK, skbuf + (w & 1) * (DEC_WAVES * BC * 4) + 256 * i, 4 * lane, key0 + 64 * i < Nk ? (key0 + 64 * i) * 4 : NOWHERE);
@@ -1190,8 +1181,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_draft_kerne
         in = in + 1 == R ? 0 : in + 1;
         if constexpr (k < 4) {
             const int key = key0 + 32 * ((k + turn) & 3), off = key < Nk ? key * D : NOWHERE;
-#pragma unroll
-            for (int i = 0; i < KS; ++i) lds_copy16(rK, dst + 1024 * i, lo.gk, off + 1024 * i);
+            lds_copy16_run<KS>(rK, dst, lo.gk, lo.gk, off);
             if constexpr (k == 0) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) lds_copy4(rSK, skbuf + 256 * i, 4 * lane, key0 + 64 * i < Nk ? (key0 + 64 * i) * 4 : NOWHERE);
@@ -1496,7 +1486,7 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_scores_kernel(
     const lds_ptr kbuf = (lds_ptr)(&sm.k[0][0]);
     const lds_ptr skbuf = (lds_ptr)(&sm.sk[0][0][0]);
     const LaneOffsets<D> lo(lane, wave);
-    // Line 8 for this wavefront's key tile of block jb (rows 32 wave .. + 31 of K_j: the pieces prefetch_k_piece gives
+    // Line 8 for this wavefront's key tile of block jb (rows 32 wave .. + 31 of K_j: the pieces prefetch_k gives
     // this wavefront; its 32 s_K, lanes 32-63 repeating lanes 0-31) into stage (jb - jb0) % NSTAGE.  A block past the
     // run is requested nowhere, so that every block costs PER_BLOCK copy instructions and the counted waits stay valid.
     auto stage_block = [&](int jb) {
@@ -1504,8 +1494,7 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_scores_kernel(
         const bool real = jb < jb1;
         const Prefetch pf = {rK, rK, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE,
                              kbuf + st * BC * D, kbuf, skbuf + (st * 4 + wave) * 256};
-#pragma unroll
-        for (int i = 0; i < KS; ++i) prefetch_k_piece<D, SPLIT_NT>(pf, lo, wave, i);
+        prefetch_k<D, SPLIT_NT>(pf, lo, wave);
         lds_copy4(pf.sk, pf.lsk, 4 * r + 128 * wave, pf.skoff);
     };
     stage_block(jb0);
@@ -1599,14 +1588,13 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_kernel(
     const lds_ptr abuf = (lds_ptr)(&sm.a[0][0][0][0]);
     const lds_ptr tbuf = (lds_ptr)(&sm.tmin[0][0][0]);
     const LaneOffsets<D> lo(lane, wave);
-    // This wavefront's key tile of V_j (the rows prefetch_v_piece gives it), the scores of that tile (Nq x 32 floats,
+    // This wavefront's key tile of V_j (the rows prefetch_v gives it), the scores of that tile (Nq x 32 floats,
     // contiguous; the copy moves 1 KB, whatever follows the record is not read) and the block's 32 tile minima.
     auto stage_block = [&](int jb) {
         const int st = (jb - jb0) % SPLIT_NSTAGE_V;
         const bool real = jb < jb1;
         const Prefetch pf = {rV, rV, rV, real ? jb * BC * D : NOWHERE, NOWHERE, vbuf, vbuf + st * BC * D, vbuf};
-#pragma unroll
-        for (int i = 0; i < DT; ++i) prefetch_v_piece<D, SPLIT_NT>(pf, lo, wave, i);
+        prefetch_v<D, SPLIT_NT>(pf, lo, wave);
         lds_copy16(rA, abuf + (st * 4 + wave) * 1024, 16 * lane, real ? (jb * 4 + wave) * Nq * 128 : NOWHERE);
         lds_copy4(rT, tbuf + (st * 4 + wave) * 256, 4 * r, real ? jb * (SPLIT_MAX_Q * 4 * 4) : NOWHERE);
     };
@@ -1737,10 +1725,8 @@ __global__ __launch_bounds__(THREADS, 2) void splitk_pv_recompute_kernel(
         const bool real = jb < jb1;
         const Prefetch pf = {rK, rV, rSK, real ? jb * BC * D : NOWHERE, real ? jb * BC * 4 : NOWHERE,
                              kbuf + st * BC * D, vbuf + st * BC * D, skbuf + (st * 4 + wave) * 256};
-#pragma unroll
-        for (int i = 0; i < KS; ++i) prefetch_k_piece<D, SPLIT_NT>(pf, lo, wave, i);
-#pragma unroll
-        for (int i = 0; i < DT; ++i) prefetch_v_piece<D, SPLIT_NT>(pf, lo, wave, i);
+        prefetch_k<D, SPLIT_NT>(pf, lo, wave);
+        prefetch_v<D, SPLIT_NT>(pf, lo, wave);
         lds_copy4(pf.sk, pf.lsk, 4 * r + 128 * wave, pf.skoff);
         lds_copy16(rT, tbuf + (st * 4 + wave) * 1024, 16 * r, real ? jb * (MAXQ * 4 * 4) : NOWHERE);
     };

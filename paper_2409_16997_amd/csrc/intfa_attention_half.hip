@@ -99,9 +99,9 @@ template <int D>
 __device__ __forceinline__ void prefetch_block(const PrefetchH &nx, const LaneOffsetsH<D> &lo, int wave, int lane) {
     constexpr int KP = D / 64, VP = D / 32;
 #pragma unroll
-    for (int i = 0; i < KP; ++i) lds_copy16(nx.k, nx.lk + (wave * KP + i) * 1024, lo.gk, nx.koff + 1024 * i);
+    for (int i = 0; i < KP; ++i) lds_copy16_piece<KP>(i, nx.k, nx.lk + wave * KP * 1024, lo.gk, lo.gk, nx.koff);
 #pragma unroll
-    for (int i = 0; i < VP; ++i) lds_copy16(nx.v, nx.lv + (wave * VP + i) * 1024, lo.gv, nx.voff + 1024 * i);
+    for (int i = 0; i < VP; ++i) lds_copy16_piece<VP>(i, nx.v, nx.lv + wave * VP * 1024, lo.gv, lo.gv, nx.voff);
     if (wave == 3) lds_copy4(nx.sk, nx.lsk, 4 * lane, nx.skoff);       // 64 lanes x 4 bytes = the 64 scales of the block
 }
 
@@ -608,13 +608,8 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
             const bool real = jb < nblocks;
             const int koff = real ? jb * BCH * D : NOWHERE_H;
             const lds_ptr dst = kbuf + (gi & 1) * (NB * BCH * D) + t * (32 * D);
-            if (once) {
-#pragma unroll
-                for (int i = 0; i < KS; ++i) lds_copy16_nt(rK, dst + i * 1024, lo.gk, koff + 1024 * i);
-            } else {
-#pragma unroll
-                for (int i = 0; i < KS; ++i) lds_copy16(rK, dst + i * 1024, lo.gk, koff + 1024 * i);
-            }
+            if (once) lds_copy16_run<KS, true>(rK, dst, lo.gk, lo.gk, koff);
+            else lds_copy16_run<KS>(rK, dst, lo.gk, lo.gk, koff);
             if (g == 0) lds_copy4(rSK, skbuf + (gi & 1) * (FEW_S_WAVES * 128), 4 * r + 128 * t, real ? jb * BCH * 4 : NOWHERE_H);
         };
         stage_group(0);
@@ -716,13 +711,15 @@ __global__ __launch_bounds__(FEW_THREADS) void int_flash_attn_fwd_half_few_kerne
             const int jb = gi * NB + b;
             const int voff = jb < nblocks ? jb * BCH * D * 2 : NOWHERE_H;
             const lds_ptr dst = vbuf + ((gi & 1) * NB + b) * (BCH * DV * 2) + dt * PIECES * 1024;
-            if (once) {
+            auto copy = [&](auto nt) {
+                if constexpr (DS == 1) lds_copy16_run<PIECES, decltype(nt)::value>(rV, dst, gvs, gvs, voff);
+                else {
 #pragma unroll
-                for (int i = 0; i < PIECES; ++i) lds_copy16_nt(rV, dst + i * 1024, gvs, voff + 1024 * DS * i);
-            } else {
-#pragma unroll
-                for (int i = 0; i < PIECES; ++i) lds_copy16(rV, dst + i * 1024, gvs, voff + 1024 * DS * i);
-            }
+                    for (int i = 0; i < PIECES; ++i) lds_copy16<decltype(nt)::value>(rV, dst + i * 1024, gvs, voff + 1024 * DS * i);
+                }
+            };
+            if (once) copy(std::true_type{});
+            else copy(std::false_type{});
         }
     };
     v16f o;

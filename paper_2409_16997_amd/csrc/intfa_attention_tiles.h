@@ -39,7 +39,7 @@ template <int D> struct LaneOffsets {
     // staging: byte offset inside the K / V tile in HBM of the chunk this lane moves in piece i of its wavefront.
     // Piece i covers rows 1024 i / D further on, and the row bits the swizzles look at do not change with i except
     // one bit of the V swizzle (D = 128) that follows the parity of i: offset(i) = gk + 1024 i for K and
-    // gv[i & 1] + 1024 (i - (i & 1)) for V, the multiples of 1024 going into the scalar offset of the copy.
+    // gv[i & 1] + 1024 i for V, the multiples of 1024 being scalar or the instruction's.
     unsigned gk;
     unsigned gv[2];
     __device__ __forceinline__ LaneOffsets(int lane, int wave) {
@@ -49,7 +49,7 @@ template <int D> struct LaneOffsets {
         for (int i = 0; i < 2; ++i) {
             const int p = (wave * ITER + i) * 64 + lane, row = p / CH, slot = p % CH;
             if (i == 0) gk = row * D + 16 * (slot ^ k_swz<D>(row));
-            gv[i] = row * D + 16 * (slot ^ v_swz<D>(row));
+            gv[i] = row * D + 16 * (slot ^ v_swz<D>(row)) - 1024 * i;
         }
         k0 = r * D + ((g ^ k_swz<D>(r)) * 16);
         // transposing read: 16-lane group G = lane / 16 serves d columns 16*(G%2) .. +15 of the tile and key
@@ -93,16 +93,22 @@ struct Prefetch {
 // next wait + barrier.  Cheaper than a branch around each copy: the block stays one basic block for the scheduler.
 constexpr int NOWHERE = 0x7fff0000;
 
-// (NT: with the non-temporal hint, for the passes that read every byte once)
-template <int D, bool NT = false>
+template <int D>
 __device__ __forceinline__ void prefetch_k_piece(const Prefetch &nx, const LaneOffsets<D> &lo, int wave, int i) {
-    if (NT) lds_copy16_nt(nx.k, nx.lk + (wave * (D / 32) + i) * 1024, lo.gk, nx.koff + 1024 * i);
-    else lds_copy16(nx.k, nx.lk + (wave * (D / 32) + i) * 1024, lo.gk, nx.koff + 1024 * i);
+    lds_copy16_piece<D / 32>(i, nx.k, nx.lk + wave * (D / 32) * 1024, lo.gk, lo.gk, nx.koff);
+}
+template <int D>
+__device__ __forceinline__ void prefetch_v_piece(const Prefetch &nx, const LaneOffsets<D> &lo, int wave, int i) {
+    lds_copy16_piece<D / 32>(i, nx.v, nx.lv + wave * (D / 32) * 1024, lo.gv[0], lo.gv[1], nx.koff);
+}
+// all pieces of a wavefront, one after the other (NT: with the non-temporal hint, for the passes that read every byte once)
+template <int D, bool NT = false>
+__device__ __forceinline__ void prefetch_k(const Prefetch &nx, const LaneOffsets<D> &lo, int wave) {
+    lds_copy16_run<D / 32, NT>(nx.k, nx.lk + wave * (D / 32) * 1024, lo.gk, lo.gk, nx.koff);
 }
 template <int D, bool NT = false>
-__device__ __forceinline__ void prefetch_v_piece(const Prefetch &nx, const LaneOffsets<D> &lo, int wave, int i) {
-    if (NT) lds_copy16_nt(nx.v, nx.lv + (wave * (D / 32) + i) * 1024, lo.gv[i & 1], nx.koff + 1024 * (i - (i & 1)));
-    else lds_copy16(nx.v, nx.lv + (wave * (D / 32) + i) * 1024, lo.gv[i & 1], nx.koff + 1024 * (i - (i & 1)));
+__device__ __forceinline__ void prefetch_v(const Prefetch &nx, const LaneOffsets<D> &lo, int wave) {
+    lds_copy16_run<D / 32, NT>(nx.v, nx.lv + wave * (D / 32) * 1024, lo.gv[0], lo.gv[1], nx.koff);
 }
 __device__ __forceinline__ void prefetch_sk(const Prefetch &nx, int wave, int lane) {
     // 2 x 64 lanes x 4 bytes = the 128 scales of the block, by wavefronts 2 and 3.  Dword copies: a head's

@@ -122,18 +122,43 @@ __device__ __forceinline__ BufRsrc make_rsrc(const void *base, unsigned bytes) {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 // (M0 written by a scalar instruction has to be one wait state old when a copy to LDS reads it, or the copy may land where the one before it went.  The
-// compiler's hazard handling does not look inside an assembly statement, so the s_nop stands in each.)
-// 64 lanes x 16 bytes: lane t's bytes [voff, voff + 16) past soff land at LDS address lds + 16 t
-__device__ __forceinline__ void lds_copy16(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
+// compiler's hazard handling does not look inside an assembly statement, so what fills the wait state stands in each.)
+// 64 lanes x 16 bytes: lane t's bytes [voff, voff + 16) past soff land at LDS address lds + 16 t.  NT: with the non-temporal hint, for bytes that are read
+// exactly once (the streaming passes of the key-split path).
+template <bool NT = false> __device__ __forceinline__ void lds_copy16(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
     const v4i rs = {r.w[0], r.w[1], r.w[2], r.w[3]};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds))), "v"(voff), "s"(rs), "s"(soff) : "m0");
+    const unsigned m0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds));
+    if constexpr (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" :: "s"(m0), "v"(voff), "s"(rs), "s"(soff) : "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(m0), "v"(voff), "s"(rs), "s"(soff) : "m0");
 }
-// the same with the non-temporal hint: for bytes that are read exactly once (the streaming passes of the key-split path)
-__device__ __forceinline__ void lds_copy16_nt(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
+// Piece i < N of a run of whole KB at lds and voff + soff (of even and of odd pieces).  Both additions stand in the statement, the second in the wait state.
+// (With an s_nop for it and the additions outside 24 calls of the fused kernel took .3 % longer, with the KB in the instruction's offset 1.1 %.)
+template <int N, int I = 0> __device__ __forceinline__ void lds_copy16_piece(int i, const BufRsrc &r, lds_ptr lds, unsigned even, unsigned odd, int soff) {
+    if (i != I) {
+        if constexpr (I + 1 < N) lds_copy16_piece<N, I + 1>(i, r, lds, even, odd, soff);
+    } else if constexpr (I == 0) lds_copy16(r, lds, even, soff);
+    else {
+        const v4i rs = {r.w[0], r.w[1], r.w[2], r.w[3]};
+        const unsigned m0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds));
+        int at;
+        asm volatile("s_add_i32 m0, %1, %5\n\ts_add_i32 %0, %4, %5\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
+                     : "=&s"(at) : "s"(m0), "v"(I & 1 ? odd : even), "s"(rs), "s"(soff), "n"(1024 * I) : "m0", "scc");
+    }
+}
+// All of them, one after the other, M0 written once: the instruction's offset counts on both sides.
+template <int N, bool NT = false> __device__ __forceinline__ void lds_copy16_run(const BufRsrc &r, lds_ptr lds, unsigned even, unsigned odd, int soff) {
+    static_assert(N == 1 || N == 2 || N == 4, "pieces");
     const v4i rs = {r.w[0], r.w[1], r.w[2], r.w[3]};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                 :: "s"(static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds))), "v"(voff), "s"(rs), "s"(soff) : "m0");
+    const unsigned m0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds));
+#define INTFA_RUN2(HINT) "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, %4 offen" HINT " lds\n\tbuffer_load_dwordx4 %2, %3, %4 offen offset:1024" HINT " lds"
+#define INTFA_RUN4(HINT) INTFA_RUN2(HINT) "\n\tbuffer_load_dwordx4 %1, %3, %4 offen offset:2048" HINT " lds\n\tbuffer_load_dwordx4 %2, %3, %4 offen offset:3072" HINT " lds"
+    if constexpr (N == 1) lds_copy16<NT>(r, lds, even, soff);
+    else if constexpr (N == 2 && NT) asm volatile(INTFA_RUN2(" nt") :: "s"(m0), "v"(even), "v"(odd), "s"(rs), "s"(soff) : "m0");
+    else if constexpr (N == 2) asm volatile(INTFA_RUN2("") :: "s"(m0), "v"(even), "v"(odd), "s"(rs), "s"(soff) : "m0");
+    else if constexpr (NT) asm volatile(INTFA_RUN4(" nt") :: "s"(m0), "v"(even), "v"(odd), "s"(rs), "s"(soff) : "m0");
+    else asm volatile(INTFA_RUN4("") :: "s"(m0), "v"(even), "v"(odd), "s"(rs), "s"(soff) : "m0");
+#undef INTFA_RUN4
+#undef INTFA_RUN2
 }
 // 64 lanes x 4 bytes, lane t's dword lands at lds + 4 t
 __device__ __forceinline__ void lds_copy4(const BufRsrc &r, lds_ptr lds, unsigned voff, int soff) {
