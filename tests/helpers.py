@@ -1,5 +1,11 @@
 """Shared test helpers: build quantized Algorithm-1 inputs from the seeded workloads using the
 ORACLE's quantizer (never the HIP path's), so expected values depend on oracle/ alone."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
 import numpy as np
 
 import oracle
@@ -36,42 +42,39 @@ def random_int8_problem(rng, heads, N, d, score_sigma=1.0):
     return Qq, Kq, Vq, sQ, sK, sV
 
 
+_RULES = r"""
+#include "intfa_internal.h"
+extern "C" int route(int heads, int Nq, int Nk, int d, int causal) { return ifa_fwd_kernel(heads, Nq, Nk, d, causal); }
+extern "C" int few_half(int heads, int Nq, int Nk, int d) { return ifa_few_queries(heads, Nq, Nk, d, true); }
+extern "C" int unsplit(int heads, int Nq, int Nk, int d) { return ifa_unsplit_queries(heads, Nq, Nk, d); }
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def library_rules():
+    """The library's own dispatch rules, compiled for the host: tests say which kernel they reach without a line of their own."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with tempfile.TemporaryDirectory() as tmp:
+        src, lib = os.path.join(tmp, "rules.hip"), os.path.join(tmp, "rules.so")
+        with open(src, "w") as f:
+            f.write(_RULES)
+        subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(root, "include"), "-I",
+                        os.path.join(root, "paper_2409_16997_amd", "csrc"), src, "-o", lib], check=True, stdout=subprocess.DEVNULL)
+        return ctypes.CDLL(lib)
+
+
 def route(heads, Nq, Nk, d, causal=None, half=False):
     """Which kernel a plain attention call runs: "fused", "few" (twelve wavefronts per 32 queries, half-INT8 eight), "packed" or "pair" (two groups of 32
-    queries).  `causal` decides nothing for half-INT8.  tests/test_routes.py holds this to the library's own rule."""
-    groups = heads * -(-Nq // 32)
-    if not half:
-        assert causal is not None
-        if Nq > 32 and groups > 256:
-            wgs, uneven = heads * -(-Nq // 64), causal and 2 * Nq >= Nk
-            if wgs <= 256:
-                pair = Nk >= (512 if d == 128 else 384) and not (uneven and Nk >= 2048 and (heads == 1 or wgs <= 192))
-            else:
-                line = 4 * wgs - 100 if d == 128 else 3 * wgs - 200
-                if wgs <= 512:
-                    pair = causal and 4 * Nq >= Nk >= line and (uneven or Nk >= (3000 if d == 128 else 2048))
-                else:
-                    pair = uneven and Nk >= 2048 and heads * Nk <= 56 << 10 and (heads <= 8 and wgs <= 768 or wgs <= 576 and Nk >= (4000 if d == 128 else 3000))
-            if pair:
-                return "pair"
-        if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (768 if groups <= 1024 else 1152) if Nq <= 32 else
-                                                        Nq <= 64 and groups <= 512 and 128 <= Nk < 384):
-            return "packed"
-    short_keys = {(True, 128): 256, (True, 64): 64, (False, 128): 384, (False, 64): 0}[half, d]
-    if groups <= 5 << 20 and (groups <= 256 or (Nk > short_keys if Nq <= 32 else groups <= 512 and Nk >= 2048)):
-        return "few"
-    return "fused"
+    queries).  `causal` decides nothing for half-INT8."""
+    if half:
+        return "few" if library_rules().few_half(heads, Nq, Nk, d) else "fused"
+    assert causal is not None
+    return ("fused", "pair", "packed", "few")[library_rules().route(heads, Nq, Nk, d, int(causal))]
 
 
 def unsplit(heads, Nq, Nk, d):
-    """Whether a call of the key-split entry points runs the kernel of the plain call.  tests/test_routes.py holds this to the library's own rule."""
-    if heads <= (64 if d == 128 else 128) and (Nq == 1 or Nq <= 8 and Nk > 384):      # the decode kernel's
-        return Nk <= 3000 + 75 * heads or heads >= 108 if Nq == 1 else Nk <= 2000 + (86 + 4 * Nq) * heads or heads >= 120 - 3 * Nq
-    if Nq <= 8:
-        E, S, H = (2048, 1536, 134 - 5 * Nq) if d == 128 else (1024, 1536, 146 - 7 * Nq)
-    else:
-        E, S, H = 1024, 2304, (104 if d == 128 else 122) - Nq
-    return Nk <= 2048 or heads * (Nk + E) >= H * (Nk - S)
+    """Whether a call of the key-split entry points runs the kernel of the plain call."""
+    return bool(library_rules().unsplit(heads, Nq, Nk, d))
 
 
 def copies_for(kernel, heads, Nq, Nk, d, causal=None, half=False):

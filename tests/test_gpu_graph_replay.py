@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 import torch
 
+from helpers import unsplit
+
 pytestmark = pytest.mark.gpu
 
 
@@ -65,9 +67,10 @@ def test_a_captured_step_replays_to_the_eager_result(ifa, shape, causal):
             assert torch.equal(a, b), (shape, causal, rep)
 
 
-@pytest.mark.parametrize("Nq,Nk", [(1, 5000), (4, 2100), (20, 3000)])
+@pytest.mark.parametrize("Nq,Nk", [(1, 5000), (4, 2100), (4, 3000), (8, 6000), (20, 3000)])
 def test_a_captured_key_split_call_on_the_static_workspace_replays_to_the_eager_result(ifa, Nq, Nk):
     B, H, d = 1, 8, 128
+    assert unsplit(H, Nq, Nk, d) == (Nk == 2100)                 # the passes, with the scores in memory and without, and a call that goes without them
     rng = np.random.default_rng(Nq + Nk)
 
     def problem():

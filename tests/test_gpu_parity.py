@@ -498,35 +498,37 @@ def test_few_query_calls_equal_the_square_kernel_rows(ifa, Nq, d, out_dtype):
     # A call with a few queries per head (a decode step, a short chunk) runs a kernel of its own that splits every key
     # block over the wavefronts of a workgroup; it performs the arithmetic of the square kernel on the same operands, so
     # its rows are the last Nq rows of the square problem bit for bit, with and without the mask, on a ragged length.
-    H, N = 30, 1231
-    assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == "few" for c in (False, True))
-    rng = np.random.default_rng(Nq * 131 + d)
-    Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, N, d, score_sigma=2.0)
-    args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sV[None]))
-    for causal in (False, True):
-        full = ifa.int_flash_attn_fwd(*args(Qq, sQ), causal=causal, out_dtype=out_dtype)
-        few = ifa.int_flash_attn_fwd(*args(np.ascontiguousarray(Qq[:, N - Nq:]), np.ascontiguousarray(sQ[:, N - Nq:])),
-                                     causal=causal, out_dtype=out_dtype)
-        torch.cuda.synchronize()
-        assert torch.equal(few, full[:, :, N - Nq:]), (Nq, d, causal)
+    N = 1231
+    for H in (15, 30):
+        assert all(route(H, N, N, d, c) in ("fused", "pair") and route(H, Nq, N, d, c) == "few" for c in (False, True))
+        rng = np.random.default_rng(Nq * 131 + d)
+        Qq, Kq, Vq, sQ, sK, sV = random_int8_problem(rng, H, N, d, score_sigma=2.0)
+        args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sV[None]))
+        for causal in (False, True):
+            full = ifa.int_flash_attn_fwd(*args(Qq, sQ), causal=causal, out_dtype=out_dtype)
+            few = ifa.int_flash_attn_fwd(*args(np.ascontiguousarray(Qq[:, N - Nq:]), np.ascontiguousarray(sQ[:, N - Nq:])),
+                                         causal=causal, out_dtype=out_dtype)
+            torch.cuda.synchronize()
+            assert torch.equal(few, full[:, :, N - Nq:]), (H, Nq, d, causal)
 
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq", [1, 7, 33, 64])
 def test_few_query_calls_with_blockwise_v_scales_equal_the_square_kernel_rows(ifa, Nq, d):
     # the same with one V scale per key block (the running output is carried in units of the current block's scale)
-    H, N = 30, 1231
-    assert all(route(H, N, N, d, c) == "fused" and route(H, Nq, N, d, c) == "few" for c in (False, True))
-    rng = np.random.default_rng(Nq * 17 + d)
-    Qq, Kq, Vq, sQ, sK, _ = random_int8_problem(rng, H, N, d, score_sigma=2.0)
-    sVb = rng.uniform(0.005, 0.05, (H, -(-N // ifa.block_cols(d, True)))).astype(np.float32)
-    args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sVb[None]))
-    for causal in (False, True):
-        full = ifa.int_flash_attn_fwd(*args(Qq, sQ), causal=causal, out_dtype=torch.float32)
-        few = ifa.int_flash_attn_fwd(*args(np.ascontiguousarray(Qq[:, N - Nq:]), np.ascontiguousarray(sQ[:, N - Nq:])),
-                                     causal=causal, out_dtype=torch.float32)
-        torch.cuda.synchronize()
-        assert torch.equal(few, full[:, :, N - Nq:]), (Nq, d, causal)
+    N = 1231
+    for H in (15, 30):
+        assert all(route(H, N, N, d, c) in ("fused", "pair") and route(H, Nq, N, d, c) == "few" for c in (False, True))
+        rng = np.random.default_rng(Nq * 17 + d)
+        Qq, Kq, Vq, sQ, sK, _ = random_int8_problem(rng, H, N, d, score_sigma=2.0)
+        sVb = rng.uniform(0.005, 0.05, (H, -(-N // ifa.block_cols(d, True)))).astype(np.float32)
+        args = lambda q, sq: (dev(q[None]), dev(Kq[None]), dev(Vq[None]), dev(sq[None]), dev(sK[None]), dev(sVb[None]))
+        for causal in (False, True):
+            full = ifa.int_flash_attn_fwd(*args(Qq, sQ), causal=causal, out_dtype=torch.float32)
+            few = ifa.int_flash_attn_fwd(*args(np.ascontiguousarray(Qq[:, N - Nq:]), np.ascontiguousarray(sQ[:, N - Nq:])),
+                                         causal=causal, out_dtype=torch.float32)
+            torch.cuda.synchronize()
+            assert torch.equal(few, full[:, :, N - Nq:]), (H, Nq, d, causal)
 
 
 @pytest.mark.parametrize("causal", [False, True])
@@ -557,7 +559,7 @@ def test_few_query_calls_against_the_oracle(ifa, Nq, Nk, d, causal):
                                       (9, 4097, 8), (32, 16384, 2), (20, 1000, 5), (32, 32, 3), (17, 300, 16), (12, 500, 100),
                                       (8, 258, 16), (32, 1026, 4),
                                       # the last run of key blocks is masked entirely for the early queries, where the call splits
-                                      (8, 2306, 16), (32, 3074, 4), (3, 5000, 5), (5, 2049, 16), (20, 3001, 5), (17, 2300, 16), (12, 2500, 30), (5, 2305, 8), (17, 2561, 4), (12, 3585, 12)])
+                                      (8, 2306, 16), (32, 3074, 4), (3, 5000, 5), (5, 2049, 16), (20, 3001, 5), (17, 2300, 16), (12, 2500, 30), (5, 2305, 8), (17, 2561, 4), (12, 3585, 12), (8, 4610, 16), (5, 4097, 16), (2, 5000, 8)])
 def test_key_split_calls_equal_the_sequential_walk(ifa, Nq, Nk, H, d):
     # The key-split path forms P on the grid of the running maximum of the sequential walk (it knows every block's
     # maximum before it forms any P), so it differs from the one-workgroup-per-head kernel only by the order of the

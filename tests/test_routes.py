@@ -1,5 +1,4 @@
-"""The rule that picks the kernel of a plain attention call, compiled for the host, against the Python statement of it that the GPU
-tests use to say which kernel they reach (helpers.route)."""
+"""The rules that pick the kernel of a call, compiled for the host, against a Python statement of them.  (The GPU tests ask the library: helpers.route, helpers.unsplit.)"""
 import os
 import subprocess
 
@@ -8,6 +7,44 @@ import pytest
 from helpers import route, unsplit
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def stated_route(heads, Nq, Nk, d, causal=None, half=False):
+    """The rule of helpers.route, stated again."""
+    groups = heads * -(-Nq // 32)
+    if not half:
+        assert causal is not None
+        if Nq > 32 and groups > 256:
+            wgs, uneven = heads * -(-Nq // 64), causal and 2 * Nq >= Nk
+            if wgs <= 256:
+                pair = Nk >= (512 if d == 128 else 384) and not (uneven and Nk >= 2048 and (heads == 1 or wgs <= 192))
+            else:
+                line = 4 * wgs - 100 if d == 128 else 3 * wgs - 200
+                if wgs <= 512:
+                    pair = causal and 4 * Nq >= Nk >= line and (uneven or Nk >= (3000 if d == 128 else 2048))
+                else:
+                    pair = uneven and Nk >= 2048 and heads * Nk <= 56 << 10 and (heads <= 8 and wgs <= 768 or wgs <= 576 and Nk >= (4000 if d == 128 else 3000))
+            if pair:
+                return "pair"
+        if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (768 if groups <= 1024 else 1152) if Nq <= 32 else
+                                                        Nq <= 64 and groups <= 512 and 128 <= Nk < 384):
+            return "packed"
+    short_keys = {(True, 128): 256, (True, 64): 64, (False, 128): 384, (False, 64): 0}[half, d]
+    if groups <= 5 << 20 and (groups <= 256 or (Nk > short_keys if Nq <= 32 else groups <= 512 and Nk >= 2048)):
+        return "few"
+    return "fused"
+
+
+def stated_unsplit(heads, Nq, Nk, d):
+    """The rule of helpers.unsplit, stated again."""
+    if heads <= (64 if d == 128 else 128) and (Nq == 1 or Nq <= 8 and Nk > 384):      # the decode kernel's
+        return Nk <= 3000 + 75 * heads or heads >= 108 if Nq == 1 else Nk <= 2000 + (86 + 4 * Nq) * heads or heads >= 120 - 3 * Nq
+    if Nq <= 8:
+        E, S, H = (2048, 1536, 134 - 5 * Nq) if d == 128 else (1024, 1536, 146 - 7 * Nq)
+    else:
+        E, S, H = 1024, 2304, (104 if d == 128 else 122) - Nq
+    return Nk <= 2048 or heads * (Nk + E) >= H * (Nk - S)
+
 
 PROGRAM = r"""
 #include "intfa_internal.h"
@@ -38,7 +75,7 @@ def test_helpers_route_is_the_librarys_rule(tmp_path):
     cases = [(heads, Nq, Nk, d, causal, half) for d in (64, 128) for causal, half in ((0, 0), (1, 0), (0, 1)) for Nq in (1, 31, 32, 33, 64, 65, 127, 128, 1000, 4100, 8192)
              for heads in (1, 2, 4, 8, 9, 64, 65, 128, 129, 171, 256, 257, 300, 512, 513, 1000, 1024, 1025, 5 << 20, (5 << 20) + 1)
              for Nk in (1, 64, 65, 127, 128, 129, 256, 257, 383, 384, 385, 511, 512, 768, 769, 1024, 1025, 1152, 1153, 1280, 1281, 2047, 2048, 7168, 7169, 16384, 28672, 28673)]
-    assert library_says(tmp_path, PROGRAM, cases) == [route(*c) for c in cases]
+    assert library_says(tmp_path, PROGRAM, cases) == [stated_route(*c) for c in cases] == [route(*c) for c in cases]
 
 
 SPLIT_PROGRAM = r"""
@@ -55,7 +92,7 @@ int main() {
 def test_helpers_unsplit_is_the_librarys_rule(tmp_path):
     cases = [(heads, Nq, Nk, d) for d in (64, 128) for Nq in range(1, 33) for heads in (1, 2, 8, 15, 16, 17, 31, 32, 33, 64, 71, 72, 95, 96, 112, 129, 160, 6_000_000)
              for Nk in (1, 2, 2047, 2048, 2049, 2304, 2305, 3000, 4096, 4097, 8192, 16384, 32768, 1 << 20, 1 << 24)]
-    assert library_says(tmp_path, SPLIT_PROGRAM, cases) == ["01"[unsplit(*c)] for c in cases]
+    assert library_says(tmp_path, SPLIT_PROGRAM, cases) == ["01"[stated_unsplit(*c)] for c in cases] == ["01"[unsplit(*c)] for c in cases]
 
 
 # Calls of the key-split entry points beside which the other side measured at least 11 % slower, on the same K and V and on K and V in rotation
