@@ -159,12 +159,24 @@ def test_quantize_blockwise_on_both_paths(shape, block, dtype):
     import paper_2409_16997_amd as ifa
     from paper_2409_16997_amd import binding
     X = torch.randn(shape, device="cuda").to(dtype)
-    if len(shape) == 4:
-        X = X.transpose(0, 1).contiguous().transpose(0, 1) if shape[0] == 1 or shape[1] == 1 else X      # (a stride of a dimension of one kept as it is)
     a, b = ifa.quantize_blockwise(X, block), general(lambda: ifa.quantize_blockwise(X, block))
     for x, y in zip(a, b):
         assert x.dtype is y.dtype and x.shape == y.shape and x.stride() == y.stride() and torch.equal(x, y)
     for bad in (0, -1, 1 << 40):                                 # the same refusals
+        refusals = []
         for path in (lambda f: f(), general):
-            with pytest.raises((binding.IntfaError, ZeroDivisionError, RuntimeError)):
+            with pytest.raises((binding.IntfaError, ZeroDivisionError, RuntimeError)) as e:
                 path(lambda: ifa.quantize_blockwise(X, bad))
+            refusals.append((e.type, str(e.value)))
+        assert refusals[0] == refusals[1]
+
+
+# A tensor is contiguous whatever the stride of a dimension of one: the outputs of either path have it, too
+@pytest.mark.parametrize("whole,cut", [((1, 4, 33, 64), (slice(None), slice(0, 1))), ((5, 2, 40, 64), (slice(2, 3), slice(0, 1))), ((3, 2, 7, 128), (slice(1, 2), slice(1, 2), slice(4, 5)))])
+def test_strides_of_dimensions_of_one(whole, cut):
+    import paper_2409_16997_amd as ifa
+    X = torch.randn(whole, device="cuda", dtype=torch.float16)[cut]
+    assert X.is_contiguous() and X.stride() != torch.empty(X.shape).stride()
+    for call in (lambda: ifa.quantize_blockwise(X, 128), lambda: ifa.quantize_tokenwise(X), lambda: ifa.quantize_headwise(X), lambda: ifa.quantize_qkv(X, X, X)):
+        for x, y in zip(call(), general(call)):
+            assert x.dtype is y.dtype and x.shape == y.shape and x.stride() == y.stride() and torch.equal(x, y)
