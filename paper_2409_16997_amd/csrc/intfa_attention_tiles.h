@@ -93,13 +93,20 @@ struct Prefetch {
 // next wait + barrier.  Cheaper than a branch around each copy: the block stays one basic block for the scheduler.
 constexpr int NOWHERE = 0x7fff0000;
 
+// Where copies stand apart between products.  d = 64: with the additions in the statement (lds_copy16_piece; 2 heads x 10584 without the mask 114.7 us, 118.1 with them outside and an
+// s_nop), d = 128: outside (421 heads x 122 queries x 158 keys 9.3 us, 9.7 inside; 131 x 198 x 457 13.0 and 13.4; long calls the same within 1 %).
+template <int D>
+__device__ __forceinline__ void prefetch_piece(int i, const BufRsrc &r, lds_ptr lds, unsigned even, unsigned odd, int off) {
+    if constexpr (D == 64) lds_copy16_piece<2>(i, r, lds, even, odd, off);
+    else lds_copy16(r, lds + 1024 * i, i & 1 ? odd : even, off + 1024 * i);
+}
 template <int D>
 __device__ __forceinline__ void prefetch_k_piece(const Prefetch &nx, const LaneOffsets<D> &lo, int wave, int i) {
-    lds_copy16_piece<D / 32>(i, nx.k, nx.lk + wave * (D / 32) * 1024, lo.gk, lo.gk, nx.koff);
+    prefetch_piece<D>(i, nx.k, nx.lk + wave * (D / 32) * 1024, lo.gk, lo.gk, nx.koff);
 }
 template <int D>
 __device__ __forceinline__ void prefetch_v_piece(const Prefetch &nx, const LaneOffsets<D> &lo, int wave, int i) {
-    lds_copy16_piece<D / 32>(i, nx.v, nx.lv + wave * (D / 32) * 1024, lo.gv[0], lo.gv[1], nx.koff);
+    prefetch_piece<D>(i, nx.v, nx.lv + wave * (D / 32) * 1024, lo.gv[0], lo.gv[1], nx.koff);
 }
 // all pieces of a wavefront, one after the other (NT: with the non-temporal hint, for the passes that read every byte once)
 template <int D, bool NT = false>
