@@ -531,7 +531,7 @@ int launch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *s
 template <int D, bool CAUSAL, bool VB>
 int launch_fwd_dtype(const int8_t *Q, const int8_t *K, const int8_t *V, const float *sQ, const float *sK,
                      const float *sV, int heads, int Nq, int Nk, void *O, int o_dtype, hipStream_t st) {
-    const IfaKernel kernel = ifa_fwd_kernel(heads, Nq, Nk, D, CAUSAL);
+    const IfaKernel kernel = ifa_fwd_kernel(heads, Nq, Nk, D, CAUSAL, VB);
     if (kernel != IFA_KERNEL_FUSED)
         return ifa_launch_narrow(kernel, Q, K, V, sQ, sK, sV, heads, Nq, Nk, D, CAUSAL ? 1 : 0, VB ? 1 : 0, O, o_dtype, st);
     switch (o_dtype) {

@@ -62,25 +62,31 @@ static inline bool ifa_packed_queries(int heads, int Nq, int Nk, int d) {
 //                                   Half of the key blocks masked: the heaviest workgroup decides, and the two waves of the few-query kernel, which
 //                                   takes such calls from 2048 keys on, even out: 2 x 5000 33 (few-query) / 37, 1 x 14000 87 / 89; but 3 x 5000 45 / 38, 8 x 2048 22.8 / 20.4
 //   more, some of the blocks masked twice as many and smaller workgroups than the fused kernel's even out better, up to 512 of them the sooner the fewer they are: the
-//                                   other one's heaviest workgroup decides, this one's second wave is light and short.  The line (key sequences from
-//                                   4 w - 100 keys on, d = 64 3 w - 200, w workgroups) fitted to 2035 calls: of the kernels it takes one 0.4 % slower on average than the fastest
-//                                   (from 2048 keys on and with at most twice as many keys as queries only, 3.9 %).  Before (fused) / this one: 10 x 1996 d = 64 24.5 / 15.5,
-//                                   12 x 1518 d = 64 19.3 / 12.6, 12 x 1444 22.8 / 17.6, 3 x 5898 x 14531 187 / 132, 8 x 3084 x 7287 d = 64 82 / 67, 8 x 4096 56 / 41, 4 x 8192 107 / 69;
-//                                   not 24 x 757 14.3 / 15.9, 24 x 732 x 1629 25.8 / 28.7, 32 x 892 x 1979 31.5 / 33.6.
-//                                   Beyond 512, half of the blocks masked: 1 x 32768 410 / 236, 5 x 8192 115 / 99, 10 x 3380 d = 64 39.9 / 32.8; then not: 20 x 1600 25.8 / 25.9, 12 x 3200
-//                                   45.5 / 45.5, 7 x 8192 112 / 119.  The gain is spent the sooner the more keys lie in front of the queries, where all blocks are visible
-//                                   (fused -> this one, d = 128 / 64): 8 x 6124 x 6124 84.0 -> 82.9 / 68.9 -> 65.3, 8 x 5612 x 7015 101.6 -> 102.2 / 81.5 -> 81.3; beyond `keys`
-//                                   8 x 5612 x 8418 126 -> 127 / 99 -> 101, 8 x 6124 x 12248 195 -> 206 / 147 -> 161, 4 x 12268 x 24536 382 -> 394 / 287 -> 310
+//                                   other one's heaviest workgroup decides, this one's second wave is light and short.  How light falls with the keys in front of
+//                                   the queries, where all blocks are visible, and so does the line, in Nk / Nq.  Over 1550 causal calls a head size it is within .2 % of the
+//                                   faster kernel on average; 2 of the 943 taken more than 2 % slower.  Fused / this one: 10 x 1996 d = 64 24.5 / 15.5,
+//                                   12 x 1518 d = 64 19.3 / 12.6, 12 x 1444 22.8 / 17.6, 3 x 5898 x 14531 187 / 132, 8 x 4096 56 / 41, 4 x 8192 107 / 69; not 24 x 757 14.3 / 15.9,
+//                                   32 x 892 x 1979 31.5 / 33.6, 23 x 995 x 1791 27.5 / 30.2, 27 x 1099 x 3885 58.2 / 61.6, d = 64 39 x 565 x 922 14.0 / 15.7, 43 x 526 x 2081 26.2 / 29.6.
+//                                   Beyond 512, half of the blocks masked, up to 8 (10) heads: 1 x 32768 410 / 236, 5 x 8192 115 / 99, 10 x 3380 d = 64 39.9 / 32.8; then not:
+//                                   20 x 1600 25.8 / 25.9, 12 x 3200 45.5 / 45.5, 12 x 3047 x 4490 71.5 / 74.3, 7 x 8192 112 / 119; beyond `keys`
+//                                   8 x 5612 x 8418 126 / 127 (d = 64 99 / 101), 8 x 6124 x 12248 195 / 206 (147 / 161), 4 x 12268 x 24536 382 / 394 (287 / 310)
+//   ... with per-block V scales     (`vblock`) the change of unit per block costs this kernel's few wavefronts more, and the second wave has to be lighter still: within .1 %
+//                                   of the faster, 14 of 798 more than 2 % slower.  2 x 8419 d = 64 92.9 / 61.7, 5 x 3562 x 5755 65.3 / 46.0, d = 128 2 x 8214 110 / 66, 12 x 1444 23.0 / 18.0; not 43 x 526 x 2081 d = 64 27.3 / 34.7, 12 x 3047 x 4490 58.2 / 69.9,
+//                                   41 x 661 x 1156 17.4 / 20.8, 5 x 9696 110 / 122, d = 128 26 x 846 x 1479 24.9 / 28.6, 12 x 3047 x 4490 74 / 85
 //   more, all blocks visible        two waves of workgroups against one of the fused kernel's: 48 x 512 x 8192 107 (fused) / 111
-static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causal) {
+static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causal, bool vblock = false) {
     if (Nq <= 32 || ifa_query_groups(heads, Nq) <= 256) return false;
-    const long wgs = static_cast<long>(heads) * ((Nq + 63) / 64);
+    const long wgs = static_cast<long>(heads) * ((Nq + 63) / 64), keys = heads * static_cast<long>(Nk);
     const bool uneven = causal && 2L * Nq >= Nk;
     if (wgs <= 256) return Nk >= (d == 128 ? 512 : 384) && !(uneven && Nk >= 2048 && (heads == 1 || wgs <= 192));
     if (!causal || 4L * Nq < Nk) return false;
-    if (wgs <= 512) return Nk >= (d == 128 ? 4 * wgs - 100 : 3 * wgs - 200) && (uneven || Nk >= (d == 128 ? 3000 : 2048));
-    const long keys = 56L << 10;                                 // of all heads
-    return uneven && Nk >= 2048 && heads * static_cast<long>(Nk) <= keys && ((heads <= 8 && wgs <= 768) || (wgs <= 576 && Nk >= (d == 128 ? 4000 : 3000)));
+    if (vblock && (d == 128 ? 7L : 6L) * Nq < 2L * Nk) return false;
+    if (wgs <= 512) {                                            // Nk >= wgs (a + b (Nk / Nq - 1)) - c
+        const long a2 = d == 64 ? 6 : vblock ? 9 : 7, b = d == 64 ? (vblock ? 6 : 2) : (vblock ? 4 : 3), c = d == 64 ? 200 : vblock ? 400 : 100;   // (a2 = 2 a)
+        return 2 * (Nk + c) * Nq >= wgs * (a2 * Nq + 2 * b * (Nk > Nq ? Nk - Nq : 0));
+    }
+    if (vblock) return wgs <= (heads <= 8 ? (d == 128 ? 680 : 640) : heads <= 10 ? 576 : 0) && 4L * Nk <= (d == 128 ? 6L : 5L) * Nq && keys <= (d == 128 ? 48L : 40L) << 10;
+    return uneven && Nk >= 2048 && keys <= 56L << 10 && ((heads <= 8 && wgs <= 768) || (wgs <= 576 && Nk >= (d == 128 ? 4000 : 3000) && (heads <= 10 || 4L * Nk <= 5L * Nq)));
 }
 
 // Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  The
@@ -113,8 +119,8 @@ static inline bool ifa_unsplit_queries(int heads, int Nq, int Nk, int d) {
 
 // The kernel of an INT8 call
 enum IfaKernel { IFA_KERNEL_FUSED, IFA_KERNEL_PAIR, IFA_KERNEL_PACKED, IFA_KERNEL_FEW };
-static inline IfaKernel ifa_fwd_kernel(int heads, int Nq, int Nk, int d, bool causal) {
-    return ifa_pair_queries(heads, Nq, Nk, d, causal) ? IFA_KERNEL_PAIR : ifa_packed_queries(heads, Nq, Nk, d) ? IFA_KERNEL_PACKED :
+static inline IfaKernel ifa_fwd_kernel(int heads, int Nq, int Nk, int d, bool causal, bool vblock = false) {
+    return ifa_pair_queries(heads, Nq, Nk, d, causal, vblock) ? IFA_KERNEL_PAIR : ifa_packed_queries(heads, Nq, Nk, d) ? IFA_KERNEL_PACKED :
            ifa_few_queries(heads, Nq, Nk, d, false) ? IFA_KERNEL_FEW : IFA_KERNEL_FUSED;
 }
 

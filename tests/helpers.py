@@ -44,7 +44,7 @@ def random_int8_problem(rng, heads, N, d, score_sigma=1.0):
 
 _RULES = r"""
 #include "intfa_internal.h"
-extern "C" int route(int heads, int Nq, int Nk, int d, int causal) { return ifa_fwd_kernel(heads, Nq, Nk, d, causal); }
+extern "C" int route(int heads, int Nq, int Nk, int d, int causal, int vblock) { return ifa_fwd_kernel(heads, Nq, Nk, d, causal, vblock); }
 extern "C" int few_half(int heads, int Nq, int Nk, int d) { return ifa_few_queries(heads, Nq, Nk, d, true); }
 extern "C" int unsplit(int heads, int Nq, int Nk, int d) { return ifa_unsplit_queries(heads, Nq, Nk, d); }
 """
@@ -63,13 +63,13 @@ def library_rules():
         return ctypes.CDLL(lib)
 
 
-def route(heads, Nq, Nk, d, causal=None, half=False):
+def route(heads, Nq, Nk, d, causal=None, half=False, vblock=False):
     """Which kernel a plain attention call runs: "fused", "few" (twelve wavefronts per 32 queries, half-INT8 eight), "packed" or "pair" (two groups of 32
-    queries).  `causal` decides nothing for half-INT8."""
+    queries).  `causal` decides nothing for half-INT8; `vblock`: per-block V scales."""
     if half:
         return "few" if library_rules().few_half(heads, Nq, Nk, d) else "fused"
     assert causal is not None
-    return ("fused", "pair", "packed", "few")[library_rules().route(heads, Nq, Nk, d, int(causal))]
+    return ("fused", "pair", "packed", "few")[library_rules().route(heads, Nq, Nk, d, int(causal), int(vblock))]
 
 
 def unsplit(heads, Nq, Nk, d):

@@ -9,7 +9,7 @@ from helpers import route, unsplit
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def stated_route(heads, Nq, Nk, d, causal=None, half=False):
+def stated_route(heads, Nq, Nk, d, causal=None, half=False, vblock=False):
     """The rule of helpers.route, stated again."""
     groups = heads * -(-Nq // 32)
     if not half:
@@ -19,11 +19,18 @@ def stated_route(heads, Nq, Nk, d, causal=None, half=False):
             if wgs <= 256:
                 pair = Nk >= (512 if d == 128 else 384) and not (uneven and Nk >= 2048 and (heads == 1 or wgs <= 192))
             else:
-                line = 4 * wgs - 100 if d == 128 else 3 * wgs - 200
-                if wgs <= 512:
-                    pair = causal and 4 * Nq >= Nk >= line and (uneven or Nk >= (3000 if d == 128 else 2048))
+                keys = heads * Nk
+                if not causal or (4 if not vblock else 3 if d == 64 else 3.5) * Nq < Nk:
+                    pair = False
+                elif wgs <= 512:
+                    a, b, c = {(64, 0): (3, 2, 200), (64, 1): (3, 6, 200), (128, 0): (3.5, 3, 100), (128, 1): (4.5, 4, 400)}[d, int(vblock)]
+                    pair = (Nk + c) * Nq >= wgs * (a * Nq + b * max(Nk - Nq, 0))
+                elif vblock:
+                    pair = (wgs <= ((680 if d == 128 else 640) if heads <= 8 else 576 if heads <= 10 else 0) and 4 * Nk <= (6 if d == 128 else 5) * Nq and
+                            keys <= (48 if d == 128 else 40) << 10)
                 else:
-                    pair = uneven and Nk >= 2048 and heads * Nk <= 56 << 10 and (heads <= 8 and wgs <= 768 or wgs <= 576 and Nk >= (4000 if d == 128 else 3000))
+                    pair = uneven and Nk >= 2048 and keys <= 56 << 10 and (heads <= 8 and wgs <= 768 or wgs <= 576 and Nk >= (4000 if d == 128 else 3000) and
+                                                                           (heads <= 10 or 4 * Nk <= 5 * Nq))
             if pair:
                 return "pair"
         if Nk <= 128 if groups <= 256 else d == 64 and (Nk <= (768 if groups <= 1024 else 1152) if Nq <= 32 else
@@ -51,9 +58,9 @@ PROGRAM = r"""
 #include <cstdio>
 int main() {
     const char *const name[] = {"fused", "pair", "packed", "few"};
-    int heads, Nq, Nk, d, causal, half;
-    while (scanf("%d %d %d %d %d %d", &heads, &Nq, &Nk, &d, &causal, &half) == 6)
-        puts(half ? name[ifa_few_queries(heads, Nq, Nk, d, true) ? IFA_KERNEL_FEW : IFA_KERNEL_FUSED] : name[ifa_fwd_kernel(heads, Nq, Nk, d, causal)]);
+    int heads, Nq, Nk, d, causal, half, vblock;
+    while (scanf("%d %d %d %d %d %d %d", &heads, &Nq, &Nk, &d, &causal, &half, &vblock) == 7)
+        puts(half ? name[ifa_few_queries(heads, Nq, Nk, d, true) ? IFA_KERNEL_FEW : IFA_KERNEL_FUSED] : name[ifa_fwd_kernel(heads, Nq, Nk, d, causal, vblock)]);
     return 0;
 }
 """
@@ -72,7 +79,7 @@ def library_says(tmp_path, program, cases):
 
 
 def test_helpers_route_is_the_librarys_rule(tmp_path):
-    cases = [(heads, Nq, Nk, d, causal, half) for d in (64, 128) for causal, half in ((0, 0), (1, 0), (0, 1)) for Nq in (1, 31, 32, 33, 64, 65, 127, 128, 1000, 4100, 8192)
+    cases = [(heads, Nq, Nk, d, causal, half, vblock) for d in (64, 128) for causal, half, vblock in ((0, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 0, 1)) for Nq in (1, 31, 32, 33, 64, 65, 127, 128, 1000, 4100, 8192)
              for heads in (1, 2, 4, 8, 9, 64, 65, 128, 129, 171, 256, 257, 300, 512, 513, 1000, 1024, 1025, 5 << 20, (5 << 20) + 1)
              for Nk in (1, 64, 65, 127, 128, 129, 256, 257, 383, 384, 385, 511, 512, 768, 769, 1024, 1025, 1152, 1153, 1280, 1281, 2047, 2048, 7168, 7169, 16384, 28672, 28673)]
     assert library_says(tmp_path, PROGRAM, cases) == [stated_route(*c) for c in cases] == [route(*c) for c in cases]
@@ -93,6 +100,15 @@ def test_helpers_unsplit_is_the_librarys_rule(tmp_path):
     cases = [(heads, Nq, Nk, d) for d in (64, 128) for Nq in range(1, 33) for heads in (1, 2, 8, 15, 16, 17, 31, 32, 33, 64, 71, 72, 95, 96, 112, 129, 160, 6_000_000)
              for Nk in (1, 2, 2047, 2048, 2049, 2304, 2305, 3000, 4096, 4097, 8192, 16384, 32768, 1 << 20, 1 << 24)]
     assert library_says(tmp_path, SPLIT_PROGRAM, cases) == ["01"[stated_unsplit(*c)] for c in cases] == ["01"[unsplit(*c)] for c in cases]
+
+
+# Causal calls with more workgroups of 64 queries than CUs: the side on which a call ran at least 8 % faster
+@pytest.mark.parametrize("heads,Nq,Nk,d,vblock,kernel", [
+    (12, 1444, 1444, 128, False, "pair"), (3, 5898, 14531, 128, False, "pair"), (10, 3380, 3380, 64, False, "pair"), (23, 995, 1791, 128, False, "fused"), (43, 526, 2081, 64, False, "fused"),
+    (39, 565, 922, 64, False, "fused"), (12, 1444, 1444, 128, True, "pair"), (12, 3047, 4490, 64, True, "fused"), (43, 526, 2081, 64, True, "fused"), (21, 1419, 5215, 64, True, "fused"),
+    (26, 846, 1479, 128, True, "fused"), (5, 9696, 9696, 64, True, "fused"), (13, 2813, 3520, 64, True, "fused")])
+def test_calls_with_a_second_wave_on_the_faster_side(heads, Nq, Nk, d, vblock, kernel):
+    assert route(heads, Nq, Nk, d, True, vblock=vblock) == kernel
 
 
 # Calls of the key-split entry points beside which the other side measured at least 11 % slower, on the same K and V and on K and V in rotation
