@@ -81,9 +81,10 @@ static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causa
     if (wgs <= 256) return Nk >= (d == 128 ? 512 : 384) && !(uneven && Nk >= 2048 && (heads == 1 || wgs <= 192));
     if (!causal || 4L * Nq < Nk) return false;
     if (vblock && (d == 128 ? 7L : 6L) * Nq < 2L * Nk) return false;
-    if (wgs <= 512) {                                            // Nk >= wgs (a + b (Nk / Nq - 1)) - c
-        const long a2 = d == 64 ? 6 : vblock ? 9 : 7, b = d == 64 ? (vblock ? 6 : 2) : (vblock ? 4 : 3), c = d == 64 ? 200 : vblock ? 400 : 100;   // (a2 = 2 a)
-        return 2 * (Nk + c) * Nq >= wgs * (a2 * Nq + 2 * b * (Nk > Nq ? Nk - Nq : 0));
+    if (wgs <= 512) {                                            // Nk >= wgs (a + b max(0, Nk / Nq - 9 / 8)) - c
+        const long a2 = d == 64 ? 6 : vblock ? 9 : 8, b2 = d == 64 ? (vblock ? 14 : 5) : (vblock ? 10 : 6), c = d == 64 ? 200 : vblock ? 400 : 100;   // 2 a, 2 b
+        const long front = 8L * Nk - 9L * Nq;
+        return 16 * (Nk + c) * Nq >= wgs * (8 * a2 * Nq + b2 * (front > 0 ? front : 0));
     }
     if (vblock) return wgs <= (heads <= 8 ? (d == 128 ? 680 : 640) : heads <= 10 ? 576 : 0) && 4L * Nk <= (d == 128 ? 6L : 5L) * Nq && keys <= (d == 128 ? 48L : 40L) << 10;
     return uneven && Nk >= 2048 && keys <= 56L << 10 && ((heads <= 8 && wgs <= 768) || (wgs <= 576 && Nk >= (d == 128 ? 4000 : 3000) && (heads <= 10 || 4L * Nk <= 5L * Nq)));

@@ -23,8 +23,8 @@ def stated_route(heads, Nq, Nk, d, causal=None, half=False, vblock=False):
                 if not causal or (4 if not vblock else 3 if d == 64 else 3.5) * Nq < Nk:
                     pair = False
                 elif wgs <= 512:
-                    a, b, c = {(64, 0): (3, 2, 200), (64, 1): (3, 6, 200), (128, 0): (3.5, 3, 100), (128, 1): (4.5, 4, 400)}[d, int(vblock)]
-                    pair = (Nk + c) * Nq >= wgs * (a * Nq + b * max(Nk - Nq, 0))
+                    a, b, c = {(64, 0): (3, 2.5, 200), (64, 1): (3, 7, 200), (128, 0): (4, 3, 100), (128, 1): (4.5, 5, 400)}[d, int(vblock)]
+                    pair = (Nk + c) * Nq >= wgs * (a * Nq + b * max(Nk - 1.125 * Nq, 0))
                 elif vblock:
                     pair = (wgs <= ((680 if d == 128 else 640) if heads <= 8 else 576 if heads <= 10 else 0) and 4 * Nk <= (6 if d == 128 else 5) * Nq and
                             keys <= (48 if d == 128 else 40) << 10)
