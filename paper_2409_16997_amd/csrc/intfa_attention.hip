@@ -67,7 +67,7 @@ using namespace ifa_tiles;
 // block, 2000 measured): one wavefront in its MFMAs leaves the other to issue vector instructions alone, at half of the rate two reach.  For three,
 // 168 registers hold the block: Q comes from LDS every block (8 registers less) and V1 keeps the s_K of one key tile, reloaded as they
 // are used (16 less).  Two / three, us: 128 x 4096 causal 289 / 263, 32 x 9974 causal 377 / 346, 256 x 1398 131 / 121, 96 x 1024 28.5 / 25.8, 600 x 128
-// causal 8.0 / 6.0, 90 x 700 22.5 / 19.1.  Which calls take three: launch_fwd().
+// causal 8.0 / 6.0, 90 x 700 22.5 / 19.1.  Which calls take three: ifa_fused_wavefronts().
 template <int D, int W> struct Smem {
     alignas(4096) int8_t k[2][BC * D];   // K_j, row = key, 16-byte slots XOR-swizzled by row
     alignas(1024) int8_t v[2][BC * D];   // V_j, row = key, 16-byte slots XOR-swizzled by row
@@ -507,22 +507,14 @@ int launch_fwd(const int8_t *Q, const int8_t *K, const int8_t *V, const float *s
                int heads, int Nq, int Nk, void *O, hipStream_t st) {
     const int T_r = (Nq + BR - 1) / BR;
     const long wgs = static_cast<long>(heads) * T_r;
+    const int head_group = head_group_for(CAUSAL, 2L * Nk * D, T_r);
     auto launch = [&](auto w) {
         hipLaunchKernelGGL((int_flash_attn_fwd_kernel<D, decltype(w)::value, CAUSAL, VB, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,
-                           st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, head_group_for(CAUSAL, 2L * Nk * D, T_r), static_cast<OutT *>(O),
+                           st, Q, K, V, sQ, sK, sV, heads, Nq, Nk, head_group, static_cast<OutT *>(O),
                            DebugDump{nullptr, nullptr, nullptr, nullptr, 0});
     };
     if constexpr (D == 64) {
-        // Three wavefronts per SIMD where a third workgroup per CU has something to do.  If a little more than 512 are uneven, all of them start at
-        // once and the heaviest decide; with two to a CU the light ones start where a CU has become free.  Two / three, us: 96 x 800 causal
-        // 16.9 / 20.0 (672 workgroups), 100 x 900 20.2 / 23.3 (800), 14 x 7800 103 / 112 (854); but 110 x 1024 25.6 / 25.1 (880), 90 x 1300 32.5 /
-        // 29.0 (990), and with three query blocks a head and fewer 300 x 250 9.5 / 8.6 (600), 230 x 300 11.3 / 9.5 (690), 280 x 300 12.9 / 11.8 (840).
-        // With 12 to 15 query blocks a head that goes on for longer, with more of them a little: 100 x 1732 49.0 / 54.6 (1400), 107 x 1900 58.9 / 66.6 (1605), 158 x 1732
-        // 76.5 / 78.8 (2212), 215 x 1732 106.7 / 99.6 (3010); 32 x 3519 53.9 / 54.6 (896), 50 x 3012 62.4 / 63.9 (1200), 83 x 2116 66.6 / 61.2 (1411), 67 x 2628 67.8 / 64.5
-        // (1407).  277 such calls with a scale per token take .965 of the time of two everywhere, with the better of both for each .959; off by most 45 x 5740, 197 / 214.
-        // Up to 512 the shorter way to the operands is worth 1 - 2 %: 100 x 512 10.5 / 10.8.
-        const bool uneven = CAUSAL && 2L * Nq >= Nk && T_r > 3;
-        if (wgs > (!uneven ? 512 : T_r <= 11 ? 864 : T_r <= 15 ? 2250 : 1250)) launch(std::integral_constant<int, 3>{});
+        if (ifa_fused_wavefronts(heads, Nq, Nk, D, CAUSAL, head_group) == 3) launch(std::integral_constant<int, 3>{});
         else launch(std::integral_constant<int, 2>{});
     } else launch(std::integral_constant<int, 2>{});
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;

@@ -18,7 +18,6 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <hip/hip_bf16.h>
-#include <limits.h>
 #include <stdint.h>
 #include <type_traits>
 
@@ -816,19 +815,13 @@ int launch_half(const int8_t *Q, const int8_t *K, const _Float16 *V, const float
     }
     const int T_r = (Nq + BR - 1) / BR;
     const long wgs = static_cast<long>(heads) * T_r;
+    // T_r = 0: under the mask this kernel keeps 4 heads per group (8 measured 4-17 % slower here at N = 1280 .. 2048)
+    const int head_group = head_group_for(CAUSAL, 3L * Nk * D, 0);
     auto launch = [&](auto w) {
-        // T_r = 0: under the mask this kernel keeps 4 heads per group (8 measured 4-17 % slower here at N = 1280 .. 2048)
         hipLaunchKernelGGL((int_flash_attn_fwd_half_kernel<D, decltype(w)::value, CAUSAL, OutT>), dim3(static_cast<unsigned>(wgs)), dim3(THREADS), 0,
-                           st, Q, K, V, sQ, sK, heads, Nq, Nk, head_group_for(CAUSAL, 3L * Nk * D, 0), static_cast<OutT *>(O));
+                           st, Q, K, V, sQ, sK, heads, Nq, Nk, head_group, static_cast<OutT *>(O));
     };
-    // More wavefronts per SIMD where there are workgroups for them: 768 (d = 64: 1024) then start at once instead of 512.  Uneven ones even out better two to a CU
-    // while there are few, and between 25 and 63 query tiles always (two / more, us: d = 128, 70 x 1000 causal 30.4 / 33.8 = 560 workgroups, 16 x 6656 174 / 188 = 832,
-    // 192 x 668 39.3 / 43.0 = 1152, 256 x 1024 1.6 % slower = 2048, 87 x 3837 313 / 332 = 2610, 128 x 4096 0.8 % slower = 4096; 267 x 768 61.0 / 58.8 = 1602,
-    // 222 x 2204 310 / 295 = 3996, 32 x 8192 488 / 472 = 2048; d = 64, 130 x 1000 36.9 / 39.7 = 1040, 144 x 1152 47.4 / 41.1 = 1296), and at d = 128 769 to 1024 even
-    // ones, which start in two waves of 512, would do so in two waves of 768 (71 x 1792 3 % slower, 20 x 5120 4 %; 32 x 5120 11 % faster).
-    const bool uneven = CAUSAL && 2L * Nq >= Nk && T_r > 3;
-    const bool more = uneven ? wgs > (D == 64 ? 1024 : T_r <= 6 ? 1250 : T_r <= 24 ? 2700 : T_r >= 64 ? 1100 : LONG_MAX) : wgs > 512 && !(D == 128 && T_r > 3 && wgs > 768 && wgs <= 1024);
-    if (more) launch(std::integral_constant<int, D == 64 ? 4 : 3>{});
+    if (ifa_half_wavefronts(heads, Nq, Nk, D, CAUSAL, head_group) > 2) launch(std::integral_constant<int, D == 64 ? 4 : 3>{});
     else launch(std::integral_constant<int, 2>{});
     return hipGetLastError() == hipSuccess ? IFA_OK : IFA_ERR_HIP;
 }

@@ -90,6 +90,40 @@ static inline bool ifa_pair_queries(int heads, int Nq, int Nk, int d, bool causa
     return uneven && Nk >= 2048 && keys <= 56L << 10 && ((heads <= 8 && wgs <= 768) || (wgs <= 576 && Nk >= (d == 128 ? 4000 : 3000) && (heads <= 10 || 4L * Nk <= 5L * Nq)));
 }
 
+// ---- wavefronts per SIMD of the fused kernels ------------------------------------------------------------------------
+// Workgroups have 128 queries and two, three or four of them share a CU.  Calls with more than 512 of them have work for a third (half-INT8, d = 64: a fourth); calls that
+// two to a CU hold in one round keep two, whose way to the operands is shorter.
+//   Even calls (no mask, few keys masked, or up to three workgroups a head): rounds decide.  769 to 1024 are two rounds of 512 and two of 768.
+//   Uneven ones (under the mask, at most twice as many keys as queries): an XCD takes its heads in groups, the heaviest workgroups of a group first (map_workgroup()), and a workgroup
+// runs the slower the more share its CU.  With one whole group and part of a second, the heavy ones of the second start when the light ones of the first end, and there is little
+// left to even them out: two to a CU end sooner.  `groups` = heads / 8 / heads of a group.  Each line with what it measured, us, two / three (four), from 2024 and 1762 uneven calls
+// a head size.
+static inline bool ifa_even_workgroups(int Nq, int Nk, bool causal) { return !causal || 2L * Nq < Nk || Nq <= 3 * 128; }
+// INT8, d = 64: from 865 workgroups (12 to 15 a head: 2251, 16 and more: 1251) on, without one and a half groups of heads that have 20 to 49 each.  96 x 800 causal 16.9 / 20.0 (672),
+// 100 x 900 20.2 / 23.3 (800); 110 x 1024 25.6 / 25.1 (880), 100 x 1732 49.0 / 54.6 (1400, 14 a head), 215 x 1732 106.7 / 99.6 (3010), 83 x 2116 66.6 / 61.2 (1411, 17 a head); in one and a
+// half groups 45 x 5740 197 / 214, 50 x 6174 242 / 255, 50 x 4446 135 / 143, 88 x 3016 118 / 124.  The calls so taken: .956 of two everywhere (with the better of both .947), 17 of 2024
+// more than 3 % slower than with two, 37 without the last condition; off by most 109 x 1293 x 2061 62.6 / 69.1.  Even: 300 x 250 9.5 / 8.6 (600), 230 x 300 11.3 / 9.5; 70 x 1516 x 3308 80.6 / 83.7 (840), 31 x 3216 100 / 102 (806).
+static inline int ifa_fused_wavefronts(int heads, int Nq, int Nk, int d, bool causal, int head_group) {
+    if (d != 64) return 2;                                       // (256 registers a wavefront)
+    const long T_r = (Nq + 127) / 128, wgs = heads * T_r, group = 8L * head_group;
+    if (ifa_even_workgroups(Nq, Nk, causal)) return wgs > 512 && !(T_r > 3 && wgs > 768 && wgs <= 1024) ? 3 : 2;
+    if (wgs <= (T_r <= 11 ? 864 : T_r <= 15 ? 2250 : 1250)) return 2;
+    return T_r >= 20 && T_r < 50 && 8L * heads >= 11 * group && 4L * heads < 7 * group ? 2 : 3;
+}
+// Half-INT8, d = 64, four: from 1025 on, without one and a quarter to two groups (of four heads here) of 30 to 41 a head: 35 x 4446 ... 50 x 4446 180 / 208, 40 x 4948 192 / 214, 42 x 4770 185 / 205; but
+// 82 x 2008 84 / 65 (1312), 144 x 1152 47.4 / 41.1 (1296).  .939 of two everywhere (.930), 18 of 1762 more than 3 % slower, 51 without; off by most 69 x 1831 (1035).
+//   d = 128, three: with up to 6 a head from 1251 on, with more from 2251 on with five groups of heads and more; one group of 35 and more a head from 1101 on.  192 x 668 39.3 / 43.0 (1152), 87 x 3837
+// 313 / 332 (2610), 46 x 8099 684 / 713 (2944, one and a half groups); 267 x 768 61.0 / 58.8, 222 x 2204 310 / 295 (3996), 32 x 8192 488 / 472 (2048, one group), 32 x 16384 1874 / 1811.  .985 of two
+// everywhere (.973), 1 of 1768 more than 3 % slower.  Even: 71 x 1792 3 % slower (994), 490 x 180 x 685 50.2 / 54.4 (980), 264 x 258 x 697 45.6 / 48.2 (792); 32 x 5120 11 % faster (1280).
+static inline int ifa_half_wavefronts(int heads, int Nq, int Nk, int d, bool causal, int head_group) {
+    const long T_r = (Nq + 127) / 128, wgs = heads * T_r, group = 8L * head_group, h8 = 8L * heads;
+    const int more = d == 64 ? 4 : 3;
+    if (ifa_even_workgroups(Nq, Nk, causal)) return wgs > 512 && !(d == 128 && wgs > 768 && wgs <= 1024) ? more : 2;
+    if (d == 64) return wgs > 1024 && !(T_r >= 30 && T_r < 42 && h8 >= 10 * group && 16L * heads < 33 * group) ? more : 2;
+    if (T_r <= 6) return wgs > 1250 ? more : 2;
+    return (heads >= 5 * group && wgs > 2250) || (T_r >= 35 && wgs > 1100 && h8 >= (T_r >= 46 ? 5 : 6) * group && h8 < 9 * group) ? more : 2;
+}
+
 // Which calls of the key-split entry points do without the split: they run the kernel that int_flash_attn_fwd_rect picks.  The
 // few-query kernel walks 1000 keys of every head in 5 us (d = 64: 3.5) however many heads there are, until the chip is full, and
 // starts 7 us sooner (from 9 queries on 10); the split passes stream K, V and the scores (or K twice) of all heads, so they win while heads are few and keys are many:

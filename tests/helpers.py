@@ -44,9 +44,14 @@ def random_int8_problem(rng, heads, N, d, score_sigma=1.0):
 
 _RULES = r"""
 #include "intfa_internal.h"
+#include "intfa_device.h"
 extern "C" int route(int heads, int Nq, int Nk, int d, int causal, int vblock) { return ifa_fwd_kernel(heads, Nq, Nk, d, causal, vblock); }
 extern "C" int few_half(int heads, int Nq, int Nk, int d) { return ifa_few_queries(heads, Nq, Nk, d, true); }
 extern "C" int unsplit(int heads, int Nq, int Nk, int d) { return ifa_unsplit_queries(heads, Nq, Nk, d); }
+extern "C" int wavefronts(int heads, int Nq, int Nk, int d, int causal, int half) {
+    if (half) return ifa_half_wavefronts(heads, Nq, Nk, d, causal, ifa_dev::head_group_for(causal, 3L * Nk * d, 0));
+    return ifa_fused_wavefronts(heads, Nq, Nk, d, causal, ifa_dev::head_group_for(causal, 2L * Nk * d, (Nq + 127) / 128));
+}
 """
 
 
@@ -75,6 +80,12 @@ def route(heads, Nq, Nk, d, causal=None, half=False, vblock=False):
 def unsplit(heads, Nq, Nk, d):
     """Whether a call of the key-split entry points runs the kernel of the plain call."""
     return bool(library_rules().unsplit(heads, Nq, Nk, d))
+
+
+def wavefronts(heads, Nq, Nk, d, causal, half=False):
+    """Wavefronts per SIMD of the fused kernel (half-INT8: of its own) for a call that runs it."""
+    assert route(heads, Nq, Nk, d, causal, half) == "fused"
+    return library_rules().wavefronts(heads, Nq, Nk, d, int(causal), int(half))
 
 
 def copies_for(kernel, heads, Nq, Nk, d, causal=None, half=False):

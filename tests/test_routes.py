@@ -4,7 +4,7 @@ import subprocess
 
 import pytest
 
-from helpers import route, unsplit
+from helpers import route, unsplit, wavefronts
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -118,3 +118,13 @@ def test_calls_with_a_second_wave_on_the_faster_side(heads, Nq, Nk, d, vblock, k
     (64, 5, 16384, 64, False), (24, 32, 16384, 128, False), (48, 1, 8192, 64, False)])
 def test_key_split_calls_on_the_faster_side(heads, Nq, Nk, d, few):
     assert unsplit(heads, Nq, Nk, d) == few
+
+
+# Wavefronts per SIMD where a call ran at least 4 % faster with two, or with more
+@pytest.mark.parametrize("heads,Nq,Nk,d,causal,half,more", [
+    (45, 5740, 5740, 64, True, False, False), (50, 6174, 6174, 64, True, False, False), (88, 3016, 3016, 64, True, False, False), (100, 1732, 1732, 64, True, False, False),
+    (83, 2116, 2116, 64, True, False, True), (128, 4096, 4096, 64, True, False, True), (300, 250, 250, 64, False, False, True), (50, 4446, 4446, 64, True, True, False),
+    (40, 4948, 4948, 64, True, True, False), (82, 2008, 2008, 64, True, True, True), (490, 180, 685, 128, True, True, False), (32, 5120, 5120, 128, False, True, True),
+    (267, 768, 768, 128, True, True, True), (192, 668, 668, 128, True, True, False)])
+def test_wavefronts_on_the_faster_side(heads, Nq, Nk, d, causal, half, more):
+    assert (wavefronts(heads, Nq, Nk, d, causal, half) > 2) == more
