@@ -167,8 +167,8 @@ int int_flash_attn_fwd_rect(const signed char *Q_i8, const signed char *K_i8, co
  * them again from K), so that each part of the key axis forms P on the grid of the running maximum the sequential
  * walk of Algorithm 1 would have at that block: P and the int32 P V are those of int_flash_attn_fwd_rect bit for bit,
  * and O differs from its result only by the order of the fp32 additions of lines 12-13 (the partial (m, l, O) of the
- * parts are merged with e^{m_part - m}, once per part instead of once per block).  With at most 2048 keys or with many heads
- * (at 4096 keys from 24 to 70 on, at 32768 from 66 to 130, by Nq and d) the split does not pay and the call is
+ * parts are merged with e^{m_part - m}, once per part instead of once per block).  On short key sequences (2048 keys, with one
+ * query 3000, the more the more heads) or with many heads (at 4096 keys from 15 to 40 on, at 32768 from 65 to 116, by Nq and d) the split does not pay and the call is
  * int_flash_attn_fwd_rect.
  *   workspace         device memory, 256-byte aligned, at least ifa_splitk_workspace_bytes(B, H, Nq, Nk, d) bytes
  *                     (else IFA_ERR_WORKSPACE); owned by the caller, contents undefined before and after, must not be

@@ -876,7 +876,8 @@ __global__ __launch_bounds__(THREADS) void int_flash_attn_fwd_packed_kernel(
 // brings in, the others find in L2 (a CU takes in 59 GB/s from beyond it and 120 - 140 out of it).
 // What bounds it is the chain of a wavefront through a window, 5 us at d = 128 (4.9 with the next entry of the ring requested before the operands of this one are read,
 // as it is; 5.9 with the place of this one refilled once they are read, twice as much in flight; with products of 32 x 32 x 32, whose chains are
-// twice as long, 5.9 and 6.2; eight wavefronts with two blocks each and 32 x 32 x 32 6.4), beside 2.3 us that 320 KB take at best.  Few-query kernel / this one, us, in a graph:
+// twice as long, 5.9 and 6.2; eight wavefronts with two blocks each and 32 x 32 x 32 6.4), beside 2.3 us that 320 KB take at best (23 % of the cycles issue vector
+// instructions, 27 % are LDS's); as long with per-block V scales, which cost .6 us a call.  Few-query kernel / this one, us, in a graph:
 // 32 heads x 4099 keys 20.7 / 14.6, 8 x 2603 13.1 / 8.9, 64 x 579 6.3 / 4.9, 16 x 16384 64.8 / 42.1, 64 x 18595 97.6 / 79; d = 64, 32 x 4099 16.2 / 11.0, 64 x 32768 109 / 74.
 // The numbers are those of the other kernels: integer sums, the maximum is order-independent, the row sum is kept per half of the keys (bit 2 of the key's index)
 // as their lanes do, and the fp32 folds are the same, block by block.
@@ -1133,7 +1134,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void int_flash_attn_fwd_decode_kern
 
 // ---- two to eight queries per head (a few draft tokens) ------------------------------------------------------------
 // The decode kernel with the queries in the columns of its products: a lane (c, G) holds the scores of query c for 32 of the block's keys, and P in the order in which
-// the second product takes it, so neither goes through LDS.  A window takes 5.3 us (the decode kernel's 4.9), with eight queries as with two.  Few-query kernel / this
+// the second product takes it, so neither goes through LDS.  A window takes 5.3 - 6 us (the decode kernel's 5), half of it vector issue; per-block V scales add .4 - 1.4 us a call.  Few-query kernel / this
 // one, us: 32 heads x 5 queries x 4900 keys 23.9 / 19.1, 8 x 8 x 2048 10.8 / 8.1, 32 x 8 x 16384 75 / 51; d = 64, 64 x 8 x 4900 20.3 / 15.2, 32 x 2 x 16384 56 / 37.
 constexpr int DRAFT_MAX_Q = 8;
 template <int D, int DS> struct SmemDraft {
@@ -1926,7 +1927,7 @@ int launch_narrow(IfaKernel kernel, const int8_t *Q, const int8_t *K, const int8
     // find a line gone: right after K and V were written the call below fetched 730 - 790 MB, 545 with DS = 1.)  128 heads x 1 x 16384, 537 MB, us, after
     // the same call / after a read of 512 MB elsewhere / after a copy of 512 MB / right after K and V were quantized:
     //   hint, DS = 1 94 / 95 / 112 / 108;  hint, DS = 2 89 / 91 / 109 / 139;  no hint, DS = 2 100 / 100 / 120 / 122;  key split 100 / 103 / 112 / 112.
-    // Below the line, 64 x 1 x 4096, 67 MB: hint, DS = 1 22.9 / 27.3 / 27.8 / 23.5; no hint, DS = 2 20.0 / 27.4 / 32.4 / 22.5.
+    // (At d = 128 the line matters from 65 heads on, at d = 64 from 129 on: fewer with one query run the decode kernel.)
     const int once = qgroups == 1 && 2L * heads * Nk * D > (64L << 20);
     auto launch = [&](auto ds) {
         constexpr int DS = decltype(ds)::value;

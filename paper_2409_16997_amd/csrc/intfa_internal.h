@@ -128,15 +128,13 @@ static inline int ifa_half_wavefronts(int heads, int Nq, int Nk, int d, bool cau
 // few-query kernel walks 1000 keys of every head in 5 us (d = 64: 3.5) however many heads there are, until the chip is full, and
 // starts 7 us sooner (from 9 queries on 10); the split passes stream K, V and the scores (or K twice) of all heads, so they win while heads are few and keys are many:
 //     few-query  u + v Nk,   split  u' + w heads (Nk + E),   the same at heads (Nk + E) = H (Nk - S).
-// S is the start in keys; H falls with Nq, whose scores and partial outputs only the split moves through memory.  Fitted to 3590 calls, each
-// repeated on the same K and V and on K and V in rotation: of the two ways the rule takes one that is 0.1 % slower on average than the faster.
+// S is the start in keys; H falls with Nq, whose scores and partial outputs only the split moves through memory.  Fitted to 3590 calls, each repeated on the same K and V
+// and on K and V in rotation; it decides the calls that the decode kernel and its form for two to eight do not take (below): of those of up to eight queries the ones of
+// more than 64 heads, at d = 64 128, where only one or two queries on more than 34000 keys still split.
 // Both sides of the line, heads x queries x keys, few-query / split, us, repeated; (in rotation):
-//   d = 128   32 x 1 x 3000 14.8 / 15.5 (17.7 / 17.0), 40 15.4 / 16.3 (18.1 / 17.7);  80 x 1 x 8192 45.4 / 41.6, 88 45.6 / 43.5;  112 x 1 x 32768 178 / 177, 128 181 / 194;
-//             32 x 8 x 4096 19.7 / 18.0 (23.3 / 19.8), 40 19.9 / 23.8;  72 x 8 x 16384 85 / 79, 80 86 / 88;  56 x 9 x 8192 43.2 / 43.9, 64 43.6 / 46.6;
+//   d = 128   80 x 1 x 8192 45.4 / 41.6, 88 45.6 / 43.5;  112 x 1 x 32768 178 / 177, 128 181 / 194;  72 x 8 x 16384 85 / 78, 80 85 / 86;  56 x 9 x 8192 43.2 / 43.9, 64 43.6 / 46.6;
 //             64 x 16 x 16384 83.8 / 80.4, 72 84.8 / 89.4;  24 x 32 x 4096 19.1 / 20.0 (22.9 / 21.5), 32 20.4 / 21.1;  64 x 32 x 32768 164 / 154, 72 166 / 177
-//   d = 64    48 x 1 x 3000 12.5 / 13.4 (14.1 / 15.0);  96 x 1 x 8192 31.7 / 28.7, 104 32.2 / 31.0;  128 x 1 x 32768 113 / 114, 144 113 / 131;  80 x 4 x 8192 30.4 / 29.1,
-//             88 30.5 / 30.4;  72 x 8 x 16384 56.9 / 53.1, 80 57.2 / 58.2;  72 x 9 x 8192 30.9 / 29.6, 80 31.4 / 32.7;  80 x 16 x 16384 57.9 / 55.3, 88 58.2 / 59.0;  80 x 32 x 32768
-//             112 / 109, 88 114 / 118
+//   d = 64    144 x 1 x 32768 114 / 131;  72 x 9 x 8192 30.9 / 29.6, 80 31.4 / 32.7;  80 x 16 x 16384 57.9 / 55.3, 88 58.2 / 59.0;  80 x 32 x 32768 112 / 109, 88 114 / 118
 // Off by most: 8 x 16 x 2500 at d = 128 (12.5 us split, 15.7 taken; in rotation 15.1 and 15.8), 32 x 16 x 4096 (18.4 split, 19.8 taken).
 // One query: the decode kernel's own line, decode kernel / split, K and V in rotation: 1 x 3000 .97 of the time, x 4100 1.26; 16 x 4100 .97, x 6200 1.19; 32 x 6200 1.01; 56 x 6200 .96,
 // x 8200 1.09; 64 x 8200 .92; d = 64, 1 x 3000 .87, x 4100 1.21; 32 x 6200 .91, x 8200 1.26; 64 x 6200 .87, x 8200 1.08; 96 x 8200 1.00; 112 x 8200 .93, x 16500 .77, x 32800 1.06; 128 x 4100 .75, x 32800 .93.
